@@ -1,0 +1,59 @@
+"""Outputs and inputs that begin at any element of a larger buffer: every offset
+modulo 16 bytes, sizes at the edges of a lane's 16 bytes, a wave's 4 KB and a
+workgroup's 16 KB, and one size that takes the two-launch decoder.  Bit exact
+against the oracle; the bytes around the output keep their values."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1705_01626_amd import zvc
+from tests.gpu_util import raw_bytes, say
+from tests.test_gpu_parity import random_tensor
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+GUARD = 64
+
+
+def guarded(n, dtype, offset):
+    """A buffer of n + offset + GUARD elements filled with 0x5A bytes and the view that begins at `offset`."""
+    base = torch.empty(offset + n + GUARD, dtype=dtype, device=DEV)
+    base.view(torch.uint8).fill_(0x5A)
+    return base, base[offset:offset + n]
+
+
+def assert_guard(base, n, offset, label):
+    w = base.element_size()
+    image = raw_bytes(base)
+    assert (image[:offset * w] == 0x5A).all() and (image[(offset + n) * w:] == 0x5A).all(), label
+
+
+def sizes(w):
+    lane, wave = 16 // w, 4096 // w
+    return [1, lane - 1, lane, lane + 1, wave - 1, wave, wave + 1, 4 * wave - 1, 4 * wave + 1, 9 * wave + 3 * lane + 1]
+
+
+@pytest.mark.parametrize("w,offset", [(4, k) for k in (1, 2, 3)] + [(2, k) for k in range(1, 8)])
+def test_decoders_at_every_output_offset(oracle, w, offset):
+    big = (17 << 20) // w + 5                       # above the single-launch decoder's limit
+    for n in sizes(w) + [big]:
+        x = random_tensor(n, w, 0.45, seed=n + offset)
+        host = raw_bytes(x)
+        ws = zvc.new_workspace(n, w, DEV)
+        comp = torch.from_numpy(np.ascontiguousarray(oracle.compress_stream(host, w))).to(DEV)
+        say("unaligned decode n=%d w=%d offset=%d" % (n, w, offset))
+        base, out = guarded(n, x.dtype, offset)
+        zvc.zvc_decompress(comp, comp.numel(), out, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(raw_bytes(out), host), "planar n=%d" % n
+        assert_guard(base, n, offset, "planar n=%d" % n)
+        for window in (1024, 4096, 65536):
+            stream, table = oracle.window_compress(host, w, window // w)
+            d_stream = torch.from_numpy(np.ascontiguousarray(stream)).to(DEV)
+            d_table = torch.from_numpy(table.astype(np.int64)).to(DEV)
+            base, out = guarded(n, x.dtype, offset)
+            zvc.zvc_window_decompress(d_stream, d_stream.numel(), d_table, n, 0, len(table) - 1, out,
+                                      window_bytes=window)
+            torch.cuda.synchronize()
+            assert np.array_equal(raw_bytes(out), host), "window %d n=%d" % (window, n)
+            assert_guard(base, n, offset, "window %d n=%d" % (window, n))
