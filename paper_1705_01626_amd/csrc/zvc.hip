@@ -1534,19 +1534,149 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
 //     elements, twice that of 16-bit ones);
 //   windows of 8..64 KB: a wave takes one window and goes through its pieces
 //     in order; lane 0 walks, and where its walk ends the next piece begins.
+//     Few windows of 16 KB and more take a workgroup each (window_split_kernel).
 // Reads stay inside [0, stream_bytes) and inside the staged bytes whatever the
 // table and the masks say; what a damaged stream asks for beyond that decodes
 // as zero.
 constexpr int kWindowUnitBytes = 1024;  // one load of a wave; window sizes are 1 KB << shift
 constexpr unsigned kMaxWindowShift = 6; // 64 KB
 
+template <int W>
+struct WindowGeometry {
+    static constexpr int kElemsPerLane = 16 / W;                       // per 16-byte store: 4 | 8
+    static constexpr int kLanesPerGroup = 32 / kElemsPerLane;          // 8 | 4
+    static constexpr int kUnitGroups = kWaveSize / kLanesPerGroup;     // masks per KB of output: 8 | 16
+    static constexpr int kPieceGroups = kStageLoads * kUnitGroups;     // masks per 4 KB piece: 32 | 64
+    static constexpr int kUnitElems = kUnitGroups * 32;
+    static constexpr unsigned kGroupBytes = 4 + 32 * W;                // a group with nothing dropped
+    static constexpr unsigned kPieceBytes = kPieceGroups * kGroupBytes;
+    static_assert(kUnitElems * W == kWindowUnitBytes, "1 KB of output is one load of a wave");
+};
 
-// The mask at an LDS address that is a multiple of W.
+// The mask at an LDS address that is a multiple of W, and its popcount alone.  (The
+// latter reads two halves for W = 2: where many lanes read, an LDS access that is
+// not aligned takes them one after the other.)
 template <int W>
 __device__ inline unsigned lds_mask(const unsigned char* p) {
     typedef unsigned at2 __attribute__((aligned(2)));
     if (W == 4) return *reinterpret_cast<const unsigned*>(p);
     return *reinterpret_cast<const at2*>(p);
+}
+template <int W>
+__device__ inline unsigned lds_mask_bits(const unsigned char* p) {
+    if (W == 4) return static_cast<unsigned>(__popc(*reinterpret_cast<const unsigned*>(p)));
+    unsigned low = *reinterpret_cast<const unsigned short*>(p), high = *reinterpret_cast<const unsigned short*>(p + 2);
+    asm("" : "+v"(low), "+v"(high));      // (or the compiler goes on in 16 bits, with masks of its own)
+    return static_cast<unsigned>(__popc(low) + __popc(high));
+}
+
+// The serial walk of one lane over `count` masks (a multiple of 8) from LDS offset
+// p on: a record of each group, its mask and the mask's offset, and where the walk
+// ends.  Every step waits for the one before, and with eight waves per SIMD what a
+// step costs is its instructions, so it holds little but the chain: read a mask,
+// add its popcount (6.5 instructions instead of 14; 822 MB fp32 at density 0.05 in
+// 4 KB windows: 170 -> 146 us, 149 MB bf16 in 64 KB windows: 128 -> 104 us.  The
+// same walk on the scalar unit, v_readlane and s_bcnt1, takes 229 and 170 us: it
+// issues an instruction per four clocks and SIMD too, and needs 19 of them).  Past
+// the staged bytes (`limit`) the walk reads whatever lies at their end:
+// empty_missing_groups() sorts those groups out.
+template <int W>
+__device__ inline unsigned walk_masks(const unsigned char* stage, unsigned p, unsigned limit, unsigned count,
+                                      uint2* record) {
+    for (unsigned g0 = 0; g0 < count; g0 += 8) {       // p, limit: less the 4 bytes of every mask since g0
+#pragma unroll
+        for (unsigned g = 0; g < 8; ++g) {
+            const unsigned m = lds_mask<W>(stage + p + 4 * g);
+            record[g0 + g] = make_uint2(m, p + 4 * g);
+            limit -= 4u;
+            p = min(p + W * static_cast<unsigned>(__popc(m)), limit);
+        }
+        p += 32u;
+        limit += 32u;
+    }
+    return p;
+}
+
+// A damaged mask can ask for more elements than are staged (`beyond`, of any lane):
+// the rest of the wave's LDS slice is zeroed for it.
+template <int W>
+__device__ inline void zero_beyond(bool beyond, unsigned char* stage, unsigned limit, unsigned slice_bytes, int lane) {
+    if (__ballot(beyond) != 0ull) {
+        for (unsigned i = limit + W * lane; i + W <= slice_bytes; i += W * kWaveSize) {
+            if (W == 4) *reinterpret_cast<unsigned*>(stage + i) = 0u;
+            else *reinterpret_cast<unsigned short*>(stage + i) = 0;
+        }
+        wave_lds_sync();
+    }
+}
+
+// After a walk: the records' offsets become those of the groups' first stored
+// elements, and masks that are not there (from record `groups` on, or not wholly
+// before `limit`) become empty.
+template <int W>
+__device__ inline void empty_missing_groups(uint2* record, int records, unsigned groups, unsigned char* stage,
+                                            unsigned limit, unsigned slice_bytes, int lane) {
+    wave_lds_sync();
+    bool beyond = false;
+    if (lane < records) {
+        uint2 group = record[lane];
+        if (static_cast<unsigned>(lane) >= groups || group.y + 4u > limit) group.x = 0u;
+        group.y += 4u;
+        beyond = group.y + W * static_cast<unsigned>(__popc(group.x)) > limit;
+        record[lane] = group;
+    }
+    wave_lds_sync();
+    zero_beyond<W>(beyond, stage, limit, slice_bytes, lane);
+}
+
+// Output of up to UNITS KB, elements elem0 .. elem_end - 1 of the tensor (elem_end -
+// elem0 may be more than that), to `out`, where element elem0 goes.  group_at(i):
+// mask of the i-th group from elem0 on and LDS offset of its first stored element.
+template <int W, int UNITS, bool ALIGNED, class GroupAt>
+__device__ __forceinline__ void expand_groups(const unsigned char* stage, const GroupAt& group_at, size_t elem0,
+                                              size_t elem_end, unsigned char* out, unsigned dummy, int lane) {
+    using G = WindowGeometry<W>;
+    constexpr int E = G::kElemsPerLane, LPG = G::kLanesPerGroup;
+    const bool full = elem0 + static_cast<size_t>(UNITS) * G::kUnitElems <= elem_end;
+#pragma unroll
+    for (int jj = 0; jj < UNITS; ++jj) {
+        if (elem0 + static_cast<size_t>(jj) * G::kUnitElems >= elem_end) break;
+        const unsigned in_piece = static_cast<unsigned>((jj * kWaveSize + lane) * E);
+        const uint2 group = group_at(jj * G::kUnitGroups + lane / LPG);
+        const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E;
+        unsigned at = group.y + W * __popc(group.x & ((1u << bit0) - 1u));
+        const unsigned field = group.x >> bit0;
+        unsigned d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int c = 0; c < E; ++c) {
+            const bool set = ((field >> c) & 1u) != 0u;
+            const unsigned from = set ? at : dummy;
+            if (W == 4) {
+                const unsigned v = *reinterpret_cast<const unsigned*>(stage + from);
+                d[c] = set ? v : 0u;
+            } else {
+                const unsigned v = *reinterpret_cast<const unsigned short*>(stage + from);
+                d[c >> 1] |= (set ? v : 0u) << (16 * (c & 1));
+            }
+            at += set ? W : 0;
+        }
+        const size_t e0 = elem0 + in_piece;
+        if (full || e0 + E <= elem_end) {
+            if (ALIGNED) store16_stream(out + in_piece * W, make_uint4(d[0], d[1], d[2], d[3]));
+            else store16_loose<W>(out + in_piece * W, make_uint4(d[0], d[1], d[2], d[3]));
+        } else {
+#pragma unroll
+            for (int c = 0; c < E; ++c) {
+                if (e0 + c < elem_end) {
+                    if (W == 4)
+                        reinterpret_cast<unsigned*>(out)[in_piece + c] = d[c];
+                    else
+                        reinterpret_cast<unsigned short*>(out)[in_piece + c] = static_cast<unsigned short>(
+                            (d[c >> 1] >> (16 * (c & 1))) & 0xFFFFu);
+                }
+            }
+        }
+    }
 }
 
 template <int W, bool ALIGNED>
@@ -1555,19 +1685,11 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     const unsigned long long* __restrict__ offsets, size_t n, size_t num_groups,
     size_t first_window, size_t num_windows, unsigned window_shift, unsigned char* __restrict__ out,
     bool interleave) {
-    constexpr int E = 16 / W;
-    constexpr int LPG = 32 / E;
-    constexpr int GPL = kWaveSize / LPG;                    // masks per KB of output: 8 | 16
-    constexpr int kPieceGroups = kStageLoads * GPL;         // masks per piece: 32 | 64
-    constexpr int kUnitElems = GPL * 32;
-    constexpr unsigned kPieceBytes = kStageLoads * kWindowUnitBytes;
-    constexpr unsigned kMaxBytes = kPieceBytes + 4 * kPieceGroups;   // a piece with nothing dropped
-    static_assert(kUnitElems * W == kWindowUnitBytes, "1 KB of output is one load of a wave");
-
+    using G = WindowGeometry<W>;
     // shift < 16, then a piece, then what a mask that ends on its last byte can ask for
-    constexpr unsigned kSliceBytes = (16 + kMaxBytes + 4 + 32 * W + 15) / 16 * 16;
+    constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + G::kGroupBytes + 15) / 16 * 16;
     __shared__ __align__(16) unsigned char s_stage[kWaves][kSliceBytes];
-    __shared__ uint2 s_group[kWaves][kPieceGroups];        // a group's mask, LDS offset of its first stored element
+    __shared__ __align__(16) uint2 s_group[kWaves][G::kPieceGroups];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
@@ -1576,7 +1698,7 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     // windows in a piece (small windows) | pieces in a window (large ones)
     const unsigned piece_windows = shift_w <= 2 ? kStageLoads >> shift_w : 1u;
     const unsigned window_pieces = shift_w <= 2 ? 1u : 1u << (shift_w - 2);
-    const unsigned walker_groups = static_cast<unsigned>(kPieceGroups) / piece_windows;
+    const unsigned walker_groups = static_cast<unsigned>(G::kPieceGroups) / piece_windows;
     // the wave's share: dealt out in a row or, as in the planar decoder, interleaved over the XCDs
     const size_t share = interleave ? (static_cast<size_t>(blockIdx.x / 8) * kWaves + wave) * 8 + blockIdx.x % 8
                                     : static_cast<size_t>(blockIdx.x) * kWaves + wave;
@@ -1585,7 +1707,7 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     const size_t window0 = first_window + local;
     const unsigned windows_here =
         num_windows - local < piece_windows ? static_cast<unsigned>(num_windows - local) : piece_windows;
-    const size_t units = div_up(num_groups, static_cast<size_t>(GPL));   // KBs of output in the tensor
+    const size_t units = div_up(num_groups, static_cast<size_t>(G::kUnitGroups));   // KBs of output in the tensor
 
     const auto clamped = [&](size_t k) {
         const unsigned long long o = offsets[k];
@@ -1596,18 +1718,14 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     if (hi < lo) hi = lo;
     unsigned char* stage = s_stage[wave];
 
-    static_assert(kMaxBytes + 16 <= kFetchSlots * kWaveSize * 16, "a piece fits the fetch slots");
+    static_assert(G::kPieceBytes + 16 <= kFetchSlots * kWaveSize * 16, "a piece fits the fetch slots");
 
     for (unsigned piece = 0; piece < window_pieces; ++piece) {
         const size_t unit0 = (window0 << shift_w) + static_cast<size_t>(piece) * kStageLoads;
         if (unit0 >= units) break;
-        size_t units_left = units - unit0;
-        if (shift_w <= 2 && units_left > (static_cast<size_t>(windows_here) << shift_w))
-            units_left = static_cast<size_t>(windows_here) << shift_w;
-        const unsigned units_here = units_left < kStageLoads ? static_cast<unsigned>(units_left) : kStageLoads;
 
         // ---- the piece's bytes, clamped to what can be there
-        const unsigned cur_bytes = hi - lo > kMaxBytes ? kMaxBytes : static_cast<unsigned>(hi - lo);
+        const unsigned cur_bytes = hi - lo > G::kPieceBytes ? G::kPieceBytes : static_cast<unsigned>(hi - lo);
         const unsigned char* src = stream + lo;    // wave-uniform, aligned to W
         const unsigned cur_shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
         const unsigned cur_limit = cur_shift + cur_bytes;
@@ -1620,8 +1738,8 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
 
         // ---- the serial walk: one lane per window of the piece
         const unsigned groups_here = static_cast<unsigned>(
-            min(num_groups - unit0 * GPL, static_cast<size_t>(shift_w <= 2 ? windows_here * walker_groups
-                                                                           : static_cast<unsigned>(kPieceGroups))));
+            min(num_groups - unit0 * G::kUnitGroups, static_cast<size_t>(shift_w <= 2 ? windows_here * walker_groups
+                                                                                      : G::kPieceGroups)));
         unsigned walk_end = 0;
         if (static_cast<unsigned>(lane) < piece_windows) {
             // a small window begins where the table says; a piece of a large one where the last walk ended.
@@ -1631,45 +1749,9 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
                 const unsigned long long o = piece == 0 ? clamped(window0 + lane) : lo;
                 if (o >= lo && o - lo <= cur_bytes) p = cur_shift + static_cast<unsigned>(o - lo);
             }
-            // Every step waits for the one before, and with eight waves per SIMD what a step costs
-            // is its instructions, so it holds little but the chain: read a mask, add its popcount
-            // (6.5 instructions instead of 14; 822 MB fp32 at density 0.05 in 4 KB windows: 170 ->
-            // 146 us, 149 MB bf16 in 64 KB windows: 128 -> 104 us.  The same walk on the scalar
-            // unit, v_readlane and s_bcnt1, takes 229 and 170 us: it issues an instruction per
-            // four clocks and SIMD too, and needs 19 of them.)  (p: offset of mask g less 4 g.)  Past the staged bytes the walk
-            // reads whatever lies at their end; the groups found there are emptied below.
-            uint2* record = s_group[wave] + lane * walker_groups;
-            unsigned limit = cur_limit;                      // of p, less 4 g
-            for (unsigned g0 = 0; g0 < walker_groups; g0 += 8) {
-#pragma unroll
-                for (unsigned g = 0; g < 8; ++g) {
-                    const unsigned m = lds_mask<W>(stage + p + 4 * g);
-                    record[g0 + g] = make_uint2(m, p + 4 * g);
-                    limit -= 4u;
-                    p = min(p + W * static_cast<unsigned>(__popc(m)), limit);
-                }
-                p += 32u;
-                limit += 32u;
-            }
-            walk_end = p;
+            walk_end = walk_masks<W>(stage, p, cur_limit, walker_groups, s_group[wave] + lane * walker_groups);
         }
-        wave_lds_sync();
-        // masks that are not there (past the tensor's end, past the staged bytes) are empty
-        bool beyond = false;
-        if (static_cast<unsigned>(lane) < static_cast<unsigned>(kPieceGroups)) {
-            uint2 group = s_group[wave][lane];
-            if (static_cast<unsigned>(lane) >= groups_here || group.y + 4u > cur_limit) group.x = 0u;
-            group.y += 4u;
-            beyond = group.y + W * static_cast<unsigned>(__popc(group.x)) > cur_limit;
-            s_group[wave][lane] = group;
-        }
-        // a damaged mask asks for more elements than are staged: they are zero
-        if (__ballot(beyond) != 0ull)
-            for (unsigned i = cur_limit + W * lane; i + W <= kSliceBytes; i += W * kWaveSize) {
-                if (W == 4) *reinterpret_cast<unsigned*>(stage + i) = 0u;
-                else *reinterpret_cast<unsigned short*>(stage + i) = 0;
-            }
-        wave_lds_sync();
+        empty_missing_groups<W>(s_group[wave], G::kPieceGroups, groups_here, stage, cur_limit, kSliceBytes, lane);
 
         // ---- a large window's next piece begins where lane 0's walk ended (never beyond the
         // window).  (Asking for its bytes here, before this piece is expanded, measured no faster.)
@@ -1681,56 +1763,189 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
             next_lo = next < hi ? next : hi;
         }
 
-        // ---- expand: load jj is KB jj of the piece
-        const size_t elem0 = unit0 * kUnitElems;                                  // in the tensor
-        unsigned char* wout = out + ((local << shift_w) + static_cast<size_t>(piece) * kStageLoads) *
-                                        kWindowUnitBytes;                         // this piece's output
-        const bool full = units_here == kStageLoads && elem0 + kStageLoads * kUnitElems <= n;
-#pragma unroll
-        for (int jj = 0; jj < kStageLoads; ++jj) {
-            if (static_cast<unsigned>(jj) >= units_here) break;
-            // element within the piece
-            const unsigned in_step = static_cast<unsigned>((jj * kWaveSize + lane) * E);
-            const int gl = jj * GPL + lane / LPG;
-            const uint2 group = s_group[wave][gl];
-            const unsigned gm = group.x;
-            const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E;
-            unsigned at = group.y + W * __popc(gm & ((1u << bit0) - 1u));
-            const unsigned field = gm >> bit0;
-            unsigned d[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int c = 0; c < E; ++c) {
-                const bool set = ((field >> c) & 1u) != 0u;
-                const unsigned from = set ? at : cur_shift;
-                if (W == 4) {
-                    const unsigned v = *reinterpret_cast<const unsigned*>(stage + from);
-                    d[c] = set ? v : 0u;
-                } else {
-                    const unsigned v = *reinterpret_cast<const unsigned short*>(stage + from);
-                    d[c >> 1] |= (set ? v : 0u) << (16 * (c & 1));
-                }
-                at += set ? W : 0;
-            }
-            const size_t e0 = elem0 + in_step;
-            if (full || e0 + E <= n) {
-                if (ALIGNED) store16_stream(wout + in_step * W, make_uint4(d[0], d[1], d[2], d[3]));
-                else store16_loose<W>(wout + in_step * W, make_uint4(d[0], d[1], d[2], d[3]));
-            } else {
-#pragma unroll
-                for (int c = 0; c < E; ++c) {
-                    if (e0 + c < n) {
-                        if (W == 4)
-                            reinterpret_cast<unsigned*>(wout)[in_step + c] = d[c];
-                        else
-                            reinterpret_cast<unsigned short*>(wout)[in_step + c] = static_cast<unsigned short>(
-                                (d[c >> 1] >> (16 * (c & 1))) & 0xFFFFu);
-                    }
-                }
-            }
-        }
+        // ---- expand
+        const size_t elem0 = unit0 * G::kUnitElems;
+        expand_groups<W, kStageLoads, ALIGNED>(
+            stage, [&](int i) { return s_group[wave][i]; }, elem0,
+            min(n, elem0 + static_cast<size_t>(groups_here) * 32),
+            out + ((local << shift_w) + static_cast<size_t>(piece) * kStageLoads) * kWindowUnitBytes, cur_shift, lane);
         if (!more) break;
         lo = next_lo;
         wave_lds_sync();     // the expand's reads of the stage are done before it is overwritten
+    }
+}
+
+// The same for a few large windows: a workgroup of NW = window / 4 KB waves takes
+// one.  A walk cannot start in the middle of a window, but where it can come from
+// is limited: a group is 1 to 33 words of 32 bits (2 to 34 of 16), so of the walks
+// that cross a given byte one enters what follows at one of its first 33 (34)
+// words.  The window's bytes are cut into 4 NW equal parts, 4 in a row per wave,
+// and each wave
+//   1. walks each of its parts from all those words at once, a lane each (the four
+//      parts' chains overlap), which takes as long as a single walk over a part,
+//      and notes where in the next part the walks come out and how many groups they
+//      have passed; of a wave's four parts that makes one such table, in LDS;
+//   2. looks up wave by wave which of the walks was the true one, and so its own
+//      first word and first group;
+//   3. walks its parts again from the four true words, a lane each, and expands
+//      their groups, 32 at a time.
+// So a window takes a 32nd of the serial walk (64 KB) and a table look-up per wave
+// instead of all of it, for about five times the instructions.
+template <int W, int NW, bool ALIGNED>
+__global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
+    const unsigned char* __restrict__ stream, unsigned long long stream_bytes,
+    const unsigned long long* __restrict__ offsets, size_t n, size_t num_groups, size_t first_window,
+    unsigned char* __restrict__ out) {
+    using G = WindowGeometry<W>;
+    constexpr unsigned kWindowGroups = NW * G::kPieceGroups;
+    constexpr unsigned kEntries = 32 + 4 / W;               // 33 | 34
+    constexpr unsigned kLost = kWaveSize - 1;               // as a word: no walk goes on from here
+    constexpr int kParts = 4;                               // per wave
+    constexpr unsigned kBatch = 32;                         // groups expanded at a time
+    constexpr unsigned kPositions = 128;                    // groups of a wave whose walk is recorded at once
+    // shift < 16, parts with nothing dropped, the rest of their last group, what a damaged mask can ask for
+    constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + kParts * W + 2 * G::kGroupBytes + 15) / 16 * 16;
+    static_assert(kSliceBytes <= kFetchSlots * kWaveSize * 16, "a wave's parts fit the fetch slots");
+    __shared__ __align__(16) unsigned char s_stage[NW * kSliceBytes];
+    __shared__ unsigned short s_at[NW][kPositions];         // offset of a group's mask in the wave's slice
+    __shared__ unsigned s_exit[NW][kEntries];               // groups << 8 | word of the next wave's first part
+
+    const int lane = static_cast<int>(threadIdx.x) & (kWaveSize - 1);
+    const int wave = static_cast<int>(uniform(threadIdx.x / kWaveSize));
+    const size_t window = first_window + blockIdx.x;
+    const size_t window_group0 = window * kWindowGroups;
+    const unsigned groups = num_groups - window_group0 < kWindowGroups ? static_cast<unsigned>(num_groups - window_group0)
+                                                                       : kWindowGroups;
+    const auto clamped = [&](size_t k) {
+        const unsigned long long o = offsets[k];
+        return o > stream_bytes ? stream_bytes : o;
+    };
+    const unsigned long long lo = clamped(window), hi = clamped(window + 1);
+    const unsigned long long there = hi > lo ? hi - lo : 0ull;
+    const unsigned bytes = there > groups * G::kGroupBytes ? groups * G::kGroupBytes : static_cast<unsigned>(there);
+
+    // ---- the wave's parts, and the rest of the group that begins on their last word.
+    //      Offsets below are from the beginning of s_stage.
+    const unsigned part = (bytes + NW * kParts * W - 1) / (NW * kParts * W) * W;
+    const unsigned wave0 = min(kParts * part * wave, bytes);
+    const unsigned own = min(kParts * part, bytes - wave0);
+    const unsigned readable = min(kParts * part + G::kGroupBytes, bytes - wave0);
+    const unsigned char* src = stream + lo + wave0;
+    const unsigned skew = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
+    const unsigned slice = wave * kSliceBytes, slice_end = slice + kSliceBytes;
+    const unsigned begin = slice + skew, limit = begin + readable;
+    {
+        uint4 fetched[kFetchSlots];
+        wave_fetch(fetched, src - skew, readable != 0 ? skew + readable : 0u, false, lane);
+        wave_commit(s_stage + slice, fetched, skew + readable, readable != 0 ? skew + readable : 0u, lane);
+    }
+    wave_lds_sync();
+
+    // ---- 1. all walks that can enter the parts (a finished walk goes on reading where it stands)
+    unsigned part_end[kParts], walk_end[kParts], p[kParts], passed[kParts];
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) {
+        part_end[q] = begin + min((q + 1) * part, own);
+        walk_end[q] = min(part_end[q], max(limit, 3u) - 3u);       // a mask lies wholly before `limit`
+        p[q] = begin + min(q * part, own) + static_cast<unsigned>(W * lane);
+        passed[q] = 0;
+    }
+    bool going = true;
+    while (going) {
+        bool on[kParts];
+#pragma unroll
+        for (int twice = 0; twice < 2; ++twice) {
+            unsigned bits[kParts];
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) bits[q] = lds_mask_bits<W>(s_stage + p[q]);
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) {
+                on[q] = p[q] < walk_end[q];
+                passed[q] += on[q] ? 1u : 0u;
+                p[q] = on[q] ? p[q] + (W * bits[q] + 4u) : p[q];
+            }
+        }
+        going = __any(on[0] | on[1] | on[2] | on[3]);
+    }
+    // entry[q]: where the walk that entered the first part at the lane's word enters part q; before[q]:
+    // groups it has passed by then
+    unsigned entry[kParts + 1], before[kParts + 1];
+    entry[0] = lane < static_cast<int>(kEntries) ? static_cast<unsigned>(lane) : kLost;
+    before[0] = 0;
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) {
+        const unsigned come_out = lane >= static_cast<int>(kEntries) || p[q] < part_end[q] ? kLost
+                                                                                           : (p[q] - part_end[q]) / W;
+        const unsigned v = __shfl(lane == static_cast<int>(kLost) ? kLost : passed[q] << 8 | come_out,
+                                  static_cast<int>(entry[q]));
+        entry[q + 1] = v & 255u;
+        before[q + 1] = before[q] + (v >> 8);
+    }
+    if (lane < static_cast<int>(kEntries)) s_exit[wave][lane] = before[kParts] << 8 | entry[kParts];
+    lds_barrier();
+
+    // ---- 2. the true one
+    unsigned word = 0, first = 0;
+    for (int k = 0; k < wave && word != kLost; ++k) {
+        const unsigned v = uniform(s_exit[k][word]);
+        first += v >> 8;
+        word = v & 255u;
+    }
+    const unsigned count = lane_value(before[kParts], static_cast<int>(word));     // (0 in lane kLost)
+    const unsigned end = min(first + count, groups);
+
+    // ---- 3. its groups: all at once if there is room for their offsets, else 32 at a time
+    unsigned char* const window_out = out + static_cast<size_t>(blockIdx.x) * (kWindowGroups * 32 * W);
+    const size_t window_elem0 = window_group0 * 32;
+    const bool at_once = count <= kPositions;
+    unsigned at = begin, left = 0, slot = 0;               // a lane's walk
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) {
+        // (read by the whole wave: what one lane alone goes on to compute is not there in the others)
+        const unsigned part_word = lane_value(entry[q], static_cast<int>(word));
+        const unsigned part_first = lane_value(before[q], static_cast<int>(word));
+        const unsigned part_last = lane_value(before[q + 1], static_cast<int>(word));
+        if (lane == q && at_once) {
+            at = begin + min(q * part, own) + W * part_word;
+            slot = part_first;
+            left = part_last - part_first;
+        }
+    }
+    while (left != 0) {
+        s_at[wave][slot++] = static_cast<unsigned short>(at - slice);
+        at += W * (lds_mask_bits<W>(s_stage + at) + 4u / W);
+        --left;
+    }
+    unsigned walker = begin + W * word;                    // where group g begins, if not all at once
+    for (unsigned g = first; g < end; g += kBatch) {
+        const unsigned here = min(end - g, kBatch);
+        if (!at_once && lane == 0) {
+            for (unsigned i = 0; i < here; ++i) {
+                s_at[wave][i] = static_cast<unsigned short>(walker - slice);
+                walker += W * (lds_mask_bits<W>(s_stage + walker) + 4u / W);
+            }
+        }
+        wave_lds_sync();
+        unsigned mask = 0, value = limit;
+        if (static_cast<unsigned>(lane) < here) {
+            const unsigned m = slice + s_at[wave][(at_once ? g - first : 0u) + lane];
+            mask = lds_mask<W>(s_stage + m);
+            value = m + 4u;
+        }
+        zero_beyond<W>(value + W * static_cast<unsigned>(__popc(mask)) > limit, s_stage, limit, slice_end, lane);
+        const size_t elem0 = window_elem0 + static_cast<size_t>(g) * 32;
+        expand_groups<W, kBatch / G::kUnitGroups, ALIGNED>(
+            s_stage, [&](int i) { return make_uint2(__shfl(mask, i), __shfl(value, i)); }, elem0,
+            min(n, elem0 + static_cast<size_t>(here) * 32), window_out + static_cast<size_t>(g) * (32 * W), begin, lane);
+        wave_lds_sync();
+    }
+    // ---- groups that a damaged stream has no mask for are zero
+    if (wave == NW - 1) {
+        const size_t to = min(n, window_elem0 + static_cast<size_t>(groups) * 32);
+        for (size_t e = window_elem0 + static_cast<size_t>(end) * 32 + lane; e < to; e += kWaveSize) {
+            if (W == 4) reinterpret_cast<unsigned*>(window_out)[e - window_elem0] = 0u;
+            else reinterpret_cast<unsigned short*>(window_out)[e - window_elem0] = 0;
+        }
     }
 }
 
@@ -1974,6 +2189,37 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     return launch(decompress_kernel<W, LOADS, ALIGNED>, grid, dim3(kThreads), stream,
                   masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
                   interleave);
+}
+
+// Which windows a workgroup each decodes (window_split_kernel) instead of a wave
+// each: large ones, while there are too few of them to fill the GPU with waves.  A
+// wave's walk over a 64 KB window takes 50 us (fp32) or 75 (16-bit) however few there
+// are; a workgroup takes 10.9 or 21.5, but 5 times the instructions.  In us, wave |
+// workgroup each, densities 0.1 to 0.9:
+//   fp32    64 KB: 15 windows 52 | 11,  977 windows 53 | 31,  3906 windows 89 | 100
+//           16 KB: 61 windows 15 | 10,  977 windows 15 | 12,  3906 windows 23 | 28
+//   bf16    64 KB:  8 windows 79 | 21, 1134 windows 90 | 65
+//           16 KB: 31 windows 22 | 15,  488 windows 22 | 19,  1953 windows 25 | 33
+inline bool splits_windows(size_t num_windows, int shift, int w) {
+    return shift >= 4 && num_windows <= (w == 4 ? size_t{2048} : size_t{448} << (shift - 4));
+}
+
+template <int W, int NW>
+hipError_t launch_window_split_as(bool aligned, hipStream_t stream, const unsigned char* in,
+                                  unsigned long long stream_bytes, const unsigned long long* offsets, size_t n,
+                                  size_t groups, size_t first_window, size_t num_windows, unsigned char* out) {
+    return launch(aligned ? window_split_kernel<W, NW, true> : window_split_kernel<W, NW, false>,
+                  dim3(static_cast<unsigned>(num_windows)), dim3(NW * kWaveSize), stream, in, stream_bytes, offsets, n,
+                  groups, first_window, out);
+}
+template <int W, typename... Args>
+hipError_t launch_window_split(int waves, Args... args) {
+    switch (waves) {
+        case 4: return launch_window_split_as<W, 4>(args...);
+        case 8: return launch_window_split_as<W, 8>(args...);
+        case 16: return launch_window_split_as<W, 16>(args...);
+    }
+    return hipErrorInvalidValue;   // splits_windows() takes no other
 }
 
 // Picks the instantiation for (w, tile shape).  16-bit elements at an odd half
@@ -2332,17 +2578,23 @@ zvc_status zvc_window_decompress(const void* d_stream, size_t stream_bytes, cons
                                  ? (first_window + num_windows) * elems_per_window : n;
     const size_t out_bytes = (last_elem - first_window * elems_per_window) * static_cast<size_t>(w);
     if (ranges_overlap(d_stream, stream_bytes, d_out, out_bytes)) return ZVC_E_ARG;
+    const unsigned char* in = static_cast<const unsigned char*>(d_stream);
+    const unsigned long long* offs = reinterpret_cast<const unsigned long long*>(d_offsets);
+    unsigned char* out = static_cast<unsigned char*>(d_out);
+    const size_t groups = div_up(n, 32);
+    const bool al = aligned_to(d_out, 16);
+    if (splits_windows(num_windows, shift, w)) {
+        return hip_ok(w == 4 ? launch_window_split<4>(1 << (shift - 2), al, stream, in, stream_bytes, offs, n, groups,
+                                                      first_window, num_windows, out)
+                             : launch_window_split<2>(1 << (shift - 2), al, stream, in, stream_bytes, offs, n, groups,
+                                                      first_window, num_windows, out));
+    }
     // a wave takes 4 KB of output, or one window if that is more
     const size_t wave_windows = shift <= 2 ? static_cast<size_t>(kStageLoads >> shift) : 1;
     // (a multiple of 8 workgroups for the interleaved order)
     const size_t blocks = div_up(div_up(num_windows, static_cast<size_t>(kWaves) * wave_windows), 8) * 8;
     if (blocks > 0x7FFFFFFFull) return ZVC_E_ARG;
     const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    const unsigned char* in = static_cast<const unsigned char*>(d_stream);
-    const unsigned long long* offs = reinterpret_cast<const unsigned long long*>(d_offsets);
-    unsigned char* out = static_cast<unsigned char*>(d_out);
-    const size_t groups = div_up(n, 32);
-    const bool al = aligned_to(d_out, 16);
     // dense streams of large ranges decode 3-8 % faster in the interleaved order, others slower
     const bool interleave = stream_bytes / 3 > n * static_cast<size_t>(w) / 4 && out_bytes >= (size_t{64} << 20);
     const auto kernel = w == 4 ? (al ? window_decode_kernel<4, true> : window_decode_kernel<4, false>)

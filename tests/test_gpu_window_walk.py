@@ -33,7 +33,7 @@ def walk(stream, table, n, w, per, end):
 
 
 @pytest.mark.parametrize("w", [4, 2])
-@pytest.mark.parametrize("window", [1024, 2048, 4096, 8192, 65536])
+@pytest.mark.parametrize("window", [1024, 2048, 4096, 8192, 16384, 32768, 65536])
 def test_streams_that_end_early(oracle, window, w):
     per = window // w
     n = 2 * per + per // 3 + 7
@@ -52,3 +52,51 @@ def test_streams_that_end_early(oracle, window, w):
             torch.cuda.synchronize()
             want = walk(stream, table, n, w, per, end)
             assert np.array_equal(raw_bytes(out), want.view(np.uint8)), "end=%d" % end
+
+
+@pytest.mark.parametrize("w", [4, 2])
+@pytest.mark.parametrize("window", [16384, 32768, 65536])
+def test_windows_of_mixed_density(oracle, window, w):
+    """Dense, empty and middling stretches inside a window: equal shares of its bytes are very unequal
+    shares of its groups (one wave's share can be most of the window)."""
+    per = window // w
+    rng = np.random.default_rng(window + w)
+    n = 7 * per + per // 2 + 3
+    host = rng.integers(1, 2 ** (8 * w - 1), size=n, dtype=np.int64).astype({2: np.int16, 4: np.int32}[w])
+    at, kinds = 0, (0.0, 1.0, 0.0, 0.02, 0.6)
+    for k in range(200):
+        run = int(rng.integers(per // 20, per))
+        host[at:at + run] *= rng.random(len(host[at:at + run])) < kinds[k % len(kinds)]
+        at += run
+    x = torch.from_numpy(host)
+    stream, table = oracle.window_compress(raw_bytes(x), w, per)
+    d_stream = torch.from_numpy(np.ascontiguousarray(stream)).to(DEV)
+    d_table = torch.from_numpy(table.astype(np.int64)).to(DEV)
+    say("mixed density window=%d w=%d" % (window, w))
+    out = torch.empty(n, dtype=x.dtype, device=DEV)
+    out.view(torch.uint8).fill_(0xEE)
+    zvc.zvc_window_decompress(d_stream, d_stream.numel(), d_table, n, 0, len(table) - 1, out, window_bytes=window)
+    torch.cuda.synchronize()
+    assert np.array_equal(raw_bytes(out), raw_bytes(x))
+
+
+@pytest.mark.parametrize("window,w,most", [(16384, 4, 2048), (16384, 2, 448), (32768, 2, 896), (65536, 2, 1792)])
+def test_both_sides_of_the_number_of_windows(window, w, most):
+    """As many windows as take a workgroup each, and one more: the same elements (which the GPU's own
+    encoder compressed; its streams are compared with the oracle's elsewhere)."""
+    per = window // w
+    n = (most + 1) * per - 37
+    g = torch.Generator(device=DEV).manual_seed(window + w)
+    x = torch.randint(1, 2 ** (8 * w - 1), (n,), generator=g, device=DEV, dtype=torch.int32)
+    x = (x * (torch.rand(n, generator=g, device=DEV) < 0.4)).to({2: torch.int16, 4: torch.int32}[w])
+    ws = zvc.new_workspace(n, w, DEV)
+    comp = zvc.new_compressed_buffer(n, w, DEV)
+    table = torch.zeros(most + 2, dtype=torch.int64, device=DEV)
+    size = torch.zeros(1, dtype=torch.int64, device=DEV)
+    zvc.zvc_window_compress(x, comp, table, size, ws, window_bytes=window)
+    for first, count in ((0, most), (0, most + 1), (most, 1)):
+        say("window=%d w=%d windows %d+%d" % (window, w, first, count))
+        lo, hi = first * per, min(n, (first + count) * per)
+        out = torch.full((hi - lo,), -1, dtype=x.dtype, device=DEV)
+        zvc.zvc_window_decompress(comp, int(size.item()), table, n, first, count, out, window_bytes=window)
+        assert torch.equal(out, x[lo:hi])
