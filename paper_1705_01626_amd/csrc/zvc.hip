@@ -223,8 +223,17 @@ __device__ inline unsigned wave_sum_small(unsigned v) {
 // share cache lines; with the hint those re-reads went back to memory, which
 // cost 10-25 % of the decoder's time at low density.
 typedef unsigned int vec4u __attribute__((ext_vector_type(4)));
+typedef vec4u vec4u_at4 __attribute__((aligned(4)));
+typedef vec4u vec4u_at2 __attribute__((aligned(2)));
 __device__ inline uint4 load16_stream(const void* p) {
     const vec4u v = __builtin_nontemporal_load(reinterpret_cast<const vec4u*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+// 16 bytes from an address that is a multiple of W only, see store16_loose().
+template <int W>
+__device__ inline uint4 load16_loose(const void* p) {
+    const vec4u v = W == 4 ? __builtin_nontemporal_load(reinterpret_cast<const vec4u_at4*>(p))
+                           : __builtin_nontemporal_load(reinterpret_cast<const vec4u_at2*>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ inline void store16_stream(void* p, const uint4& d) {
@@ -239,8 +248,6 @@ __device__ inline void store16_stream(void* p, const uint4& d) {
 // neighbours.  Against a store per element: 44.5 -> 21.2 us for 29 M fp16 elements at
 // an odd element (aligned: 18.9), 49 -> 32.7 us for 26 M fp32 ones (24.4), 307 ->
 // 126 us for 206 M bf16 ones (109).
-typedef vec4u vec4u_at4 __attribute__((aligned(4)));
-typedef vec4u vec4u_at2 __attribute__((aligned(2)));
 template <int W>
 __device__ inline void store16_loose(void* p, const uint4& d) {
     vec4u v;
@@ -610,16 +617,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ inline unsigned load_stream(const unsigned* p) { return __builtin_nontemporal_load(p); }
 __device__ inline unsigned load_stream(const unsigned short* p) { return __builtin_nontemporal_load(p); }
 
-// Dword d of a tensor that is wholly inside it.  SPLIT: 16-bit elements at an
-// address that is not a multiple of 4 are fetched as two halves.
-template <bool SPLIT>
-__device__ __forceinline__ unsigned load_dword(const unsigned char* in, size_t d) {
-    if (SPLIT) {
-        const unsigned short* p = reinterpret_cast<const unsigned short*>(in) + 2 * d;
-        return static_cast<unsigned>(load_stream(p)) | (static_cast<unsigned>(load_stream(p + 1)) << 16);
-    }
-    return load_stream(reinterpret_cast<const unsigned*>(in) + d);
-}
+// A raw buffer's descriptor word (32-bit data, no swizzle), the non-temporal bit of a buffer load.
+constexpr int kRawBuffer = 0x00020000;
+constexpr int kNonTemporal = 2;
 
 // Dword `index` of a run of dwords that starts at `base` (wave-uniform, inside
 // the tensor) and of which only dwords 0 .. room belong to the tensor, the last
@@ -793,7 +793,6 @@ template <int W, int CH, int WV, bool RELU, bool WINDOWED, bool SPLIT>
 __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a) {
     using G = EncoderGeometry<W, CH, WV>;
     constexpr int CG = G::kChunkGroups;
-    constexpr int kAhead = CH;                    // all of a wave's loads are in flight from the start (measured: 3-6 % over 8 KB at a time)
     constexpr int kWindowChunks = 4;              // the windowed stream's unit: 1 KB of input
     static_assert(W == 2 || !SPLIT, "only 16-bit elements can sit at an odd half dword");
 
@@ -815,7 +814,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // ---- 1. loads, zero tests, masks (section 5.2: words compared to zero form the mask
     //         bits) and, fused with them where the queue has room, 3. compaction (section
     //         5.2: shift non-zeros to their packed slots)
-    unsigned cur[CH];
+    unsigned cur[SPLIT ? CH + 1 : CH];
     unsigned mask_reg[G::kMaskRegs];
     unsigned second_reg[W == 2 ? G::kMaskRegs : 1];   // 16-bit elements: the ballots of the lanes' second elements
     unsigned step_total[G::kSteps];               // wave-uniform
@@ -842,6 +841,12 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     const auto chunk = [&](auto kc, auto test_c, auto stage_c) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
         constexpr bool TEST = decltype(test_c)::value, STAGE = decltype(stage_c)::value;
+        if constexpr (SPLIT && TEST) {
+            // the next lane's dword: lanes shifted by one, the last lane's from the next chunk's first
+            const int next = __builtin_amdgcn_update_dpp(__builtin_amdgcn_readfirstlane(static_cast<int>(cur[k + 1])),
+                                                         static_cast<int>(cur[k]), 0x130, 0xF, 0xF, false);
+            cur[k] = __builtin_amdgcn_alignbit(static_cast<unsigned>(next), cur[k], 16);
+        }
         const unsigned x = cur[k];
         const unsigned chunk_groups = STAGE && WINDOWED ? groups_from(k * CG, CG) : 0u;
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
@@ -903,68 +908,61 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
 
-    // A wave that lies wholly inside the tensor needs no bounds checks: it keeps
-    // kAhead loads in flight and tests each chunk as it arrives.  A step is
-    // compacted in the same pass while the queue is sure to hold it whatever its
-    // density (the first two steps always are): the compaction then happens
-    // while the wave would otherwise wait for its loads, and needs nothing from
-    // other tiles.  The barrier makes the cleared arrival word visible to the
-    // tile's waves; it comes after the first loads have been issued, so it costs
-    // them nothing.
-    int staged = 0;                               // steps in the queue so far, wave-uniform
-    if (wave_elem0 + G::kWaveElems <= a.n) {
-        static_for<0, kAhead>([&](auto kc) __attribute__((always_inline)) {
+    // All of the wave's loads are in flight from the start (measured: 3-6 % over 8 KB at a
+    // time), and each chunk is tested as it arrives.  They are buffer loads: what lies past
+    // the tensor reads as zero without a test, so the wave that holds the tensor's end runs
+    // the same instructions as the others.  (With loads and tests of its own, that wave,
+    // usually the call's last, fetched several KB of code that no other wave had: 5.9 against
+    // 4.8 us for a call of 64,000 fp32 elements, 1.5 to 6 us on every size that is not a
+    // multiple of the tile.)
+    {
+        // Aligned dwords from the one that holds the tensor's first element to the one that holds
+        // its last.  SPLIT: the tensor begins in the middle of the first of them, so a lane's two
+        // elements are the halves of two of them, its own and the next lane's.
+        const size_t bytes = div_up(a.n * W + (SPLIT ? 2 : 0), size_t{4}) * 4, wave_byte0 = wave_dword0 * 4;
+        const unsigned most = CH * kChunkBytes + (SPLIT ? 4 : 0);
+        const unsigned readable = wave_byte0 >= bytes ? 0u
+                                  : bytes - wave_byte0 < most ? static_cast<unsigned>(bytes - wave_byte0) : most;
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char*>(a.in) - (SPLIT ? 2 : 0) + wave_byte0, 0, static_cast<int>(readable), kRawBuffer);
+        static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            cur[k] = load_dword<SPLIT>(a.in, wave_dword0 + static_cast<size_t>(k) * kWaveSize + lane);
+            constexpr int step = k / 16 * 16 * kChunkBytes;
+            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane + k % 16 * kChunkBytes, step, kNonTemporal);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
-        lds_barrier();
-        static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
-            constexpr int h = decltype(hc)::value;
-            const bool fuse = staged == h && q_end + G::kStepMaxBytes <= static_cast<unsigned>(G::kQueueBytes);
-            const auto next_load = [&](auto kc) __attribute__((always_inline)) {
-                constexpr int k = decltype(kc)::value;
-                if constexpr (k + kAhead < CH)
-                    cur[k + kAhead] =
-                        load_dword<SPLIT>(a.in, wave_dword0 + static_cast<size_t>(k + kAhead) * kWaveSize + lane);
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            if (fuse) {
-                static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
-                    chunk(kc, yes, yes);
-                    next_load(kc);
-                });
-                staged = h + 1;
-            } else {
-                static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
-                    chunk(kc, yes, no);
-                    next_load(kc);
-                });
-            }
-        });
-    } else if (wave_elem0 < a.n) {
-        // the wave that holds the tensor's end
-        const size_t last = (a.n * W - 1) / 4;                       // last dword with an element in it
-        const unsigned room = static_cast<unsigned>(last - wave_dword0);
-        const bool half_tail = W == 2 && (a.n & 1u) != 0u;
-        const unsigned char* base = a.in + wave_dword0 * 4;
-        static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            cur[k] = load_dword_ragged<SPLIT>(base, static_cast<unsigned>(k * kWaveSize + lane), room, half_tail);
-            asm volatile("" : "+v"(cur[k]));     // (or the compiler keeps the masked halves of all chunks for the tests)
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        lds_barrier();
-        static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
-            chunk(kc, yes, no);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    } else {
-        // past the tensor's end: nothing kept, no masks (the wave still takes part in the tile's protocol)
+        if constexpr (SPLIT)
+            cur[CH] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, CH % 16 * kChunkBytes, CH / 16 * 16 * kChunkBytes, 0);
+        // the second half of the last dword is not the tensor's
+        const size_t half = a.n / 2;             // the dword with element n - 1 (n odd), or with element n in its first half
+        if (W == 2 && (a.n & 1u) != (SPLIT ? 1u : 0u) && half >= wave_dword0 && half - wave_dword0 < CH * kWaveSize) {
+            const unsigned last = static_cast<unsigned>(half - wave_dword0);
 #pragma unroll
-        for (int k = 0; k < CH; ++k) cur[k] = 0u;
-        lds_barrier();
+            for (int k = 0; k < CH; ++k)
+                if (static_cast<unsigned>(k * kWaveSize + lane) == last) cur[k] &= 0xFFFFu;
+        }
     }
+    lds_barrier();                                // the cleared arrival word, after the loads have been issued
+
+    // A step is compacted in the same pass while the queue is sure to hold it whatever its
+    // density (the first two steps always are): the compaction then happens while the wave
+    // would otherwise wait for its loads, and needs nothing from other tiles.
+    int staged = 0;                               // steps in the queue so far, wave-uniform
+    static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        if (staged == h && q_end + G::kStepMaxBytes <= static_cast<unsigned>(G::kQueueBytes)) {
+            static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
+                chunk(kc, yes, yes);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            staged = h + 1;
+        } else {
+            static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
+                chunk(kc, yes, no);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    });
     unsigned wave_total = 0;
 #pragma unroll
     for (int h = 0; h < G::kSteps; ++h) wave_total += step_total[h];
@@ -1973,10 +1971,12 @@ __global__ __launch_bounds__(kThreads) void count_kernel(const unsigned char* __
     const unsigned tile = blockIdx.x;
     const size_t q0 = static_cast<size_t>(tile) * (kThreads * kCountLoads) + tid;
     uint4 v[kCountLoads];
-    if (ALIGNED && (q0 - tid + kThreads * kCountLoads) * E <= n) {
+    if ((q0 - tid + kThreads * kCountLoads) * E <= n) {
 #pragma unroll
-        for (int j = 0; j < kCountLoads; ++j)
-            v[j] = load16_stream(in + (q0 + static_cast<size_t>(j) * kThreads) * 16);
+        for (int j = 0; j < kCountLoads; ++j) {
+            const unsigned char* p = in + (q0 + static_cast<size_t>(j) * kThreads) * 16;
+            v[j] = ALIGNED ? load16_stream(p) : load16_loose<W>(p);
+        }
     } else {
 #pragma unroll
         for (int j = 0; j < kCountLoads; ++j)
@@ -2116,29 +2116,32 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 
 // Shape of the encoder's tile: chunks per wave x waves per workgroup.  Each tile
 // costs a fixed few nanoseconds of chip-wide time (workgroup launch plus the
-// scan's state traffic), so large fp32 tensors use 64 KB tiles; smaller tensors
-// use smaller tiles so that every CU still gets several.  16-bit elements are
-// twice the vector work per byte, and the 32 KB tile's eight waves per SIMD
-// (against four) hide it better: 32 KB tiles measure up to 9 % faster than
-// 64 KB ones at 411 MB, 822 MB and 1.6 GB alike.  The limits are measured
-// crossover points (8 KB tiles, and 8 or 16 waves per tile, were no faster
-// at any size).
+// scan's state traffic), so large tensors use larger tiles.  A small tile is
+// through its chain of load, test, publish, store sooner, and its straight-line
+// code is shorter (a call's first wave on a CU fetches it from memory: one tile
+// alone takes 3.7 us with 16 KB, 4.8 with 32 KB, 6.9 with 64 KB).  Measured, us
+// with 16 | 32 | 64 KB tiles, density 0.5 (windowed fp32: 0.1 to 0.9):
+//   fp32      12 MB 7.7 | 9.0 | 9.0   24 MB 10.6 | 10.1 | 11.5   48 MB 18.3 | 14.9 | 16.0
+//            103 MB 35.4 | 31.2 | 32.4   200 MB 65.7 | 57.4 | 55.1
+//   windowed  24 MB 14.1 | 14.6   48 MB 22.8 | 22.1   (822 MB: nothing gained from 64 KB)
+//   16-bit    24 MB 11.8 | 12.4   51 MB 21.4 | 21.8   100 MB 37.0 | 35.6   411 MB 136 | 117
+//   windowed 100 MB 55.5 | 59.0   200 MB 104 | 104   411 MB 207 | 197
+// 16-bit elements are twice the vector work per byte, and the 32 KB tile's eight
+// waves per SIMD (against four) hide it better: 64 KB tiles lose up to 9 % there.
+// (8 KB tiles, and 8 or 16 waves per tile, were no faster at any size.)
 struct TileShape {
     int chunks;   // per wave: 16, 32 or 64
     int waves;    // per workgroup
 };
-constexpr size_t kLargeTensorBytes = size_t{160} << 20;   // (cold inputs: 64 KB tiles are 4-6 % ahead at 205 MB, 2 % behind at 103 MB)
-constexpr size_t kMediumTensorBytes = size_t{12} << 20;
+constexpr size_t kLargeTensorBytes = size_t{160} << 20;
 constexpr TileShape kMinShape{16, 4};             // 16 KB, the smallest tile (sizes the workspace)
 static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16 * kThreads, "smallest tile");
 
-inline TileShape choose_shape(size_t n, int w, bool split, bool windowed) {
-    if (split) return kMinShape;
+inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    // (the windowed stream's encoder gains nothing from 64 KB tiles at 822 MB and loses 20 % with
-    // them on the 297 MB tensor whose channels differ widely in density)
+    const size_t medium = w == 4 ? size_t{windowed ? 40u : 24u} << 20 : size_t{windowed ? 200u : 48u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
-         : bytes >= kMediumTensorBytes ? TileShape{32, 4} : kMinShape;
+         : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }
 
 enum class Encoder { kPlain, kRelu, kWindowed };
@@ -2222,15 +2225,14 @@ hipError_t launch_window_split(int waves, Args... args) {
     return hipErrorInvalidValue;   // splits_windows() takes no other
 }
 
-// Picks the instantiation for (w, tile shape).  16-bit elements at an odd half
-// dword always use the smallest tile.
+// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword).
 template <typename... Args>
 hipError_t launch_compress(int w, TileShape shape, bool split, Args... args) {
-    if (split) return launch_compress_as<2, kMinShape.chunks, kMinShape.waves, true>(args...);
 #define ZVC_SHAPE_CASE(C, V)                                                    \
     if (shape.chunks == C && shape.waves == V)                                  \
         return w == 4 ? launch_compress_as<4, C, V, false>(args...)             \
-                      : launch_compress_as<2, C, V, false>(args...);
+               : split ? launch_compress_as<2, C, V, true>(args...)             \
+                       : launch_compress_as<2, C, V, false>(args...);
     if (shape.chunks == 64 && shape.waves == 4 && w == 4) return launch_compress_as<4, 64, 4, false, false>(args...);
     ZVC_SHAPE_CASE(32, 4)
     ZVC_SHAPE_CASE(16, 4)
@@ -2277,7 +2279,7 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
         return hip_ok(e);
     }
     const bool split = !aligned_to(d_in, 4);        // 16-bit elements at an odd half dword
-    const TileShape shape = choose_shape(n, w, split, mode == Encoder::kWindowed);
+    const TileShape shape = choose_shape(n, w, mode == Encoder::kWindowed);
     const size_t tiles = div_up(n * static_cast<size_t>(w), static_cast<size_t>(shape.waves) * shape.chunks * kChunkBytes);
     if (tiles > 0x7FFFFFFFull) return ZVC_E_ARG;
     if (scan_state_only && kHeaderBytes + scan_state_bytes(tiles) > ws) return ZVC_E_WORKSPACE;

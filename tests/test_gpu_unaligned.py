@@ -57,3 +57,40 @@ def test_decoders_at_every_output_offset(oracle, w, offset):
             torch.cuda.synchronize()
             assert np.array_equal(raw_bytes(out), host), "window %d n=%d" % (window, n)
             assert_guard(base, n, offset, "window %d n=%d" % (window, n))
+
+
+def encoder_sizes(w):
+    """Edges of a chunk, a wave's and a workgroup's part of the smallest tile, and a ragged size in each
+    of the larger tiles' ranges (whose last wave holds 1 element, or all but 1)."""
+    chunk, wave, tile = 256 // w, 4096 // w, 16384 // w
+    small = [1, chunk - 1, chunk, chunk + 1, wave - 1, wave, wave + 1, tile - 1, tile, tile + 1, 3 * tile + wave + 3]
+    return small + ([(25 << 20) // 4 + 1, (41 << 20) // 4 - 1, (160 << 20) // 4 + 1] if w == 4 else
+                    [(65 << 20) // 2 + 1, (65 << 20) // 2 - 1])
+
+
+@pytest.mark.parametrize("w,offset", [(4, 0), (4, 1), (2, 0), (2, 1), (2, 2)])
+def test_encoders_at_every_tile_edge(oracle, w, offset):
+    """The tensor's neighbours in its buffer are not zero: what lies past its end, and before its
+    beginning, must not count."""
+    for n in encoder_sizes(w):
+        dense = random_tensor(n + offset + GUARD, w, 1.0, seed=n + offset)
+        inner = random_tensor(n, w, 0.4, seed=n + offset + 1)
+        dense[offset:offset + n] = inner
+        x = dense[offset:offset + n]
+        host = raw_bytes(inner)
+        say("encode n=%d w=%d offset=%d" % (n, w, offset))
+        expect = oracle.compress_stream(host, w)
+        ws = zvc.new_workspace(n, w, DEV)
+        out = torch.zeros(zvc.zvc_max_compressed_bytes(n, w) + GUARD, dtype=torch.uint8, device=DEV)
+        size = torch.zeros(1, dtype=torch.int64, device=DEV)
+        zvc.zvc_compress(x, out, size, ws)
+        got = out.cpu().numpy()
+        assert int(size.item()) == expect.size and np.array_equal(got[:expect.size], expect), "planar n=%d" % n
+        assert not got[expect.size:].any(), "planar n=%d: written past the stream" % n
+        zvc.zvc_compressed_size(x, size.zero_(), ws)
+        assert int(size.item()) == expect.size, "size n=%d" % n
+        stream, table = oracle.window_compress(host, w, 4096 // w)
+        d_table = torch.zeros(len(table), dtype=torch.int64, device=DEV)
+        zvc.zvc_window_compress(x, out, d_table, size, ws)
+        assert np.array_equal(out[:len(stream)].cpu().numpy(), stream), "windowed n=%d" % n
+        assert d_table.cpu().numpy().astype(np.uint64).tolist() == table.tolist(), "windowed n=%d" % n
