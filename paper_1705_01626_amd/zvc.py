@@ -34,6 +34,7 @@ EXPORTS = ("zvc_status_string", "zvc_mask_bytes", "zvc_max_compressed_bytes",
            "zvc_compress_static", "zvc_reference_stream")
 
 _lib = None
+_calls = None       # the device calls, see csrc/calls.cpp
 
 
 class ZvcError(RuntimeError):
@@ -44,7 +45,7 @@ class ZvcError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the built library (paper_1705_01626_amd/libzvc.so) and declare signatures."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIBRARY):
@@ -99,8 +100,21 @@ def load() -> ctypes.CDLL:
     lib.zvc_reference_stream.argtypes = [vp, sz, vp, sz, vp]
     lib.zvc_workspace_self_help_count.restype = ci
     lib.zvc_workspace_self_help_count.argtypes = [vp, vp]
-    _lib = lib
+    try:
+        from . import _calls as calls
+    except ImportError as e:
+        raise ImportError("%s is not built: run `python -m paper_1705_01626_amd.build`"
+                          % os.path.join(_PKG, "_calls.so")) from e
+    calls.open(LIBRARY)
+    _lib, _calls = lib, calls
     return lib
+
+
+def _native():
+    """The device calls: integers in, status out (loads the library at the first call)."""
+    if _calls is None:
+        load()
+    return _calls
 
 
 def status_string(status: int) -> str:
@@ -112,9 +126,17 @@ def _check(status: int, where: str) -> None:
         raise ZvcError(status, where)
 
 
+# the current stream as an integer, without a Stream object for it (part of what a call from Python saves: 7.4 -> 4.0 us of host time)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device())
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 def element_width(t: torch.Tensor) -> int:
@@ -193,7 +215,7 @@ def zvc_compressed_size(x: torch.Tensor, d_bytes: torch.Tensor, ws: torch.Tensor
                         stream=None, n: Optional[int] = None) -> None:
     """Enqueue the count-only pass; d_bytes (int64[1] on the device) receives the size."""
     n = x.numel() if n is None else n
-    _check(load().zvc_compressed_size(x.data_ptr(), n, x.element_size(), d_bytes.data_ptr(),
+    _check(_native().zvc_compressed_size(x.data_ptr(), n, x.element_size(), d_bytes.data_ptr(),
                                       ws.data_ptr(), ws.numel(), _stream_handle(stream)),
            "zvc_compressed_size")
 
@@ -202,7 +224,7 @@ def zvc_compress(x: torch.Tensor, out: torch.Tensor, d_bytes: torch.Tensor, ws: 
                  stream=None, n: Optional[int] = None) -> None:
     """Enqueue compression of x (any w-byte dtype, contiguous) into the uint8 buffer `out`."""
     n = x.numel() if n is None else n
-    _check(load().zvc_compress(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
+    _check(_native().zvc_compress(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
                                d_bytes.data_ptr(), ws.data_ptr(), ws.numel(),
                                _stream_handle(stream)), "zvc_compress")
 
@@ -215,7 +237,7 @@ def zvc_compress_static(x: torch.Tensor, out: torch.Tensor, d_bytes: torch.Tenso
     """zvc_compress without a workspace argument: the scan state lives in an array inside the
     library (for callers that cannot allocate).  Calls on one GPU must not overlap."""
     n = x.numel() if n is None else n
-    _check(load().zvc_compress_static(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
+    _check(_native().zvc_compress_static(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
                                       d_bytes.data_ptr(), _stream_handle(stream)), "zvc_compress_static")
 
 
@@ -223,7 +245,7 @@ def zvc_relu_compress(x: torch.Tensor, out: torch.Tensor, d_bytes: torch.Tensor,
                       stream=None, n: Optional[int] = None) -> None:
     """Enqueue compression of ReLU(x) (x: fp32, fp16 or bf16 pre-activations) into `out`."""
     n = x.numel() if n is None else n
-    _check(load().zvc_relu_compress(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
+    _check(_native().zvc_relu_compress(x.data_ptr(), n, x.element_size(), out.data_ptr(), out.numel(),
                                     d_bytes.data_ptr(), ws.data_ptr(), ws.numel(),
                                     _stream_handle(stream)), "zvc_relu_compress")
 
@@ -234,19 +256,19 @@ def zvc_compress_bounded(x: torch.Tensor, out: torch.Tensor, d_bytes: torch.Tens
     """Enqueue compression of x (relu: of ReLU(x)) into `out`, which may be smaller than the
     worst case; d_bytes receives the size needed, to be compared with the capacity."""
     n = x.numel() if n is None else n
-    _check(load().zvc_compress_bounded(x.data_ptr(), n, x.element_size(), int(bool(relu)),
+    _check(_native().zvc_compress_bounded(x.data_ptr(), n, x.element_size(), int(bool(relu)),
                                        out.data_ptr(), out.numel() if out_cap is None else out_cap,
                                        d_bytes.data_ptr(), ws.data_ptr(), ws.numel(),
                                        _stream_handle(stream)), "zvc_compress_bounded")
 
 
 def zvc_window_count(n: int, w: int, window_bytes: int = WINDOW_PAPER_BYTES) -> int:
-    return int(load().zvc_window_count(n, w, window_bytes))
+    return _native().zvc_window_count(n, w, window_bytes)
 
 
 def zvc_window_elements(w: int, window_bytes: int = WINDOW_PAPER_BYTES) -> int:
     """Elements per window; 0 for a width or window size the library does not take."""
-    return int(load().zvc_window_elements(w, window_bytes))
+    return _native().zvc_window_elements(w, window_bytes)
 
 
 def zvc_window_compress(x: torch.Tensor, out: torch.Tensor, offsets: torch.Tensor,
@@ -255,10 +277,10 @@ def zvc_window_compress(x: torch.Tensor, out: torch.Tensor, offsets: torch.Tenso
     """Enqueue compression of x into the paper-order windowed stream `out` (uint8) and its
     offset table `offsets` (int64, zvc_window_count + 1 entries)."""
     n = x.numel()
-    if zvc_window_elements(x.element_size(), window_bytes) != 0 and \
-            offsets.numel() < zvc_window_count(n, x.element_size(), window_bytes) + 1:
+    if offsets.numel() < zvc_window_count(n, x.element_size(), window_bytes) + 1 and \
+            zvc_window_elements(x.element_size(), window_bytes) != 0:
         raise ZvcError(ZVC_E_CAPACITY, "zvc_window_compress (offset table too small)")
-    _check(load().zvc_window_compress(x.data_ptr(), n, x.element_size(), window_bytes, out.data_ptr(),
+    _check(_native().zvc_window_compress(x.data_ptr(), n, x.element_size(), window_bytes, out.data_ptr(),
                                       out.numel(), offsets.data_ptr(), d_bytes.data_ptr(), ws.data_ptr(),
                                       ws.numel(), _stream_handle(stream)), "zvc_window_compress")
 
@@ -273,7 +295,7 @@ def zvc_window_decompress(comp: torch.Tensor, comp_bytes: int, offsets: torch.Te
     if out.numel() < need:
         raise ZvcError(ZVC_E_CAPACITY, "zvc_window_decompress (output holds %d elements, %d needed)"
                        % (out.numel(), need))
-    _check(load().zvc_window_decompress(comp.data_ptr(), comp_bytes, offsets.data_ptr(), n, w, window_bytes,
+    _check(_native().zvc_window_decompress(comp.data_ptr(), comp_bytes, offsets.data_ptr(), n, w, window_bytes,
                                         first_window, num_windows, out.data_ptr(),
                                         _stream_handle(stream)), "zvc_window_decompress")
 
@@ -282,7 +304,7 @@ def zvc_decompress(comp: torch.Tensor, comp_bytes: int, out: torch.Tensor, ws: t
                    stream=None, n: Optional[int] = None) -> None:
     """Enqueue decompression of the first comp_bytes bytes of `comp` into `out`."""
     n = out.numel() if n is None else n
-    _check(load().zvc_decompress(comp.data_ptr(), comp_bytes, n, out.element_size(),
+    _check(_native().zvc_decompress(comp.data_ptr(), comp_bytes, n, out.element_size(),
                                  out.data_ptr(), ws.data_ptr(), ws.numel(),
                                  _stream_handle(stream)), "zvc_decompress")
 
@@ -292,7 +314,7 @@ def zvc_offload(x: torch.Tensor, stage: torch.Tensor, h_pinned: torch.Tensor,
                 copy: torch.cuda.Stream) -> int:
     """Compress x into `stage` on `compute`, then copy exactly the compressed bytes to the
     pinned host tensor on `copy`.  Returns the compressed size (the call waits for it)."""
-    _check(load().zvc_offload(x.data_ptr(), x.numel(), x.element_size(), stage.data_ptr(),
+    _check(_native().zvc_offload(x.data_ptr(), x.numel(), x.element_size(), stage.data_ptr(),
                               stage.numel(), h_pinned.data_ptr(), h_pinned.numel(),
                               h_bytes.data_ptr(), ws.data_ptr(), ws.numel(),
                               _stream_handle(compute), _stream_handle(copy)), "zvc_offload")
@@ -304,7 +326,7 @@ def zvc_relu_offload(x: torch.Tensor, stage: torch.Tensor, h_pinned: torch.Tenso
                      copy: torch.cuda.Stream) -> int:
     """zvc_offload with the fused ReLU encoder: x holds pre-activations, the host gets the
     stream of ReLU(x)."""
-    _check(load().zvc_relu_offload(x.data_ptr(), x.numel(), x.element_size(), stage.data_ptr(),
+    _check(_native().zvc_relu_offload(x.data_ptr(), x.numel(), x.element_size(), stage.data_ptr(),
                                    stage.numel(), h_pinned.data_ptr(), h_pinned.numel(),
                                    h_bytes.data_ptr(), ws.data_ptr(), ws.numel(),
                                    _stream_handle(compute), _stream_handle(copy)), "zvc_relu_offload")
@@ -315,7 +337,7 @@ def zvc_prefetch(h_pinned: torch.Tensor, nbytes: int, stage: torch.Tensor, out: 
                  ws: torch.Tensor, copy: torch.cuda.Stream, compute: torch.cuda.Stream) -> None:
     """Copy nbytes of compressed data back to `stage` on `copy`, then decompress into `out`
     on `compute` (ordered after the copy)."""
-    _check(load().zvc_prefetch(h_pinned.data_ptr(), nbytes, out.numel(), out.element_size(),
+    _check(_native().zvc_prefetch(h_pinned.data_ptr(), nbytes, out.numel(), out.element_size(),
                                stage.data_ptr(), stage.numel(), out.data_ptr(), ws.data_ptr(),
                                ws.numel(), _stream_handle(copy), _stream_handle(compute)),
            "zvc_prefetch")

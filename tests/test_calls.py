@@ -1,0 +1,49 @@
+"""The device calls as Python reaches them (csrc/calls.cpp): the same statuses as through ctypes for
+arguments that the library refuses before any GPU work, and errors for what is no integer."""
+import pytest
+
+from paper_1705_01626_amd import zvc
+
+IN, OUT, BYTES, WS = 1 << 20, 2 << 20, 3 << 20, 4 << 20
+BIG = 1 << 40
+
+REFUSED = [
+    ("zvc_compress", (IN, 100, 3, OUT, BIG, BYTES, WS, BIG, 0)),
+    ("zvc_compress", (IN, 100, 4, OUT, 10, BYTES, WS, BIG, 0)),
+    ("zvc_compress", (IN + 1, 100, 2, OUT, BIG, BYTES, WS, BIG, 0)),
+    ("zvc_compress", (0, 100, 4, OUT, BIG, BYTES, WS, BIG, 0)),
+    ("zvc_compress_static", (IN, 1 << 40, 4, OUT, BIG, BYTES, 0)),
+    ("zvc_relu_compress", (IN, 100, 4, OUT, BIG, BYTES, WS + 8, BIG, 0)),
+    ("zvc_compress_bounded", (IN, 100, 4, 2, OUT, BIG, BYTES, WS, BIG, 0)),
+    ("zvc_compressed_size", (IN, 100, 4, BYTES + 4, WS, BIG, 0)),
+    ("zvc_decompress", (IN, 1, 100, 4, OUT, WS, BIG, 0)),
+    ("zvc_window_compress", (IN, 100, 4, 4097, OUT, BIG, BYTES, BYTES + 64, WS, BIG, 0)),
+    ("zvc_window_decompress", (IN, 100, BYTES, 100, 4, 4096, 5, 1, OUT, 0)),
+    ("zvc_offload", (IN, 100, 4, OUT, BIG, 0, 10, BYTES, WS, BIG, 0, 0)),
+    ("zvc_relu_offload", (IN, 100, 5, OUT, BIG, 0, 10, BYTES, WS, BIG, 0, 0)),
+    ("zvc_prefetch", (IN, 3, 100, 4, OUT, BIG, BYTES, WS, BIG, 0, 0)),
+    ("zvc_window_count", (100000, 4, 4096)),
+    ("zvc_window_elements", (2, 65536)),
+]
+
+
+@pytest.mark.parametrize("name,args", REFUSED)
+def test_same_result_as_ctypes(name, args):
+    want = getattr(zvc.load(), name)(*args)
+    assert getattr(zvc._native(), name)(*args) == want
+    if name not in ("zvc_window_count", "zvc_window_elements"):
+        assert want != zvc.ZVC_OK
+
+
+def test_what_is_no_call_is_an_error():
+    calls = zvc._native()
+    with pytest.raises(TypeError):
+        calls.zvc_window_count(100000, 4)
+    with pytest.raises(TypeError):
+        calls.zvc_window_count(100000, 4, "4096")
+    with pytest.raises(TypeError):
+        calls.zvc_window_count(1.5, 4, 4096)
+    assert calls.zvc_window_count(-1, 4, 4096) == zvc.load().zvc_window_count(-1, 4, 4096)
+    with pytest.raises(ImportError):
+        calls.open("/nowhere/libzvc.so")
+    assert calls.zvc_window_elements(4, 4096) == 1024
