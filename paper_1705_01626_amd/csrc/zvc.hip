@@ -664,17 +664,6 @@ __device__ inline bool kept_second(unsigned x) {
     return RELU ? static_cast<int>(x) > 0xFFFF : x > 0xFFFFu;
 }
 
-// Bits of `even` and `odd` interleaved: bit 2i of the result is bit i of even,
-// bit 2i+1 is bit i of odd (wave-uniform operands, scalar unit).  With 16-bit
-// elements a lane holds two neighbours, so the ballots of the first and of the
-// second elements zip into the masks.
-__device__ inline unsigned long long zip_bits(unsigned even, unsigned odd) {
-    unsigned long long e, o;
-    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(e) : "s"(even));
-    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(o) : "s"(odd));
-    return (e & 0x5555555555555555ull) | (o & 0xAAAAAAAAAAAAAAAAull);
-}
-
 // The 16 low bits of v moved apart: bit i goes to bit 2i.
 __device__ inline unsigned spread_bits(unsigned v) {
     v = (v | (v << 8)) & 0x00FF00FFu;
@@ -828,12 +817,29 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     unsigned q_lo = 0, q_end = 0;                 // the wave's queue: slice offsets, wave-uniform
     unsigned zero_local = 0;                      // offset within the wave's run of slice offset 0
     unsigned window_local = 0;                    // lane i: offset within the wave's run of its window i
-    // groups of the tensor among `count` groups of this wave from `first_group` on (fewer where the tensor ends)
-    const auto groups_from = [&](int first_group, int count) -> unsigned {
-        const size_t g = wave_group0 + static_cast<size_t>(first_group);
-        return g >= a.num_groups ? 0u
-             : a.num_groups - g < static_cast<size_t>(count) ? static_cast<unsigned>(a.num_groups - g)
-                                                             : static_cast<unsigned>(count);
+    // groups of the tensor in this wave's part, and among `count` of them from `first_group` on
+    const unsigned groups_here =
+        wave_group0 >= a.num_groups ? 0u
+        : a.num_groups - wave_group0 < static_cast<size_t>(G::kWaveGroups) ? static_cast<unsigned>(a.num_groups - wave_group0)
+                                                                           : static_cast<unsigned>(G::kWaveGroups);
+    const auto groups_from = [&](unsigned first_group, unsigned count) -> unsigned {
+        return first_group >= groups_here ? 0u : min(count, groups_here - first_group);
+    };
+    // 16-bit elements: masks from a register with 32 bits of the first elements' ballot in every even
+    // lane and one with the same 32 bits of the second elements' ballot.  An even lane zips the low
+    // halves into its mask, its odd neighbour (which reads them with a DPP row shift) the high halves
+    // into the next mask.
+    const auto zip_ballot_lanes = [&](unsigned first, unsigned second) __attribute__((always_inline)) -> unsigned {
+        // (a DPP read of a register needs two wait states after the instruction that wrote it;
+        // the compiler sees the lane writes only as opaque statements)
+        asm volatile("s_nop 1" : "+v"(first), "+v"(second));
+        const unsigned first_prev =
+            static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(first), 0x111, 0xF, 0xF, true));
+        const unsigned second_prev =
+            static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(second), 0x111, 0xF, 0xF, true));
+        const bool odd_lane = (lane & 1) != 0;
+        return spread_bits(odd_lane ? first_prev >> 16 : first & 0xFFFFu) |
+               (spread_bits(odd_lane ? second_prev >> 16 : second & 0xFFFFu) << 1);
     };
 
     // One chunk.  TEST: its masks and its share of the totals.  STAGE: its kept
@@ -851,57 +857,71 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         const unsigned chunk_groups = STAGE && WINDOWED ? groups_from(k * CG, CG) : 0u;
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
             set_lane<k / kWindowChunks>(window_local, zero_local + q_end);
+        // (windowed: the lane's group has its mask, and the masks of the chunk's earlier groups, before it;
+        // write_step_masks() puts the masks there)
         if constexpr (W == 4) {
             const bool keep = kept_first<4, RELU>(x);
             const unsigned long long b = __ballot(keep);
             const unsigned kept = static_cast<unsigned>(__popcll(b));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
-                if (!WINDOWED)
-                    set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
+                set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
             }
             if (STAGE) {
-                // windowed: the lane's group has its mask, and the masks of the chunk's earlier groups, before it
                 const unsigned at = 4u * lanes_below(b, 0u) + q_end + (WINDOWED ? 4u + 4u * (lane >> 5) : 0u);
                 if (__builtin_expect(keep, 1)) *reinterpret_cast<unsigned*>(stage + at) = x;   // predicated, no branch
-                if (WINDOWED && (lane & 31) == 0 && static_cast<unsigned>(lane >> 5) < chunk_groups)
-                    *reinterpret_cast<unsigned*>(stage + at - 4u) =
-                        lane == 0 ? static_cast<unsigned>(b) : static_cast<unsigned>(b >> 32);
                 q_end += 4u * kept + 4u * chunk_groups;
             }
         } else {
             const bool keep0 = kept_first<2, RELU>(x), keep1 = kept_second<RELU>(x);
             const unsigned long long be = __ballot(keep0), bo = __ballot(keep1);
             const unsigned kept = static_cast<unsigned>(__popcll(be)) + static_cast<unsigned>(__popcll(bo));
-            unsigned long long z0 = 0, z1 = 0;
-            if (STAGE && WINDOWED) {
-                z0 = zip_bits(static_cast<unsigned>(be), static_cast<unsigned>(bo));
-                z1 = zip_bits(static_cast<unsigned>(be >> 32), static_cast<unsigned>(bo >> 32));
-            }
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
-                if (!WINDOWED) {
-                    // The ballots as they are, 32 bits each in lanes 4k and 4k+2 (two masks' worth of
-                    // first elements in mask_reg, of second elements in second_reg): they are zipped
-                    // into the four masks once per wave, on the vector unit (zip_ballot_lanes),
-                    // which measures 8-15 % faster than zipping every chunk on the scalar unit.
-                    set_lanes<(4 * k) % kWaveSize, (4 * k + 2) % kWaveSize>(mask_reg[(4 * k) / kWaveSize], be);
-                    set_lanes<(4 * k) % kWaveSize, (4 * k + 2) % kWaveSize>(second_reg[(4 * k) / kWaveSize], bo);
-                }
+                // The ballots as they are, 32 bits each in lanes 4k and 4k+2 (two masks' worth of
+                // first elements in mask_reg, of second elements in second_reg): they are zipped
+                // into the four masks once per wave (windowed: once per step), on the vector unit,
+                // which measures 8-15 % faster than zipping every chunk on the scalar unit.
+                set_lanes<(4 * k) % kWaveSize, (4 * k + 2) % kWaveSize>(mask_reg[(4 * k) / kWaveSize], be);
+                set_lanes<(4 * k) % kWaveSize, (4 * k + 2) % kWaveSize>(second_reg[(4 * k) / kWaveSize], bo);
             }
             if (STAGE) {
                 const unsigned at = 2u * lanes_below(bo, lanes_below(be, 0u)) + q_end +
                                     (WINDOWED ? 4u + 4u * (lane >> 4) : 0u);
-                if (WINDOWED && (lane & 15) == 0 && static_cast<unsigned>(lane >> 4) < chunk_groups) {
-                    const unsigned m = lane == 0 ? static_cast<unsigned>(z0)
-                                     : lane == 16 ? static_cast<unsigned>(z0 >> 32)
-                                     : lane == 32 ? static_cast<unsigned>(z1) : static_cast<unsigned>(z1 >> 32);
-                    *reinterpret_cast<unsigned short*>(stage + at - 4u) = static_cast<unsigned short>(m);
-                    *reinterpret_cast<unsigned short*>(stage + at - 2u) = static_cast<unsigned short>(m >> 16);
-                }
                 if (__builtin_expect(keep0, 1)) *reinterpret_cast<unsigned short*>(stage + at) = static_cast<unsigned short>(x);
                 if (__builtin_expect(keep1, 1)) *reinterpret_cast<unsigned short*>(stage + at + (keep0 ? 2u : 0u)) = static_cast<unsigned short>(x >> 16);
                 q_end += 2u * kept + 4u * chunk_groups;
+            }
+        }
+    };
+    // Windowed: the masks of step h, which was staged from queue offset q_step on, into the gaps that
+    // its chunks left for them: a lane per mask, whose place is the sum of the sizes of the step's
+    // groups before it (a scan over 16 or 32 lanes).  Per step instead of per chunk: 89.1 ->
+    // 87.7 us for 297 MB fp32, 87.8 -> 59.9 us for 149 MB bf16 (whose chunks zipped their masks on
+    // the scalar unit).
+    const auto write_step_masks = [&](auto hc, unsigned q_step) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        constexpr int reg = h * G::kStepGroups / kWaveSize, lane0 = h * G::kStepGroups % kWaveSize;
+        static_assert(G::kStepGroups == 16 || G::kStepGroups == 32, "one or two rows of lanes");
+        unsigned mask = mask_reg[reg];
+        if (W == 2) mask = zip_ballot_lanes(mask, second_reg[W == 2 ? reg : 0]);
+        else asm volatile("s_nop 1" : "+v"(mask));            // (as in zip_ballot_lanes)
+        const unsigned size = 4u + W * static_cast<unsigned>(__popc(mask));
+        unsigned upto = size;
+        upto += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(upto), 0x111, 0xF, 0xF, true));
+        upto += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(upto), 0x112, 0xF, 0xF, true));
+        upto += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(upto), 0x114, 0xF, 0xF, true));
+        upto += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(upto), 0x118, 0xF, 0xF, true));
+        if (G::kStepGroups == 32)                             // the first row's sum to the second row (and the third's to the fourth)
+            upto += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(upto), 0x142, 0xA, 0xF, false));
+        unsigned char* const at = stage + (q_step + upto - size);
+        const int group = lane - lane0;
+        if (group >= 0 && group < G::kStepGroups && static_cast<unsigned>(h * G::kStepGroups + group) < groups_here) {
+            if (W == 4) {
+                *reinterpret_cast<unsigned*>(at) = mask;
+            } else {
+                *reinterpret_cast<unsigned short*>(at) = static_cast<unsigned short>(mask);
+                *reinterpret_cast<unsigned short*>(at + 2) = static_cast<unsigned short>(mask >> 16);
             }
         }
     };
@@ -951,10 +971,12 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
         if (staged == h && q_end + G::kStepMaxBytes <= static_cast<unsigned>(G::kQueueBytes)) {
+            const unsigned q_step = q_end;
             static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
                 chunk(kc, yes, yes);
                 __builtin_amdgcn_sched_barrier(0);
             });
+            if constexpr (WINDOWED) write_step_masks(hc, q_step);
             staged = h + 1;
         } else {
             static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
@@ -979,23 +1001,9 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     if (publisher && lane == 0)
         store32(a.counts + tile, kCountValid | ((arrived & 0xFFFFFFu) + wave_total));
 
-    if (!WINDOWED && W == 2) {
-        // zip_ballot_lanes: an even lane holds 32 bits of the first elements' ballot and the same
-        // 32 bits of the second elements' ballot.  It zips the low halves into its mask, its odd
-        // neighbour (which reads them with a DPP row shift) the high halves into the next mask.
+    if constexpr (!WINDOWED && W == 2) {
 #pragma unroll
-        for (int r = 0; r < G::kMaskRegs; ++r) {
-            // (a DPP read of a register needs two wait states after the instruction that wrote it;
-            // the compiler sees the lane writes above only as opaque statements)
-            asm volatile("s_nop 1" : "+v"(mask_reg[r]), "+v"(second_reg[r]));
-            const unsigned first_prev =
-                static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(mask_reg[r]), 0x111, 0xF, 0xF, true));
-            const unsigned second_prev =
-                static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(second_reg[r]), 0x111, 0xF, 0xF, true));
-            const bool odd_lane = (lane & 1) != 0;
-            mask_reg[r] = spread_bits(odd_lane ? first_prev >> 16 : mask_reg[r] & 0xFFFFu) |
-                          (spread_bits(odd_lane ? second_prev >> 16 : second_reg[r] & 0xFFFFu) << 1);
-        }
+        for (int r = 0; r < G::kMaskRegs; ++r) mask_reg[r] = zip_ballot_lanes(mask_reg[r], second_reg[r]);
     }
     if (!WINDOWED) {
 #pragma unroll
@@ -1013,10 +1021,12 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     };
     const auto stage_step = [&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
+        const unsigned q_step = q_end;
         static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
             chunk(kc, no, yes);
             __builtin_amdgcn_sched_barrier(0);
         });
+        if constexpr (WINDOWED) write_step_masks(hc, q_step);
     };
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
@@ -2123,9 +2133,9 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 // with 16 | 32 | 64 KB tiles, density 0.5 (windowed fp32: 0.1 to 0.9):
 //   fp32      12 MB 7.7 | 9.0 | 9.0   24 MB 10.6 | 10.1 | 11.5   48 MB 18.3 | 14.9 | 16.0
 //            103 MB 35.4 | 31.2 | 32.4   200 MB 65.7 | 57.4 | 55.1
-//   windowed  24 MB 14.1 | 14.6   48 MB 22.8 | 22.1   (822 MB: nothing gained from 64 KB)
+//   windowed  24 MB 14.2 | 14.3   48 MB 22.0 | 20.8   103 MB 38.9 | 36.5   (822 MB: nothing gained from 64 KB)
 //   16-bit    24 MB 11.8 | 12.4   51 MB 21.4 | 21.8   100 MB 37.0 | 35.6   411 MB 136 | 117
-//   windowed 100 MB 55.5 | 59.0   200 MB 104 | 104   411 MB 207 | 197
+//   windowed 100 MB 42.4 | 43.3   149 MB 60.3 | 59.9   200 MB 76.2 | 75.0   411 MB 148 | 140
 // 16-bit elements are twice the vector work per byte, and the 32 KB tile's eight
 // waves per SIMD (against four) hide it better: 64 KB tiles lose up to 9 % there.
 // (8 KB tiles, and 8 or 16 waves per tile, were no faster at any size.)
@@ -2139,7 +2149,7 @@ static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16
 
 inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    const size_t medium = w == 4 ? size_t{windowed ? 40u : 24u} << 20 : size_t{windowed ? 200u : 48u} << 20;
+    const size_t medium = w == 4 ? size_t{windowed ? 32u : 24u} << 20 : size_t{windowed ? 160u : 48u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }
