@@ -1,7 +1,8 @@
-"""ctypes binding of libzvc.so (C ABI in include/zvc.h).
+"""Binding of libzvc.so (C ABI in include/zvc.h).
 
 Argument marshalling only: torch tensors supply device memory and streams, the
-library's HIP kernels do all the work.  There is no CPU fallback: if the
+library's HIP kernels do all the work.  Host arithmetic goes through ctypes, the
+device calls through the extension module _calls (csrc/calls.cpp).  There is no CPU fallback: if the
 library is missing, `load()` raises.
 """
 from __future__ import annotations
