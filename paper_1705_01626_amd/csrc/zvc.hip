@@ -945,14 +945,19 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                                   : bytes - wave_byte0 < most ? static_cast<unsigned>(bytes - wave_byte0) : most;
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<unsigned char*>(a.in) - (SPLIT ? 2 : 0) + wave_byte0, 0, static_cast<int>(readable), kRawBuffer);
+        // The descriptor's range check covers the vector and the immediate offset, not the scalar one,
+        // which is zero throughout: the immediate reaches 16 chunks, a register each takes the lanes to
+        // the next 16.
+        int lane_byte[CH / 16];
+#pragma unroll
+        for (int j = 0; j < CH / 16; ++j) lane_byte[j] = 4 * lane + j * 16 * kChunkBytes;
         static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            constexpr int step = k / 16 * 16 * kChunkBytes;
-            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane + k % 16 * kChunkBytes, step, kNonTemporal);
+            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_byte[k / 16] + k % 16 * kChunkBytes, 0, kNonTemporal);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
         if constexpr (SPLIT)
-            cur[CH] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, CH % 16 * kChunkBytes, CH / 16 * 16 * kChunkBytes, 0);
+            cur[CH] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, CH * kChunkBytes, 0, 0);
         // the second half of the last dword is not the tensor's
         const size_t half = a.n / 2;             // the dword with element n - 1 (n odd), or with element n in its first half
         if (W == 2 && (a.n & 1u) != (SPLIT ? 1u : 0u) && half >= wave_dword0 && half - wave_dword0 < CH * kWaveSize) {
