@@ -1616,36 +1616,31 @@ __device__ inline unsigned walk_masks(const unsigned char* stage, unsigned p, un
     return p;
 }
 
-// A damaged mask can ask for more elements than are staged (`beyond`, of any lane):
-// the rest of the wave's LDS slice is zeroed for it.
+// What a mask asks for beyond the bytes that are there decodes as zero, an element
+// that is only partly there included: the mask without its bits for elements that are
+// not wholly before `limit` (its highest ones).  `at`: LDS offset of the group's first
+// stored element.  Only damaged or cut streams enter the loop.
 template <int W>
-__device__ inline void zero_beyond(bool beyond, unsigned char* stage, unsigned limit, unsigned slice_bytes, int lane) {
-    if (__ballot(beyond) != 0ull) {
-        for (unsigned i = limit + W * lane; i + W <= slice_bytes; i += W * kWaveSize) {
-            if (W == 4) *reinterpret_cast<unsigned*>(stage + i) = 0u;
-            else *reinterpret_cast<unsigned short*>(stage + i) = 0;
-        }
-        wave_lds_sync();
-    }
+__device__ inline unsigned whole_elements(unsigned mask, unsigned at, unsigned limit) {
+    const unsigned room = limit > at ? (limit - at) / W : 0u;
+    while (static_cast<unsigned>(__popc(mask)) > room) mask &= ~(0x80000000u >> __clz(mask));
+    return mask;
 }
 
 // After a walk: the records' offsets become those of the groups' first stored
 // elements, and masks that are not there (from record `groups` on, or not wholly
 // before `limit`) become empty.
 template <int W>
-__device__ inline void empty_missing_groups(uint2* record, int records, unsigned groups, unsigned char* stage,
-                                            unsigned limit, unsigned slice_bytes, int lane) {
+__device__ inline void empty_missing_groups(uint2* record, int records, unsigned groups, unsigned limit, int lane) {
     wave_lds_sync();
-    bool beyond = false;
     if (lane < records) {
         uint2 group = record[lane];
         if (static_cast<unsigned>(lane) >= groups || group.y + 4u > limit) group.x = 0u;
         group.y += 4u;
-        beyond = group.y + W * static_cast<unsigned>(__popc(group.x)) > limit;
+        group.x = whole_elements<W>(group.x, group.y, limit);
         record[lane] = group;
     }
     wave_lds_sync();
-    zero_beyond<W>(beyond, stage, limit, slice_bytes, lane);
 }
 
 // Output of up to UNITS KB, elements elem0 .. elem_end - 1 of the tensor (elem_end -
@@ -1705,7 +1700,7 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     size_t first_window, size_t num_windows, unsigned window_shift, unsigned char* __restrict__ out,
     bool interleave) {
     using G = WindowGeometry<W>;
-    // shift < 16, then a piece, then what a mask that ends on its last byte can ask for
+    // shift < 16, then a piece, then what a walk that is past its end reads
     constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + G::kGroupBytes + 15) / 16 * 16;
     __shared__ __align__(16) unsigned char s_stage[kWaves][kSliceBytes];
     __shared__ __align__(16) uint2 s_group[kWaves][G::kPieceGroups];
@@ -1770,7 +1765,7 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
             }
             walk_end = walk_masks<W>(stage, p, cur_limit, walker_groups, s_group[wave] + lane * walker_groups);
         }
-        empty_missing_groups<W>(s_group[wave], G::kPieceGroups, groups_here, stage, cur_limit, kSliceBytes, lane);
+        empty_missing_groups<W>(s_group[wave], G::kPieceGroups, groups_here, cur_limit, lane);
 
         // ---- a large window's next piece begins where lane 0's walk ended (never beyond the
         // window).  (Asking for its bytes here, before this piece is expanded, measured no faster.)
@@ -1822,7 +1817,7 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
     constexpr int kParts = 4;                               // per wave
     constexpr unsigned kBatch = 32;                         // groups expanded at a time
     constexpr unsigned kPositions = 128;                    // groups of a wave whose walk is recorded at once
-    // shift < 16, parts with nothing dropped, the rest of their last group, what a damaged mask can ask for
+    // shift < 16, parts with nothing dropped, the rest of their last group, what a walk that is past them reads
     constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + kParts * W + 2 * G::kGroupBytes + 15) / 16 * 16;
     static_assert(kSliceBytes <= kFetchSlots * kWaveSize * 16, "a wave's parts fit the fetch slots");
     __shared__ __align__(16) unsigned char s_stage[NW * kSliceBytes];
@@ -1851,7 +1846,7 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
     const unsigned readable = min(kParts * part + G::kGroupBytes, bytes - wave0);
     const unsigned char* src = stream + lo + wave0;
     const unsigned skew = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
-    const unsigned slice = wave * kSliceBytes, slice_end = slice + kSliceBytes;
+    const unsigned slice = wave * kSliceBytes;
     const unsigned begin = slice + skew, limit = begin + readable;
     {
         uint4 fetched[kFetchSlots];
@@ -1948,10 +1943,9 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
         unsigned mask = 0, value = limit;
         if (static_cast<unsigned>(lane) < here) {
             const unsigned m = slice + s_at[wave][(at_once ? g - first : 0u) + lane];
-            mask = lds_mask<W>(s_stage + m);
             value = m + 4u;
+            mask = whole_elements<W>(lds_mask<W>(s_stage + m), value, limit);
         }
-        zero_beyond<W>(value + W * static_cast<unsigned>(__popc(mask)) > limit, s_stage, limit, slice_end, lane);
         const size_t elem0 = window_elem0 + static_cast<size_t>(g) * 32;
         expand_groups<W, kBatch / G::kUnitGroups, ALIGNED>(
             s_stage, [&](int i) { return make_uint2(__shfl(mask, i), __shfl(value, i)); }, elem0,

@@ -44,7 +44,10 @@ def test_streams_that_end_early(oracle, window, w):
         d_stream = torch.from_numpy(stream).to(DEV)
         d_table = torch.from_numpy(table.astype(np.int64)).to(DEV)
         total = int(table[-1])
-        for end in {total, total - w, total // 2 // w * w, total // 5 // w * w + w, 8, 4, 0}:
+        half, fifth = total // 2 // w * w, total // 5 // w * w
+        # whole words, and ends inside an element or a mask
+        for end in {total, total - w, half, fifth + w, 8, 4, 0,
+                    total - 1, total - 2, total - 3, half + 1, half + 3, fifth + 2, 9, 6, 3}:
             say("early end window=%d w=%d d=%.2f end=%d of %d" % (window, w, density, end, total))
             out = torch.empty(n, dtype=x.dtype, device=DEV)
             out.view(torch.uint8).fill_(0xEE)
