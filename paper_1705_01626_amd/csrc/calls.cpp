@@ -32,6 +32,9 @@ R call(R (*f)(Params...), const unsigned long long* words, std::index_sequence<I
 template <auto F>
 decltype(F) g_function = nullptr;
 
+// Raised for an argument that is no integer: ctypes.ArgumentError, as before this module, and a TypeError.
+PyObject* g_argument_error = nullptr;
+
 template <auto F, typename R, typename... Params>
 PyObject* forward(R (*)(Params...), PyObject* const* args, Py_ssize_t count) {
     constexpr Py_ssize_t kParams = sizeof...(Params);
@@ -46,7 +49,14 @@ PyObject* forward(R (*)(Params...), PyObject* const* args, Py_ssize_t count) {
     unsigned long long words[kParams];
     for (Py_ssize_t i = 0; i < kParams; ++i) {
         words[i] = PyLong_AsUnsignedLongLongMask(args[i]);
-        if (words[i] == ~0ull && PyErr_Occurred()) return nullptr;
+        if (words[i] == ~0ull && PyErr_Occurred()) {
+            if (PyErr_ExceptionMatches(PyExc_TypeError)) {
+                PyErr_Clear();
+                PyErr_Format(g_argument_error, "argument %zd: an integer expected, %s given", i + 1,
+                             Py_TYPE(args[i])->tp_name);
+            }
+            return nullptr;
+        }
     }
     R result;
     Py_BEGIN_ALLOW_THREADS
@@ -101,4 +111,16 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__calls() {
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (ctypes == nullptr) return nullptr;
+    PyObject* base = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    if (base == nullptr) return nullptr;
+    PyObject* bases = PyTuple_Pack(2, base, PyExc_TypeError);
+    Py_DECREF(base);
+    if (bases == nullptr) return nullptr;
+    g_argument_error = PyErr_NewException("paper_1705_01626_amd._calls.ArgumentError", bases, nullptr);
+    Py_DECREF(bases);
+    return g_argument_error == nullptr ? nullptr : PyModule_Create(&module);
+}

@@ -1,6 +1,9 @@
 """The device calls as Python reaches them (csrc/calls.cpp): the same statuses as through ctypes for
 arguments that the library refuses before any GPU work, and errors for what is no integer."""
+import ctypes
+
 import pytest
+import torch
 
 from paper_1705_01626_amd import zvc
 
@@ -47,3 +50,15 @@ def test_what_is_no_call_is_an_error():
     with pytest.raises(ImportError):
         calls.open("/nowhere/libzvc.so")
     assert calls.zvc_window_elements(4, 4096) == 1024
+
+
+@pytest.mark.parametrize("size", [1000.0, "1000", None, (1000,)])
+def test_what_is_no_integer_raises_the_error_of_ctypes(size):
+    """... which callers of the functions may catch."""
+    with pytest.raises(ctypes.ArgumentError):
+        zvc.load().zvc_window_count(size, 4, 4096)
+    with pytest.raises(ctypes.ArgumentError):
+        zvc.zvc_window_count(size, 4)
+    buffer = torch.zeros(8192, dtype=torch.uint8)
+    with pytest.raises(ctypes.ArgumentError):
+        zvc._native().zvc_decompress(buffer.data_ptr(), size, 100, 4, buffer.data_ptr(), buffer.data_ptr(), 0, 0)
