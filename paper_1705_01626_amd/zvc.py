@@ -46,7 +46,7 @@ class ZvcError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the built library (paper_1705_01626_amd/libzvc.so) and declare signatures."""
-    global _lib, _calls
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIBRARY):
@@ -101,21 +101,25 @@ def load() -> ctypes.CDLL:
     lib.zvc_reference_stream.argtypes = [vp, sz, vp, sz, vp]
     lib.zvc_workspace_self_help_count.restype = ci
     lib.zvc_workspace_self_help_count.argtypes = [vp, vp]
-    try:
-        from . import _calls as calls
-    except ImportError as e:
-        raise ImportError("%s is not built: run `python -m paper_1705_01626_amd.build`"
-                          % os.path.join(_PKG, "_calls.so")) from e
-    calls.open(LIBRARY)
-    _lib, _calls = lib, calls
+    _lib = lib
     return lib
 
 
 def _native():
-    """The device calls: integers in, status out (loads the library at the first call)."""
-    if _calls is None:
+    """The device calls: integers in, status out (loads the library at the first call, which several
+    threads may make at once: what is returned is ready, whoever made it)."""
+    global _calls
+    calls = _calls
+    if calls is None:
         load()
-    return _calls
+        try:
+            from . import _calls as calls
+        except ImportError as e:
+            raise ImportError("%s is not built: run `python -m paper_1705_01626_amd.build`"
+                              % os.path.join(_PKG, "_calls.so")) from e
+        calls.open(LIBRARY)
+        _calls = calls
+    return calls
 
 
 def status_string(status: int) -> str:

@@ -62,3 +62,10 @@ def test_what_is_no_integer_raises_the_error_of_ctypes(size):
     buffer = torch.zeros(8192, dtype=torch.uint8)
     with pytest.raises(ctypes.ArgumentError):
         zvc._native().zvc_decompress(buffer.data_ptr(), size, 100, 4, buffer.data_ptr(), buffer.data_ptr(), 0, 0)
+
+
+def test_a_call_while_another_thread_loads(monkeypatch):
+    """The library is loaded and its entry is not yet: a call in between makes it ready itself."""
+    zvc.load()
+    monkeypatch.setattr(zvc, "_calls", None)
+    assert zvc.zvc_window_count(100000, 4) == 98
