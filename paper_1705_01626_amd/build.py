@@ -1,5 +1,6 @@
 """Compile in-tree: csrc/zvc.hip -> paper_1705_01626_amd/libzvc.so (the HIP library) and
-csrc/calls.cpp -> paper_1705_01626_amd/_calls.so (its entry from Python).
+csrc/calls.cpp -> paper_1705_01626_amd/_calls.<interpreter's tag>.so (its entry from Python,
+which is left out where the interpreter's headers are not installed).
 
 Usage: python -m paper_1705_01626_amd.build
 hipcc cross-compiles for gfx950, so this works on a machine without a GPU.
@@ -10,16 +11,17 @@ import os
 import subprocess
 import sys
 import sysconfig
+from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SOURCE = os.path.join(PKG, "csrc", "zvc.hip")
 LIBRARY = os.path.join(PKG, "libzvc.so")
 CALLS_SOURCE = os.path.join(PKG, "csrc", "calls.cpp")
-CALLS = os.path.join(PKG, "_calls.so")
+HEADER = os.path.join(ROOT, "include", "zvc.h")
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))   # no other interpreter loads it
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-
-ROCM_INCLUDE = os.environ.get("ROCM_INCLUDE", "/opt/rocm/include")
+ROCM_INCLUDE = os.environ.get("ROCM_INCLUDE", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"))
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -35,21 +37,28 @@ def build(output: str = LIBRARY, extra=()) -> str:
     return output
 
 
-def build_calls(output: str = CALLS) -> str:
-    """The Python entry: host code only; it takes the functions from the loaded library."""
-    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+def build_calls(output: str = CALLS) -> Optional[str]:
+    """The Python entry: host code only; it takes the functions from the loaded library.  None, with a
+    line that says so, if the interpreter's headers are not there: the calls then go through ctypes."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print("_calls is not built: no Python.h in %s; device calls go through ctypes" % include, file=sys.stderr)
+        return None
+    subprocess.run([HIPCC, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-no-hip-rt", "-Wall", "-Wextra",
                     "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", ROCM_INCLUDE,
-                    "-I", sysconfig.get_paths()["include"], CALLS_SOURCE, "-o", output, "-ldl"], check=True)
+                    "-I", include, CALLS_SOURCE, "-o", output, "-ldl"], check=True)
     return output
 
 
+def _older(output: str, *sources: str) -> bool:
+    return not os.path.exists(output) or any(os.path.getmtime(output) < os.path.getmtime(s) for s in sources)
+
+
 def ensure_built() -> str:
-    """Build only if nothing is built yet (or the source is newer)."""
-    if (not os.path.exists(LIBRARY)
-            or os.path.getmtime(LIBRARY) < os.path.getmtime(SOURCE)):
+    """Build only what is not built yet (or whose sources are newer)."""
+    if _older(LIBRARY, SOURCE, HEADER):
         build()
-    if (not os.path.exists(CALLS)
-            or os.path.getmtime(CALLS) < os.path.getmtime(CALLS_SOURCE)):
+    if _older(CALLS, CALLS_SOURCE, HEADER):
         build_calls()
     return LIBRARY
 

@@ -2,13 +2,16 @@
 
 Argument marshalling only: torch tensors supply device memory and streams, the
 library's HIP kernels do all the work.  Host arithmetic goes through ctypes, the
-device calls through the extension module _calls (csrc/calls.cpp).  There is no CPU fallback: if the
-library is missing, `load()` raises.
+device calls through the extension module _calls (csrc/calls.cpp) or, where that is not built
+for this interpreter, through ctypes too.  There is no CPU fallback: if the library is missing,
+`load()` raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -35,7 +38,7 @@ EXPORTS = ("zvc_status_string", "zvc_mask_bytes", "zvc_max_compressed_bytes",
            "zvc_compress_static", "zvc_reference_stream")
 
 _lib = None
-_calls = None       # the device calls, see csrc/calls.cpp
+_calls = None       # the device calls, see _native()
 
 
 class ZvcError(RuntimeError):
@@ -111,12 +114,15 @@ def _native():
     global _calls
     calls = _calls
     if calls is None:
-        load()
+        lib = load()
         try:
-            from . import _calls as calls
-        except ImportError as e:
-            raise ImportError("%s is not built: run `python -m paper_1705_01626_amd.build`"
-                              % os.path.join(_PKG, "_calls.so")) from e
+            calls = importlib.import_module(__package__ + "._calls")
+        except ModuleNotFoundError:
+            # the same functions with the same arguments, 3 us more of host time per call
+            warnings.warn("paper_1705_01626_amd._calls is not built for this interpreter (`python -m "
+                          "paper_1705_01626_amd.build`): calls go through ctypes", RuntimeWarning, stacklevel=3)
+            _calls = lib
+            return lib
         calls.open(LIBRARY)
         _calls = calls
     return calls

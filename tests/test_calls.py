@@ -1,10 +1,14 @@
 """The device calls as Python reaches them (csrc/calls.cpp): the same statuses as through ctypes for
 arguments that the library refuses before any GPU work, and errors for what is no integer."""
 import ctypes
+import importlib.machinery
+import os
+import sys
 
 import pytest
 import torch
 
+from paper_1705_01626_amd import build as zvc_build
 from paper_1705_01626_amd import zvc
 
 IN, OUT, BYTES, WS = 1 << 20, 2 << 20, 3 << 20, 4 << 20
@@ -69,3 +73,33 @@ def test_a_call_while_another_thread_loads(monkeypatch):
     zvc.load()
     monkeypatch.setattr(zvc, "_calls", None)
     assert zvc.zvc_window_count(100000, 4) == 98
+
+
+def test_without_the_extension_module_calls_go_through_ctypes(monkeypatch):
+    """The library needs the HIP compiler alone; a machine that built no more than that makes every call."""
+    monkeypatch.setattr(zvc, "_calls", None)
+    monkeypatch.setitem(sys.modules, "paper_1705_01626_amd._calls", None)
+    monkeypatch.setattr(zvc, "_lib", None)
+    assert zvc.load().zvc_mask_bytes(65) == 12
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert zvc.zvc_window_count(100000, 4) == 98
+    for name, args in REFUSED[:3]:
+        assert getattr(zvc._native(), name)(*args) == getattr(zvc.load(), name)(*args) != zvc.ZVC_OK
+
+
+def test_the_module_is_built_for_this_interpreter_only(tmp_path, monkeypatch):
+    calls = importlib.import_module("paper_1705_01626_amd._calls")
+    assert calls.__file__ == zvc_build.CALLS and calls.__file__.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])
+    assert "python" in os.path.basename(calls.__file__) or "cp3" in os.path.basename(calls.__file__)
+    # no headers of the interpreter: nothing is built, and that is no error
+    monkeypatch.setattr(zvc_build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert zvc_build.build_calls(str(tmp_path / "out.so")) is None and not os.listdir(tmp_path)
+
+
+def test_a_newer_header_is_built_again(tmp_path):
+    """The signatures of include/zvc.h are compiled into both files."""
+    old, new = tmp_path / "a.so", tmp_path / "zvc.h"
+    old.write_text(""), new.write_text("")
+    os.utime(old, (1000, 1000)), os.utime(new, (2000, 2000))
+    assert zvc_build._older(str(old), str(new)) and not zvc_build._older(str(new), str(old))
+    assert zvc_build._older(str(tmp_path / "not there.so"), str(new))
