@@ -30,8 +30,8 @@ def both_streams(x):
 
 @pytest.mark.parametrize("w", [4, 2])
 def test_static_scratch_matches_workspace_call(w):
-    # 70 MB then 5 MB at w = 4 (32 KB then 16 KB tiles), half that at w = 2; ragged sizes
-    for k, n in enumerate((17_500_003, 1_300_021)):
+    # 70 MB then 5 MB at w = 4, 54 MB then 2.6 MB at w = 2: 32 KB then 16 KB tiles; ragged sizes
+    for k, n in enumerate((17_500_003 if w == 4 else 27_000_003, 1_300_021)):
         x = random_tensor(n, w, (0.35, 0.7)[k], seed=1000 + n + w)
         say("zvc_compress_static n=%d w=%d" % (n, w))
         ref, ref_bytes, got, got_bytes = both_streams(x)
