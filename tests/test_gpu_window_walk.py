@@ -8,6 +8,7 @@ import torch
 from paper_1705_01626_amd import zvc
 from tests.gpu_util import raw_bytes, say
 from tests.test_gpu_parity import random_tensor
+from tests.test_gpu_unaligned import assert_guard, guarded
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -15,10 +16,18 @@ DEV = "cuda"
 
 def walk(stream, table, n, w, per, end):
     """What the decoder gives for the first `end` bytes of a stream: a mask that is not wholly there is
-    empty, an element that is not wholly there is zero."""
+    empty, an element that is not wholly there is zero.  What is there, is up to the end of the window, or of
+    the 4 KB of windows that are decoded together, and no more than those can need; a window that does not
+    begin in it has nothing."""
     out = np.zeros(n, dtype={2: np.uint16, 4: np.uint32}[w])
-    for k in range(len(table) - 1):
-        p, hi = min(int(table[k]), end), min(int(table[k + 1]), end)
+    table = [min(int(o), end) for o in table]
+    windows = len(table) - 1
+    together = max(1, 4096 // (per * w))
+    for k in range(windows):
+        first = k // together * together
+        lo, hi = table[first], table[min(first + together, windows)]
+        hi = min(max(lo, hi), lo + together * per // 32 * (4 + 32 * w))
+        p = table[k] if lo <= table[k] <= hi else hi
         for g in range(k * per // 32, -(-min(n, (k + 1) * per) // 32)):
             if p + 4 > hi:
                 break
@@ -26,7 +35,7 @@ def walk(stream, table, n, w, per, end):
             p += 4
             for b in range(32):
                 if mask >> b & 1:
-                    if p + w <= hi:
+                    if p + w <= hi and 32 * g + b < n:
                         out[32 * g + b] = stream[p:p + w].view(out.dtype)[0]
                     p += w
     return out
@@ -55,6 +64,36 @@ def test_streams_that_end_early(oracle, window, w):
             torch.cuda.synchronize()
             want = walk(stream, table, n, w, per, end)
             assert np.array_equal(raw_bytes(out), want.view(np.uint8)), "end=%d" % end
+
+
+@pytest.mark.parametrize("w", [4, 2])
+@pytest.mark.parametrize("window", [1024, 2048, 4096, 8192, 16384, 32768, 65536])
+def test_damaged_streams_and_tables(oracle, window, w):
+    """Random bytes, sparse and dense ones, as the stream, and random numbers as the table (odd ones among
+    them, ends before beginnings, beyond the stream): the walk's result, and nothing beside the output."""
+    per = window // w
+    n = 5 * per + per // 3 + 7
+    rng = np.random.default_rng(window + w)
+    x = random_tensor(n, w, 0.5, seed=window + w)
+    stream, table = oracle.window_compress(raw_bytes(x), w, per)
+    total = stream.size
+    noise = rng.integers(0, 256, size=total, dtype=np.uint8)
+    thin = noise & rng.integers(0, 256, size=total, dtype=np.uint8) & rng.integers(0, 256, size=total, dtype=np.uint8)
+    empty = np.where(rng.random(total) < 0.02, noise, 0).astype(np.uint8)
+    inside = np.sort(rng.integers(0, total, size=len(table)))
+    cases = [(s, table, end) for s in (noise, thin, empty, np.full(total, 255, np.uint8)) for end in (total, total - 5)]
+    cases += [(stream, t, total) for t in (inside, inside // 4 * 4, rng.permutation(inside),
+                                           rng.integers(0, 1 << 62, size=len(table)))]
+    cases += [(noise, inside, total - 1)]
+    for k, (s, t, end) in enumerate(cases):
+        s, t = np.ascontiguousarray(s), t.astype(np.int64)
+        say("damaged window=%d w=%d case %d" % (window, w, k))
+        base, out = guarded(n, x.dtype, 0)
+        zvc.zvc_window_decompress(torch.from_numpy(s).to(DEV), end, torch.from_numpy(t).to(DEV), n, 0, len(t) - 1, out,
+                                  window_bytes=window)
+        torch.cuda.synchronize()
+        assert np.array_equal(raw_bytes(out), walk(s, t, n, w, per, end).view(np.uint8)), "case %d" % k
+        assert_guard(base, n, 0, "case %d" % k)
 
 
 @pytest.mark.parametrize("w", [4, 2])
