@@ -935,14 +935,28 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // usually the call's last, fetched several KB of code that no other wave had: 5.9 against
     // 4.8 us for a call of 64,000 fp32 elements, 1.5 to 6 us on every size that is not a
     // multiple of the tile.)
-    {
+    // In the smallest fp32 tile a wave that lies wholly inside the tensor takes plain loads: a
+    // call of a few tiles per CU waits for its first loads, and these need no descriptor (us,
+    // cold whole-tile tensors of 4 | 6 | 8 MB: 6.6 | 7.3 | 7.8, with buffer loads alone 7.0 |
+    // 7.8 | 8.1).  The larger tiles gain nothing from it (30 MB: 11.5 against 11.3).
+    if (W == 4 && CH == 16 && __builtin_expect(wave_elem0 + G::kWaveElems <= a.n, 1)) {
+        const unsigned* base = reinterpret_cast<const unsigned*>(a.in) + wave_dword0;
+        static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            cur[k] = load_stream(base + k * kWaveSize + lane);
+            __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
+        });
+    } else {
         // Aligned dwords from the one that holds the tensor's first element to the one that holds
         // its last.  SPLIT: the tensor begins in the middle of the first of them, so a lane's two
         // elements are the halves of two of them, its own and the next lane's.
         const size_t bytes = div_up(a.n * W + (SPLIT ? 2 : 0), size_t{4}) * 4, wave_byte0 = wave_dword0 * 4;
         const unsigned most = CH * kChunkBytes + (SPLIT ? 4 : 0);
-        const unsigned readable = wave_byte0 >= bytes ? 0u
-                                  : bytes - wave_byte0 < most ? static_cast<unsigned>(bytes - wave_byte0) : most;
+        // (in words of 32 bits, which the scalar unit compares: with 64-bit comparisons on the vector
+        // unit the descriptor takes 0.2 to 0.8 us longer where a call waits for its first loads)
+        const size_t left = bytes - wave_byte0;
+        const int left_high = static_cast<int>(left >> 32);
+        const unsigned readable = left_high < 0 ? 0u : left_high > 0 ? most : min(static_cast<unsigned>(left), most);
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<unsigned char*>(a.in) - (SPLIT ? 2 : 0) + wave_byte0, 0, static_cast<int>(readable), kRawBuffer);
         // The descriptor's range check covers the vector and the immediate offset, not the scalar one,
