@@ -783,6 +783,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     using G = EncoderGeometry<W, CH, WV>;
     constexpr int CG = G::kChunkGroups;
     constexpr int kWindowChunks = 4;              // the windowed stream's unit: 1 KB of input
+    constexpr bool kChunkMasks = WINDOWED && W == 4 && CH == 16;   // windowed: masks by chunk, see write_step_masks
     static_assert(W == 2 || !SPLIT, "only 16-bit elements can sit at an odd half dword");
 
     __shared__ __align__(16) unsigned char s_stage[WV][G::kQueueBytes];
@@ -858,18 +859,22 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
             set_lane<k / kWindowChunks>(window_local, zero_local + q_end);
         // (windowed: the lane's group has its mask, and the masks of the chunk's earlier groups, before it;
-        // write_step_masks() puts the masks there)
+        // write_step_masks() puts the masks there, but for kChunkMasks)
         if constexpr (W == 4) {
             const bool keep = kept_first<4, RELU>(x);
             const unsigned long long b = __ballot(keep);
             const unsigned kept = static_cast<unsigned>(__popcll(b));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
-                set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
+                if (!kChunkMasks)
+                    set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
             }
             if (STAGE) {
                 const unsigned at = 4u * lanes_below(b, 0u) + q_end + (WINDOWED ? 4u + 4u * (lane >> 5) : 0u);
                 if (__builtin_expect(keep, 1)) *reinterpret_cast<unsigned*>(stage + at) = x;   // predicated, no branch
+                if (kChunkMasks && (lane & 31) == 0 && static_cast<unsigned>(lane >> 5) < chunk_groups)
+                    *reinterpret_cast<unsigned*>(stage + at - 4u) =
+                        lane == 0 ? static_cast<unsigned>(b) : static_cast<unsigned>(b >> 32);
                 q_end += 4u * kept + 4u * chunk_groups;
             }
         } else {
@@ -898,7 +903,9 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // its chunks left for them: a lane per mask, whose place is the sum of the sizes of the step's
     // groups before it (a scan over 16 or 32 lanes).  Per step instead of per chunk: 89.1 ->
     // 87.7 us for 297 MB fp32, 87.8 -> 59.9 us for 149 MB bf16 (whose chunks zipped their masks on
-    // the scalar unit).
+    // the scalar unit).  In the smallest fp32 tile the scan's chain of dependent steps costs more than
+    // two lanes' writes per chunk: 6 | 8 | 11 MB take 8.5 | 8.9 | 9.4 us with those and 9.0 | 9.5 |
+    // 10.0 with the scan.
     const auto write_step_masks = [&](auto hc, unsigned q_step) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
         constexpr int reg = h * G::kStepGroups / kWaveSize, lane0 = h * G::kStepGroups % kWaveSize;
@@ -995,7 +1002,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                 chunk(kc, yes, yes);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            if constexpr (WINDOWED) write_step_masks(hc, q_step);
+            if constexpr (WINDOWED && !kChunkMasks) write_step_masks(hc, q_step);
             staged = h + 1;
         } else {
             static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
@@ -1045,7 +1052,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             chunk(kc, no, yes);
             __builtin_amdgcn_sched_barrier(0);
         });
-        if constexpr (WINDOWED) write_step_masks(hc, q_step);
+        if constexpr (WINDOWED && !kChunkMasks) write_step_masks(hc, q_step);
     };
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
