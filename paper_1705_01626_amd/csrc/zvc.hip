@@ -2155,13 +2155,17 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 // scan's state traffic), so large tensors use larger tiles.  A small tile is
 // through its chain of load, test, publish, store sooner, and its straight-line
 // code is shorter (a call's first wave on a CU fetches it from memory: one tile
-// alone takes 3.7 us with 16 KB, 4.8 with 32 KB, 6.9 with 64 KB).  Measured, us
-// with 16 | 32 | 64 KB tiles, density 0.5 (windowed fp32: 0.1 to 0.9):
-//   fp32      12 MB 7.7 | 9.0 | 9.0   24 MB 10.6 | 10.1 | 11.5   48 MB 18.3 | 14.9 | 16.0
-//            103 MB 35.4 | 31.2 | 32.4   200 MB 65.7 | 57.4 | 55.1
-//   windowed  24 MB 14.2 | 14.3   48 MB 22.0 | 20.8   103 MB 38.9 | 36.5   (822 MB: nothing gained from 64 KB)
-//   16-bit    24 MB 11.8 | 12.4   51 MB 21.4 | 21.8   100 MB 37.0 | 35.6   411 MB 136 | 117
-//   windowed 100 MB 42.4 | 43.3   149 MB 60.3 | 59.9   200 MB 76.2 | 75.0   411 MB 148 | 140
+// alone takes 3.7 us with 16 KB, 4.8 with 32 KB, 6.9 with 64 KB).  Measured us with
+// 16 | 32 KB tiles, density 0.5 (windowed: 0.1 to 0.9), sizes a few elements above a
+// whole number of tiles, on both sides of every limit below (fp32's first line and
+// its windowed one on cold inputs, the others on three buffers in turn):
+//   fp32      14 MB 8.7 | 8.6   16 MB 9.0 | 8.5   20 MB 10.0 | 9.7   48 MB 18.9 | 15.3   103 MB 37.4 | 32.3
+//            103 MB 32.1 | 32.0   150 MB 45.1 | 44.6   170 MB 51.1 | 49.8   300 MB 87.0 | 82.1   (32 | 64 KB)
+//   windowed  28 MB 14.9 | 17.2   33 MB 17.6 | 18.4   36 MB 18.6 | 18.7   40 MB 20.2 | 19.2   103 MB 40.8 | 37.9
+//             (822 MB: nothing gained from 64 KB)
+//   16-bit    24 MB 12.0 | 12.6   47 MB 20.0 | 20.0   50 MB 21.0 | 21.5   64 MB 25.9 | 24.5   200 MB 71.6 | 63.3
+//   windowed 100 MB 43.5 | 45.1   150 MB 61.0 | 62.0   161 MB 65.3 | 65.2   200 MB 79.4 | 78.0   400 MB 152 | 143
+// (fp32 of a whole number of tiles: 14 MB 8.6 | 8.8, 16 MB 9.1 | 9.0, 21 MB 10.5 | 9.9.)
 // 16-bit elements are twice the vector work per byte, and the 32 KB tile's eight
 // waves per SIMD (against four) hide it better: 64 KB tiles lose up to 9 % there.
 // (8 KB tiles, and 8 or 16 waves per tile, were no faster at any size.)
@@ -2175,7 +2179,7 @@ static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16
 
 inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    const size_t medium = w == 4 ? size_t{windowed ? 32u : 24u} << 20 : size_t{windowed ? 160u : 48u} << 20;
+    const size_t medium = w == 4 ? size_t{windowed ? 36u : 16u} << 20 : size_t{windowed ? 160u : 48u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }

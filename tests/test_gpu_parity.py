@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 SIZES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 255, 256, 257, 4095, 4096, 4097, 8191, 8192, 8193,
          3 * 4096 + 17, 5 * 8192 - 1, 100003, (1 << 20) + 5,
-         5 * (1 << 20) + 777, (1 << 24) + 8192 + 77]  # the last takes 32 KB tiles at w = 4 (the larger tiles: test_gpu_encoder_shapes.py)
+         5 * (1 << 20) + 777, (1 << 24) + 8192 + 77]  # the last two take 32 KB tiles at w = 4 (all tiles: test_gpu_encoder_shapes.py)
 DTYPES = {4: torch.int32, 2: torch.int16}
 
 
