@@ -2238,13 +2238,17 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
 // each: large ones, while there are too few of them to fill the GPU with waves.  A
 // wave's walk over a 64 KB window takes 50 us (fp32) or 75 (16-bit) however few there
 // are; a workgroup takes 10.9 or 21.5, but 5 times the instructions.  In us, wave |
-// workgroup each, densities 0.1 to 0.9:
-//   fp32    64 KB: 15 windows 52 | 11,  977 windows 53 | 31,  3906 windows 89 | 100
-//           16 KB: 61 windows 15 | 10,  977 windows 15 | 12,  3906 windows 23 | 28
-//   bf16    64 KB:  8 windows 79 | 21, 1134 windows 90 | 65
-//           16 KB: 31 windows 22 | 15,  488 windows 22 | 19,  1953 windows 25 | 33
+// workgroup each, channels of densities 0.1 to 0.9 (of one density throughout, the
+// workgroups gain more: 21.1 | 10.7 at 768 windows of 16 KB of 16-bit elements):
+//   fp32    16 KB: 1000 windows 15 | 12, 2000 windows 17.4 | 17.0, 3000 windows 19.6 | 22.4
+//           32 KB: 1000 windows 28 | 18, 2000 windows 30.4 | 28.2, 3000 windows 34.8 | 38.4
+//           64 KB: 1000 windows 52 | 31, 2000 windows 56.5 | 53.1, 3000 windows 74.8 | 78.6
+//   16-bit  16 KB:  440 windows 21.3 | 19.5,  768 windows 21.2 | 20.8,  900 windows 21.9 | 22.9
+//           32 KB: 1024 windows 40.5 | 34.5, 1536 windows 46.4 | 45.4, 1700 windows 46.3 | 47.6
+//           64 KB: 1536 windows 87.6 | 79.3, 1792 windows 87.6 | 91.1 (cold 93.6 | 92.4), 1900 windows 87.8 | 94.5
 inline bool splits_windows(size_t num_windows, int shift, int w) {
-    return shift >= 4 && num_windows <= (w == 4 ? size_t{2048} : size_t{448} << (shift - 4));
+    const size_t most = w == 4 ? 2048 : shift == 4 ? 768 : shift == 5 ? 1536 : 1792;
+    return shift >= 4 && num_windows <= most;
 }
 
 template <int W, int NW>

@@ -122,7 +122,7 @@ def test_windows_of_mixed_density(oracle, window, w):
     assert np.array_equal(raw_bytes(out), raw_bytes(x))
 
 
-@pytest.mark.parametrize("window,w,most", [(16384, 4, 2048), (16384, 2, 448), (32768, 2, 896), (65536, 2, 1792)])
+@pytest.mark.parametrize("window,w,most", [(16384, 4, 2048), (16384, 2, 768), (32768, 2, 1536), (65536, 2, 1792)])
 def test_both_sides_of_the_number_of_windows(window, w, most):
     """As many windows as take a workgroup each, and one more: the same elements (which the GPU's own
     encoder compressed; its streams are compared with the oracle's elsewhere)."""
