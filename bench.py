@@ -480,8 +480,8 @@ def main() -> int:
                          "tensor, zvc_compress, zvc_decompress] and nothing else")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on exactly one GPU (the hot path is single-GPU; "
-              "see DESIGN.md for how it would shard); --gpus %d is refused" % args.gpus,
+        print("bench.py: this build runs on exactly one GPU (the hot path is single-GPU); "
+              "--gpus %d is refused" % args.gpus,
               file=sys.stderr)
         return 2
     if args.window_bytes not in (1024 << k for k in range(7)):
