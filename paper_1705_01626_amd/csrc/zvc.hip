@@ -256,6 +256,10 @@ __device__ inline void store16_loose(void* p, const uint4& d) {
     else *reinterpret_cast<vec4u_at2*>(p) = v;
 }
 
+// A raw buffer's descriptor word (32-bit data, no swizzle), the non-temporal bit of a buffer load.
+constexpr int kRawBuffer = 0x00020000;
+constexpr int kNonTemporal = 2;
+
 // LDS written by some lanes of a wave is read by other lanes of the same wave:
 // order the accesses (LDS operations of one wave execute in order).
 __device__ inline void wave_lds_sync() {
@@ -415,48 +419,74 @@ __device__ inline void wave_flush(unsigned char*& gzero, unsigned char* stage, u
     end = rem;
 }
 
-// Global bytes into the LDS slice at the same offsets modulo 16, in two halves,
-// so that a wave can have the loads of several steps in flight before it
-// touches LDS.  wave_fetch requests the aligned
-// 16-byte chunks that hold global bytes [shift, end_valid) at gbase (gbase is
-// 16-byte aligned, shift < 16): chunk q goes to lane q % 64, slot q / 64.  A
-// chunk is loaded whole even where the run begins or ends inside it -- an
-// aligned 16-byte chunk never straddles a page, so the access is as safe as
-// that of the bytes wanted -- and what lies at or past end_valid is cleared.
-// wave_commit stores the chunks to LDS at the same offsets.
-constexpr int kFetchSlots = (kStageLoads * kWaveSize * 16 + 16 + 15) / 16 / kWaveSize + 1;   // 5
+// Global bytes [0, end) at gbase (16-byte aligned, the same in all lanes) into LDS at
+// `stage`, by one wave, without a register in between: 1 KB per instruction, lane i's 16
+// bytes behind lane i - 1's.  A slot that holds nothing is left out by a scalar branch.  A
+// 16-byte chunk is loaded whole even where the run begins or ends inside it: an aligned
+// chunk never straddles a page, so the access is as safe as that of the bytes wanted.
+// stage_wait() before LDS is read.  (Through registers, with the bytes behind the run
+// cleared, this was 110 of the expand kernel's 500 vector instructions per 4 KB of 16-bit
+// output, and that kernel had the vector units busy 83 % of its time.)
+constexpr unsigned kSlotBytes = kWaveSize * 16;
+constexpr int kFetchSlots = kStageLoads + 1;      // a run of 4 KB that begins anywhere in a chunk
 
-__device__ inline void wave_fetch(uint4 (&r)[kFetchSlots], const unsigned char* gbase, unsigned end_valid,
-                                  bool streaming, int lane) {
+// Slot at byte AT behind gbase and stage (an immediate of the instruction, for both).
+template <bool STREAMING, unsigned AT>
+__device__ __forceinline__ void stage_slot(unsigned char* stage, const unsigned char* gbase, unsigned end, int lane) {
+    if (AT >= end) return;                                               // uniform
+    if (AT + 16u * lane < end)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned*)(gbase + 16u * lane),
+                                         (__attribute__((address_space(3))) unsigned*)stage, 16, AT,
+                                         STREAMING ? kNonTemporal : 0);
+}
+template <bool STREAMING>
+__device__ __forceinline__ void wave_stage(unsigned char* stage, const unsigned char* gbase, unsigned end, int lane) {
+    static_assert(kStageLoads == 4 && kFetchSlots == 5 && 4 * kSlotBytes == 4096, "immediates are below 4096");
+    stage_slot<STREAMING, 0>(stage, gbase, end, lane);
+    stage_slot<STREAMING, kSlotBytes>(stage, gbase, end, lane);
+    stage_slot<STREAMING, 2 * kSlotBytes>(stage, gbase, end, lane);
+    stage_slot<STREAMING, 3 * kSlotBytes>(stage, gbase, end, lane);
+    if (end > 4 * kSlotBytes) stage_slot<STREAMING, 0>(stage + 4 * kSlotBytes, gbase + 4 * kSlotBytes, end - 4 * kSlotBytes, lane);
+}
+__device__ __forceinline__ void stage_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// 16 bytes of output: element c is "bit c of `field` ? next stored element : 0", and the
+// next stored element is at `at` in `lds`, whose first 16 bytes are zero (an absent
+// element is read from there).  Three instructions per element beside its LDS read: the
+// bit as 0 or -1, the address (at & that), the next address (at - W * that).  Selecting
+// address and value by comparison took 8.  With the staging above: 202 vector
+// instructions per 4 KB of 16-bit output instead of 499 (32-bit: 108, 303), the expand
+// kernel 13.8 -> 12.4 us for 51 MB bf16; 822 MB fp32, bound by memory, 158 either way.
+template <int W>
+__device__ __forceinline__ uint4 expand_lane(const unsigned char* lds, unsigned at, unsigned field) {
+    unsigned d[4], half[2];
 #pragma unroll
-    for (int k = 0; k < kFetchSlots; ++k) {
-        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
-        r[k] = make_uint4(0u, 0u, 0u, 0u);
-        if (q * 16u < end_valid)
-            r[k] = streaming ? load16_stream(gbase + q * 16u)
-                             : *reinterpret_cast<const uint4*>(gbase + q * 16u);
+    for (int c = 0; c < 16 / W; ++c) {
+        const int bit = __builtin_amdgcn_sbfe(static_cast<int>(field), c, 1);
+        const unsigned from = at & static_cast<unsigned>(bit);
+        if (W == 4) d[c] = *reinterpret_cast<const unsigned*>(lds + from);
+        else half[c % 2] = *reinterpret_cast<const unsigned short*>(lds + from);
+        if (W == 2 && c % 2 == 1) {
+            asm("" : "+v"(half[0]), "+v"(half[1]));         // (or the compiler goes on in 16 bits, an instruction more)
+            d[c / 2] = half[1] << 16 | half[0];
+        }
+        if (c + 1 < 16 / W) asm("v_mad_i32_i24 %0, %1, %2, %0" : "+v"(at) : "v"(bit), "n"(-W));
     }
+    return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-__device__ inline void wave_commit(unsigned char* stage, const uint4 (&r)[kFetchSlots], unsigned end,
-                                   unsigned end_valid, int lane) {
-#pragma unroll
-    for (int k = 0; k < kFetchSlots; ++k) {
-        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
-        if (q * 16u >= end) continue;
-        uint4 v = r[k];
-        if (q * 16u + 16u > end_valid) {          // only when the stream is cut short
-            const unsigned valid = end_valid > q * 16u ? end_valid - q * 16u : 0u;   // bytes to keep: 0 .. 15
-            unsigned d[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned lo = 4u * i;
-                d[i] = valid >= lo + 4u ? d[i] : valid > lo ? d[i] & ((1u << (8u * (valid - lo))) - 1u) : 0u;
-            }
-            v = make_uint4(d[0], d[1], d[2], d[3]);
-        }
-        *reinterpret_cast<uint4*>(stage + q * 16u) = v;
-    }
+// Inclusive sum over the first LANES lanes (whole wave active; later lanes: unspecified).
+template <int LANES>
+__device__ __forceinline__ unsigned wave_scan_small(unsigned v) {
+    static_assert(LANES == 32 || LANES == 64, "two or four rows of lanes");
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xF, 0xF, true));
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xF, 0xF, true));
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xF, 0xF, true));
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xF, 0xF, true));
+    // a row's last lane to the whole next row, the second row's last to the third and fourth
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xA, 0xF, false));
+    if (LANES == 64) v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xC, 0xF, false));
+    return v;
 }
 
 // Device-wide exclusive scan of the per-tile counts, single pass (the paper's
@@ -616,10 +646,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 __device__ inline unsigned load_stream(const unsigned* p) { return __builtin_nontemporal_load(p); }
 __device__ inline unsigned load_stream(const unsigned short* p) { return __builtin_nontemporal_load(p); }
-
-// A raw buffer's descriptor word (32-bit data, no swizzle), the non-temporal bit of a buffer load.
-constexpr int kRawBuffer = 0x00020000;
-constexpr int kNonTemporal = 2;
 
 // Dword `index` of a run of dwords that starts at `base` (wave-uniform, inside
 // the tensor) and of which only dwords 0 .. room belong to the tensor, the last
@@ -1294,80 +1320,90 @@ __global__ __launch_bounds__(kThreads) void mask_prefix_kernel(
     if (tid == 0) hdr->finish_top.value = 0u;
 }
 
-// One step of the decoder, by one wave: 4 KB of output from `m` (lane i holds
-// the step's mask i, bits past n cleared) and the step's `step_total` stored
-// elements, which begin at element `first` of the value area.  Stages them in
-// the wave's LDS slice with aligned 16-byte loads (never past values_avail
-// elements: anything the masks ask for beyond that decodes as zero); every lane
-// then rebuilds 16 bytes of output per load from "bit ? next stored element :
-// 0".  Slots whose bit is clear read a valid dummy address and select zero.
+// 4 KB of output by one wave: every lane rebuilds 16 bytes per store (expand_lane).
+// Lane i holds mask i of the 32 (64) and the offset in `lds` of its first stored
+// element; of the output only elements 0 .. left - 1 are the tensor's (`left` is the
+// same in all lanes).  `lds` begins with 16 bytes that belong to nothing else.
 template <int W, bool ALIGNED>
-__device__ __forceinline__ void expand_step(unsigned char* stage, const unsigned char* __restrict__ values,
-                                            unsigned long long values_avail, unsigned long long first,
-                                            unsigned step_total, unsigned m, size_t wave_elem0, size_t n,
-                                            unsigned char* __restrict__ out, bool stream_values, int lane) {
+__device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, unsigned mask_at, unsigned left,
+                                             unsigned char* __restrict__ to, int lane) {
     using G = Geometry<W, kMinLoads>;
     constexpr int E = G::kElemsPerLane;
     constexpr int LPG = G::kLanesPerGroup;
-    constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // 32 | 64 masks per step
-    const bool full_wave = wave_elem0 + static_cast<size_t>(kStageLoads) * kWaveSize * E <= n;
-    const unsigned char* src = values + first * W;  // wave-uniform
-    const unsigned shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
-    unsigned long long readable = values_avail > first ? values_avail - first : 0ull;
-    if (readable > step_total) readable = step_total;
-    const unsigned end = shift + step_total * W;
-    const unsigned end_valid = shift + static_cast<unsigned>(readable) * W;
-    uint4 fetched[kFetchSlots];
-    wave_fetch(fetched, src - shift, readable != 0 ? end_valid : 0u, stream_values, lane);
-    wave_commit(stage, fetched, end, end_valid > shift ? end_valid : 0u, lane);
-    // stored elements of the step before each of its masks (lane i holds mask i)
-    const unsigned cnt = __popc(m);
-    unsigned incl = cnt;
-#pragma unroll
-    for (int off = 1; off < kStepMasks; off <<= 1) {
-        const unsigned t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
-    const unsigned before_mask = incl - cnt;
+    // (every wave writes the zeros itself: LDS operations of one wave execute in order)
+    if (lane == 0) *reinterpret_cast<uint4*>(lds) = make_uint4(0u, 0u, 0u, 0u);
     wave_lds_sync();
+    const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E, lower = (1u << bit0) - 1u;
+    uint4 v[kStageLoads];
 #pragma unroll
     for (int jj = 0; jj < kStageLoads; ++jj) {
-        const size_t e0 = wave_elem0 + (static_cast<size_t>(jj) * kWaveSize + lane) * E;
-        const int gl = jj * G::kGroupsPerLoad + lane / LPG;     // the lane's mask within the step
-        const unsigned gm = __shfl(m, gl);
-        const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E;
-        unsigned at = shift + W * (__shfl(before_mask, gl) + __popc(gm & ((1u << bit0) - 1u)));
-        const unsigned field = gm >> bit0;
-        unsigned d[4] = {0u, 0u, 0u, 0u};
+        const int from = 4 * (jj * G::kGroupsPerLoad + lane / LPG);     // the lane's mask
+        const unsigned gm = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask)));
+        const unsigned at = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask_at)));
+        v[jj] = expand_lane<W>(lds, at + W * static_cast<unsigned>(__popc(gm & lower)), gm >> bit0);
+    }
+    if (__builtin_expect(left >= kStageLoads * kWaveSize * E, 1)) {     // uniform
 #pragma unroll
-        for (int c = 0; c < E; ++c) {
-            const bool set = (field >> c) & 1u;
-            const unsigned from = set ? at : shift;
-            if (W == 4) {
-                const unsigned v = *reinterpret_cast<const unsigned*>(stage + from);
-                d[c] = set ? v : 0u;
-            } else {
-                const unsigned v = *reinterpret_cast<const unsigned short*>(stage + from);
-                d[c >> 1] |= (set ? v : 0u) << (16 * (c & 1));
-            }
-            at += set ? W : 0;
+        for (int jj = 0; jj < kStageLoads; ++jj) {
+            if (ALIGNED) store16_stream(to + (jj * kWaveSize + lane) * 16, v[jj]);
+            else store16_loose<W>(to + (jj * kWaveSize + lane) * 16, v[jj]);
         }
-        if (full_wave || e0 + E <= n) {
-            if (ALIGNED) store16_stream(out + e0 * W, make_uint4(d[0], d[1], d[2], d[3]));
-            else store16_loose<W>(out + e0 * W, make_uint4(d[0], d[1], d[2], d[3]));
-        } else {
+        return;
+    }
 #pragma unroll
-            for (int c = 0; c < E; ++c) {
-                if (e0 + c < n) {
-                    if (W == 4)
-                        reinterpret_cast<unsigned*>(out)[e0 + c] = d[c];
-                    else
-                        reinterpret_cast<unsigned short*>(out)[e0 + c] = static_cast<unsigned short>(
-                            (d[c >> 1] >> (16 * (c & 1))) & 0xFFFFu);
+    for (int jj = 0; jj < kStageLoads; ++jj) {
+        const unsigned e0 = static_cast<unsigned>(jj * kWaveSize + lane) * E;
+        if (e0 + E <= left) {
+            if (ALIGNED) store16_stream(to + e0 * W, v[jj]);
+            else store16_loose<W>(to + e0 * W, v[jj]);
+        } else if (e0 < left) {                                         // the tensor's last elements
+            const unsigned d[4] = {v[jj].x, v[jj].y, v[jj].z, v[jj].w};
+#pragma unroll
+            for (int c = 0; c + 1 < E; ++c) {
+                if (e0 + c < left) {
+                    if (W == 4) reinterpret_cast<unsigned*>(to)[e0 + c] = d[c];
+                    else reinterpret_cast<unsigned short*>(to)[e0 + c] = static_cast<unsigned short>(d[c >> 1] >> (16 * (c & 1)));
                 }
             }
         }
     }
+}
+
+// One step of the decoder, by one wave: 4 KB of output from `m` (lane i holds
+// the step's mask i, bits past n cleared) and the step's `step_total` stored
+// elements, which begin at element `first` of the value area.  Stages them in
+// the wave's slice of `lds` (at offset `slice`; see expand_piece) with aligned 16-byte
+// loads, never past values_avail elements: anything the masks ask for beyond that
+// decodes as zero.  `first`, `step_total` and `slice` are the same in all lanes.
+template <int W, bool ALIGNED>
+__device__ __forceinline__ void expand_step(unsigned char* lds, unsigned slice, const unsigned char* __restrict__ values,
+                                            unsigned long long values_avail, unsigned long long first,
+                                            unsigned step_total, unsigned m, size_t wave_elem0, size_t n,
+                                            unsigned char* __restrict__ out, bool stream_values, int lane) {
+    using G = Geometry<W, kMinLoads>;
+    constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // 32 | 64 masks per step
+    constexpr unsigned kStepElems = kStageLoads * kWaveSize * G::kElemsPerLane;
+    const unsigned char* src = values + first * W;
+    const unsigned shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
+    unsigned long long readable = values_avail > first ? values_avail - first : 0ull;
+    if (readable > step_total) readable = step_total;
+    const unsigned valid = static_cast<unsigned>(readable) * W;
+    const unsigned end = valid != 0u ? shift + valid : 0u;
+    if (stream_values) wave_stage<true>(lds + slice, src - shift, end, lane);
+    else wave_stage<false>(lds + slice, src - shift, end, lane);
+    // stored elements of the step before each of its masks, while the loads are under way
+    const unsigned cnt = static_cast<unsigned>(__popc(m));
+    const unsigned mask_at = slice + shift + W * (wave_scan_small<kStepMasks>(cnt) - cnt);
+    stage_wait();
+    if (__builtin_expect(valid < step_total * W, 0)) {           // the stream is cut short
+        wave_lds_sync();
+        for (unsigned i = shift + valid + W * lane; i < shift + step_total * W; i += W * kWaveSize) {
+            if (W == 4) *reinterpret_cast<unsigned*>(lds + slice + i) = 0u;
+            else *reinterpret_cast<unsigned short*>(lds + slice + i) = 0;
+        }
+    }
+    const unsigned left = n - wave_elem0 < kStepElems ? static_cast<unsigned>(n - wave_elem0) : kStepElems;
+    expand_piece<W, ALIGNED>(lds, m, mask_at, left, out + wave_elem0 * W, lane);
 }
 
 // Section 5.2 decoder.  Every wave works on its own: it expands one step, 4 KB
@@ -1386,7 +1422,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     constexpr int kSteps = G::kStageSteps;
     static_assert(kChunkMasks % (LOADS * G::kGroupsPerLoad) == 0, "a wave's masks lie in one chunk");
 
-    __shared__ __align__(16) unsigned char s_stage[kWaves][G::kWaveStageBytes];
+    __shared__ __align__(16) unsigned char s_stage[16 + kWaves * G::kWaveStageBytes];   // (16: see expand_piece)
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
@@ -1410,45 +1446,47 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     //      -> 17.0 us for 51 MB bf16, 79.2 -> 78.7 for 297 MB fp32; with the masks
     //      asked for first 8 M fp32 elements take 12.5 us instead of 12.0)
     static_assert(kFewChunks == 4 * kThreads, "four totals per thread");
-    unsigned total[4] = {0u, 0u, 0u, 0u};          // of at most 2^17 each
+    unsigned total = 0;                            // of chunks with at most 2^17 stored elements each
     if (chunk_prefix == nullptr) {
-        const size_t before = min(chunk, div_up(num_groups, static_cast<size_t>(kChunkMasks)));   // (a workgroup past the tensor's end)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (before <= static_cast<size_t>(k) * kThreads) break;          // uniform
-            const size_t c = static_cast<size_t>(k) * kThreads + tid;
-            if (c < before) total[k] = chunk_total[c];
+        const unsigned before = static_cast<unsigned>(
+            min(chunk, div_up(num_groups, static_cast<size_t>(kChunkMasks))));   // (a workgroup past the tensor's end)
+        const unsigned c = 4u * tid;               // (the array is padded to whole 256 bytes)
+        if (c < before) {
+            const uint4 t = *reinterpret_cast<const uint4*>(chunk_total + c);
+            total = t.x + (c + 1u < before ? t.y : 0u) + (c + 2u < before ? t.z : 0u) + (c + 3u < before ? t.w : 0u);
         }
     }
     // ---- the step's masks and where it begins and ends within its chunk, on their way meanwhile
     static_assert(kSteps == 1, "a wave expands one step");
     unsigned m = 0, step_begin = 0, step_end = 0;
     if (wave_elem0 < n) {
-        const size_t g = wave_group0 + lane;
-        if (lane < kStepMasks && g < num_groups) {
-            m = masks[g];
-            if (g == num_groups - 1 && tail != 0) m &= (1u << tail) - 1u;   // bits past n never count
+        const unsigned here = num_groups - wave_group0 < kStepMasks ? static_cast<unsigned>(num_groups - wave_group0) : kStepMasks;
+        if (static_cast<unsigned>(lane) < here) {
+            m = masks[wave_group0 + lane];
+            if (tail != 0 && wave_group0 + lane == num_groups - 1) m &= (1u << tail) - 1u;   // bits past n never count
         }
         const size_t u = wave_group0 / kUnitMasks;
         step_begin = u % kChunkUnits != 0 ? unit_end[u - 1] : 0u;
         step_end = unit_end[u + kStepUnits - 1];
     }
 
-    // ---- stored elements before the wave's chunk: the sum, or from the pre-pass
+    // ---- stored elements before the wave's chunk: the sum (below 2^27), or from the pre-pass
     unsigned long long before_chunk = 0;
     if (chunk_prefix == nullptr) {
-        __shared__ unsigned s_before[kWaves];
-        const unsigned wave_part = wave_sum_small(total[0] + total[1] + total[2] + total[3]);
+        __shared__ __align__(16) unsigned s_before[kWaves];
+        const unsigned wave_part = wave_sum_small(total);
         if (lane == 0) s_before[wave] = wave_part;
         lds_barrier();
+        unsigned sum = 0;
 #pragma unroll
-        for (int v = 0; v < kWaves; ++v) before_chunk += s_before[v];
+        for (int v = 0; v < kWaves; ++v) sum += s_before[v];
+        before_chunk = uniform(sum);
     }
     if (wave_elem0 >= n) return;                  // nothing of the tensor in this wave's part
     if (chunk_prefix != nullptr) before_chunk = chunk_prefix[chunk];
 
-    expand_step<W, ALIGNED>(s_stage[wave], values, values_avail, before_chunk + step_begin, step_end - step_begin, m,
-                            wave_elem0, n, out, stream_values, lane);
+    expand_step<W, ALIGNED>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, before_chunk + step_begin,
+                            step_end - step_begin, m, wave_elem0, n, out, stream_values, lane);
 }
 
 // The same decoder in one launch, for small tensors: no pre-pass.  A workgroup
@@ -1492,7 +1530,7 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // masks per wave: 32 | 64
     static_assert(G::kStageSteps == 1, "a wave expands one step");
 
-    __shared__ __align__(16) unsigned char s_stage[kWaves][G::kWaveStageBytes];
+    __shared__ __align__(16) unsigned char s_stage[16 + kWaves * G::kWaveStageBytes];   // (16: see expand_piece)
     __shared__ unsigned s_wave_total[kWaves];
     __shared__ unsigned s_arrive;                 // waves arrived << 24 | set bits so far
     __shared__ unsigned long long s_prefix;
@@ -1555,10 +1593,52 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     }
 
     if (wave_elem0 < n)
-        expand_step<W, ALIGNED>(s_stage[wave], values, values_avail, exclusive + wave_offset, wave_total, m,
-                                wave_elem0, n, out, stream_values, lane);
+        expand_step<W, ALIGNED>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset,
+                                wave_total, m, wave_elem0, n, out, stream_values, lane);
 
     if (tile == num_tiles - 1 && wave == 0) finish_call(hdr, counts, num_tiles, lane, state_bytes);
+}
+
+// Global bytes into the LDS slice at the same offsets modulo 16, in two halves,
+// so that a wave can have the loads of several steps in flight before it
+// touches LDS.  wave_fetch requests the aligned
+// 16-byte chunks that hold global bytes [shift, end_valid) at gbase (gbase is
+// 16-byte aligned, shift < 16): chunk q goes to lane q % 64, slot q / 64.  A
+// chunk is loaded whole even where the run begins or ends inside it -- an
+// aligned 16-byte chunk never straddles a page, so the access is as safe as
+// that of the bytes wanted -- and what lies at or past end_valid is cleared.
+// wave_commit stores the chunks to LDS at the same offsets.
+__device__ inline void wave_fetch(uint4 (&r)[kFetchSlots], const unsigned char* gbase, unsigned end_valid,
+                                  bool streaming, int lane) {
+#pragma unroll
+    for (int k = 0; k < kFetchSlots; ++k) {
+        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
+        r[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (q * 16u < end_valid)
+            r[k] = streaming ? load16_stream(gbase + q * 16u)
+                             : *reinterpret_cast<const uint4*>(gbase + q * 16u);
+    }
+}
+
+__device__ inline void wave_commit(unsigned char* stage, const uint4 (&r)[kFetchSlots], unsigned end,
+                                   unsigned end_valid, int lane) {
+#pragma unroll
+    for (int k = 0; k < kFetchSlots; ++k) {
+        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
+        if (q * 16u >= end) continue;
+        uint4 v = r[k];
+        if (q * 16u + 16u > end_valid) {          // only when the stream is cut short
+            const unsigned valid = end_valid > q * 16u ? end_valid - q * 16u : 0u;   // bytes to keep: 0 .. 15
+            unsigned d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned lo = 4u * i;
+                d[i] = valid >= lo + 4u ? d[i] : valid > lo ? d[i] & ((1u << (8u * (valid - lo))) - 1u) : 0u;
+            }
+            v = make_uint4(d[0], d[1], d[2], d[3]);
+        }
+        *reinterpret_cast<uint4*>(stage + q * 16u) = v;
+    }
 }
 
 // Decoder of the windowed stream.  No scan and no pre-pass: the offset table
