@@ -1599,122 +1599,45 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     if (tile == num_tiles - 1 && wave == 0) finish_call(hdr, counts, num_tiles, lane, state_bytes);
 }
 
-// Global bytes into the LDS slice at the same offsets modulo 16, in two halves,
-// so that a wave can have the loads of several steps in flight before it
-// touches LDS.  wave_fetch requests the aligned
-// 16-byte chunks that hold global bytes [shift, end_valid) at gbase (gbase is
-// 16-byte aligned, shift < 16): chunk q goes to lane q % 64, slot q / 64.  A
-// chunk is loaded whole even where the run begins or ends inside it -- an
-// aligned 16-byte chunk never straddles a page, so the access is as safe as
-// that of the bytes wanted -- and what lies at or past end_valid is cleared.
-// wave_commit stores the chunks to LDS at the same offsets.
-__device__ inline void wave_fetch(uint4 (&r)[kFetchSlots], const unsigned char* gbase, unsigned end_valid,
-                                  bool streaming, int lane) {
-#pragma unroll
-    for (int k = 0; k < kFetchSlots; ++k) {
-        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
-        r[k] = make_uint4(0u, 0u, 0u, 0u);
-        if (q * 16u < end_valid)
-            r[k] = streaming ? load16_stream(gbase + q * 16u)
-                             : *reinterpret_cast<const uint4*>(gbase + q * 16u);
-    }
-}
-
-__device__ inline void wave_commit(unsigned char* stage, const uint4 (&r)[kFetchSlots], unsigned end,
-                                   unsigned end_valid, int lane) {
-#pragma unroll
-    for (int k = 0; k < kFetchSlots; ++k) {
-        const unsigned q = static_cast<unsigned>(lane + k * kWaveSize);
-        if (q * 16u >= end) continue;
-        uint4 v = r[k];
-        if (q * 16u + 16u > end_valid) {          // only when the stream is cut short
-            const unsigned valid = end_valid > q * 16u ? end_valid - q * 16u : 0u;   // bytes to keep: 0 .. 15
-            unsigned d[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned lo = 4u * i;
-                d[i] = valid >= lo + 4u ? d[i] : valid > lo ? d[i] & ((1u << (8u * (valid - lo))) - 1u) : 0u;
-            }
-            v = make_uint4(d[0], d[1], d[2], d[3]);
-        }
-        *reinterpret_cast<uint4*>(stage + q * 16u) = v;
-    }
-}
-
-// Decoder of the windowed stream.  No scan and no pre-pass: the offset table
+// Decoders of the windowed stream.  No scan and no pre-pass: the offset table
 // says where a window's bytes are, and a window decodes from its own bytes alone
-// (section 5.2: the popcount of a mask gives the offset of the next mask).  The
-// kernel works in pieces of 4 KB of output (four 1 KB loads of a wave): it
-// stages the piece's bytes in LDS, a few lanes walk the masks one after the
-// other -- the serial chain the paper's decoder has too -- and leave every mask
-// and the position of its first element for the other lanes, which then rebuild
-// 16 bytes of output per load as in the planar decoder.
-//   windows of 1, 2 or 4 KB: a wave takes one piece; it holds 4, 2 or 1 windows,
-//     and lanes 0..3, 0..1 or 0 walk one window each (8..32 masks of 32-bit
-//     elements, twice that of 16-bit ones);
-//   windows of 8..64 KB: a wave takes one window and goes through its pieces
-//     in order; lane 0 walks, and where its walk ends the next piece begins.
-//     Few windows of 16 KB and more take a workgroup each (window_split_kernel).
+// (section 5.2: the popcount of a mask gives the offset of the next mask).  A wave
+// expands 4 KB of output (a piece, expand_piece) from bytes that are staged in LDS;
+// what the kernels differ in is how the masks are found, one after the other -- the
+// serial chain the paper's decoder has too:
+//   windows of 1, 2 or 4 KB (window_decode_kernel): a piece is 4, 2 or 1 windows and
+//     a lane walks each (8..32 masks of 32-bit elements, twice that of 16-bit ones);
+//   windows of 8..64 KB (window_split_kernel): a workgroup takes a window and cuts
+//     the walk into parts.
 // Reads stay inside [0, stream_bytes) and inside the staged bytes whatever the
 // table and the masks say; what a damaged stream asks for beyond that decodes
 // as zero.
-constexpr int kWindowUnitBytes = 1024;  // one load of a wave; window sizes are 1 KB << shift
+constexpr int kWindowUnitBytes = 1024;  // window sizes are 1 KB << shift
 constexpr unsigned kMaxWindowShift = 6; // 64 KB
 
 template <int W>
 struct WindowGeometry {
-    static constexpr int kElemsPerLane = 16 / W;                       // per 16-byte store: 4 | 8
-    static constexpr int kLanesPerGroup = 32 / kElemsPerLane;          // 8 | 4
-    static constexpr int kUnitGroups = kWaveSize / kLanesPerGroup;     // masks per KB of output: 8 | 16
-    static constexpr int kPieceGroups = kStageLoads * kUnitGroups;     // masks per 4 KB piece: 32 | 64
-    static constexpr int kUnitElems = kUnitGroups * 32;
+    static constexpr int kPieceGroups = kStageLoads * kWaveSize * 16 / W / 32;   // masks per 4 KB piece: 32 | 64
+    static constexpr int kPieceElems = kPieceGroups * 32;
     static constexpr unsigned kGroupBytes = 4 + 32 * W;                // a group with nothing dropped
     static constexpr unsigned kPieceBytes = kPieceGroups * kGroupBytes;
-    static_assert(kUnitElems * W == kWindowUnitBytes, "1 KB of output is one load of a wave");
 };
 
-// The mask at an LDS address that is a multiple of W, and its popcount alone.  (The
-// latter reads two halves for W = 2: where many lanes read, an LDS access that is
-// not aligned takes them one after the other.)
+// The mask at an LDS address that is a multiple of W (or, in a damaged stream, of
+// nothing), and its popcount plus `more`.  Two halves for W = 2: an LDS access that is
+// not aligned takes the lanes one after the other.
 template <int W>
-__device__ inline unsigned lds_mask(const unsigned char* p) {
-    typedef unsigned at2 __attribute__((aligned(2)));
+__device__ __forceinline__ unsigned lds_mask(const unsigned char* p) {
     if (W == 4) return *reinterpret_cast<const unsigned*>(p);
-    return *reinterpret_cast<const at2*>(p);
+    return static_cast<unsigned>(*reinterpret_cast<const unsigned short*>(p)) |
+           static_cast<unsigned>(*reinterpret_cast<const unsigned short*>(p + 2)) << 16;
 }
 template <int W>
-__device__ inline unsigned lds_mask_bits(const unsigned char* p) {
-    if (W == 4) return static_cast<unsigned>(__popc(*reinterpret_cast<const unsigned*>(p)));
+__device__ __forceinline__ unsigned lds_mask_bits(const unsigned char* p, unsigned more) {
+    if (W == 4) return static_cast<unsigned>(__popc(*reinterpret_cast<const unsigned*>(p))) + more;
     unsigned low = *reinterpret_cast<const unsigned short*>(p), high = *reinterpret_cast<const unsigned short*>(p + 2);
     asm("" : "+v"(low), "+v"(high));      // (or the compiler goes on in 16 bits, with masks of its own)
-    return static_cast<unsigned>(__popc(low) + __popc(high));
-}
-
-// The serial walk of one lane over `count` masks (a multiple of 8) from LDS offset
-// p on: a record of each group, its mask and the mask's offset, and where the walk
-// ends.  Every step waits for the one before, and with eight waves per SIMD what a
-// step costs is its instructions, so it holds little but the chain: read a mask,
-// add its popcount (6.5 instructions instead of 14; 822 MB fp32 at density 0.05 in
-// 4 KB windows: 170 -> 146 us, 149 MB bf16 in 64 KB windows: 128 -> 104 us.  The
-// same walk on the scalar unit, v_readlane and s_bcnt1, takes 229 and 170 us: it
-// issues an instruction per four clocks and SIMD too, and needs 19 of them).  Past
-// the staged bytes (`limit`) the walk reads whatever lies at their end:
-// empty_missing_groups() sorts those groups out.
-template <int W>
-__device__ inline unsigned walk_masks(const unsigned char* stage, unsigned p, unsigned limit, unsigned count,
-                                      uint2* record) {
-    for (unsigned g0 = 0; g0 < count; g0 += 8) {       // p, limit: less the 4 bytes of every mask since g0
-#pragma unroll
-        for (unsigned g = 0; g < 8; ++g) {
-            const unsigned m = lds_mask<W>(stage + p + 4 * g);
-            record[g0 + g] = make_uint2(m, p + 4 * g);
-            limit -= 4u;
-            p = min(p + W * static_cast<unsigned>(__popc(m)), limit);
-        }
-        p += 32u;
-        limit += 32u;
-    }
-    return p;
+    return static_cast<unsigned>(__popc(low)) + (static_cast<unsigned>(__popc(high)) + more);
 }
 
 // What a mask asks for beyond the bytes that are there decodes as zero, an element
@@ -1728,72 +1651,13 @@ __device__ inline unsigned whole_elements(unsigned mask, unsigned at, unsigned l
     return mask;
 }
 
-// After a walk: the records' offsets become those of the groups' first stored
-// elements, and masks that are not there (from record `groups` on, or not wholly
-// before `limit`) become empty.
-template <int W>
-__device__ inline void empty_missing_groups(uint2* record, int records, unsigned groups, unsigned limit, int lane) {
-    wave_lds_sync();
-    if (lane < records) {
-        uint2 group = record[lane];
-        if (static_cast<unsigned>(lane) >= groups || group.y + 4u > limit) group.x = 0u;
-        group.y += 4u;
-        group.x = whole_elements<W>(group.x, group.y, limit);
-        record[lane] = group;
-    }
-    wave_lds_sync();
-}
-
-// Output of up to UNITS KB, elements elem0 .. elem_end - 1 of the tensor (elem_end -
-// elem0 may be more than that), to `out`, where element elem0 goes.  group_at(i):
-// mask of the i-th group from elem0 on and LDS offset of its first stored element.
-template <int W, int UNITS, bool ALIGNED, class GroupAt>
-__device__ __forceinline__ void expand_groups(const unsigned char* stage, const GroupAt& group_at, size_t elem0,
-                                              size_t elem_end, unsigned char* out, unsigned dummy, int lane) {
-    using G = WindowGeometry<W>;
-    constexpr int E = G::kElemsPerLane, LPG = G::kLanesPerGroup;
-    const bool full = elem0 + static_cast<size_t>(UNITS) * G::kUnitElems <= elem_end;
-#pragma unroll
-    for (int jj = 0; jj < UNITS; ++jj) {
-        if (elem0 + static_cast<size_t>(jj) * G::kUnitElems >= elem_end) break;
-        const unsigned in_piece = static_cast<unsigned>((jj * kWaveSize + lane) * E);
-        const uint2 group = group_at(jj * G::kUnitGroups + lane / LPG);
-        const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E;
-        unsigned at = group.y + W * __popc(group.x & ((1u << bit0) - 1u));
-        const unsigned field = group.x >> bit0;
-        unsigned d[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int c = 0; c < E; ++c) {
-            const bool set = ((field >> c) & 1u) != 0u;
-            const unsigned from = set ? at : dummy;
-            if (W == 4) {
-                const unsigned v = *reinterpret_cast<const unsigned*>(stage + from);
-                d[c] = set ? v : 0u;
-            } else {
-                const unsigned v = *reinterpret_cast<const unsigned short*>(stage + from);
-                d[c >> 1] |= (set ? v : 0u) << (16 * (c & 1));
-            }
-            at += set ? W : 0;
-        }
-        const size_t e0 = elem0 + in_piece;
-        if (full || e0 + E <= elem_end) {
-            if (ALIGNED) store16_stream(out + in_piece * W, make_uint4(d[0], d[1], d[2], d[3]));
-            else store16_loose<W>(out + in_piece * W, make_uint4(d[0], d[1], d[2], d[3]));
-        } else {
-#pragma unroll
-            for (int c = 0; c < E; ++c) {
-                if (e0 + c < elem_end) {
-                    if (W == 4)
-                        reinterpret_cast<unsigned*>(out)[in_piece + c] = d[c];
-                    else
-                        reinterpret_cast<unsigned short*>(out)[in_piece + c] = static_cast<unsigned short>(
-                            (d[c >> 1] >> (16 * (c & 1))) & 0xFFFFu);
-                }
-            }
-        }
-    }
-}
-
+// A workgroup takes four pieces, a wave each.  A wave walks its own windows, a lane per
+// window, but for 4 KB windows of 16-bit elements, whose one lane would keep the wave for 64
+// steps: there one of the waves (not the same one in every workgroup, so that the SIMDs
+// share the work) walks for all four, which saves instructions and costs two barriers (51 MB
+// bf16: 16.9 us, a wave its own 18.6; but 103 MB fp32 in 4 KB windows 23.5 and 19.6, 51 MB
+// bf16 in 2 KB windows 15.1 and 13.6).  The walk was bound by its instructions, and so was
+// the rest: 103 MB fp32 from 4 KB windows 23.9 us before, 16-bit 22.5.
 template <int W, bool ALIGNED>
 __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     const unsigned char* __restrict__ stream, unsigned long long stream_bytes,
@@ -1803,111 +1667,119 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     using G = WindowGeometry<W>;
     // shift < 16, then a piece, then what a walk that is past its end reads
     constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + G::kGroupBytes + 15) / 16 * 16;
-    __shared__ __align__(16) unsigned char s_stage[kWaves][kSliceBytes];
-    __shared__ __align__(16) uint2 s_group[kWaves][G::kPieceGroups];
+    constexpr unsigned kMostWindows = kStageLoads;          // per piece
+    static_assert(G::kPieceBytes + 15 <= kFetchSlots * kSlotBytes, "a piece fits the fetch slots");
+    __shared__ __align__(16) unsigned char s_stage[16 + kWaves * kSliceBytes];      // (16: see expand_piece)
+    __shared__ unsigned s_mask_at[kWaves * G::kPieceGroups];
+    __shared__ __align__(8) uint2 s_window[kWaves * kMostWindows];                  // where a window begins, where the piece ends
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = static_cast<int>(uniform(static_cast<unsigned>(tid / kWaveSize)));
-    const unsigned shift_w = window_shift;
-    // windows in a piece (small windows) | pieces in a window (large ones)
-    const unsigned piece_windows = shift_w <= 2 ? kStageLoads >> shift_w : 1u;
-    const unsigned window_pieces = shift_w <= 2 ? 1u : 1u << (shift_w - 2);
-    const unsigned walker_groups = static_cast<unsigned>(G::kPieceGroups) / piece_windows;
-    // the wave's share: dealt out in a row or, as in the planar decoder, interleaved over the XCDs
+    const bool together = W == 2 && window_shift == 2;
+    const unsigned piece_windows = kMostWindows >> window_shift;                    // 4, 2, 1
+    const unsigned window_groups = static_cast<unsigned>(G::kPieceGroups) / kMostWindows << window_shift;
+    // the wave's piece: dealt out in a row or, as in the planar decoder, interleaved over the XCDs
     const size_t share = interleave ? (static_cast<size_t>(blockIdx.x / 8) * kWaves + wave) * 8 + blockIdx.x % 8
                                     : static_cast<size_t>(blockIdx.x) * kWaves + wave;
     const size_t local = share * piece_windows;             // first of the wave's windows, within the range
-    if (local >= num_windows) return;
+    const unsigned windows_here = local >= num_windows ? 0u
+                                : num_windows - local < piece_windows ? static_cast<unsigned>(num_windows - local) : piece_windows;
     const size_t window0 = first_window + local;
-    const unsigned windows_here =
-        num_windows - local < piece_windows ? static_cast<unsigned>(num_windows - local) : piece_windows;
-    const size_t units = div_up(num_groups, static_cast<size_t>(G::kUnitGroups));   // KBs of output in the tensor
-
     const auto clamped = [&](size_t k) {
         const unsigned long long o = offsets[k];
         return o > stream_bytes ? stream_bytes : o;
     };
-    unsigned long long lo = clamped(window0);               // where the piece's bytes begin
-    unsigned long long hi = clamped(window0 + windows_here);
-    if (hi < lo) hi = lo;
-    unsigned char* stage = s_stage[wave];
+    const unsigned slice = 16u + wave * kSliceBytes;
+    unsigned limit = slice;
 
-    static_assert(G::kPieceBytes + 16 <= kFetchSlots * kWaveSize * 16, "a piece fits the fetch slots");
-
-    for (unsigned piece = 0; piece < window_pieces; ++piece) {
-        const size_t unit0 = (window0 << shift_w) + static_cast<size_t>(piece) * kStageLoads;
-        if (unit0 >= units) break;
-
-        // ---- the piece's bytes, clamped to what can be there
-        const unsigned cur_bytes = hi - lo > G::kPieceBytes ? G::kPieceBytes : static_cast<unsigned>(hi - lo);
-        const unsigned char* src = stream + lo;    // wave-uniform, aligned to W
-        const unsigned cur_shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
-        const unsigned cur_limit = cur_shift + cur_bytes;
-        {
-            uint4 fetched[kFetchSlots];
-            wave_fetch(fetched, src - cur_shift, cur_bytes != 0 ? cur_limit : 0u, false, lane);
-            wave_commit(stage, fetched, cur_limit, cur_bytes != 0 ? cur_limit : 0u, lane);
-        }
-        wave_lds_sync();
-
-        // ---- the serial walk: one lane per window of the piece
-        const unsigned groups_here = static_cast<unsigned>(
-            min(num_groups - unit0 * G::kUnitGroups, static_cast<size_t>(shift_w <= 2 ? windows_here * walker_groups
-                                                                                      : G::kPieceGroups)));
-        unsigned walk_end = 0;
+    // ---- the piece's bytes, clamped to what can be there, and where its windows begin: a window whose
+    //      offset is off reads nothing
+    if (windows_here != 0) {
+        const unsigned long long lo = clamped(window0), hi = clamped(window0 + windows_here);
+        const unsigned bytes = hi <= lo ? 0u : hi - lo > G::kPieceBytes ? G::kPieceBytes : static_cast<unsigned>(hi - lo);
+        const unsigned char* src = stream + lo;             // wave-uniform
+        const unsigned shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
+        limit = slice + shift + bytes;
+        wave_stage<false>(s_stage + slice, src - shift, bytes != 0 ? shift + bytes : 0u, lane);
         if (static_cast<unsigned>(lane) < piece_windows) {
-            // a small window begins where the table says; a piece of a large one where the last walk ended.
-            // A window that is not there, or whose offset is off, reads nothing.
-            unsigned p = cur_limit;
+            unsigned p = limit;
             if (static_cast<unsigned>(lane) < windows_here) {
-                const unsigned long long o = piece == 0 ? clamped(window0 + lane) : lo;
-                if (o >= lo && o - lo <= cur_bytes) p = cur_shift + static_cast<unsigned>(o - lo);
+                const unsigned long long o = clamped(window0 + lane);
+                if (o >= lo && o - lo <= bytes) p = slice + shift + static_cast<unsigned>(o - lo);
             }
-            walk_end = walk_masks<W>(stage, p, cur_limit, walker_groups, s_group[wave] + lane * walker_groups);
+            s_window[wave * piece_windows + lane] = make_uint2(p, limit);
         }
-        empty_missing_groups<W>(s_group[wave], G::kPieceGroups, groups_here, cur_limit, lane);
-
-        // ---- a large window's next piece begins where lane 0's walk ended (never beyond the
-        // window).  (Asking for its bytes here, before this piece is expanded, measured no faster.)
-        const bool more = piece + 1 < window_pieces && unit0 + kStageLoads < units;
-        unsigned long long next_lo = lo;
-        if (more) {
-            const unsigned end = lane_value(walk_end, 0);
-            const unsigned long long next = lo + ((end < cur_limit ? end : cur_limit) - cur_shift);
-            next_lo = next < hi ? next : hi;
-        }
-
-        // ---- expand
-        const size_t elem0 = unit0 * G::kUnitElems;
-        expand_groups<W, kStageLoads, ALIGNED>(
-            stage, [&](int i) { return s_group[wave][i]; }, elem0,
-            min(n, elem0 + static_cast<size_t>(groups_here) * 32),
-            out + ((local << shift_w) + static_cast<size_t>(piece) * kStageLoads) * kWindowUnitBytes, cur_shift, lane);
-        if (!more) break;
-        lo = next_lo;
-        wave_lds_sync();     // the expand's reads of the stage are done before it is overwritten
+        stage_wait();
+    } else if (static_cast<unsigned>(lane) < piece_windows) {
+        s_window[wave * piece_windows + lane] = make_uint2(limit, limit);
     }
+    if (together) lds_barrier();
+    else wave_lds_sync();
+
+    // ---- the walks.  Every step waits for the one before: read a mask, add its popcount.  Past the
+    //      staged bytes a walk reads whatever lies at their end; those masks are sorted out below.
+    const unsigned walkers = together ? kWaves * piece_windows : piece_windows;
+    if ((!together || static_cast<unsigned>(wave) == blockIdx.x / 8 % kWaves) && static_cast<unsigned>(lane) < walkers) {
+        const unsigned k = together ? lane : wave * piece_windows + lane;
+        const uint2 window = s_window[k];
+        unsigned* at = s_mask_at + k * window_groups;
+        unsigned p = window.x, stop = window.y;
+        for (unsigned g0 = 0; g0 < window_groups; g0 += 8) {     // p, stop: less the 4 bytes of every mask since g0
+#pragma unroll
+            for (unsigned g = 0; g < 8; ++g) {
+                at[g0 + g] = p + 4 * g;
+                stop -= 4u;
+                p = min(p + W * lds_mask_bits<W>(s_stage + p + 4 * g, 0u), stop);
+            }
+            p += 32u;
+            stop += 32u;
+        }
+    }
+    if (together) lds_barrier();
+    else wave_lds_sync();
+    if (windows_here == 0) return;
+
+    // ---- the piece's masks, a lane each: none where there is no group, or not the whole mask
+    const size_t group0 = window0 * window_groups;
+    const size_t there = num_groups > group0 ? num_groups - group0 : 0;
+    const unsigned groups_here = min(static_cast<unsigned>(min(there, static_cast<size_t>(G::kPieceGroups))),
+                                     windows_here * window_groups);
+    unsigned mask = 0, value_at = slice;
+    if (static_cast<unsigned>(lane) < groups_here) {
+        const unsigned at = s_mask_at[wave * G::kPieceGroups + lane];
+        value_at = at + 4u;
+        if (value_at <= limit) mask = whole_elements<W>(lds_mask<W>(s_stage + at), value_at, limit);
+    }
+    const unsigned left = static_cast<unsigned>(min(n - min(n, group0 * 32), static_cast<size_t>(groups_here) * 32));
+    expand_piece<W, ALIGNED>(s_stage, mask, value_at, left, out + (local << window_shift) * kWindowUnitBytes, lane);
 }
 
-// The same for a few large windows: a workgroup of NW = window / 4 KB waves takes
-// one.  A walk cannot start in the middle of a window, but where it can come from
-// is limited: a group is 1 to 33 words of 32 bits (2 to 34 of 16), so of the walks
-// that cross a given byte one enters what follows at one of its first 33 (34)
-// words.  The window's bytes are cut into 4 NW equal parts, 4 in a row per wave,
-// and each wave
-//   1. walks each of its parts from all those words at once, a lane each (the four
-//      parts' chains overlap), which takes as long as a single walk over a part,
-//      and notes where in the next part the walks come out and how many groups they
-//      have passed; of a wave's four parts that makes one such table, in LDS;
-//   2. looks up wave by wave which of the walks was the true one, and so its own
-//      first word and first group;
-//   3. walks its parts again from the four true words, a lane each, and expands
-//      their groups, 32 at a time.
-// So a window takes a 32nd of the serial walk (64 KB) and a table look-up per wave
-// instead of all of it, for twice the instructions (51 MB bf16 at density 0.3, 784
-// windows of 64 KB: 25.4 M wave instructions against 12.9 M; 12 % of the LDS cycles
-// are bank conflicts).
+// Windows of 8 KB and more: a workgroup of NW = window / 4 KB waves takes one.  A walk
+// cannot start in the middle of a window, but where it can come from is limited: a
+// group is 1 to 33 words of 32 bits (2 to 34 of 16), so of the walks that cross a given
+// byte one enters what follows at one of its first 33 (34) words.  The window's bytes
+// are cut into equal parts, and
+//   1. every part is walked from all those words at once, a lane each: the (part, word)
+//      pairs of the window are laid over the lanes of all waves, kRows per lane (whose
+//      chains overlap), so that hardly a lane is idle.  Tables say for each pair where in
+//      the next part the walk comes out, where in the part's second half it came out, and
+//      how many groups it had passed by then;
+//   2. the tables of kPartsPerBlock parts in a row are made one, a wave for each block;
+//   3. one or two waves follow the true walk through those, so that they have the first
+//      word and the first group of every half of a part, and walk these again from there, a
+//      lane each, noting the masks' offsets;
+//   4. every wave expands its 4 KB of the window.
+// Phase 1 is most of the instructions (6 per step and row) and, like 3, a chain of LDS
+// reads: 74 MB bf16 from 64 KB windows of densities 0.1 to 0.9 take 23 us with no walks at
+// all, phase 1 adds 5, 3 adds 5, the expansion of real masks 5: 38 us, two workgroups per CU
+// (LDS).  Before, every wave walked four parts of its own from 34 of its 64 lanes and
+// expanded what it found, 64 us; large numbers of windows went to a wave each, whose one
+// lane walked: 822 MB fp32 from 8 KB windows 214 us, now 200; from 64 KB windows 273, now
+// 232; 411 MB bf16 145 and 192, now 130 and 168; one or two windows of 64 KB, fp32 and bf16,
+// 11.4 and 22.1, now 8.4 and 12.0.  Three or four rows (shorter chains, more of them) are
+// slower by 3 to 5 %, walking parts whole in phase 3 by 4 to 9 %, its starts handed over by
+// the lanes that walked there (two barriers more) by 6 %.
 template <int W, int NW, bool ALIGNED>
 __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
     const unsigned char* __restrict__ stream, unsigned long long stream_bytes,
@@ -1916,19 +1788,30 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
     using G = WindowGeometry<W>;
     constexpr unsigned kWindowGroups = NW * G::kPieceGroups;
     constexpr unsigned kEntries = 32 + 4 / W;               // 33 | 34
-    constexpr unsigned kLost = kWaveSize - 1;               // as a word: no walk goes on from here
-    constexpr int kParts = 4;                               // per wave
-    constexpr unsigned kBatch = 32;                         // groups expanded at a time
-    constexpr unsigned kPositions = 128;                    // groups of a wave whose walk is recorded at once
-    // shift < 16, parts with nothing dropped, the rest of their last group, what a walk that is past them reads
-    constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + kParts * W + 2 * G::kGroupBytes + 15) / 16 * 16;
-    static_assert(kSliceBytes <= kFetchSlots * kWaveSize * 16, "a wave's parts fit the fetch slots");
-    __shared__ __align__(16) unsigned char s_stage[NW * kSliceBytes];
-    __shared__ unsigned short s_at[NW][kPositions];         // offset of a group's mask in the wave's slice
-    __shared__ unsigned s_exit[NW][kEntries];               // groups << 8 | word of the next wave's first part
+    constexpr unsigned kLost = 63;                          // as a word: no walk goes on from here
+    constexpr int kRows = 2;
+    constexpr unsigned kSubs = 2;                           // a part is walked again in halves
+    constexpr unsigned kPairs = NW * kRows * kWaveSize;
+    constexpr unsigned kParts = kPairs / kEntries;
+    constexpr unsigned kBlocks = NW < 8 ? (NW + 1) / 2 : 8;
+    constexpr unsigned kPartsPerBlock = (kParts + kBlocks - 1) / kBlocks;
+    constexpr unsigned kMostBytes = kWindowGroups * G::kGroupBytes;
+    constexpr unsigned kNoGroup = 0xFFFF;
+    static_assert(kBlocks <= NW && kParts * kSubs <= NW * kWaveSize, "a wave per block, a lane per half of a part");
+    static_assert(kEntries < kLost && kWindowGroups <= 1024, "a table entry is 6 bits of word, 10 of groups");
+    static_assert(kMostBytes / W + 2 * kEntries < kNoGroup, "words in a window are counted in 16 bits");
+    static_assert((kMostBytes / kParts + W) / 4 < 1024, "groups of a part in 10");
+    // 16: see expand_piece; shift < 16; behind the window what a walk that is past its end reads: from any
+    // entry a group further
+    constexpr unsigned kStageBytes = (16 + 16 + kMostBytes + W * kEntries + G::kGroupBytes + 4 + 15) / 16 * 16;
+    __shared__ __align__(16) unsigned char s_stage[kStageBytes];
+    // of every pair, at the end of its part's halves: groups passed << 6 | word that the walk comes out at
+    __shared__ unsigned short s_exit[kSubs][kParts * kEntries];
+    __shared__ unsigned short s_block[kBlocks][kEntries];   // of every entry into a block of parts: the same at its end
+    __shared__ unsigned short s_mask_at[kWindowGroups];     // words from the window's beginning to a group's mask
 
-    const int lane = static_cast<int>(threadIdx.x) & (kWaveSize - 1);
-    const int wave = static_cast<int>(uniform(threadIdx.x / kWaveSize));
+    const unsigned lane = threadIdx.x & (kWaveSize - 1);
+    const unsigned wave = uniform(threadIdx.x / kWaveSize);
     const size_t window = first_window + blockIdx.x;
     const size_t window_group0 = window * kWindowGroups;
     const unsigned groups = num_groups - window_group0 < kWindowGroups ? static_cast<unsigned>(num_groups - window_group0)
@@ -1941,128 +1824,135 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
     const unsigned long long there = hi > lo ? hi - lo : 0ull;
     const unsigned bytes = there > groups * G::kGroupBytes ? groups * G::kGroupBytes : static_cast<unsigned>(there);
 
-    // ---- the wave's parts, and the rest of the group that begins on their last word.
-    //      Offsets below are from the beginning of s_stage.
-    const unsigned part = (bytes + NW * kParts * W - 1) / (NW * kParts * W) * W;
-    const unsigned wave0 = min(kParts * part * wave, bytes);
-    const unsigned own = min(kParts * part, bytes - wave0);
-    const unsigned readable = min(kParts * part + G::kGroupBytes, bytes - wave0);
-    const unsigned char* src = stream + lo + wave0;
-    const unsigned skew = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
-    const unsigned slice = wave * kSliceBytes;
-    const unsigned begin = slice + skew, limit = begin + readable;
-    {
-        uint4 fetched[kFetchSlots];
-        wave_fetch(fetched, src - skew, readable != 0 ? skew + readable : 0u, false, lane);
-        wave_commit(s_stage + slice, fetched, skew + readable, readable != 0 ? skew + readable : 0u, lane);
+    // ---- the window's bytes: all waves, 1 KB at a time
+    const unsigned char* src = stream + lo;
+    const unsigned shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
+    const unsigned begin = 16u + shift;                     // in s_stage
+    const unsigned end = bytes != 0 ? shift + bytes : 0u;
+#pragma unroll
+    for (unsigned at = 0; at < kMostBytes + 15; at += NW * kSlotBytes) {
+        const unsigned slot = at + wave * kSlotBytes;
+        if (slot >= end) break;                             // uniform
+        stage_slot<false, 0>(s_stage + 16 + slot, src - shift + slot, end - slot, static_cast<int>(lane));
     }
-    wave_lds_sync();
-
-    // ---- 1. all walks that can enter the parts (a finished walk goes on reading where it stands)
-    unsigned part_end[kParts], walk_end[kParts], p[kParts], passed[kParts];
-#pragma unroll
-    for (int q = 0; q < kParts; ++q) {
-        part_end[q] = begin + min((q + 1) * part, own);
-        walk_end[q] = min(part_end[q], max(limit, 3u) - 3u);       // a mask lies wholly before `limit`
-        p[q] = begin + min(q * part, own) + static_cast<unsigned>(W * lane);
-        passed[q] = 0;
-    }
-    bool going = true;
-    while (going) {
-        bool on[kParts];
-#pragma unroll
-        for (int twice = 0; twice < 2; ++twice) {
-            unsigned bits[kParts];
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) bits[q] = lds_mask_bits<W>(s_stage + p[q]);
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) {
-                on[q] = p[q] < walk_end[q];
-                passed[q] += on[q] ? 1u : 0u;
-                p[q] = on[q] ? p[q] + (W * bits[q] + 4u) : p[q];
-            }
-        }
-        going = __any(on[0] | on[1] | on[2] | on[3]);
-    }
-    // entry[q]: where the walk that entered the first part at the lane's word enters part q; before[q]:
-    // groups it has passed by then
-    unsigned entry[kParts + 1], before[kParts + 1];
-    entry[0] = lane < static_cast<int>(kEntries) ? static_cast<unsigned>(lane) : kLost;
-    before[0] = 0;
-#pragma unroll
-    for (int q = 0; q < kParts; ++q) {
-        const unsigned come_out = lane >= static_cast<int>(kEntries) || p[q] < part_end[q] ? kLost
-                                                                                           : (p[q] - part_end[q]) / W;
-        const unsigned v = __shfl(lane == static_cast<int>(kLost) ? kLost : passed[q] << 8 | come_out,
-                                  static_cast<int>(entry[q]));
-        entry[q + 1] = v & 255u;
-        before[q + 1] = before[q] + (v >> 8);
-    }
-    if (lane < static_cast<int>(kEntries)) s_exit[wave][lane] = before[kParts] << 8 | entry[kParts];
+    if (lane < static_cast<unsigned>(G::kPieceGroups)) s_mask_at[wave * G::kPieceGroups + lane] = kNoGroup;
+    stage_wait();
     lds_barrier();
 
-    // ---- 2. the true one
-    unsigned word = 0, first = 0;
-    for (int k = 0; k < wave && word != kLost; ++k) {
-        const unsigned v = uniform(s_exit[k][word]);
-        first += v >> 8;
-        word = v & 255u;
-    }
-    const unsigned count = lane_value(before[kParts], static_cast<int>(word));     // (0 in lane kLost)
-    const unsigned end = min(first + count, groups);
-
-    // ---- 3. its groups: all at once if there is room for their offsets, else 32 at a time
-    unsigned char* const window_out = out + static_cast<size_t>(blockIdx.x) * (kWindowGroups * 32 * W);
-    const size_t window_elem0 = window_group0 * 32;
-    const bool at_once = count <= kPositions;
-    unsigned at = begin, left = 0, slot = 0;               // a lane's walk
+    // ---- 1. all walks that can enter a part.  Words are counted from the window's beginning; a walk's state
+    //         is its word and, in the upper half, the groups it has passed.  (A finished walk goes on reading
+    //         where it stands.)
+    const unsigned words = (bytes + W - 1) / W, part = (words + kParts - 1) / kParts, sub = (part + kSubs - 1) / kSubs;
+    const unsigned mask_words = bytes >= 4u ? (bytes - 4u) / W + 1u : 0u;   // a mask that begins before this is wholly there
+    const auto sub_end = [&](unsigned q, unsigned c) { return min(q * part + min((c + 1) * sub, part), words); };
+    const auto step = [&](unsigned state) __attribute__((always_inline)) {
+        unsigned at;                                        // begin + W * (the lower half of state)
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(state), "n"(W), "s"(begin));
+        return state + lds_mask_bits<W>(s_stage + at, (1u << 16) + 4u / W);
+    };
+    unsigned state[kRows], q[kRows], entry[kRows];
 #pragma unroll
-    for (int q = 0; q < kParts; ++q) {
-        // (read by the whole wave: what one lane alone goes on to compute is not there in the others)
-        const unsigned part_word = lane_value(entry[q], static_cast<int>(word));
-        const unsigned part_first = lane_value(before[q], static_cast<int>(word));
-        const unsigned part_last = lane_value(before[q + 1], static_cast<int>(word));
-        if (lane == q && at_once) {
-            at = begin + min(q * part, own) + W * part_word;
-            slot = part_first;
-            left = part_last - part_first;
+    for (int r = 0; r < kRows; ++r) {
+        const unsigned i = (wave * kRows + r) * kWaveSize + lane;
+        q[r] = i / kEntries;
+        entry[r] = i - q[r] * kEntries;
+        state[r] = min(q[r] * part, words) + entry[r];
+    }
+#pragma unroll
+    for (unsigned c = 0; c < kSubs; ++c) {
+        unsigned stop[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) stop[r] = q[r] < kParts ? min(sub_end(q[r], c), mask_words) : 0u;
+        bool going = true;
+        while (going) {
+            going = false;
+#pragma unroll
+            for (int twice = 0; twice < 2; ++twice) {
+                unsigned next[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) next[r] = step(state[r]);
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    const bool on = static_cast<unsigned short>(state[r]) < static_cast<unsigned short>(stop[r]);
+                    state[r] = on ? next[r] : state[r];
+                    if (twice == 1) going |= on;
+                }
+            }
+            going = __any(going);
+        }
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const unsigned word = state[r] & 0xFFFFu, from = sub_end(q[r], c);
+            if (q[r] < kParts)
+                s_exit[c][q[r] * kEntries + entry[r]] =
+                    static_cast<unsigned short>(state[r] >> 16 << 6 | (word < from ? kLost : word - from));
         }
     }
-    while (left != 0) {
-        s_at[wave][slot++] = static_cast<unsigned short>(at - slice);
-        at += W * (lds_mask_bits<W>(s_stage + at) + 4u / W);
-        --left;
+    lds_barrier();
+
+    // ---- 2. the tables of a block of parts made one; a part's own table then says how a walk gets from the
+    //         block's beginning to the part.  (A walk that has passed 1024 groups has passed all there can be.)
+    if (wave < kBlocks) {
+        unsigned word = lane < kEntries ? lane : kLost, before = 0;
+#pragma unroll
+        for (unsigned j = 0; j < kPartsPerBlock; ++j) {
+            const unsigned part_entry = (wave * kPartsPerBlock + j) * kEntries;
+            if (part_entry >= kParts * kEntries) break;     // uniform
+            const unsigned v = word != kLost ? s_exit[kSubs - 1][part_entry + word] : kLost;
+            if (lane < kEntries)
+                s_exit[kSubs - 1][part_entry + lane] = static_cast<unsigned short>(before < kWindowGroups ? before << 6 | word : kLost);
+            before += v >> 6;
+            word = v & 63u;
+        }
+        if (lane < kEntries) s_block[wave][lane] = static_cast<unsigned short>(before < kWindowGroups ? before << 6 | word : kLost);
     }
-    unsigned walker = begin + W * word;                    // where group g begins, if not all at once
-    for (unsigned g = first; g < end; g += kBatch) {
-        const unsigned here = min(end - g, kBatch);
-        if (!at_once && lane == 0) {
-            for (unsigned i = 0; i < here; ++i) {
-                s_at[wave][i] = static_cast<unsigned short>(walker - slice);
-                walker += W * (lds_mask_bits<W>(s_stage + walker) + 4u / W);
+    lds_barrier();
+
+    // ---- 3. the true walk
+    const unsigned k = wave * kWaveSize + lane;
+    if (k < kParts * kSubs) {
+        const unsigned mine = k / kSubs, c = k - mine * kSubs;
+        unsigned word = 0, first = 0;
+        for (unsigned b = 0; b < mine / kPartsPerBlock && word != kLost; ++b) {
+            const unsigned v = s_block[b][word];
+            first += v >> 6;
+            word = v & 63u;
+        }
+        if (word != kLost) {
+            const unsigned v = s_exit[kSubs - 1][mine * kEntries + word];
+            first += v >> 6;
+            word = v & 63u;
+        }
+        if (word != kLost && c != 0) {
+            const unsigned v = s_exit[c - 1][mine * kEntries + word];
+            first += v >> 6;
+            word = v & 63u;
+        }
+        if (word != kLost && first < groups) {
+            unsigned at = (c == 0 ? min(mine * part, words) : sub_end(mine, c - 1)) + word;
+            const unsigned last = min(sub_end(mine, c), mask_words);
+            while (at < last && first < groups) {
+                s_mask_at[first++] = static_cast<unsigned short>(at);
+                at += lds_mask_bits<W>(s_stage + begin + W * at, 4u / W);
             }
         }
-        wave_lds_sync();
-        unsigned mask = 0, value = limit;
-        if (static_cast<unsigned>(lane) < here) {
-            const unsigned m = slice + s_at[wave][(at_once ? g - first : 0u) + lane];
-            value = m + 4u;
-            mask = whole_elements<W>(lds_mask<W>(s_stage + m), value, limit);
-        }
-        const size_t elem0 = window_elem0 + static_cast<size_t>(g) * 32;
-        expand_groups<W, kBatch / G::kUnitGroups, ALIGNED>(
-            s_stage, [&](int i) { return make_uint2(__shfl(mask, i), __shfl(value, i)); }, elem0,
-            min(n, elem0 + static_cast<size_t>(here) * 32), window_out + static_cast<size_t>(g) * (32 * W), begin, lane);
-        wave_lds_sync();
     }
-    // ---- groups that a damaged stream has no mask for are zero
-    if (wave == NW - 1) {
-        const size_t to = min(n, window_elem0 + static_cast<size_t>(groups) * 32);
-        for (size_t e = window_elem0 + static_cast<size_t>(end) * 32 + lane; e < to; e += kWaveSize) {
-            if (W == 4) reinterpret_cast<unsigned*>(window_out)[e - window_elem0] = 0u;
-            else reinterpret_cast<unsigned short*>(window_out)[e - window_elem0] = 0;
+    lds_barrier();
+
+    // ---- 4. the wave's masks, a lane each (none for groups that a damaged stream has no mask for)
+    const size_t elem0 = (window_group0 + wave * G::kPieceGroups) * 32;
+    if (elem0 >= n) return;
+    unsigned mask = 0, value_at = begin;
+    if (lane < static_cast<unsigned>(G::kPieceGroups)) {
+        const unsigned at = s_mask_at[wave * G::kPieceGroups + lane];
+        if (at != kNoGroup) {
+            value_at = begin + W * at + 4u;
+            mask = whole_elements<W>(lds_mask<W>(s_stage + value_at - 4), value_at, begin + bytes);
         }
     }
+    const unsigned left = static_cast<unsigned>(min(n - elem0, static_cast<size_t>(G::kPieceElems)));
+    expand_piece<W, ALIGNED>(s_stage, mask, value_at, left,
+                             out + (static_cast<size_t>(blockIdx.x) * NW + wave) * (G::kPieceElems * W), static_cast<int>(lane));
 }
 
 // Count-only pass (section 5.4's size, without producing the stream).  One
@@ -2316,39 +2206,34 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
                   interleave);
 }
 
-// Which windows a workgroup each decodes (window_split_kernel) instead of a wave
-// each: large ones, while there are too few of them to fill the GPU with waves.  A
-// wave's walk over a 64 KB window takes 50 us (fp32) or 75 (16-bit) however few there
-// are; a workgroup takes 10.9 or 21.5, but twice the instructions.  In us, wave |
-// workgroup each, channels of densities 0.1 to 0.9 (of one density throughout, the
-// workgroups gain more: 21.1 | 10.7 at 768 windows of 16 KB of 16-bit elements):
-//   fp32    16 KB: 1000 windows 15 | 12, 2000 windows 17.4 | 17.0, 3000 windows 19.6 | 22.4
-//           32 KB: 1000 windows 28 | 18, 2000 windows 30.4 | 28.2, 3000 windows 34.8 | 38.4
-//           64 KB: 1000 windows 52 | 31, 2000 windows 56.5 | 53.1, 3000 windows 74.8 | 78.6
-//   16-bit  16 KB:  440 windows 21.3 | 19.5,  768 windows 21.2 | 20.8,  900 windows 21.9 | 22.9
-//           32 KB: 1024 windows 40.5 | 34.5, 1536 windows 46.4 | 45.4, 1700 windows 46.3 | 47.6
-//           64 KB: 1536 windows 87.6 | 79.3, 1792 windows 87.6 | 91.1 (cold 93.6 | 92.4), 1900 windows 87.8 | 94.5
-inline bool splits_windows(size_t num_windows, int shift, int w) {
-    const size_t most = w == 4 ? 2048 : shift == 4 ? 768 : shift == 5 ? 1536 : 1792;
-    return shift >= 4 && num_windows <= most;
-}
+// Windows that a workgroup each decodes (window_split_kernel) instead of a lane each: from
+// 8 KB on, at every number of windows (in us, lane | workgroup each, densities 0.1 to 0.9:
+// 8 KB, 103 MB fp32 30.3 | 27.5, 51 MB bf16 28.1 | 24.0; the lane's chain is a quarter of
+// that at 2 KB and the workgroup's three barriers stay).
+constexpr int kSplitShift = 3;
 
 template <int W, int NW>
 hipError_t launch_window_split_as(bool aligned, hipStream_t stream, const unsigned char* in,
                                   unsigned long long stream_bytes, const unsigned long long* offsets, size_t n,
                                   size_t groups, size_t first_window, size_t num_windows, unsigned char* out) {
-    return launch(aligned ? window_split_kernel<W, NW, true> : window_split_kernel<W, NW, false>,
-                  dim3(static_cast<unsigned>(num_windows)), dim3(NW * kWaveSize), stream, in, stream_bytes, offsets, n,
-                  groups, first_window, out);
+    constexpr size_t kWindowBytes = size_t{4096} * NW, kMostWindows = (size_t{1} << 31) / (NW * kWaveSize);
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < num_windows && e == hipSuccess; k += kMostWindows)     // (a launch takes fewer than 2^32 threads)
+        e = launch(aligned ? window_split_kernel<W, NW, true> : window_split_kernel<W, NW, false>,
+                   dim3(static_cast<unsigned>(num_windows - k < kMostWindows ? num_windows - k : kMostWindows)),
+                   dim3(NW * kWaveSize), stream, in, stream_bytes, offsets, n, groups, first_window + k,
+                   out + k * kWindowBytes);
+    return e;
 }
 template <int W, typename... Args>
 hipError_t launch_window_split(int waves, Args... args) {
     switch (waves) {
+        case 2: return launch_window_split_as<W, 2>(args...);
         case 4: return launch_window_split_as<W, 4>(args...);
         case 8: return launch_window_split_as<W, 8>(args...);
         case 16: return launch_window_split_as<W, 16>(args...);
     }
-    return hipErrorInvalidValue;   // splits_windows() takes no other
+    return hipErrorInvalidValue;   // there is no other window size from kSplitShift on
 }
 
 // Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword).
@@ -2711,14 +2596,14 @@ zvc_status zvc_window_decompress(const void* d_stream, size_t stream_bytes, cons
     unsigned char* out = static_cast<unsigned char*>(d_out);
     const size_t groups = div_up(n, 32);
     const bool al = aligned_to(d_out, 16);
-    if (splits_windows(num_windows, shift, w)) {
+    if (shift >= kSplitShift) {
         return hip_ok(w == 4 ? launch_window_split<4>(1 << (shift - 2), al, stream, in, stream_bytes, offs, n, groups,
                                                       first_window, num_windows, out)
                              : launch_window_split<2>(1 << (shift - 2), al, stream, in, stream_bytes, offs, n, groups,
                                                       first_window, num_windows, out));
     }
-    // a wave takes 4 KB of output, or one window if that is more
-    const size_t wave_windows = shift <= 2 ? static_cast<size_t>(kStageLoads >> shift) : 1;
+    // a wave takes 4 KB of output
+    const size_t wave_windows = static_cast<size_t>(kStageLoads >> shift);
     // (a multiple of 8 workgroups for the interleaved order)
     const size_t blocks = div_up(div_up(num_windows, static_cast<size_t>(kWaves) * wave_windows), 8) * 8;
     if (blocks > 0x7FFFFFFFull) return ZVC_E_ARG;
