@@ -804,7 +804,9 @@ struct EncoderArgs {
 // masks leave with the values instead of going to a mask area.  The scan is the
 // same: a window's byte offset is 4 x (groups before it) + W x (kept elements
 // before it).
-template <int W, int CH, int WV, bool RELU, bool WINDOWED, bool SPLIT>
+//
+// SMALL: a tensor below kSmallTensorBytes, which is read without the streaming hint.
+template <int W, int CH, int WV, bool RELU, bool WINDOWED, bool SPLIT, bool SMALL>
 __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a) {
     using G = EncoderGeometry<W, CH, WV>;
     constexpr int CG = G::kChunkGroups;
@@ -976,7 +978,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         const unsigned* base = reinterpret_cast<const unsigned*>(a.in) + wave_dword0;
         static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            cur[k] = load_stream(base + k * kWaveSize + lane);
+            cur[k] = SMALL ? base[k * kWaveSize + lane] : load_stream(base + k * kWaveSize + lane);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
     } else {
@@ -1000,7 +1002,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         for (int j = 0; j < CH / 16; ++j) lane_byte[j] = 4 * lane + j * 16 * kChunkBytes;
         static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_byte[k / 16] + k % 16 * kChunkBytes, 0, kNonTemporal);
+            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_byte[k / 16] + k % 16 * kChunkBytes, 0,
+                                                          SMALL ? 0 : kNonTemporal);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
         if constexpr (SPLIT)
@@ -1965,7 +1968,7 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
 constexpr int kCountLoads = 8;
 constexpr int kCountShift = 40;
 
-template <int W, bool ALIGNED>
+template <int W, bool ALIGNED, bool SMALL>
 __global__ __launch_bounds__(kThreads) void count_kernel(const unsigned char* __restrict__ in,
                                                          size_t n, WsHeader* hdr,
                                                          unsigned long long* d_bytes,
@@ -1983,7 +1986,7 @@ __global__ __launch_bounds__(kThreads) void count_kernel(const unsigned char* __
 #pragma unroll
         for (int j = 0; j < kCountLoads; ++j) {
             const unsigned char* p = in + (q0 + static_cast<size_t>(j) * kThreads) * 16;
-            v[j] = ALIGNED ? load16_stream(p) : load16_loose<W>(p);
+            v[j] = ALIGNED && SMALL ? *reinterpret_cast<const uint4*>(p) : ALIGNED ? load16_stream(p) : load16_loose<W>(p);
         }
     } else {
 #pragma unroll
@@ -2146,6 +2149,16 @@ struct TileShape {
     int waves;    // per workgroup
 };
 constexpr size_t kLargeTensorBytes = size_t{160} << 20;
+
+// Tensors below this size are read without the streaming hint: what a layer has just
+// written is then served from the caches (us, three buffers in turn | 40, with the hint ->
+// without, ragged sizes; fp32 4 MB 6.55 -> 6.06 | 7.84 -> 7.38, 6.4 MB 8.18 -> 6.51 | 8.38
+// -> 7.64, 10 MB 8.15 -> 7.73 | 8.10 -> 8.14, 14 MB 8.58 -> 8.79 | 9.02 -> 9.40; bf16 6.4 MB
+// 8.39 -> 7.80 | 8.75 -> 8.62, 14 MB 9.96 -> 9.79 | 10.12 -> 10.40; 6.4 MB from memory, 64
+// buffers, 7.2 -> 7.5).  Kernels of their own:
+// with both kinds of load behind a branch the compiler waits for all of a wave's loads
+// before it tests the first (6.4 MB, 40 buffers: 8.8 instead of 6.8).
+constexpr size_t kSmallTensorBytes = size_t{10} << 20;
 constexpr TileShape kMinShape{16, 4};             // 16 KB, the smallest tile (sizes the workspace)
 static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16 * kThreads, "smallest tile");
 
@@ -2158,7 +2171,7 @@ inline TileShape choose_shape(size_t n, int w, bool windowed) {
 
 enum class Encoder { kPlain, kRelu, kWindowed };
 
-template <int W, int CH, int WV, bool SPLIT, bool WINDOWED_TOO = true>
+template <int W, int CH, int WV, bool SPLIT, bool SMALL, bool WINDOWED_TOO = true>
 hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned char* in, size_t n,
                         unsigned* masks, unsigned char* values, ScanState st,
                         unsigned long long* d_bytes, unsigned tiles, size_t groups,
@@ -2168,12 +2181,12 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
     const dim3 grid(tiles), block(WV * kWaveSize);
     switch (mode) {
         case Encoder::kPlain:
-            return launch(compress_kernel<W, CH, WV, false, false, SPLIT>, grid, block, stream, args);
+            return launch(compress_kernel<W, CH, WV, false, false, SPLIT, SMALL>, grid, block, stream, args);
         case Encoder::kRelu:
-            return launch(compress_kernel<W, CH, WV, true, false, SPLIT>, grid, block, stream, args);
+            return launch(compress_kernel<W, CH, WV, true, false, SPLIT, SMALL>, grid, block, stream, args);
         case Encoder::kWindowed:
             if constexpr (WINDOWED_TOO)
-                return launch(compress_kernel<W, CH, WV, false, true, SPLIT>, grid, block, stream, args);
+                return launch(compress_kernel<W, CH, WV, false, true, SPLIT, SMALL>, grid, block, stream, args);
             else
                 return hipErrorInvalidValue;   // choose_shape() gives the windowed stream no such tile
     }
@@ -2236,18 +2249,19 @@ hipError_t launch_window_split(int waves, Args... args) {
     return hipErrorInvalidValue;   // there is no other window size from kSplitShift on
 }
 
-// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword).
+// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword, small tensor).
+template <int CH, bool SMALL, typename... Args>
+hipError_t launch_compress_shape(int w, bool split, Args... args) {
+    return w == 4 ? launch_compress_as<4, CH, 4, false, SMALL>(args...)
+         : split ? launch_compress_as<2, CH, 4, true, SMALL>(args...) : launch_compress_as<2, CH, 4, false, SMALL>(args...);
+}
 template <typename... Args>
-hipError_t launch_compress(int w, TileShape shape, bool split, Args... args) {
-#define ZVC_SHAPE_CASE(C, V)                                                    \
-    if (shape.chunks == C && shape.waves == V)                                  \
-        return w == 4 ? launch_compress_as<4, C, V, false>(args...)             \
-               : split ? launch_compress_as<2, C, V, true>(args...)             \
-                       : launch_compress_as<2, C, V, false>(args...);
-    if (shape.chunks == 64 && shape.waves == 4 && w == 4) return launch_compress_as<4, 64, 4, false, false>(args...);
-    ZVC_SHAPE_CASE(32, 4)
-    ZVC_SHAPE_CASE(16, 4)
-#undef ZVC_SHAPE_CASE
+hipError_t launch_compress(int w, TileShape shape, bool split, bool small, Args... args) {
+    switch (shape.waves == 4 ? shape.chunks : 0) {
+        case 16: return small ? launch_compress_shape<16, true>(w, split, args...) : launch_compress_shape<16, false>(w, split, args...);
+        case 32: return launch_compress_shape<32, false>(w, split, args...);
+        case 64: if (w == 4) return launch_compress_as<4, 64, 4, false, false, false>(args...);
+    }
     return hipErrorInvalidValue;   // choose_shape() returns nothing else
 }
 
@@ -2299,7 +2313,7 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
     const unsigned char* in = static_cast<const unsigned char*>(d_in);
     unsigned* masks = static_cast<unsigned*>(d_out);
     unsigned char* values = static_cast<unsigned char*>(d_out) + 4 * groups;
-    return hip_ok(launch_compress(w, shape, split, mode, stream, in, n, masks,
+    return hip_ok(launch_compress(w, shape, split, n * static_cast<size_t>(w) < kSmallTensorBytes, mode, stream, in, n, masks,
                     mode == Encoder::kWindowed ? static_cast<unsigned char*>(d_out) : values,
                     scan_state(d_ws, tiles), out_bytes, static_cast<unsigned>(tiles), groups,
                     !bounded ? ~0ull : out_cap - (mode == Encoder::kWindowed ? 0 : 4 * groups),
@@ -2512,8 +2526,11 @@ zvc_status zvc_compressed_size(const void* d_in, size_t n, int w, uint64_t* d_by
     const dim3 grid(static_cast<unsigned>(tiles)), block(kThreads);
     const unsigned nt = static_cast<unsigned>(tiles);
     const bool al = aligned_to(d_in, 16);
-    const auto kernel = w == 4 ? (al ? count_kernel<4, true> : count_kernel<4, false>)
-                               : (al ? count_kernel<2, true> : count_kernel<2, false>);
+    // (without the streaming hint, us, three buffers in turn | 40: 6.4 MB fp32 4.96 -> 4.22 | 5.29 -> 5.37, 10 MB
+    // bf16 5.79 -> 4.66 | 5.92 -> 6.00, 16 MB fp32 6.13 -> 6.05 | 6.45 -> 6.84)
+    const bool small = n * static_cast<size_t>(w) < kSmallTensorBytes;
+    const auto kernel = w == 4 ? (!al ? count_kernel<4, false, false> : small ? count_kernel<4, true, true> : count_kernel<4, true, false>)
+                               : (!al ? count_kernel<2, false, false> : small ? count_kernel<2, true, true> : count_kernel<2, true, false>);
     return hip_ok(launch(kernel, grid, block, stream, in, n, hdr, out, groups, nt));
 }
 
