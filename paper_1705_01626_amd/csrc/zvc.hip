@@ -100,7 +100,11 @@ struct EncoderGeometry {
     // staged whole before the scan ends) plus a little, never less than a
     // carried-over partial line plus a step.  (More workgroups per CU with a
     // smaller queue measure the same or worse.)
+    // The smallest tile's queues hold all of it (eight workgroups still fit a CU): no step waits
+    // for the scan, however dense the tensor is (4 MB fp32 without a zero: 6.20 -> 5.52 us).
+    static constexpr bool kHoldsAll = CH == 16;
     static constexpr int kQueueBytes =
+        kHoldsAll ? CH * kChunkBytes + 4 * kWaveGroups :
         CH == 64 ? 8704 : (CH * kChunkBytes / 2 > kStepMaxBytes ? CH * kChunkBytes / 2 : kStepMaxBytes) + 256;
     static_assert(kQueueBytes >= 128 + kStepMaxBytes, "a step always fits behind a carried-over partial line");
     static_assert(CH % kStepChunks == 0, "a wave's chunks are staged in whole steps");
@@ -787,8 +791,9 @@ struct EncoderArgs {
 //      arrives last publishes the tile's count for the tiles behind it, at once.
 //   3. the wave stages its kept elements in its LDS queue in packed order
 //      (position = ballot bits in lower lanes + kept elements of earlier
-//      chunks), as many steps as the queue holds: that needs nothing from other
-//      tiles, and it gives the tiles in front the time to publish their counts.
+//      chunks), as many steps as the queue holds (some of them earlier, with
+//      their tests, see kFusedSteps): that needs nothing from other tiles, and it
+//      gives the tiles in front the time to publish their counts.
 //   4. wave 0 finishes the device-wide scan (its first round trip has been
 //      under way since the tile started); one barrier hands the result to the
 //      other waves.
@@ -812,7 +817,19 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     using G = EncoderGeometry<W, CH, WV>;
     constexpr int CG = G::kChunkGroups;
     constexpr int kWindowChunks = 4;              // the windowed stream's unit: 1 KB of input
-    constexpr bool kChunkMasks = WINDOWED && W == 4 && CH == 16;   // windowed: masks by chunk, see write_step_masks
+    // Steps that may be staged in the same pass as their tests, while the wave waits for its next
+    // loads anyway.  The others are staged once the tile's count is published: the tiles behind
+    // wait for the count, and staging then fills the time until the counts of the tiles in front
+    // are there.  Windowed staging is long (a step ends with a scan for the places of its masks), so
+    // none of it goes in front: us with all steps fused -> none, 1 MB fp32 6.5 -> 5.5, 25 MB 13.6 ->
+    // 11.1, 103 MB 36.3 -> 33.6, 297 MB 87.6 -> 83.5; 206 MB bf16 76.7 -> 72.0, 51 MB 21.7 -> 21.9.
+    // Planar fp32: half of the smaller tiles (256 KB 4.91 -> 4.86, none 5.08; dense 5.66 -> 4.86; 4 MB
+    // dense 5.94 -> 5.38; 20 MB 10.2 -> 8.9; 51 MB 15.6 either way, none 16.8), all of 64 KB (822 MB
+    // 202.8, none 205.5).  16-bit: half of the smallest tile of a small tensor (8 MB 7.26 -> 7.06, dense
+    // 8.1 -> 7.2, none 7.46), else all (51 MB dense 22.5, half 24.8).
+    constexpr int kFusedSteps = WINDOWED ? 0
+                              : (W == 4 && CH != 64) || SMALL ? G::kSteps / 2 : G::kSteps;
+    static_assert(!SMALL || CH == 16, "small tensors take the smallest tile");
     static_assert(W == 2 || !SPLIT, "only 16-bit elements can sit at an odd half dword");
 
     __shared__ __align__(16) unsigned char s_stage[WV][G::kQueueBytes];
@@ -888,22 +905,18 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
             set_lane<k / kWindowChunks>(window_local, zero_local + q_end);
         // (windowed: the lane's group has its mask, and the masks of the chunk's earlier groups, before it;
-        // write_step_masks() puts the masks there, but for kChunkMasks)
+        // write_step_masks() puts the masks there)
         if constexpr (W == 4) {
             const bool keep = kept_first<4, RELU>(x);
             const unsigned long long b = __ballot(keep);
             const unsigned kept = static_cast<unsigned>(__popcll(b));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
-                if (!kChunkMasks)
-                    set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
+                set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
             }
             if (STAGE) {
                 const unsigned at = 4u * lanes_below(b, 0u) + q_end + (WINDOWED ? 4u + 4u * (lane >> 5) : 0u);
                 if (__builtin_expect(keep, 1)) *reinterpret_cast<unsigned*>(stage + at) = x;   // predicated, no branch
-                if (kChunkMasks && (lane & 31) == 0 && static_cast<unsigned>(lane >> 5) < chunk_groups)
-                    *reinterpret_cast<unsigned*>(stage + at - 4u) =
-                        lane == 0 ? static_cast<unsigned>(b) : static_cast<unsigned>(b >> 32);
                 q_end += 4u * kept + 4u * chunk_groups;
             }
         } else {
@@ -932,9 +945,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // its chunks left for them: a lane per mask, whose place is the sum of the sizes of the step's
     // groups before it (a scan over 16 or 32 lanes).  Per step instead of per chunk: 89.1 ->
     // 87.7 us for 297 MB fp32, 87.8 -> 59.9 us for 149 MB bf16 (whose chunks zipped their masks on
-    // the scalar unit).  In the smallest fp32 tile the scan's chain of dependent steps costs more than
-    // two lanes' writes per chunk: 6 | 8 | 11 MB take 8.5 | 8.9 | 9.4 us with those and 9.0 | 9.5 |
-    // 10.0 with the scan.
+    // the scalar unit), 4 MB fp32 5.83 -> 5.74 (all the tests done by then, see kFusedSteps).
     const auto write_step_masks = [&](auto hc, unsigned q_step) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
         constexpr int reg = h * G::kStepGroups / kWaveSize, lane0 = h * G::kStepGroups % kWaveSize;
@@ -1026,13 +1037,14 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     int staged = 0;                               // steps in the queue so far, wave-uniform
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
-        if (staged == h && q_end + G::kStepMaxBytes <= static_cast<unsigned>(G::kQueueBytes)) {
+        if (h < kFusedSteps &&
+            (G::kHoldsAll || (staged == h && q_end + G::kStepMaxBytes <= static_cast<unsigned>(G::kQueueBytes)))) {
             const unsigned q_step = q_end;
             static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
                 chunk(kc, yes, yes);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            if constexpr (WINDOWED && !kChunkMasks) write_step_masks(hc, q_step);
+            if constexpr (WINDOWED) write_step_masks(hc, q_step);
             staged = h + 1;
         } else {
             static_for<h * kStepChunks, (h + 1) * kStepChunks>([&](auto kc) __attribute__((always_inline)) {
@@ -1082,11 +1094,11 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             chunk(kc, no, yes);
             __builtin_amdgcn_sched_barrier(0);
         });
-        if constexpr (WINDOWED && !kChunkMasks) write_step_masks(hc, q_step);
+        if constexpr (WINDOWED) write_step_masks(hc, q_step);
     };
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
-        if (staged == h && q_end + step_bytes(h) <= static_cast<unsigned>(G::kQueueBytes)) {
+        if (G::kHoldsAll ? h >= kFusedSteps : staged == h && q_end + step_bytes(h) <= static_cast<unsigned>(G::kQueueBytes)) {
             stage_step(hc);
             staged = h + 1;
         }
@@ -1128,14 +1140,14 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             a.values + (exclusive + wave_offset) * W +
             (WINDOWED ? 4 * (wave_group0 < a.num_groups ? wave_group0 : a.num_groups) : 0);
         unsigned char* gzero = run_begin;
-        if (staged != 0) {
-            wave_flush<W>(gzero, stage, q_lo, q_end, staged == G::kSteps, lane);
+        if (G::kHoldsAll || staged != 0) {
+            wave_flush<W>(gzero, stage, q_lo, q_end, G::kHoldsAll || staged == G::kSteps, lane);
             zero_local = static_cast<unsigned>(gzero - run_begin);
             wave_lds_sync();
         }
         static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
             constexpr int h = decltype(hc)::value;
-            if (h >= staged) {
+            if (!G::kHoldsAll && h >= staged) {
                 stage_step(hc);
                 wave_lds_sync();
                 wave_flush<W>(gzero, stage, q_lo, q_end, h == G::kSteps - 1, lane);
@@ -2156,16 +2168,15 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 // through its chain of load, test, publish, store sooner, and its straight-line
 // code is shorter (a call's first wave on a CU fetches it from memory: one tile
 // alone takes 3.7 us with 16 KB, 4.8 with 32 KB, 6.9 with 64 KB).  Measured us with
-// 16 | 32 KB tiles, density 0.5 (windowed: 0.1 to 0.9), sizes a few elements above a
-// whole number of tiles, on both sides of every limit below (fp32's first line and
-// its windowed one on cold inputs, the others on three buffers in turn):
-//   fp32      14 MB 8.7 | 8.6   16 MB 9.0 | 8.5   20 MB 10.0 | 9.7   48 MB 18.9 | 15.3   103 MB 37.4 | 32.3
+// 16 | 32 KB tiles, density 0.5 (windowed: 0.1 to 0.9, 12 and 14 MB: 0.1 to 0.7), sizes a few elements
+// above a whole number of tiles, three buffers in turn, on both sides of every limit below:
+//   fp32      12 MB 7.3 | 8.2   14 MB 8.3 | 8.2   16 MB 8.2 | 7.8   20 MB 9.6 | 9.2   24 MB 10.7 | 9.7   56 MB 20.9 | 17.1
 //            103 MB 32.1 | 32.0   150 MB 45.1 | 44.6   170 MB 51.1 | 49.8   300 MB 87.0 | 82.1   (32 | 64 KB)
-//   windowed  28 MB 14.9 | 17.2   33 MB 17.6 | 18.4   36 MB 18.6 | 18.7   40 MB 20.2 | 19.2   103 MB 40.8 | 37.9
+//   windowed  32 MB 14.1 | 14.3   36 MB 15.4 | 15.6   40 MB 16.6 | 16.4   48 MB 19.4 | 18.2   100 MB 36.5 | 34.1
 //             (822 MB: nothing gained from 64 KB)
-//   16-bit    24 MB 12.0 | 12.6   47 MB 20.0 | 20.0   50 MB 21.0 | 21.5   64 MB 25.9 | 24.5   200 MB 71.6 | 63.3
-//   windowed 100 MB 43.5 | 45.1   150 MB 61.0 | 62.0   161 MB 65.3 | 65.2   200 MB 79.4 | 78.0   400 MB 152 | 143
-// (fp32 of a whole number of tiles: 14 MB 8.6 | 8.8, 16 MB 9.1 | 9.0, 21 MB 10.5 | 9.9.)
+//   16-bit    32 MB 13.8 | 15.7   49 MB 20.9 | 21.2   52 MB 21.7 | 21.9   56 MB 23.0 | 22.7   64 MB 25.8 | 25.0   80 MB 31.3 | 29.9
+//             fused ReLU 49 MB 19.0 | 19.0   52 MB 20.1 | 19.4   64 MB 23.8 | 22.5
+//   windowed  90 MB 38.4 | 39.7  110 MB 45.3 | 45.8  120 MB 49.0 | 48.9  150 MB 59.1 | 57.7  200 MB 77.8 | 73.0
 // 16-bit elements are twice the vector work per byte, and the 32 KB tile's eight
 // waves per SIMD (against four) hide it better: 64 KB tiles lose up to 9 % there.
 // (8 KB tiles, and 8 or 16 waves per tile, were no faster at any size.)
@@ -2189,7 +2200,7 @@ static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16
 
 inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    const size_t medium = w == 4 ? size_t{windowed ? 36u : 16u} << 20 : size_t{windowed ? 160u : 48u} << 20;
+    const size_t medium = w == 4 ? size_t{windowed ? 38u : 14u} << 20 : size_t{windowed ? 120u : 50u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }
