@@ -2248,8 +2248,11 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     const bool stream_values = avail >= n / 4 * 3;
     // Order in which the parts of the tensor are dealt out to the workgroups (see the
     // kernel): interleaved where it measures faster, 2-15 % below a twelfth and 2-5 %
-    // above a third of the elements stored; in between the plain order is 1 % ahead.
-    const bool interleave = (avail < n / 12 || avail > n / 3) && interleaves(n, W);
+    // above a third of the elements stored; in between the plain order is 1 % ahead, but not
+    // for the largest tensors (us, plain | interleaved, fp32: 250 MB at density 0.2 50.8 | 51.2, 500 MB
+    // 107.1 | 106.2, at 0.1 89.7 | 86.7, at 0.3 116.5 | 113.8; 822 MB at 0.2 168.2 | 163.7, its first pass
+    // over new buffers 246 | 220).
+    const bool interleave = ((avail < n / 12 || avail > n / 3) && interleaves(n, W)) || n * W >= (size_t{400} << 20);
     return launch(decompress_kernel<W, LOADS, ALIGNED>, grid, dim3(kThreads), stream,
                   masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
                   interleave);
