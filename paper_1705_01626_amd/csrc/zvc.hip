@@ -1351,6 +1351,7 @@ __device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, 
     if (lane == 0) *reinterpret_cast<uint4*>(lds) = make_uint4(0u, 0u, 0u, 0u);
     wave_lds_sync();
     const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E, lower = (1u << bit0) - 1u;
+    const bool whole = left >= kStageLoads * kWaveSize * E;             // uniform
     uint4 v[kStageLoads];
 #pragma unroll
     for (int jj = 0; jj < kStageLoads; ++jj) {
@@ -1358,15 +1359,15 @@ __device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, 
         const unsigned gm = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask)));
         const unsigned at = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask_at)));
         v[jj] = expand_lane<W>(lds, at + W * static_cast<unsigned>(__popc(gm & lower)), gm >> bit0);
-    }
-    if (__builtin_expect(left >= kStageLoads * kWaveSize * E, 1)) {     // uniform
-#pragma unroll
-        for (int jj = 0; jj < kStageLoads; ++jj) {
+        if (__builtin_expect(whole, 1)) {
             if (ALIGNED) store16_stream(to + (jj * kWaveSize + lane) * 16, v[jj]);
             else store16_loose<W>(to + (jj * kWaveSize + lane) * 16, v[jj]);
         }
-        return;
+        // Each store goes as soon as its 16 bytes are there: all four at the end cost the largest
+        // tensors about 1 % (822 MB fp32 at density 0.5: 210.4 us against 207.8).
+        __builtin_amdgcn_sched_barrier(0);
     }
+    if (__builtin_expect(whole, 1)) return;
 #pragma unroll
     for (int jj = 0; jj < kStageLoads; ++jj) {
         const unsigned e0 = static_cast<unsigned>(jj * kWaveSize + lane) * E;
@@ -2122,15 +2123,21 @@ inline zvc_status hip_ok(hipError_t e) { return e == hipSuccess ? ZVC_OK : ZVC_E
 // would also report, and clear, an earlier error of the calling thread).
 template <typename... Params, size_t... I>
 hipError_t launch_impl(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream,
-                       std::tuple<Params...>& values, std::index_sequence<I...>) {
+                       std::tuple<Params...>& values, std::index_sequence<I...>, unsigned lds_bytes) {
     void* pointers[] = {static_cast<void*>(&std::get<I>(values))...};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, pointers, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, pointers, lds_bytes, stream);
+}
+// lds_bytes: more LDS per workgroup than the kernel declares, for fewer workgroups per CU.
+template <typename... Params, typename... Args>
+hipError_t launch_padded(void (*kernel)(Params...), unsigned lds_bytes, dim3 grid, dim3 block,
+                         hipStream_t stream, Args... args) {
+    static_assert(sizeof...(Params) == sizeof...(Args), "one argument per kernel parameter");
+    std::tuple<Params...> values{static_cast<Params>(args)...};
+    return launch_impl(kernel, grid, block, stream, values, std::index_sequence_for<Params...>{}, lds_bytes);
 }
 template <typename... Params, typename... Args>
 hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, Args... args) {
-    static_assert(sizeof...(Params) == sizeof...(Args), "one argument per kernel parameter");
-    std::tuple<Params...> values{static_cast<Params>(args)...};
-    return launch_impl(kernel, grid, block, stream, values, std::index_sequence_for<Params...>{});
+    return launch_padded(kernel, 0, grid, block, stream, args...);
 }
 
 // Zeroes the header and the first state_bytes bytes of scan state.
@@ -2253,9 +2260,15 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     // 107.1 | 106.2, at 0.1 89.7 | 86.7, at 0.3 116.5 | 113.8; 822 MB at 0.2 168.2 | 163.7, its first pass
     // over new buffers 246 | 220).
     const bool interleave = ((avail < n / 12 || avail > n / 3) && interleaves(n, W)) || n * W >= (size_t{400} << 20);
-    return launch(decompress_kernel<W, LOADS, ALIGNED>, grid, dim3(kThreads), stream,
-                  masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
-                  interleave);
+    // From 64 MB up 7 workgroups share a CU instead of the 8 that its LDS would hold: fewer waves write at
+    // once and memory takes the writes 1-2 % faster (us, 8 | 7 | 6 | 5 per CU: 822 MB fp32 at density 0.05
+    // 130.2 | 128.6 | 126.7 | 123.6, 0.2 164.2 | 163.5 | 166.1 | 177.4, 0.5 207.8 | 206.8 | 205.1 | 204.3, 1
+    // 266.1 | 263.6 | 262.4 | 261.5; 297 MB 77.7 | 77.2 | 76.8 | 76.9).  6 and 5 lose where the vector units
+    // bind, and a tensor of 51 MB, where there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
+    const unsigned lds_pad = interleaves(n, W) ? 6144 : 0;
+    return launch_padded(decompress_kernel<W, LOADS, ALIGNED>, lds_pad, grid, dim3(kThreads), stream,
+                         masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
+                         interleave);
 }
 
 // Windows that a workgroup each decodes (window_split_kernel) instead of a lane each: from
