@@ -2373,23 +2373,21 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
                     reinterpret_cast<unsigned long long*>(d_offsets), window_shift));
 }
 
-// Two events per host thread and GPU for ordering a copy stream after a compute
+// One event per host thread and GPU for ordering a copy stream after a compute
 // stream (or the other way round), created at first use and kept: creating and
-// destroying one per call costs several microseconds per tensor.  kOnDevice: for what
-// this library's kernels wrote, to device memory or to the host with system scope; it has
-// no cache flush of the whole system in it, which a stream that waits for the other one
-// would wait for too (5 us of a round trip).
-enum class Order { kOnDevice, kSystem };
-hipEvent_t thread_event(Order order) {
-    thread_local hipEvent_t events[2][kMaxDevices] = {};
+// destroying one per call costs several microseconds per tensor.  An ordinary event, which
+// releases what lies before it to the whole system: the host reads the size behind one, and
+// the documents promise that of no cheaper kind (hipEventDisableSystemFence is for timing;
+// a round trip of 1.6 MB takes 44.2 us with it, 48.6 with this, 48.6 with
+// hipEventReleaseToDevice where that would do).
+hipEvent_t thread_event() {
+    thread_local hipEvent_t events[kMaxDevices] = {};
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) return nullptr;
-    hipEvent_t& event = events[order == Order::kOnDevice ? 0 : 1][device];
-    if (event == nullptr &&
-        hipEventCreateWithFlags(&event, order == Order::kOnDevice ? hipEventDisableTiming | hipEventDisableSystemFence
-                                                                  : hipEventDisableTiming) != hipSuccess)
-        event = nullptr;
-    return event;
+    if (events[device] == nullptr &&
+        hipEventCreateWithFlags(&events[device], hipEventDisableTiming) != hipSuccess)
+        events[device] = nullptr;
+    return events[device];
 }
 
 // Where the GPU sees pinned host memory at `host`; null if it is none, or not aligned there.
@@ -2431,12 +2429,11 @@ zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d
         return st;
     if (size_to == nullptr && hipMemcpyAsync(h_bytes, d_size, 8, hipMemcpyDeviceToHost, compute) != hipSuccess)
         return ZVC_E_HIP;
-    const bool ours = size_to != nullptr && link_pointer(d_stage, h_pinned, zvc_max_compressed_bytes(n, w)) != nullptr;
-    hipEvent_t ev = thread_event(ours ? Order::kOnDevice : Order::kSystem);
+    hipEvent_t ev = thread_event();
     if (ev == nullptr || hipEventRecord(ev, compute) != hipSuccess || hipEventSynchronize(ev) != hipSuccess)
         return ZVC_E_HIP;
     if (*h_bytes > h_cap) return ZVC_E_CAPACITY;
-    // (the compression is done, so `copy` has nothing to wait for)
+    // (what the event ordered is done and released to the system, so `copy` has nothing to wait for)
     if (*h_bytes == 0) return ZVC_OK;
     void* const to = link_pointer(d_stage, h_pinned, *h_bytes);
     return hip_ok(to != nullptr ? launch_link_copy(d_stage, to, *h_bytes, copy)
@@ -2794,7 +2791,7 @@ zvc_status zvc_prefetch(const void* h_pinned, uint64_t bytes, size_t n, int w, v
                          : hipMemcpyAsync(d_stage, h_pinned, bytes, hipMemcpyHostToDevice, copy)) != hipSuccess)
         return ZVC_E_HIP;
     if (copy != compute) {
-        hipEvent_t ev = thread_event(from != nullptr ? Order::kOnDevice : Order::kSystem);
+        hipEvent_t ev = thread_event();
         if (ev == nullptr || hipEventRecord(ev, copy) != hipSuccess ||
             hipStreamWaitEvent(compute, ev, 0) != hipSuccess)
             return ZVC_E_HIP;

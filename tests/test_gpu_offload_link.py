@@ -95,3 +95,41 @@ def test_several_tensors_while_their_copies_wait(oracle):
     for x, h, size in zip(xs, hosts, sizes):
         expect = oracle.compress_stream(raw_bytes(x), 4)
         assert size == expect.size and np.array_equal(h[:size].numpy(), expect)
+
+
+def test_memory_that_is_pinned_but_not_coherent(oracle):
+    """hipHostMalloc with hipHostMallocNonCoherent: the size and the stream are the host's to read once the
+    call and the copy stream are done, the stream is the GPU's to read as the host left it; one buffer for
+    several tensors, whose lines a cache may still hold from the one before."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    cap = zvc.zvc_max_compressed_bytes(400000, 4)
+    room = ctypes.c_void_p()
+    assert hip.hipHostMalloc(ctypes.byref(room), ctypes.c_size_t(cap + 64), ctypes.c_uint(0x80000000)) == 0
+    try:
+        both = torch.frombuffer((ctypes.c_uint8 * (cap + 64)).from_address(room.value), dtype=torch.uint8)
+        h_bytes, host = both[:8].view(torch.int64), both[64:]
+        compute, copy = torch.cuda.Stream(), torch.cuda.Stream()
+        ws = zvc.new_workspace(400000, 4, DEV)
+        stage = zvc.new_compressed_buffer(400000, 4, DEV)
+        for n, density in ((400000, 0.3), (400000, 0.9), (70001, 0.5), (399999, 0.1)):
+            x = random_tensor(n, 4, density, seed=n + 1).to(DEV)
+            expect = oracle.compress_stream(raw_bytes(x), 4)
+            say("not coherent n=%d stream bytes %d" % (n, expect.size))
+            h_bytes[0] = 0                            # (a size that was not seen is at worst an empty stream)
+            torch.cuda.synchronize()
+            nbytes = zvc.zvc_offload(x, stage, host, h_bytes, ws, compute, copy)
+            copy.synchronize()
+            assert nbytes == expect.size and np.array_equal(host[:nbytes].numpy(), expect)
+            # what the host writes there comes back: the same tensor with its first word changed
+            first = int(np.flatnonzero(raw_bytes(x).view(np.uint32))[0])
+            host[4 * -(-n // 32):4 * -(-n // 32) + 4] = torch.tensor([1, 2, 3, 4], dtype=torch.uint8)
+            out = torch.zeros_like(x)
+            torch.cuda.synchronize()
+            zvc.zvc_prefetch(host, nbytes, stage, out, ws, copy, compute)
+            compute.synchronize()
+            want = raw_bytes(x).copy().view(np.uint32)
+            want[first] = 0x04030201
+            assert np.array_equal(raw_bytes(out).view(np.uint32), want)
+    finally:
+        torch.cuda.synchronize()
+        assert hip.hipHostFree(room) == 0

@@ -1,0 +1,106 @@
+"""What the library asks of the HIP runtime, call by call, written down by a stand-in for the runtime
+(fake_hip.cpp) in a child process: which streams work and copies go to, and which events order them.
+No GPU needed."""
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from paper_1705_01626_amd import build as zvc_build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+COMPUTE, COPY = 0x1000, 0x2000
+IN, STAGE, WS, HOST, OUT = 1 << 41, 1 << 42, 1 << 43, 1 << 44, 1 << 45
+CHILD = """
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+fake.fake_log.restype = ctypes.c_char_p
+lib.zvc_max_compressed_bytes.restype = lib.zvc_workspace_bytes.restype = ctypes.c_size_t
+size = ctypes.c_uint64(0)
+def call(name, *args):
+    wide = [ctypes.c_size_t(a) if isinstance(a, int) else a for a in args]
+    status = getattr(lib, name)(*wide)
+    assert status == 0, (name, status)
+def worst(n, w):
+    return lib.zvc_max_compressed_bytes(ctypes.c_size_t(n), w)
+def room(n, w):
+    return lib.zvc_workspace_bytes(ctypes.c_size_t(n), w)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", zvc_build.ROCM_INCLUDE,
+                    "-o", out, os.path.join(ROOT, "tests", "fake_hip.cpp")], check=True)
+    return out
+
+
+def run(fake, code):
+    """The stand-in's lines for `code`, split into words and key=value pairs."""
+    done = subprocess.run([sys.executable, "-c", CHILD + code + "\nprint(fake.fake_log().decode())", fake,
+                           zvc_build.ensure_built()], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stderr[-2000:]
+    lines = []
+    for line in done.stdout.splitlines():
+        words = line.split()
+        if words:
+            lines.append((words[0], {k: int(v) for k, v in re.findall(r"(\w+)=(-?\d+)", line)}, words[-1]))
+    return lines
+
+
+# Flags under which an event does not order everything before it, or not for the host.
+DISABLE_SYSTEM_FENCE, RELEASE_TO_DEVICE = 0x20000000, 0x40000000
+
+OFFLOAD = """
+n, w = %d, %d
+fake.fake_host_memory(%d)
+fake.fake_written(ctypes.byref(size), %d)
+call('zvc_offload', %d, n, w, %d, worst(n, w), %d, worst(n, w), ctypes.addressof(size), %d, room(n, w), %d, %d)
+"""
+PREFETCH = """
+n, w = %d, %d
+fake.fake_host_memory(%d)
+call('zvc_prefetch', %d, %d, n, w, %d, worst(n, w), %d, %d, room(n, w), %d, %d)
+"""
+
+
+@pytest.mark.parametrize("n,w,pinned", [(100001, 4, 1), (100001, 2, 1), (100001, 4, 0), (20 << 20, 4, 1)])
+def test_order_of_an_offload(fake, n, w, pinned):
+    """The host waits for an event that releases to the whole system, recorded behind the encoder on
+    `compute`; the stream goes to `copy` after that wait."""
+    nbytes = 4 * -(-n // 32) + w * (n // 5)
+    lines = run(fake, OFFLOAD % (n, w, pinned, nbytes, IN, STAGE, HOST, WS, COMPUTE, COPY))
+    kinds = [k for k, _, _ in lines]
+    made = {v["event"]: v["flags"] for k, v, _ in lines if k == "create"}
+    assert kinds.count("synchronize") == 1
+    wait = kinds.index("synchronize")
+    record = kinds.index("record")
+    event = lines[wait][1]["event"]
+    assert lines[record][1] == {"event": event, "stream": COMPUTE} and record < wait
+    assert made[event] & (DISABLE_SYSTEM_FENCE | RELEASE_TO_DEVICE) == 0
+    encoder = [i for i, (k, v, name) in enumerate(lines) if k == "launch" and "compress_kernel" in name]
+    assert len(encoder) == 1 and encoder[0] < record and lines[encoder[0]][1]["stream"] == COMPUTE
+    assert all(i > wait for i, (k, v, _) in enumerate(lines) if v.get("stream") == COPY)
+
+
+@pytest.mark.parametrize("n,w,pinned", [(100001, 4, 1), (100001, 2, 1), (100001, 4, 0), (20 << 20, 4, 1)])
+def test_order_of_a_prefetch(fake, n, w, pinned):
+    """`compute` waits for an event that is recorded behind the copy on `copy` and that orders what
+    lies before it; the decoder's launches come behind that wait.  One stream needs no event."""
+    nbytes = 4 * -(-n // 32) + w * (n // 5)
+    lines = run(fake, PREFETCH % (n, w, pinned, HOST, nbytes, STAGE, OUT, WS, COPY, COMPUTE))
+    kinds = [k for k, _, _ in lines]
+    made = {v["event"]: v["flags"] for k, v, _ in lines if k == "create"}
+    record, wait = kinds.index("record"), kinds.index("wait")
+    event = lines[wait][1]["event"]
+    assert lines[wait][1] == {"event": event, "stream": COMPUTE}
+    assert lines[record][1] == {"event": event, "stream": COPY} and record < wait
+    assert made[event] & DISABLE_SYSTEM_FENCE == 0
+    assert all(i < record for i, (k, v, _) in enumerate(lines) if k in ("launch", "copy") and v["stream"] == COPY)
+    assert all(i > wait for i, (k, v, _) in enumerate(lines) if k == "launch" and v["stream"] == COMPUTE)
+    one = run(fake, PREFETCH % (n, w, pinned, HOST, nbytes, STAGE, OUT, WS, COMPUTE, COMPUTE))
+    assert not [k for k, _, _ in one if k in ("record", "wait", "synchronize")]
