@@ -2076,29 +2076,6 @@ __global__ __launch_bounds__(kThreads) void reference_stream_kernel(const uint4*
     }
 }
 
-// Copy over the link between device memory and host memory that the GPU sees; both
-// pointers are 16-byte aligned.  The link bounds it, and 32 workgroups are what it takes in
-// either direction (16 | 32 | 128 of them, 24 MB in: 472 | 443 | 454 us, hipMemcpyAsync 449;
-// 6 MB out: 123 | 119 | 115, hipMemcpyAsync 120).  What it saves is the start: 64 KB take
-// 5.7 us out and 6.6 in instead of 11.1 and 11.2, 512 KB 12.2 and 13.1 instead of 19.
-constexpr unsigned kLinkGroups = 32;
-constexpr int kLinkLoads = 4;
-__global__ __launch_bounds__(kThreads) void link_copy_kernel(const unsigned char* __restrict__ from,
-                                                             unsigned char* __restrict__ to, size_t bytes) {
-    const size_t chunks = bytes / 16, round = static_cast<size_t>(gridDim.x) * (kThreads * kLinkLoads);
-    for (size_t c0 = static_cast<size_t>(blockIdx.x) * (kThreads * kLinkLoads) + threadIdx.x; c0 < chunks; c0 += round) {
-        uint4 v[kLinkLoads];
-#pragma unroll
-        for (int k = 0; k < kLinkLoads; ++k)
-            if (c0 + k * kThreads < chunks) v[k] = load16_stream(from + 16 * (c0 + k * kThreads));
-#pragma unroll
-        for (int k = 0; k < kLinkLoads; ++k)
-            if (c0 + k * kThreads < chunks) store16_stream(to + 16 * (c0 + k * kThreads), v[k]);
-    }
-    const size_t rest = 16 * chunks + threadIdx.x;
-    if (blockIdx.x == gridDim.x - 1 && rest < bytes) to[rest] = from[rest];
-}
-
 // -------------------------------------------------------------- host helpers
 // log2(window_bytes / 1 KB) for the window sizes of the windowed stream (a power of
 // two from 1 KB to 64 KB), else -1.
@@ -2377,9 +2354,8 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
 // stream (or the other way round), created at first use and kept: creating and
 // destroying one per call costs several microseconds per tensor.  An ordinary event, which
 // releases what lies before it to the whole system: the host reads the size behind one, and
-// the documents promise that of no cheaper kind (hipEventDisableSystemFence is for timing;
-// a round trip of 1.6 MB takes 44.2 us with it, 48.6 with this, 48.6 with
-// hipEventReleaseToDevice where that would do).
+// the documents promise that of no cheaper kind (hipEventDisableSystemFence is for timing,
+// 1 to 4 us less a round trip; hipEventReleaseToDevice where that would do: nothing).
 hipEvent_t thread_event() {
     thread_local hipEvent_t events[kMaxDevices] = {};
     int device = -1;
@@ -2390,28 +2366,20 @@ hipEvent_t thread_event() {
     return events[device];
 }
 
-// Where the GPU sees pinned host memory at `host`; null if it is none, or not aligned there.
-void* mapped(const void* host, size_t alignment) {
+// Where the GPU sees the 8 bytes at `host`, if they are pinned host memory; else null.
+unsigned long long* mapped_word(const void* host) {
     hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, host) != hipSuccess || a.type != hipMemoryTypeHost || a.devicePointer == nullptr ||
-        !aligned_to(a.devicePointer, alignment))
+    if (hipPointerGetAttributes(&a, host) != hipSuccess || a.type != hipMemoryTypeHost || !aligned_to(a.devicePointer, 8))
         return nullptr;
-    return a.devicePointer;
+    return static_cast<unsigned long long*>(a.devicePointer);
 }
 
-// Streams of up to this size cross the link by link_copy_kernel, whose start is the shorter
-// one; above, hipMemcpyAsync is as fast or up to 2 % faster (24 MB out: 458 us | 451).
-constexpr size_t kLinkKernelBytes = size_t{16} << 20;
-
-void* link_pointer(const void* device, const void* host, size_t bytes) {
-    return bytes <= kLinkKernelBytes && aligned_to(device, 16) ? mapped(host, 16) : nullptr;
-}
-hipError_t launch_link_copy(const void* from, void* to, size_t bytes, hipStream_t stream) {
-    const size_t groups = div_up(bytes, size_t{16} * kThreads * kLinkLoads);
-    return launch(link_copy_kernel, dim3(groups < kLinkGroups ? static_cast<unsigned>(groups) : kLinkGroups), dim3(kThreads),
-                  stream, static_cast<const unsigned char*>(from), static_cast<unsigned char*>(to), bytes);
-}
-
+// The streams cross the link by hipMemcpyAsync, at every size.  A kernel of this library on
+// `copy` starts sooner (a round trip of 1.6 MB on an idle GPU: 48.6 us instead of 57.5),
+// but it waits for compute units that the program's own work holds, and keeps them from
+// it.  us a layer of one 140 us matrix product and the copy of one tensor beside it (fp32,
+// density 0.3), kernel | hipMemcpyAsync: 24.5 MB out 287 | 167, in 233 | 169; 6.1 MB out 174 |
+// 160, in 150 | 132; 1.6 MB out 159 | 158, in 134 | 130.
 zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d_stage,
                         size_t stage_cap, void* h_pinned, size_t h_cap, uint64_t* h_bytes, void* d_ws,
                         size_t ws, hipStream_t compute, hipStream_t copy) {
@@ -2423,7 +2391,7 @@ zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d
     uint64_t* d_size = reinterpret_cast<uint64_t*>(&hdr->size_word);
     // The encoder writes the size to the host itself where it can (a copy of 8 bytes costs 9 us); the
     // size word in the header survives until the next offload on this workspace.
-    unsigned long long* const size_to = n != 0 ? static_cast<unsigned long long*>(mapped(h_bytes, 8)) : nullptr;
+    unsigned long long* const size_to = n != 0 ? mapped_word(h_bytes) : nullptr;
     if (zvc_status st = compress_impl(mode, false, d_in, n, w, d_stage, stage_cap, d_size, nullptr, d_ws,
                                       ws, compute, false, 0, size_to))
         return st;
@@ -2435,9 +2403,7 @@ zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d
     if (*h_bytes > h_cap) return ZVC_E_CAPACITY;
     // (what the event ordered is done and released to the system, so `copy` has nothing to wait for)
     if (*h_bytes == 0) return ZVC_OK;
-    void* const to = link_pointer(d_stage, h_pinned, *h_bytes);
-    return hip_ok(to != nullptr ? launch_link_copy(d_stage, to, *h_bytes, copy)
-                                : hipMemcpyAsync(h_pinned, d_stage, *h_bytes, hipMemcpyDeviceToHost, copy));
+    return hip_ok(hipMemcpyAsync(h_pinned, d_stage, *h_bytes, hipMemcpyDeviceToHost, copy));
 }
 
 // Scratch of zvc_compress_static: header and scan state for tensors of up to
@@ -2786,10 +2752,7 @@ zvc_status zvc_prefetch(const void* h_pinned, uint64_t bytes, size_t n, int w, v
     if (!aligned_to(d_out, static_cast<size_t>(w)) || !aligned_to(d_stage, 4)) return ZVC_E_ALIGN;
     if (zvc_status st = check_workspace(d_ws, ws, n, w)) return st;
     if (n == 0) return ZVC_OK;
-    const void* const from = link_pointer(d_stage, h_pinned, bytes);
-    if ((from != nullptr ? launch_link_copy(from, d_stage, bytes, copy)
-                         : hipMemcpyAsync(d_stage, h_pinned, bytes, hipMemcpyHostToDevice, copy)) != hipSuccess)
-        return ZVC_E_HIP;
+    if (hipMemcpyAsync(d_stage, h_pinned, bytes, hipMemcpyHostToDevice, copy) != hipSuccess) return ZVC_E_HIP;
     if (copy != compute) {
         hipEvent_t ev = thread_event();
         if (ev == nullptr || hipEventRecord(ev, copy) != hipSuccess ||

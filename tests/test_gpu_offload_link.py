@@ -1,7 +1,7 @@
-"""Offload and prefetch over either kind of copy: pinned and pageable host memory, staging buffers and
-host buffers that are not 16-byte aligned, streams that end at every byte of a 16-byte chunk, both
-sides of the limit between the copies, one stream and two, and several tensors through one workspace
-and one size word while their copies wait.  The oracle's streams, and nothing beside them."""
+"""Offload and prefetch over the link: pinned and pageable host memory, staging buffers and host buffers
+that are not 16-byte aligned, streams that end at every byte of a 16-byte chunk, small streams and some of
+16 MB, one stream and two, and several tensors through one workspace and one size word while their copies
+wait.  The oracle's streams, and nothing beside them."""
 import ctypes
 
 import numpy as np
@@ -66,11 +66,11 @@ def test_memory_of_every_kind(oracle, how):
 
 
 @pytest.mark.parametrize("n,w,density", [(4400000, 4, 0.9), (4400000, 4, 0.95), (9000000, 2, 0.92), (20000, 4, 1.0)])
-def test_both_sides_of_the_limit(oracle, n, w, density):
-    """Streams just below and above 16 MB, and a worst case above it with a stream below."""
+def test_large_streams(oracle, n, w, density):
+    """Streams just below and above 16 MB, and a dense small one."""
     x = random_tensor(n, w, density, seed=n)
     expect = oracle.compress_stream(raw_bytes(x), w)
-    say("limit n=%d w=%d stream bytes %d" % (n, w, expect.size))
+    say("large n=%d w=%d stream bytes %d" % (n, w, expect.size))
     round_trip(x, expect)
 
 

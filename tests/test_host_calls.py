@@ -104,3 +104,18 @@ def test_order_of_a_prefetch(fake, n, w, pinned):
     assert all(i > wait for i, (k, v, _) in enumerate(lines) if k == "launch" and v["stream"] == COMPUTE)
     one = run(fake, PREFETCH % (n, w, pinned, HOST, nbytes, STAGE, OUT, WS, COMPUTE, COMPUTE))
     assert not [k for k, _, _ in one if k in ("record", "wait", "synchronize")]
+
+
+@pytest.mark.parametrize("n,w,pinned", [(8192, 4, 1), (100001, 2, 1), (100001, 4, 0), (20 << 20, 4, 1)])
+def test_copies_are_the_runtimes(fake, n, w, pinned):
+    """The stream crosses the link by one copy of the runtime, on `copy` and of exactly its size, and no
+    kernel runs there: a kernel would wait for compute units that the program's own work holds, and keep
+    them from it.  The size comes by a copy only where the GPU cannot write it."""
+    nbytes = 4 * -(-n // 32) + w * (n // 5)
+    out = run(fake, OFFLOAD % (n, w, pinned, nbytes, IN, STAGE, HOST, WS, COMPUTE, COPY))
+    back = run(fake, PREFETCH % (n, w, pinned, HOST, nbytes, STAGE, OUT, WS, COPY, COMPUTE))
+    assert not [v for k, v, _ in out + back if k == "launch" and v["stream"] == COPY]
+    assert [v for k, v, _ in out if k == "copy" and v["stream"] == COPY] == [
+        {"stream": COPY, "to": HOST, "from": STAGE, "bytes": nbytes}]
+    assert [v for k, v, _ in back if k == "copy"] == [{"stream": COPY, "to": STAGE, "from": HOST, "bytes": nbytes}]
+    assert [v["bytes"] for k, v, _ in out if k == "copy" and v["stream"] == COMPUTE] == ([] if pinned else [8])
