@@ -811,8 +811,8 @@ struct EncoderArgs {
 // same: a window's byte offset is 4 x (groups before it) + W x (kept elements
 // before it).
 //
-// SMALL: a tensor below kSmallTensorBytes, which is read without the streaming hint.
-template <int W, int CH, int WV, bool RELU, bool WINDOWED, bool SPLIT, bool SMALL>
+// EARLY: fewer of the tile's steps are staged before its count is published, see kFusedSteps.
+template <int W, int CH, int WV, bool RELU, bool WINDOWED, bool SPLIT, bool EARLY>
 __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a) {
     using G = EncoderGeometry<W, CH, WV>;
     constexpr int CG = G::kChunkGroups;
@@ -823,13 +823,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // are there.  Windowed staging is long (a step ends with a scan for the places of its masks), so
     // none of it goes in front: us with all steps fused -> none, 1 MB fp32 6.5 -> 5.5, 25 MB 13.6 ->
     // 11.1, 103 MB 36.3 -> 33.6, 297 MB 87.6 -> 83.5; 206 MB bf16 76.7 -> 72.0, 51 MB 21.7 -> 21.9.
-    // Planar fp32: half of the smaller tiles (256 KB 4.91 -> 4.86, none 5.08; dense 5.66 -> 4.86; 4 MB
-    // dense 5.94 -> 5.38; 20 MB 10.2 -> 8.9; 51 MB 15.6 either way, none 16.8), all of 64 KB (822 MB
-    // 202.8, none 205.5).  16-bit: half of the smallest tile of a small tensor (8 MB 7.26 -> 7.06, dense
-    // 8.1 -> 7.2, none 7.46), else all (51 MB dense 22.5, half 24.8).
-    constexpr int kFusedSteps = WINDOWED ? 0
-                              : (W == 4 && CH != 64) || SMALL ? G::kSteps / 2 : G::kSteps;
-    static_assert(!SMALL || CH == 16, "small tensors take the smallest tile");
+    // Planar (choose_early() says which tensors): half of them where EARLY, else all.
+    constexpr int kFusedSteps = WINDOWED ? 0 : EARLY ? G::kSteps / 2 : G::kSteps;
     static_assert(W == 2 || !SPLIT, "only 16-bit elements can sit at an odd half dword");
 
     __shared__ __align__(16) unsigned char s_stage[WV][G::kQueueBytes];
@@ -990,7 +985,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         const unsigned* base = reinterpret_cast<const unsigned*>(a.in) + wave_dword0;
         static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            cur[k] = SMALL ? base[k * kWaveSize + lane] : load_stream(base + k * kWaveSize + lane);
+            cur[k] = load_stream(base + k * kWaveSize + lane);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
     } else {
@@ -1014,8 +1009,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         for (int j = 0; j < CH / 16; ++j) lane_byte[j] = 4 * lane + j * 16 * kChunkBytes;
         static_for<0, CH>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_byte[k / 16] + k % 16 * kChunkBytes, 0,
-                                                          SMALL ? 0 : kNonTemporal);
+            cur[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_byte[k / 16] + k % 16 * kChunkBytes, 0, kNonTemporal);
             __builtin_amdgcn_sched_barrier(0);   // in the order in which the tests use them
         });
         if constexpr (SPLIT)
@@ -1983,7 +1977,7 @@ __global__ __launch_bounds__(NW * kWaveSize) void window_split_kernel(
 constexpr int kCountLoads = 8;
 constexpr int kCountShift = 40;
 
-template <int W, bool ALIGNED, bool SMALL>
+template <int W, bool ALIGNED>
 __global__ __launch_bounds__(kThreads) void count_kernel(const unsigned char* __restrict__ in,
                                                          size_t n, WsHeader* hdr,
                                                          unsigned long long* d_bytes,
@@ -2001,7 +1995,7 @@ __global__ __launch_bounds__(kThreads) void count_kernel(const unsigned char* __
 #pragma unroll
         for (int j = 0; j < kCountLoads; ++j) {
             const unsigned char* p = in + (q0 + static_cast<size_t>(j) * kThreads) * 16;
-            v[j] = ALIGNED && SMALL ? *reinterpret_cast<const uint4*>(p) : ALIGNED ? load16_stream(p) : load16_loose<W>(p);
+            v[j] = ALIGNED ? load16_stream(p) : load16_loose<W>(p);
         }
     } else {
 #pragma unroll
@@ -2170,15 +2164,6 @@ struct TileShape {
 };
 constexpr size_t kLargeTensorBytes = size_t{160} << 20;
 
-// Tensors below this size are read without the streaming hint: what a layer has just
-// written is then served from the caches (us, three buffers in turn | 40, with the hint ->
-// without, ragged sizes; fp32 4 MB 6.55 -> 6.06 | 7.84 -> 7.38, 6.4 MB 8.18 -> 6.51 | 8.38
-// -> 7.64, 10 MB 8.15 -> 7.73 | 8.10 -> 8.14, 14 MB 8.58 -> 8.79 | 9.02 -> 9.40; bf16 6.4 MB
-// 8.39 -> 7.80 | 8.75 -> 8.62, 14 MB 9.96 -> 9.79 | 10.12 -> 10.40; 6.4 MB from memory, 64
-// buffers, 7.2 -> 7.5).  Kernels of their own:
-// with both kinds of load behind a branch the compiler waits for all of a wave's loads
-// before it tests the first (6.4 MB, 40 buffers: 8.8 instead of 6.8).
-constexpr size_t kSmallTensorBytes = size_t{10} << 20;
 constexpr TileShape kMinShape{16, 4};             // 16 KB, the smallest tile (sizes the workspace)
 static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16 * kThreads, "smallest tile");
 
@@ -2189,24 +2174,42 @@ inline TileShape choose_shape(size_t n, int w, bool windowed) {
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }
 
+// The input is read with the streaming hint at every size.  us with the hint -> without, density
+// 0.4, three buffers in turn | 700 MB of buffers in turn | 700 MB, each just written by a copy:
+//   fp32      2 MB 4.9 -> 4.9 | 5.6 -> 6.1 | 5.2 -> 5.4   4 MB 5.2 -> 5.2 | 6.4 -> 6.9 | 6.0 -> 6.4
+//             6 MB 5.7 -> 5.7 | 7.4 -> 7.2 | 6.3 -> 7.0   10 MB 6.8 -> 6.7 | 7.7 -> 8.2 | 7.3 -> 8.7
+//   16-bit    4 MB 5.8 -> 5.9 | 6.5 -> 7.1 | 6.5 -> 6.9   10 MB 7.6 -> 7.6 | 8.1 -> 8.6 | 7.9 -> 8.5
+//   size pass 6 MB 4.1 -> 4.2 | 4.9 -> 5.5 | 4.7 -> 5.1   10 MB 4.4 -> 4.4 | 5.6 -> 6.1 | 5.3 -> 6.2
+
+// Which tensors' tiles stage half of their steps before their count is published and half after
+// (EARLY; the windowed stream has its own rule).  That pays while the call is a chain of tiles that
+// wait for counts; a large 16-bit tensor's vector units are busy, and the second half's staging is then in the way.
+//   fp32, us all | half | none: 256 KB 4.91 | 4.86 | 5.08, dense 5.66 | 4.86; 4 MB dense 5.94 | 5.38; 822 MB
+//   (64 KB tiles) 202.8 | | 205.5
+//   16-bit: 8 MB 7.26 | 7.06 | 7.46, dense 8.1 | 7.2; 51 MB dense 22.5 | 24.8
+inline bool choose_early(size_t n, int w, const TileShape& shape) {
+    return w == 4 ? shape.chunks != 64 : n * static_cast<size_t>(w) < (size_t{10} << 20);
+}
+
 enum class Encoder { kPlain, kRelu, kWindowed };
 
-template <int W, int CH, int WV, bool SPLIT, bool SMALL, bool WINDOWED_TOO = true>
+template <int W, int CH, bool SPLIT, bool EARLY, bool WINDOWED_TOO = true>
 hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned char* in, size_t n,
                         unsigned* masks, unsigned char* values, ScanState st,
                         unsigned long long* d_bytes, unsigned long long* h_bytes, unsigned tiles, size_t groups,
                         unsigned long long cap_values, unsigned long long* offsets, unsigned window_shift) {
     const EncoderArgs args{in, n, masks, values, st.hdr, st.counts, st.prefixes, d_bytes, h_bytes, tiles,
                            groups, scan_state_bytes(tiles), cap_values, offsets, window_shift};
+    constexpr int WV = 4;
     const dim3 grid(tiles), block(WV * kWaveSize);
     switch (mode) {
         case Encoder::kPlain:
-            return launch(compress_kernel<W, CH, WV, false, false, SPLIT, SMALL>, grid, block, stream, args);
+            return launch(compress_kernel<W, CH, WV, false, false, SPLIT, EARLY>, grid, block, stream, args);
         case Encoder::kRelu:
-            return launch(compress_kernel<W, CH, WV, true, false, SPLIT, SMALL>, grid, block, stream, args);
+            return launch(compress_kernel<W, CH, WV, true, false, SPLIT, EARLY>, grid, block, stream, args);
         case Encoder::kWindowed:
             if constexpr (WINDOWED_TOO)
-                return launch(compress_kernel<W, CH, WV, false, true, SPLIT, SMALL>, grid, block, stream, args);
+                return launch(compress_kernel<W, CH, WV, false, true, SPLIT, false>, grid, block, stream, args);
             else
                 return hipErrorInvalidValue;   // choose_shape() gives the windowed stream no such tile
     }
@@ -2278,18 +2281,18 @@ hipError_t launch_window_split(int waves, Args... args) {
     return hipErrorInvalidValue;   // there is no other window size from kSplitShift on
 }
 
-// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword, small tensor).
-template <int CH, bool SMALL, typename... Args>
-hipError_t launch_compress_shape(int w, bool split, Args... args) {
-    return w == 4 ? launch_compress_as<4, CH, 4, false, SMALL>(args...)
-         : split ? launch_compress_as<2, CH, 4, true, SMALL>(args...) : launch_compress_as<2, CH, 4, false, SMALL>(args...);
+// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword, early).
+template <int CH, typename... Args>
+hipError_t launch_compress_16bit(bool split, bool early, Args... args) {
+    if (early && CH == 16) return split ? launch_compress_as<2, 16, true, true>(args...) : launch_compress_as<2, 16, false, true>(args...);
+    return split ? launch_compress_as<2, CH, true, false>(args...) : launch_compress_as<2, CH, false, false>(args...);
 }
 template <typename... Args>
-hipError_t launch_compress(int w, TileShape shape, bool split, bool small, Args... args) {
+hipError_t launch_compress(int w, TileShape shape, bool split, bool early, Args... args) {
     switch (shape.waves == 4 ? shape.chunks : 0) {
-        case 16: return small ? launch_compress_shape<16, true>(w, split, args...) : launch_compress_shape<16, false>(w, split, args...);
-        case 32: return launch_compress_shape<32, false>(w, split, args...);
-        case 64: if (w == 4) return launch_compress_as<4, 64, 4, false, false, false>(args...);
+        case 16: return w == 4 ? launch_compress_as<4, 16, false, true>(args...) : launch_compress_16bit<16>(split, early, args...);
+        case 32: return w == 4 ? launch_compress_as<4, 32, false, true>(args...) : launch_compress_16bit<32>(split, early, args...);
+        case 64: if (w == 4) return launch_compress_as<4, 64, false, false, false>(args...);
     }
     return hipErrorInvalidValue;   // choose_shape() returns nothing else
 }
@@ -2343,7 +2346,7 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
     const unsigned char* in = static_cast<const unsigned char*>(d_in);
     unsigned* masks = static_cast<unsigned*>(d_out);
     unsigned char* values = static_cast<unsigned char*>(d_out) + 4 * groups;
-    return hip_ok(launch_compress(w, shape, split, n * static_cast<size_t>(w) < kSmallTensorBytes, mode, stream, in, n, masks,
+    return hip_ok(launch_compress(w, shape, split, choose_early(n, w, shape), mode, stream, in, n, masks,
                     mode == Encoder::kWindowed ? static_cast<unsigned char*>(d_out) : values,
                     scan_state(d_ws, tiles), out_bytes, h_bytes, static_cast<unsigned>(tiles), groups,
                     !bounded ? ~0ull : out_cap - (mode == Encoder::kWindowed ? 0 : 4 * groups),
@@ -2568,11 +2571,8 @@ zvc_status zvc_compressed_size(const void* d_in, size_t n, int w, uint64_t* d_by
     const dim3 grid(static_cast<unsigned>(tiles)), block(kThreads);
     const unsigned nt = static_cast<unsigned>(tiles);
     const bool al = aligned_to(d_in, 16);
-    // (without the streaming hint, us, three buffers in turn | 40: 6.4 MB fp32 4.96 -> 4.22 | 5.29 -> 5.37, 10 MB
-    // bf16 5.79 -> 4.66 | 5.92 -> 6.00, 16 MB fp32 6.13 -> 6.05 | 6.45 -> 6.84)
-    const bool small = n * static_cast<size_t>(w) < kSmallTensorBytes;
-    const auto kernel = w == 4 ? (!al ? count_kernel<4, false, false> : small ? count_kernel<4, true, true> : count_kernel<4, true, false>)
-                               : (!al ? count_kernel<2, false, false> : small ? count_kernel<2, true, true> : count_kernel<2, true, false>);
+    const auto kernel = w == 4 ? (al ? count_kernel<4, true> : count_kernel<4, false>)
+                               : (al ? count_kernel<2, true> : count_kernel<2, false>);
     return hip_ok(launch(kernel, grid, block, stream, in, n, hdr, out, groups, nt));
 }
 

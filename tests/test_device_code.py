@@ -34,3 +34,25 @@ def test_buffer_loads_have_their_whole_offset_in_the_range_check(assembly):
     loads = re.findall(r"buffer_load_\w+ +v[\w\[\]:]+, (?:v\w+|off), s\[[\d:]+\], (\w+)", assembly)
     assert len(loads) == len(re.findall(r"\bbuffer_load_", assembly)) > 100
     assert set(loads) == {"0"}, "%d of %d loads have a scalar offset" % (sum(x != "0" for x in loads), len(loads))
+
+
+def functions(assembly, name):
+    """The bodies of the kernels of that name, by mangled name."""
+    parts = re.split(r"^[0-9a-f]+ <(\w+)>:$", assembly, flags=re.M)
+    return {k: body for k, body in zip(parts[1::2], parts[2::2]) if re.search(r"\d%sI" % name, k)}
+
+
+def test_input_that_is_read_once_is_read_with_the_streaming_hint(assembly):
+    """Without it the tensor's lines push others out of the caches: slower for a tensor from memory, also
+    where a kernel has just written it, and no faster for one that is read again and again."""
+    encoders, counters = functions(assembly, "compress_kernel"), functions(assembly, "count_kernel")
+    assert len(encoders) > 10 and sum("Lb1E" in k for k in counters) >= 2
+    for name, body in encoders.items():
+        loads = re.findall(r"^\s*(buffer_load_.*?)(?:\s*//.*)?$", body, flags=re.M)
+        # (at an odd half dword the last lane of a load needs a dword of the next one's, once more)
+        again = re.search(r"Li2ELi\d+ELi4ELb[01]ELb[01]ELb1E", name) is not None
+        assert len(loads) >= 16 and sum(" nt" not in x for x in loads) == again, name
+    for name, body in counters.items():
+        if "Lb1E" in name:                            # (at least 16-byte aligned)
+            loads = re.findall(r"^\s*(global_load_dwordx4 .*?)(?:\s*//.*)?$", body, flags=re.M)
+            assert len(loads) >= 8 and all(" nt" in x for x in loads), name
