@@ -2182,13 +2182,14 @@ inline TileShape choose_shape(size_t n, int w, bool windowed) {
 //   size pass 6 MB 4.1 -> 4.2 | 4.9 -> 5.5 | 4.7 -> 5.1   10 MB 4.4 -> 4.4 | 5.6 -> 6.1 | 5.3 -> 6.2
 
 // Which tensors' tiles stage half of their steps before their count is published and half after
-// (EARLY; the windowed stream has its own rule).  That pays while the call is a chain of tiles that
+// (EARLY; the windowed stream has its own rule).  That pays while the call is a short chain of tiles that
 // wait for counts; a large 16-bit tensor's vector units are busy, and the second half's staging is then in the way.
 //   fp32, us all | half | none: 256 KB 4.91 | 4.86 | 5.08, dense 5.66 | 4.86; 4 MB dense 5.94 | 5.38; 822 MB
 //   (64 KB tiles) 202.8 | | 205.5
-//   16-bit: 8 MB 7.26 | 7.06 | 7.46, dense 8.1 | 7.2; 51 MB dense 22.5 | 24.8
+//   16-bit, all | half: 8 MB dense 8.1 | 7.2   12 MB 9.3 | 8.7   15 MB 10.2 | 9.6, dense 9.8 | 9.5   17 MB
+//   10.4 | 10.1   20 MB 10.7 | 10.9, dense 10.9 | 10.8   30 MB 13.9 | 14.2, dense 13.2 | 15.5
 inline bool choose_early(size_t n, int w, const TileShape& shape) {
-    return w == 4 ? shape.chunks != 64 : n * static_cast<size_t>(w) < (size_t{10} << 20);
+    return w == 4 ? shape.chunks != 64 : n * static_cast<size_t>(w) < (size_t{20} << 20);
 }
 
 enum class Encoder { kPlain, kRelu, kWindowed };

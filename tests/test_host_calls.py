@@ -119,3 +119,30 @@ def test_copies_are_the_runtimes(fake, n, w, pinned):
         {"stream": COPY, "to": HOST, "from": STAGE, "bytes": nbytes}]
     assert [v for k, v, _ in back if k == "copy"] == [{"stream": COPY, "to": STAGE, "from": HOST, "bytes": nbytes}]
     assert [v["bytes"] for k, v, _ in out if k == "copy" and v["stream"] == COMPUTE] == ([] if pinned else [8])
+
+
+ENCODERS = {
+    "compress": "call('zvc_compress', %d, n, w, %d, worst(n, w), %d, %d, room(n, w), 0)" % (IN, OUT, HOST, WS),
+    "relu": "call('zvc_relu_compress', %d, n, w, %d, worst(n, w), %d, %d, room(n, w), 0)" % (IN, OUT, HOST, WS),
+    "windowed": "call('zvc_window_compress', %d, n, w, 4096, %d, worst(n, w), %d, %d, %d, room(n, w), 0)"
+                % (IN, OUT, HOST, HOST + 64, WS),
+}
+MB = 1 << 20
+
+
+@pytest.mark.parametrize("mode,w,nbytes,tile,early", [
+    # half of the staging behind the count: 16-bit tiles where the call is one short chain of tiles
+    ("compress", 2, 4 * MB, 16384, 1), ("compress", 2, 12 * MB, 16384, 1), ("relu", 2, 17 * MB, 16384, 1),
+    ("compress", 2, 24 * MB, 16384, 0), ("compress", 2, 64 * MB, 32768, 0),
+])
+def test_encoder_by_size(fake, mode, w, nbytes, tile, early):
+    """The tile and the order of staging and count that measure best at a size (the measurements stand
+    beside the rules)."""
+    lines = run(fake, "n, w = %d, %d\n%s" % (nbytes // w, w, ENCODERS[mode]))
+    (kind, values, name), = lines
+    assert kind == "launch"
+    got = re.search(r"compress_kernelILi(\d)ELi(\d+)ELi(\d)ELb(\d)ELb(\d)ELb(\d)ELb(\d)E", name).groups()
+    got_w, chunks, waves, relu, windowed, _, got_early = map(int, got)
+    assert (got_w, relu, windowed) == (w, mode == "relu", mode == "windowed")
+    assert (chunks * waves * 256, got_early) == (tile, early)
+    assert values["grid"] == -(-nbytes // tile)
