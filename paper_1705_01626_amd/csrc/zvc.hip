@@ -2184,12 +2184,13 @@ inline TileShape choose_shape(size_t n, int w, bool windowed) {
 // Which tensors' tiles stage half of their steps before their count is published and half after
 // (EARLY; the windowed stream has its own rule).  That pays while the call is a short chain of tiles that
 // wait for counts; a large 16-bit tensor's vector units are busy, and the second half's staging is then in the way.
-//   fp32, us all | half | none: 256 KB 4.91 | 4.86 | 5.08, dense 5.66 | 4.86; 4 MB dense 5.94 | 5.38; 822 MB
-//   (64 KB tiles) 202.8 | | 205.5
+//   fp32, us all | half: 256 KB 4.91 | 4.86, dense 5.66 | 4.86   4 MB dense 5.94 | 5.38   18 MB fused ReLU 9.4 |
+//   9.0   32 MB 11.1 | 10.9   49 MB 16.3 | 16.4   56 MB 17.1 | 17.6   64 MB 19.4 | 21.3, dense 24.5 | 27.8   80 MB
+//   25.6 | 25.8   (none: 256 KB 5.08; 822 MB, 64 KB tiles, 205.5, all 202.8)
 //   16-bit, all | half: 8 MB dense 8.1 | 7.2   12 MB 9.3 | 8.7   15 MB 10.2 | 9.6, dense 9.8 | 9.5   17 MB
 //   10.4 | 10.1   20 MB 10.7 | 10.9, dense 10.9 | 10.8   30 MB 13.9 | 14.2, dense 13.2 | 15.5
-inline bool choose_early(size_t n, int w, const TileShape& shape) {
-    return w == 4 ? shape.chunks != 64 : n * static_cast<size_t>(w) < (size_t{20} << 20);
+inline bool choose_early(size_t n, int w) {
+    return n * static_cast<size_t>(w) < (size_t{w == 4 ? 48u : 20u} << 20);
 }
 
 enum class Encoder { kPlain, kRelu, kWindowed };
@@ -2282,18 +2283,23 @@ hipError_t launch_window_split(int waves, Args... args) {
     return hipErrorInvalidValue;   // there is no other window size from kSplitShift on
 }
 
-// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword, early).
-template <int CH, typename... Args>
-hipError_t launch_compress_16bit(bool split, bool early, Args... args) {
-    if (early && CH == 16) return split ? launch_compress_as<2, 16, true, true>(args...) : launch_compress_as<2, 16, false, true>(args...);
-    return split ? launch_compress_as<2, CH, true, false>(args...) : launch_compress_as<2, CH, false, false>(args...);
+// Picks the instantiation for (w, tile shape, 16-bit elements at an odd half dword, early).  Left
+// out are those that choose_shape() and choose_early() never give.
+template <int CH, bool EARLY, typename... Args>
+hipError_t launch_compress_16bit(bool split, Args... args) {
+    return split ? launch_compress_as<2, CH, true, EARLY>(args...) : launch_compress_as<2, CH, false, EARLY>(args...);
 }
 template <typename... Args>
 hipError_t launch_compress(int w, TileShape shape, bool split, bool early, Args... args) {
     switch (shape.waves == 4 ? shape.chunks : 0) {
-        case 16: return w == 4 ? launch_compress_as<4, 16, false, true>(args...) : launch_compress_16bit<16>(split, early, args...);
-        case 32: return w == 4 ? launch_compress_as<4, 32, false, true>(args...) : launch_compress_16bit<32>(split, early, args...);
-        case 64: if (w == 4) return launch_compress_as<4, 64, false, false, false>(args...);
+        case 16:
+            return w == 4 ? launch_compress_as<4, 16, false, true>(args...)
+                 : early ? launch_compress_16bit<16, true>(split, args...) : launch_compress_16bit<16, false>(split, args...);
+        case 32:
+            return w == 2 ? launch_compress_16bit<32, false>(split, args...)
+                 : early ? launch_compress_as<4, 32, false, true>(args...) : launch_compress_as<4, 32, false, false>(args...);
+        case 64:
+            if (w == 4) return launch_compress_as<4, 64, false, false, false>(args...);
     }
     return hipErrorInvalidValue;   // choose_shape() returns nothing else
 }
@@ -2347,7 +2353,7 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
     const unsigned char* in = static_cast<const unsigned char*>(d_in);
     unsigned* masks = static_cast<unsigned*>(d_out);
     unsigned char* values = static_cast<unsigned char*>(d_out) + 4 * groups;
-    return hip_ok(launch_compress(w, shape, split, choose_early(n, w, shape), mode, stream, in, n, masks,
+    return hip_ok(launch_compress(w, shape, split, choose_early(n, w), mode, stream, in, n, masks,
                     mode == Encoder::kWindowed ? static_cast<unsigned char*>(d_out) : values,
                     scan_state(d_ws, tiles), out_bytes, h_bytes, static_cast<unsigned>(tiles), groups,
                     !bounded ? ~0ull : out_cap - (mode == Encoder::kWindowed ? 0 : 4 * groups),
