@@ -2152,8 +2152,9 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 //            103 MB 32.1 | 32.0   150 MB 45.1 | 44.6   170 MB 51.1 | 49.8   300 MB 87.0 | 82.1   (32 | 64 KB)
 //   windowed  32 MB 14.1 | 14.3   36 MB 15.4 | 15.6   40 MB 16.6 | 16.4   48 MB 19.4 | 18.2   100 MB 36.5 | 34.1
 //             (822 MB: nothing gained from 64 KB)
-//   16-bit    32 MB 13.8 | 15.7   49 MB 20.9 | 21.2   52 MB 21.7 | 21.9   56 MB 23.0 | 22.7   64 MB 25.8 | 25.0   80 MB 31.3 | 29.9
-//             fused ReLU 49 MB 19.0 | 19.0   52 MB 20.1 | 19.4   64 MB 23.8 | 22.5
+//   16-bit    32 MB 13.8 | 15.7   44 MB 17.2 | 17.0   47.5 MB 18.0 | 17.6, density 0.5 19.8 | 19.9   49 MB 18.6 | 18.2,
+//             0.5 20.4 | 21.0   54 MB 20.0 | 19.0, 0.5 22.1 | 21.9   60 MB 21.9 | 20.8, 0.5 24.3 | 24.4   (0.1 to 0.5;
+//             700 MB of buffers in turn 49 MB 19.2 | 18.6; fused ReLU 47.5 MB 18.2 | 17.8, 49 MB 18.6 | 18.3, 54 MB 20.3 | 19.2)
 //   windowed  90 MB 38.4 | 39.7  110 MB 45.3 | 45.8  120 MB 49.0 | 48.9  150 MB 59.1 | 57.7  200 MB 77.8 | 73.0
 // 16-bit elements are twice the vector work per byte, and the 32 KB tile's eight
 // waves per SIMD (against four) hide it better: 64 KB tiles lose up to 9 % there.
@@ -2169,7 +2170,7 @@ static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16
 
 inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    const size_t medium = w == 4 ? size_t{windowed ? 38u : 14u} << 20 : size_t{windowed ? 120u : 50u} << 20;
+    const size_t medium = w == 4 ? size_t{windowed ? 38u : 14u} << 20 : size_t{windowed ? 120u : 48u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }

@@ -16,7 +16,7 @@ DEV = "cuda"
 MB = 1 << 20
 LIMITS = {("plain", 4): (10 * MB, 14 * MB, 48 * MB), ("relu", 4): (10 * MB, 14 * MB, 48 * MB),
           ("windowed", 4): (10 * MB, 38 * MB),
-          ("plain", 2): (10 * MB, 20 * MB, 50 * MB), ("relu", 2): (10 * MB, 20 * MB, 50 * MB),
+          ("plain", 2): (10 * MB, 20 * MB, 48 * MB), ("relu", 2): (10 * MB, 20 * MB, 48 * MB),
           ("windowed", 2): (10 * MB, 120 * MB)}
 
 

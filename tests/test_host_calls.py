@@ -134,6 +134,8 @@ MB = 1 << 20
     # half of the staging behind the count: 16-bit tiles where the call is one short chain of tiles
     ("compress", 2, 4 * MB, 16384, 1), ("compress", 2, 12 * MB, 16384, 1), ("relu", 2, 17 * MB, 16384, 1),
     ("compress", 2, 24 * MB, 16384, 0), ("compress", 2, 64 * MB, 32768, 0),
+    # 32 KB tiles from 48 MB of 16-bit elements on
+    ("compress", 2, 47 * MB, 16384, 0), ("compress", 2, 49 * MB, 32768, 0), ("relu", 2, 49 * MB, 32768, 0),
     # fp32: all but the large ones
     ("compress", 4, 4 * MB, 16384, 1), ("relu", 4, 20 * MB, 32768, 1), ("compress", 4, 40 * MB, 32768, 1),
     ("compress", 4, 64 * MB, 32768, 0), ("relu", 4, 80 * MB, 32768, 0), ("compress", 4, 300 * MB, 65536, 0),
