@@ -1633,6 +1633,9 @@ struct WindowGeometry {
     static constexpr int kPieceElems = kPieceGroups * 32;
     static constexpr unsigned kGroupBytes = 4 + 32 * W;                // a group with nothing dropped
     static constexpr unsigned kPieceBytes = kPieceGroups * kGroupBytes;
+    // window_decode_kernel, a wave's slice: shift < 16, then a piece, then what a walk that is past its end reads
+    static constexpr unsigned kSliceBytes = (16 + kPieceBytes + kGroupBytes + 15) / 16 * 16;
+    static constexpr unsigned kDecodeLdsBytes = 16 + kWaves * (kSliceBytes + 4 * kPieceGroups + 8 * kStageLoads);
 };
 
 // The mask at an LDS address that is a multiple of W (or, in a damaged stream, of
@@ -1677,13 +1680,13 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     size_t first_window, size_t num_windows, unsigned window_shift, unsigned char* __restrict__ out,
     bool interleave) {
     using G = WindowGeometry<W>;
-    // shift < 16, then a piece, then what a walk that is past its end reads
-    constexpr unsigned kSliceBytes = (16 + G::kPieceBytes + G::kGroupBytes + 15) / 16 * 16;
+    constexpr unsigned kSliceBytes = G::kSliceBytes;
     constexpr unsigned kMostWindows = kStageLoads;          // per piece
     static_assert(G::kPieceBytes + 15 <= kFetchSlots * kSlotBytes, "a piece fits the fetch slots");
     __shared__ __align__(16) unsigned char s_stage[16 + kWaves * kSliceBytes];      // (16: see expand_piece)
     __shared__ unsigned s_mask_at[kWaves * G::kPieceGroups];
     __shared__ __align__(8) uint2 s_window[kWaves * kMostWindows];                  // where a window begins, where the piece ends
+    static_assert(sizeof(s_stage) + sizeof(s_mask_at) + sizeof(s_window) == G::kDecodeLdsBytes, "as the host counts it");
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
@@ -2111,6 +2114,12 @@ hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t 
     return launch_padded(kernel, 0, grid, block, stream, args...);
 }
 
+// LDS to add for a workgroup of four waves that declares `declared` bytes, so that seven share a
+// CU's 160 KB.  Without it eight do, as many as a CU has wave slots for.
+constexpr unsigned kCuLdsBytes = 160u << 10, kSevenLdsBytes = kCuLdsBytes / 8 + 1024;
+static_assert(kWaves == 4 && kCuLdsBytes / kSevenLdsBytes == 7, "32 waves and 160 KB per CU");
+constexpr unsigned seven_per_cu(unsigned declared) { return kSevenLdsBytes - declared; }
+
 // Zeroes the header and the first state_bytes bytes of scan state.
 zvc_status launch_reset(void* d_ws, size_t state_bytes, hipStream_t stream) {
     const size_t words = (kHeaderBytes + state_bytes) / 8;
@@ -2148,7 +2157,9 @@ zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
 // alone takes 3.7 us with 16 KB, 4.8 with 32 KB, 6.9 with 64 KB).  Measured us with
 // 16 | 32 KB tiles, density 0.5 (windowed: 0.1 to 0.9, 12 and 14 MB: 0.1 to 0.7), sizes a few elements
 // above a whole number of tiles, three buffers in turn, on both sides of every limit below:
-//   fp32      12 MB 7.3 | 8.2   14 MB 8.3 | 8.2   16 MB 8.2 | 7.8   20 MB 9.6 | 9.2   24 MB 10.7 | 9.7   56 MB 20.9 | 17.1
+//   fp32      12 MB 7.3 | 8.2   14.1 MB 8.4 | 7.9, density 0.2 8.3 | 7.7, dense 8.7 | 11.2   15.5 MB 8.7 | 8.0, 0.2 8.5 | 7.8,
+//             dense 8.8 | 10.2   20 MB 9.6 | 9.4, dense 10.2 | 11.0   32 MB 12.4 | 10.9, dense 13.4 | 13.1   56 MB 20.9 | 17.1
+//             (a dense tensor pays for the lower limit: half of its 32 KB tile waits for the scan)
 //            103 MB 32.1 | 32.0   150 MB 45.1 | 44.6   170 MB 51.1 | 49.8   300 MB 87.0 | 82.1   (32 | 64 KB)
 //   windowed  32 MB 14.1 | 14.3   36 MB 15.4 | 15.6   40 MB 16.6 | 16.4   48 MB 19.4 | 18.2   100 MB 36.5 | 34.1
 //             (822 MB: nothing gained from 64 KB)
@@ -2259,6 +2270,27 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
 // 8 KB, 103 MB fp32 30.3 | 27.5, 51 MB bf16 28.1 | 24.0; the lane's chain is a quarter of
 // that at 2 KB and the workgroup's three barriers stay).
 constexpr int kSplitShift = 3;
+
+// Whether window_decode_kernel deals its windows out in the interleaved order: from the size
+// of a range on at which that order is the faster one for a stream of this density.  us,
+// plain | interleaved, windows of 1, 2 and 4 KB:
+//   fp32  0.02, 130 MB 25.6 | 25.3  25.4 | 24.8  23.2 | 23.4   250 MB 46.5 | 41.8  45.6 | 41.8  39.4 | 39.0
+//         0.05, 784 MB 145 | 122  142 | 122  123 | 113   (the plain order writes 16 KB per XCD, and with
+//         little to read and to expand the XCDs' writes then hold each other up)
+//         0.12, 400 MB 68.6 | 71.0  68.9 | 70.8  71.2 | 74.0   650 MB 125 | 122  126 | 124  133 | 128
+//         0.25, 300 MB 65.9 | 66.8  66.0 | 66.5  65.1 | 64.8   400 MB 90.3 | 89.3  89.6 | 89.2  88.7 | 87.0
+//         0.4,  175 MB 42.6 | 43.7  42.7 | 43.6  43.4 | 43.6   250 MB 63.7 | 62.3  61.7 | 61.3  62.3 | 60.7
+//         0.6,  110 MB 31.0 | 31.9  31.3 | 32.1  32.4 | 32.7   150 MB 44.2 | 42.9  42.4 | 42.2  43.4 | 42.9
+//   16-bit  0.04, 400 MB 59.6 | 61.3  72.9 | 73.6  81.5 | 81.2   0.25, 400 MB 96.9 | 91.0  90.4 | 91.0  102 | 102
+//         0.4,  250 MB 66.5 | 65.2  62.9 | 62.9  69.7 | 68.2   0.6, 150 MB 43.5 | 43.0  43.7 | 42.9  45.9 | 45.3
+inline bool interleaves_windows(size_t n, int w, int shift, size_t stream_bytes, size_t out_bytes, bool* sparse) {
+    const size_t tensor = n * static_cast<size_t>(w), masks = 4 * div_up(n, 32);
+    const size_t stored = stream_bytes > masks ? stream_bytes - masks : 0;
+    *sparse = stored <= tensor / (shift == 2 ? 16 : 12);
+    const size_t from = stream_bytes / 3 > tensor / 4 ? 64 : stored > tensor / 2 ? 150 : stored > tensor / 3 ? 250
+                      : stored > tensor / 5 ? 400 : !*sparse ? 600 : w == 4 ? 150 : 0;
+    return from != 0 && out_bytes >= from << 20;
+}
 
 template <int W, int NW>
 hipError_t launch_window_split_as(bool aligned, hipStream_t stream, const unsigned char* in,
@@ -2675,12 +2707,17 @@ zvc_status zvc_window_decompress(const void* d_stream, size_t stream_bytes, cons
     const size_t blocks = div_up(div_up(num_windows, static_cast<size_t>(kWaves) * wave_windows), 8) * 8;
     if (blocks > 0x7FFFFFFFull) return ZVC_E_ARG;
     const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    // dense streams of large ranges decode 3-8 % faster in the interleaved order, others slower
-    const bool interleave = stream_bytes / 3 > n * static_cast<size_t>(w) / 4 && out_bytes >= (size_t{64} << 20);
+    bool sparse = false;
+    const bool interleave = interleaves_windows(n, w, shift, stream_bytes, out_bytes, &sparse);
+    // Seven workgroups per CU where the stores alone bind: sparse windows of 1 and 2 KB of large ranges
+    // (us, 8 | 7 per CU, fp32, 1 KB and 2 KB windows: 0.05, 400 MB 63.3 | 61.8  64.0 | 63.7, 784 MB 121.7 | 118.8
+    // 121.9 | 120.1; 0.02, 200 MB 33.2 | 33.7  34.1 | 34.1; 4 KB windows, 784 MB 113.3 | 117.2; 16-bit 1 KB 158.7 | 178.3).
+    const unsigned lds_pad = w == 4 && shift < 2 && sparse && out_bytes >= (size_t{300} << 20)
+                                 ? seven_per_cu(WindowGeometry<4>::kDecodeLdsBytes) : 0;
     const auto kernel = w == 4 ? (al ? window_decode_kernel<4, true> : window_decode_kernel<4, false>)
                                : (al ? window_decode_kernel<2, true> : window_decode_kernel<2, false>);
-    return hip_ok(launch(kernel, grid, block, stream, in, static_cast<unsigned long long>(stream_bytes), offs, n,
-                         groups, first_window, num_windows, static_cast<unsigned>(shift), out, interleave));
+    return hip_ok(launch_padded(kernel, lds_pad, grid, block, stream, in, static_cast<unsigned long long>(stream_bytes),
+                                offs, n, groups, first_window, num_windows, static_cast<unsigned>(shift), out, interleave));
 }
 
 zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w, void* d_out,

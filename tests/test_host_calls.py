@@ -151,3 +151,29 @@ def test_encoder_by_size(fake, mode, w, nbytes, tile, early):
     assert (got_w, relu, windowed) == (w, mode == "relu", mode == "windowed")
     assert (chunks * waves * 256, got_early) == (tile, early)
     assert values["grid"] == -(-nbytes // tile)
+
+
+WINDOW_DECODE = """
+n, w, window = %d, %d, %d
+windows = -(-n * w // window)
+call('zvc_window_decompress', %d, 4 * -(-n // 32) + int(w * n * %f), %d, n, w, window, 0, windows, %d, 0)
+"""
+
+
+@pytest.mark.parametrize("w,window,nbytes,density,interleaved", [
+    # sparse streams of 32-bit elements: the order in which the XCDs write next to each other, from 150 MB up
+    (4, 1024, 784 * MB, 0.05, 1), (4, 2048, 784 * MB, 0.05, 1), (4, 4096, 784 * MB, 0.05, 1), (4, 1024, 200 * MB, 0.02, 1),
+    (4, 1024, 130 * MB, 0.05, 0), (2, 1024, 300 * MB, 0.05, 0), (2, 4096, 784 * MB, 0.05, 0),
+    # between a twelfth and a fifth only the largest, and earlier the denser
+    (4, 1024, 400 * MB, 0.12, 0), (4, 1024, 784 * MB, 0.12, 1), (2, 2048, 784 * MB, 0.12, 1), (4, 2048, 300 * MB, 0.25, 0),
+    (2, 1024, 450 * MB, 0.25, 1), (4, 4096, 200 * MB, 0.4, 0), (4, 4096, 300 * MB, 0.4, 1), (2, 2048, 160 * MB, 0.6, 1),
+    (4, 2048, 130 * MB, 0.6, 0), (4, 1024, 66 * MB, 0.9, 1), (2, 4096, 60 * MB, 0.9, 0),
+])
+def test_order_of_window_decoding(fake, w, window, nbytes, density, interleaved):
+    """In which order the windows are dealt out to the XCDs (the measurements stand beside the rule)."""
+    lines = run(fake, WINDOW_DECODE % (nbytes // w, w, window, STAGE, density, HOST, OUT))
+    (kind, values, name), = lines
+    assert kind == "launch" and "window_decode_kernelILi%d" % w in name
+    assert values["choice"] == interleaved
+    # seven workgroups per CU instead of eight for sparse windows of 1 and 2 KB
+    assert (values["lds"] > 0) == (w == 4 and window < 4096 and density < 1 / 12 and nbytes >= 300 * MB)
