@@ -67,6 +67,8 @@ struct Geometry {
     static constexpr int kStageSteps = LOADS / kStageLoads;
     // (16 bytes so the slice can mirror the destination's alignment)
     static constexpr int kWaveStageBytes = kStageLoads * kWaveSize * 16 + 16;
+    // decompress_kernel: zeros, the waves' slices, a sum per wave
+    static constexpr unsigned kDecodeLdsBytes = 16 + kWaves * kWaveStageBytes + 4 * kWaves;
     static_assert(LOADS % kStageLoads == 0, "tile is staged in whole steps");
 };
 
@@ -1486,6 +1488,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     unsigned long long before_chunk = 0;
     if (chunk_prefix == nullptr) {
         __shared__ __align__(16) unsigned s_before[kWaves];
+        static_assert(sizeof(s_stage) + sizeof(s_before) == G::kDecodeLdsBytes, "as the host counts it");
         const unsigned wave_part = wave_sum_small(total);
         if (lane == 0) s_before[wave] = wave_part;
         lds_barrier();
@@ -1635,7 +1638,6 @@ struct WindowGeometry {
     static constexpr unsigned kPieceBytes = kPieceGroups * kGroupBytes;
     // window_decode_kernel, a wave's slice: shift < 16, then a piece, then what a walk that is past its end reads
     static constexpr unsigned kSliceBytes = (16 + kPieceBytes + kGroupBytes + 15) / 16 * 16;
-    static constexpr unsigned kDecodeLdsBytes = 16 + kWaves * (kSliceBytes + 4 * kPieceGroups + 8 * kStageLoads);
 };
 
 // The mask at an LDS address that is a multiple of W (or, in a damaged stream, of
@@ -1686,7 +1688,6 @@ __global__ __launch_bounds__(kThreads) void window_decode_kernel(
     __shared__ __align__(16) unsigned char s_stage[16 + kWaves * kSliceBytes];      // (16: see expand_piece)
     __shared__ unsigned s_mask_at[kWaves * G::kPieceGroups];
     __shared__ __align__(8) uint2 s_window[kWaves * kMostWindows];                  // where a window begins, where the piece ends
-    static_assert(sizeof(s_stage) + sizeof(s_mask_at) + sizeof(s_window) == G::kDecodeLdsBytes, "as the host counts it");
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
@@ -2254,12 +2255,15 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     // 107.1 | 106.2, at 0.1 89.7 | 86.7, at 0.3 116.5 | 113.8; 822 MB at 0.2 168.2 | 163.7, its first pass
     // over new buffers 246 | 220).
     const bool interleave = ((avail < n / 12 || avail > n / 3) && interleaves(n, W)) || n * W >= (size_t{400} << 20);
-    // From 64 MB up 7 workgroups share a CU instead of the 8 that its LDS would hold: fewer waves write at
-    // once and memory takes the writes 1-2 % faster (us, 8 | 7 | 6 | 5 per CU: 822 MB fp32 at density 0.05
-    // 130.2 | 128.6 | 126.7 | 123.6, 0.2 164.2 | 163.5 | 166.1 | 177.4, 0.5 207.8 | 206.8 | 205.1 | 204.3, 1
-    // 266.1 | 263.6 | 262.4 | 261.5; 297 MB 77.7 | 77.2 | 76.8 | 76.9).  6 and 5 lose where the vector units
-    // bind, and a tensor of 51 MB, where there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
-    const unsigned lds_pad = interleaves(n, W) ? 6144 : 0;
+    // From 64 MB and a quarter of the elements stored up, 7 workgroups share a CU instead of the 8 that it has
+    // wave slots for: fewer waves write at once and memory takes the writes up to 2 % faster.  us, 8 | 7 per CU, 12
+    // streams in turn, fp32 and bf16: 784 MB at density 0.02 138.4 | 143.8, 152.7 | 159.6; 0.05 150.2 | 156.8, 165.4 | 170.8; 0.1 155.9
+    // | 159.2, 171.7 | 174.7; 0.2 161.4 | 160.6, 173.1 | 173.4; 0.3 175.1 | 174.3, 183.2 | 183.8; 0.5 205.9 | 205.2, 214.6 | 212.7; 1
+    // 263.8 | 262.0, 269.9 | 268.9; 400 MB at 0.2 85.3 | 86.4, 92.0 | 92.2, 0.5 105.8 | 105.4, 111.6 | 110.8; 80 MB at 0.1 18.6 | 19.0, 19.8 |
+    // 20.4, 0.5 27.5 | 27.3, 28.5 | 27.8.  (Sparse streams that stay in the caches, three in turn, gain 1 % with 7: 784 MB
+    // fp32 at 0.05 129.8 | 128.5.)  Fewer yet lose where the vector units bind (fp32 at 0.2, 7 | 6 | 5: 163.5 | 166.1 |
+    // 177.4), and a tensor of 51 MB, where there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
+    const unsigned lds_pad = interleaves(n, W) && avail > n / 4 ? seven_per_cu(Geometry<W, LOADS>::kDecodeLdsBytes) : 0;
     return launch_padded(decompress_kernel<W, LOADS, ALIGNED>, lds_pad, grid, dim3(kThreads), stream,
                          masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
                          interleave);
@@ -2283,12 +2287,14 @@ constexpr int kSplitShift = 3;
 //         0.6,  110 MB 31.0 | 31.9  31.3 | 32.1  32.4 | 32.7   150 MB 44.2 | 42.9  42.4 | 42.2  43.4 | 42.9
 //   16-bit  0.04, 400 MB 59.6 | 61.3  72.9 | 73.6  81.5 | 81.2   0.25, 400 MB 96.9 | 91.0  90.4 | 91.0  102 | 102
 //         0.4,  250 MB 66.5 | 65.2  62.9 | 62.9  69.7 | 68.2   0.6, 150 MB 43.5 | 43.0  43.7 | 42.9  45.9 | 45.3
-inline bool interleaves_windows(size_t n, int w, int shift, size_t stream_bytes, size_t out_bytes, bool* sparse) {
+// (Three streams in turn, which for sparse tensors stay in the caches.  From memory, 12 in turn, the interleaved order is
+// ahead by 0 to 4 % at these sizes, 16-bit 1 KB windows of density 0.2 to 0.4 by 3 to 8 %.  Seven workgroups per CU instead
+// of eight: 1 and 2 KB windows of 784 MB fp32 at 0.05 118.8 and 120.1 from the caches, but 4.8 and 1.7 % slower from memory.)
+inline bool interleaves_windows(size_t n, int w, int shift, size_t stream_bytes, size_t out_bytes) {
     const size_t tensor = n * static_cast<size_t>(w), masks = 4 * div_up(n, 32);
     const size_t stored = stream_bytes > masks ? stream_bytes - masks : 0;
-    *sparse = stored <= tensor / (shift == 2 ? 16 : 12);
     const size_t from = stream_bytes / 3 > tensor / 4 ? 64 : stored > tensor / 2 ? 150 : stored > tensor / 3 ? 250
-                      : stored > tensor / 5 ? 400 : !*sparse ? 600 : w == 4 ? 150 : 0;
+                      : stored > tensor / 5 ? 400 : stored > tensor / (shift == 2 ? 16 : 12) ? 600 : w == 4 ? 150 : 0;
     return from != 0 && out_bytes >= from << 20;
 }
 
@@ -2707,17 +2713,11 @@ zvc_status zvc_window_decompress(const void* d_stream, size_t stream_bytes, cons
     const size_t blocks = div_up(div_up(num_windows, static_cast<size_t>(kWaves) * wave_windows), 8) * 8;
     if (blocks > 0x7FFFFFFFull) return ZVC_E_ARG;
     const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    bool sparse = false;
-    const bool interleave = interleaves_windows(n, w, shift, stream_bytes, out_bytes, &sparse);
-    // Seven workgroups per CU where the stores alone bind: sparse windows of 1 and 2 KB of large ranges
-    // (us, 8 | 7 per CU, fp32, 1 KB and 2 KB windows: 0.05, 400 MB 63.3 | 61.8  64.0 | 63.7, 784 MB 121.7 | 118.8
-    // 121.9 | 120.1; 0.02, 200 MB 33.2 | 33.7  34.1 | 34.1; 4 KB windows, 784 MB 113.3 | 117.2; 16-bit 1 KB 158.7 | 178.3).
-    const unsigned lds_pad = w == 4 && shift < 2 && sparse && out_bytes >= (size_t{300} << 20)
-                                 ? seven_per_cu(WindowGeometry<4>::kDecodeLdsBytes) : 0;
+    const bool interleave = interleaves_windows(n, w, shift, stream_bytes, out_bytes);
     const auto kernel = w == 4 ? (al ? window_decode_kernel<4, true> : window_decode_kernel<4, false>)
                                : (al ? window_decode_kernel<2, true> : window_decode_kernel<2, false>);
-    return hip_ok(launch_padded(kernel, lds_pad, grid, block, stream, in, static_cast<unsigned long long>(stream_bytes),
-                                offs, n, groups, first_window, num_windows, static_cast<unsigned>(shift), out, interleave));
+    return hip_ok(launch(kernel, grid, block, stream, in, static_cast<unsigned long long>(stream_bytes), offs, n,
+                         groups, first_window, num_windows, static_cast<unsigned>(shift), out, interleave));
 }
 
 zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w, void* d_out,

@@ -175,5 +175,24 @@ def test_order_of_window_decoding(fake, w, window, nbytes, density, interleaved)
     (kind, values, name), = lines
     assert kind == "launch" and "window_decode_kernelILi%d" % w in name
     assert values["choice"] == interleaved
-    # seven workgroups per CU instead of eight for sparse windows of 1 and 2 KB
-    assert (values["lds"] > 0) == (w == 4 and window < 4096 and density < 1 / 12 and nbytes >= 300 * MB)
+    assert values["lds"] == 0
+
+
+DECODE = """
+n, w = %d, %d
+call('zvc_decompress', %d, 4 * -(-n // 32) + int(w * n * %f), n, w, %d, %d, room(n, w), 0)
+"""
+
+
+@pytest.mark.parametrize("w", [4, 2])
+@pytest.mark.parametrize("nbytes,density,interleaved,seven", [
+    (60 * MB, 0.6, 0, 0), (66 * MB, 0.6, 1, 1), (66 * MB, 0.05, 1, 0), (300 * MB, 0.2, 0, 0), (300 * MB, 0.3, 0, 1),
+    (450 * MB, 0.2, 1, 0), (784 * MB, 0.02, 1, 0), (784 * MB, 0.2, 1, 0), (784 * MB, 0.3, 1, 1), (784 * MB, 1.0, 1, 1),
+])
+def test_order_and_occupancy_of_decoding(fake, w, nbytes, density, interleaved, seven):
+    """Large planar outputs: the order of the parts, and eight workgroups per CU or seven."""
+    lines = run(fake, DECODE % (nbytes // w, w, STAGE, density, OUT, WS))
+    launched = [(v, name) for k, v, name in lines if "17decompress_kernelILi%d" % w in name]
+    assert len(launched) == 1 and len(lines) == 2
+    values = launched[0][0]
+    assert (values["choice"], values["lds"] > 0) == (interleaved, bool(seven))
