@@ -267,7 +267,8 @@ zvc_status zvc_window_compress(const void* d_in, size_t n, int w, size_t window_
  * bytes there; d_offsets is the whole table, made for this window_bytes.  d_out
  * receives the elements of those windows only, i.e. it points at where element
  * first_window * window_bytes / w of the tensor goes.  Needs no workspace.  The
- * kernel reads nothing outside [d_stream, d_stream + stream_bytes) and the
+ * kernel reads nothing outside [d_stream, d_stream + stream_bytes) (but for the
+ * rest of the aligned 16-byte chunks at its ends) and the
  * table entries of the windows asked for; what a damaged table or mask asks for
  * beyond a window's bytes decodes as zero.  ZVC_E_ARG if the range does not lie
  * within the windows. */

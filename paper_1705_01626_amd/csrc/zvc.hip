@@ -796,9 +796,8 @@ struct EncoderArgs {
 //      chunks), as many steps as the queue holds (some of them earlier, with
 //      their tests, see kFusedSteps): that needs nothing from other tiles, and it
 //      gives the tiles in front the time to publish their counts.
-//   4. wave 0 finishes the device-wide scan (its first round trip has been
-//      under way since the tile started); one barrier hands the result to the
-//      other waves.
+//   4. wave 0 does the device-wide scan, which it begins once its own steps are
+//      staged; one barrier hands the result to the other waves.
 //   5. every wave writes its queue out in whole lines (wave_flush), staging
 //      whatever did not fit before.
 //
@@ -1027,9 +1026,9 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     }
     lds_barrier();                                // the cleared arrival word, after the loads have been issued
 
-    // A step is compacted in the same pass while the queue is sure to hold it whatever its
-    // density (the first two steps always are): the compaction then happens while the wave
-    // would otherwise wait for its loads, and needs nothing from other tiles.
+    // One of the first kFusedSteps steps is compacted in the same pass while the queue is sure
+    // to hold it whatever its density (the first always is): the compaction then happens while
+    // the wave would otherwise wait for its loads, and needs nothing from other tiles.
     int staged = 0;                               // steps in the queue so far, wave-uniform
     static_for<0, G::kSteps>([&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
@@ -1078,8 +1077,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         }
     }
 
-    // ---- 3. more of the compaction before the tile knows where its run begins: the steps
-    //         that were not sure to fit but, now that their size is known, do
+    // ---- 3. more of the compaction before the tile knows where its run begins: the steps left
+    //         for now, and those that were not sure to fit but, now that their size is known, do
     const auto step_bytes = [&](int h) -> unsigned {
         return step_total[h] * W + (WINDOWED ? 4u * groups_from(h * G::kStepGroups, G::kStepGroups) : 0u);
     };
@@ -1624,9 +1623,9 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
 //     a lane walks each (8..32 masks of 32-bit elements, twice that of 16-bit ones);
 //   windows of 8..64 KB (window_split_kernel): a workgroup takes a window and cuts
 //     the walk into parts.
-// Reads stay inside [0, stream_bytes) and inside the staged bytes whatever the
-// table and the masks say; what a damaged stream asks for beyond that decodes
-// as zero.
+// Reads stay inside the aligned 16-byte chunks that [0, stream_bytes) touches and
+// inside the staged bytes whatever the table and the masks say; what a damaged
+// stream asks for beyond that decodes as zero.
 constexpr int kWindowUnitBytes = 1024;  // window sizes are 1 KB << shift
 constexpr unsigned kMaxWindowShift = 6; // 64 KB
 

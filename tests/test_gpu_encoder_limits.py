@@ -1,7 +1,7 @@
-"""The encoder at the sizes where its kernels change (smallest tile for small tensors, smallest, 32 KB) and
-its tile's queues filled to the last byte: whole tiles, a word less and a word more, at densities from
-nothing to everything, in each mode and at either alignment of 16-bit elements.  The oracle's streams, and
-nothing written past them."""
+"""The encoder at the sizes where its kernels change (16 or 32 KB tiles, half of a tile's staging before its
+count or all of it), at 10 MB, and its tile's queues filled to the last byte: whole tiles, a word less and a
+word more, at densities from nothing to everything, in each mode and at either alignment of 16-bit
+elements.  The oracle's streams, and nothing written past them."""
 import numpy as np
 import pytest
 import torch

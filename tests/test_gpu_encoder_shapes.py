@@ -15,8 +15,8 @@ DTYPES = {4: torch.int32, 2: torch.int16}
 TILE_BYTES = 64 << 10
 MB = 1 << 20
 # bytes from which a larger tile is taken: 16 -> 32 KB, 32 -> 64 KB
-LIMITS = {("plain", 4): (16 * MB, 160 * MB), ("relu", 4): (16 * MB, 160 * MB), ("windowed", 4): (36 * MB,),
-          ("plain", 2): (48 * MB,), ("relu", 2): (48 * MB,), ("windowed", 2): (160 * MB,)}
+LIMITS = {("plain", 4): (14 * MB, 160 * MB), ("relu", 4): (14 * MB, 160 * MB), ("windowed", 4): (38 * MB,),
+          ("plain", 2): (48 * MB,), ("relu", 2): (48 * MB,), ("windowed", 2): (120 * MB,)}
 
 
 def stretches(n, w, offset, seed):

@@ -1,5 +1,5 @@
-"""The window decoder's walk over masks: streams that end early, window sizes and
-numbers of windows on both sides of where the kernels change, the extremes of
+"""The window decoder's walk over masks: streams that end early, window sizes on both
+sides of where the kernels change, one window and thousands, the extremes of
 density (a group of one word, a group of 33), against a walk written out in numpy."""
 import numpy as np
 import pytest
@@ -123,9 +123,10 @@ def test_windows_of_mixed_density(oracle, window, w):
 
 
 @pytest.mark.parametrize("window,w,most", [(16384, 4, 2048), (16384, 2, 768), (32768, 2, 1536), (65536, 2, 1792)])
-def test_both_sides_of_the_number_of_windows(window, w, most):
-    """As many windows as take a workgroup each, and one more: the same elements (which the GPU's own
-    encoder compressed; its streams are compared with the oracle's elsewhere)."""
+def test_many_windows_and_the_last_alone(window, w, most):
+    """Hundreds of large windows, whose workgroups share the CUs, with and without the ragged last one, and
+    that one alone: the same elements (which the GPU's own encoder compressed; its streams are compared with
+    the oracle's elsewhere)."""
     per = window // w
     n = (most + 1) * per - 37
     g = torch.Generator(device=DEV).manual_seed(window + w)
