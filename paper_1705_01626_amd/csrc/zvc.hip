@@ -2186,12 +2186,15 @@ inline TileShape choose_shape(size_t n, int w, bool windowed) {
          : bytes >= medium ? TileShape{32, 4} : kMinShape;
 }
 
-// The input is read with the streaming hint at every size.  us with the hint -> without, density
-// 0.4, three buffers in turn | 700 MB of buffers in turn | 700 MB, each just written by a copy:
-//   fp32      2 MB 4.9 -> 4.9 | 5.6 -> 6.1 | 5.2 -> 5.4   4 MB 5.2 -> 5.2 | 6.4 -> 6.9 | 6.0 -> 6.4
-//             6 MB 5.7 -> 5.7 | 7.4 -> 7.2 | 6.3 -> 7.0   10 MB 6.8 -> 6.7 | 7.7 -> 8.2 | 7.3 -> 8.7
-//   16-bit    4 MB 5.8 -> 5.9 | 6.5 -> 7.1 | 6.5 -> 6.9   10 MB 7.6 -> 7.6 | 8.1 -> 8.6 | 7.9 -> 8.5
-//   size pass 6 MB 4.1 -> 4.2 | 4.9 -> 5.5 | 4.7 -> 5.1   10 MB 4.4 -> 4.4 | 5.6 -> 6.1 | 5.3 -> 6.2
+// The input is read with the streaming hint at every size.  A tensor that is read once, just written or
+// from memory, loses without it: its lines push others out of the caches, and where it lies in the caches it is
+// served from there with the hint as well.  us with the hint | without, density 0.4; 3 and 12 buffers in turn, each
+// just written by a copy; 700 MB of buffers, each just written; 700 MB from memory:
+//   fp32   4 MB 6.9 | 6.8  6.0 | 5.8  6.0 | 6.5  6.4 | 7.0   6.4 MB 8.3 | 8.4  6.2 | 6.3  6.3 | 6.9  7.5 | 7.3
+//          10 MB 7.7 | 7.7  7.2 | 7.3  7.4 | 8.8  7.7 | 8.3   1 MB 5.0 | 5.1  5.2 | 5.2  5.2 | 5.1  5.3 | 5.0
+//   16-bit 6.4 MB 8.8 | 8.8  7.1 | 7.1  7.1 | 7.8  7.2 | 8.0   size pass of 10 MB 5.7 | 5.8  5.2 | 5.3  5.3 | 6.2  5.6 | 6.1
+// What gains without it is a tensor that nobody writes and that is compressed again and again: the first call leaves it in the
+// caches.  Three such buffers in turn, 1 | 4 | 6.4 | 10 MB fp32: 5.4 | 6.2 | 7.0 | 7.8 with the hint, 4.8 | 5.1 | 5.6 | 6.7 without.
 
 // Which tensors' tiles stage half of their steps before their count is published and half after
 // (EARLY; the windowed stream has its own rule).  That pays while the call is a short chain of tiles that
