@@ -2257,15 +2257,19 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     // 107.1 | 106.2, at 0.1 89.7 | 86.7, at 0.3 116.5 | 113.8; 822 MB at 0.2 168.2 | 163.7, its first pass
     // over new buffers 246 | 220).
     const bool interleave = ((avail < n / 12 || avail > n / 3) && interleaves(n, W)) || n * W >= (size_t{400} << 20);
-    // From 64 MB and a quarter of the elements stored up, 7 workgroups share a CU instead of the 8 that it has
-    // wave slots for: fewer waves write at once and memory takes the writes up to 2 % faster.  us, 8 | 7 per CU, 12
-    // streams in turn, fp32 and bf16: 784 MB at density 0.02 138.4 | 143.8, 152.7 | 159.6; 0.05 150.2 | 156.8, 165.4 | 170.8; 0.1 155.9
-    // | 159.2, 171.7 | 174.7; 0.2 161.4 | 160.6, 173.1 | 173.4; 0.3 175.1 | 174.3, 183.2 | 183.8; 0.5 205.9 | 205.2, 214.6 | 212.7; 1
-    // 263.8 | 262.0, 269.9 | 268.9; 400 MB at 0.2 85.3 | 86.4, 92.0 | 92.2, 0.5 105.8 | 105.4, 111.6 | 110.8; 80 MB at 0.1 18.6 | 19.0, 19.8 |
-    // 20.4, 0.5 27.5 | 27.3, 28.5 | 27.8.  (Sparse streams that stay in the caches, three in turn, gain 1 % with 7: 784 MB
-    // fp32 at 0.05 129.8 | 128.5.)  Fewer yet lose where the vector units bind (fp32 at 0.2, 7 | 6 | 5: 163.5 | 166.1 |
-    // 177.4), and a tensor of 51 MB, where there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
-    const unsigned lds_pad = interleaves(n, W) && avail > n / 4 ? seven_per_cu(Geometry<W, LOADS>::kDecodeLdsBytes) : 0;
+    // From 64 MB and a quarter of the elements stored up (from 600 MB a sixth), 7 workgroups share a CU instead
+    // of the 8 that it has wave slots for: fewer waves write at once and memory takes the writes up to 2 % faster.
+    // us, 8 | 7 per CU, 12 streams in turn, fp32 and bf16:
+    //   784 MB  0.02 138.4 | 143.8  152.7 | 159.6   0.05 150.2 | 156.8  165.4 | 170.8   0.1 155.9 | 159.2  171.7 | 174.7
+    //           0.15 156.5 | 158.6  170.0 | 172.8   0.2  161.4 | 160.6  173.1 | 173.4   0.3 175.1 | 174.3  183.2 | 183.8
+    //           0.5  205.9 | 205.2  214.6 | 212.7   1    263.8 | 262.0  269.9 | 268.9
+    //   400 MB  0.2  85.3 | 86.4  92.0 | 92.2   0.5 105.8 | 105.4  111.6 | 110.8   80 MB  0.1 18.6 | 19.0  19.8 | 20.4   0.5 27.5 | 27.3
+    //           28.5 | 27.8
+    // (Sparse streams that stay in the caches, three in turn, gain 1 % with 7: 784 MB fp32 at 0.05 129.8 | 128.5.)  Fewer
+    // yet lose where the vector units bind (fp32 at 0.2, 7 | 6 | 5: 163.5 | 166.1 | 177.4), and a tensor of 51 MB, where
+    // there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
+    const bool seven = interleaves(n, W) && avail > n / (n * W >= (size_t{600} << 20) ? 6 : 4);
+    const unsigned lds_pad = seven ? seven_per_cu(Geometry<W, LOADS>::kDecodeLdsBytes) : 0;
     return launch_padded(decompress_kernel<W, LOADS, ALIGNED>, lds_pad, grid, dim3(kThreads), stream,
                          masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
                          interleave);
