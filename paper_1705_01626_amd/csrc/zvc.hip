@@ -860,13 +860,17 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     unsigned q_lo = 0, q_end = 0;                 // the wave's queue: slice offsets, wave-uniform
     unsigned zero_local = 0;                      // offset within the wave's run of slice offset 0
     unsigned window_local = 0;                    // lane i: offset within the wave's run of its window i
-    // groups of the tensor in this wave's part, and among `count` of them from `first_group` on
+    // groups of the tensor in this wave's part
     const unsigned groups_here =
         wave_group0 >= a.num_groups ? 0u
         : a.num_groups - wave_group0 < static_cast<size_t>(G::kWaveGroups) ? static_cast<unsigned>(a.num_groups - wave_group0)
                                                                            : static_cast<unsigned>(G::kWaveGroups);
-    const auto groups_from = [&](unsigned first_group, unsigned count) -> unsigned {
-        return first_group >= groups_here ? 0u : min(count, groups_here - first_group);
+    // Windowed: every chunk leaves room for all the masks it could have.  Groups past the tensor's end have
+    // none, and their room, which is behind everything else, is given back before the queue is written out:
+    // the queue's end when steps first .. upto - 1 have been staged since the last time.
+    const auto queue_end = [&](unsigned first, unsigned upto) -> unsigned {
+        const unsigned there = min(groups_here, upto * G::kStepGroups) - min(groups_here, first * G::kStepGroups);
+        return q_end - 4u * ((upto - first) * G::kStepGroups - there);
     };
     // 16-bit elements: masks from a register with 32 bits of the first elements' ballot in every even
     // lane and one with the same 32 bits of the second elements' ballot.  An even lane zips the low
@@ -896,8 +900,11 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                                                          static_cast<int>(cur[k]), 0x130, 0xF, 0xF, false);
             cur[k] = __builtin_amdgcn_alignbit(static_cast<unsigned>(next), cur[k], 16);
         }
+        // Windowed, 16-bit: staged in a pass of its own, the chunk is tested again.  Kept from the first pass,
+        // the ballots of all chunks are more than the scalar registers hold: they went to vector registers and
+        // back, one by one.  us before | now: 30 MB 15.0 | 13.8, 100 MB 38.8 | 36.2, 300 MB 92.8 | 83.3.
+        if constexpr (WINDOWED && W == 2 && STAGE && !TEST) asm("" : "+v"(cur[k]));
         const unsigned x = cur[k];
-        const unsigned chunk_groups = STAGE && WINDOWED ? groups_from(k * CG, CG) : 0u;
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
             set_lane<k / kWindowChunks>(window_local, zero_local + q_end);
         // (windowed: the lane's group has its mask, and the masks of the chunk's earlier groups, before it;
@@ -913,7 +920,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             if (STAGE) {
                 const unsigned at = 4u * lanes_below(b, 0u) + q_end + (WINDOWED ? 4u + 4u * (lane >> 5) : 0u);
                 if (__builtin_expect(keep, 1)) *reinterpret_cast<unsigned*>(stage + at) = x;   // predicated, no branch
-                q_end += 4u * kept + 4u * chunk_groups;
+                q_end += 4u * kept + (WINDOWED ? 4u * CG : 0u);
             }
         } else {
             const bool keep0 = kept_first<2, RELU>(x), keep1 = kept_second<RELU>(x);
@@ -921,6 +928,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             const unsigned kept = static_cast<unsigned>(__popcll(be)) + static_cast<unsigned>(__popcll(bo));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
+                // (now: the compiler would count when the totals are needed, and keep every ballot until then)
+                if constexpr (WINDOWED) asm volatile("" : "+s"(step_total[k / kStepChunks]));
                 // The ballots as they are, 32 bits each in lanes 4k and 4k+2 (two masks' worth of
                 // first elements in mask_reg, of second elements in second_reg): they are zipped
                 // into the four masks once per wave (windowed: once per step), on the vector unit,
@@ -933,7 +942,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                                     (WINDOWED ? 4u + 4u * (lane >> 4) : 0u);
                 if (__builtin_expect(keep0, 1)) *reinterpret_cast<unsigned short*>(stage + at) = static_cast<unsigned short>(x);
                 if (__builtin_expect(keep1, 1)) *reinterpret_cast<unsigned short*>(stage + at + (keep0 ? 2u : 0u)) = static_cast<unsigned short>(x >> 16);
-                q_end += 2u * kept + 4u * chunk_groups;
+                q_end += 2u * kept + (WINDOWED ? 4u * CG : 0u);
             }
         }
     };
@@ -1080,7 +1089,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     // ---- 3. more of the compaction before the tile knows where its run begins: the steps left
     //         for now, and those that were not sure to fit but, now that their size is known, do
     const auto step_bytes = [&](int h) -> unsigned {
-        return step_total[h] * W + (WINDOWED ? 4u * groups_from(h * G::kStepGroups, G::kStepGroups) : 0u);
+        return step_total[h] * W + (WINDOWED ? 4u * G::kStepGroups : 0u);
     };
     const auto stage_step = [&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
@@ -1136,6 +1145,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             (WINDOWED ? 4 * (wave_group0 < a.num_groups ? wave_group0 : a.num_groups) : 0);
         unsigned char* gzero = run_begin;
         if (G::kHoldsAll || staged != 0) {
+            if (WINDOWED) q_end = queue_end(0u, G::kHoldsAll ? G::kSteps : staged);
             wave_flush<W>(gzero, stage, q_lo, q_end, G::kHoldsAll || staged == G::kSteps, lane);
             zero_local = static_cast<unsigned>(gzero - run_begin);
             wave_lds_sync();
@@ -1144,6 +1154,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             constexpr int h = decltype(hc)::value;
             if (!G::kHoldsAll && h >= staged) {
                 stage_step(hc);
+                if (WINDOWED) q_end = queue_end(h, h + 1);
                 wave_lds_sync();
                 wave_flush<W>(gzero, stage, q_lo, q_end, h == G::kSteps - 1, lane);
                 zero_local = static_cast<unsigned>(gzero - run_begin);
