@@ -161,8 +161,8 @@ zvc_status zvc_compress(const void* d_in, size_t n, int w, void* d_out, size_t o
  * GPU current, as for every call: the stream must belong to the current
  * device).  All calls on one GPU share the array: two calls that may run at the
  * same time on one GPU (different streams without an ordering between them)
- * race and give wrong streams; order them.  Every call leaves the array in its
- * initial all-zero state; only after a call's kernel was aborted is it not, and
+ * race and give wrong streams; order them.  Every call leaves the array ready
+ * for the next one; only after a call's kernel was aborted is it not, and
  * then this entry point must not be used again in the process. */
 #define ZVC_STATIC_MAX_BYTES ((size_t)1 << 30)
 #define ZVC_STATIC_SCRATCH_BYTES ((size_t)320 << 10)

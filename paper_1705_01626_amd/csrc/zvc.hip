@@ -52,7 +52,7 @@ constexpr int kFinishLanes = 64;              // arrival counters, one 128-byte 
 constexpr size_t kHeaderBytes = 256 + 128 * (kFinishLanes + 1);  // header, then the scan state
 constexpr int kMinLoads = 4;                  // smallest tile: 16 KB (sizes the workspace)
 constexpr int kStageLoads = 4;                // 16-byte loads a wave stages through LDS at a time
-constexpr int kBlockTiles = 256;              // one running prefix is published per 256 tiles
+constexpr int kBlockShift = 9;                // one running prefix is published per 512 tiles (or more, see block_shift_of)
 constexpr int kMaxDevices = 64;                // GPUs per process that per-GPU host state is kept for
 constexpr unsigned kDefaultPatience = 2000;   // polls a waiting tile makes before it computes a missing count itself
 constexpr int kPollSleep = 8;                 // s_sleep units (64 clocks each) between polls
@@ -116,16 +116,13 @@ struct EncoderGeometry {
 // Workspace header.  Lives at the start of the caller's workspace.
 struct WsHeader {
     unsigned long long patience_plus_one;   // 0: default; else polls before a waiting tile helps itself, plus one
-    unsigned long long pad0;
+    unsigned long long scan_word;  // the next call's tag and the last one's number of tiles, see scan_word_of
     unsigned long long size_word;  // compressed size for zvc_offload's read-back
     unsigned long long helped;     // predecessor counts computed by a waiting tile since the workspace's init
-    unsigned long long pad[28];
-    // Arrival counters, shared by the encoder and the decoder's pre-pass (calls
-    // on one workspace do not overlap).  Encoder: tile t counts itself finished
-    // in finish[t % 64] once it has read all the scan state it needs; the last
-    // tile waits until all have, then zeroes the scan state and these counters,
-    // so the next call needs no reset kernel.  Pre-pass: the workgroup that
-    // completes a counter bumps finish_top, the one that completes finish_top is
+    unsigned long long helped_here;   // not 0: a waiting tile of the present call has computed a predecessor's count
+    unsigned long long pad[27];
+    // The scan's running prefixes, and arrival counters, zero between calls.  Decoder's pre-pass: the
+    // workgroup that completes a counter bumps finish_top, the one that completes finish_top is
     // the last.  Count-only pass: the same, with `sum` collecting the counts.
     // One counter per 128-byte line keeps the atomics on one address (about
     // 11 ns each) far apart in time.
@@ -133,17 +130,38 @@ struct WsHeader {
         unsigned value;
         unsigned pad;
         unsigned long long sum;
+        unsigned long long prefix[14];
     } finish[kFinishLanes], finish_top;
 };
 static_assert(sizeof(WsHeader) == kHeaderBytes, "header size");
 
-// Scan state in the workspace, after the header:
-//   counts[t]   : 32-bit word per tile, top bit = published, rest = the tile's
-//                 own count of kept elements;
-//   prefixes[b] : 64-bit word per block of kBlockTiles tiles, top bit = published,
-//                 rest = kept elements in all tiles up to and including the block's last.
-constexpr unsigned kCountValid = 0x80000000u;
-constexpr unsigned long long kPrefixValid = 1ull << 63;
+// Scan state:
+//   counts   : a 32-bit word per tile, behind the header; the call's tag in the two highest bits, a bit
+//              that the tile itself wrote it, and the tile's own count of kept elements;
+//   prefixes : a 64-bit word per block of tiles, in the header's lines; the call's tag in the two
+//              highest bits, rest = kept elements in all tiles up to and including the block's last.
+// A word counts if it has the call's tag.  Calls on a workspace take the tags 1 and 2 in turn: every tile
+// writes its words once, which replaces what the call before left there, and the words of tiles that only
+// the call before had are zeroed.  hdr->scan_word has the next call's tag; the last tile turns it over
+// at the call's end: it has every tile's count by then, and a tile publishes its count after it has
+// read the word, so nobody reads it later.  (If counts were computed by waiting tiles, the last
+// tile first sees to it that their owners have started, see scan_end.)  So no tile waits for its
+// stores or counts itself finished, and the call does not end with a clean-up.  us with words that the
+// last tile zeroed once all had counted themselves finished | now, the other changes of the scan
+// included: fp32 256 KB 4.50 | 3.98, 6.4 MB 6.83 | 5.82, 24 MB 9.66 | 9.14, 100 MB 27.6 | 26.4, 300 MB
+// 72.9 | 70.6; bf16 4 MB 6.35 | 5.53, 200 MB 55.6 | 53.0; decoding fp32 6.4 MB 6.35 | 5.8.
+constexpr unsigned kCountOwner = 1u << 29, kCountBits = kCountOwner - 1u;
+constexpr int kTagShift = 30;                 // in the upper 32 bits of a prefix
+constexpr unsigned kLinePrefixes = 14, kMostPrefixes = kLinePrefixes * kFinishLanes;
+
+// scan_word: the next call's tag less one (bit 0), the number of tiles that the last call had, and in the
+// upper 32 bits a check, so that a workspace that was never initialised is at worst scanned wrongly and
+// nothing outside it written.
+constexpr unsigned kScanCheck = 0x9E3779B1u;
+__host__ __device__ inline unsigned long long scan_word_of(unsigned tag, unsigned tiles) {
+    const unsigned low = tiles << 1 | (tag - 1u);
+    return static_cast<unsigned long long>(low * kScanCheck) << 32 | low;
+}
 
 __host__ __device__ inline size_t div_up(size_t a, size_t b) { return a / b + (a % b != 0); }
 
@@ -151,14 +169,17 @@ inline size_t tiles_for(size_t n, int w, int loads) {
     const size_t tile_elems = static_cast<size_t>(kThreads * 16 * loads / w);
     return div_up(n, tile_elems);
 }
-inline size_t counts_bytes(size_t tiles) { return 4 * div_up(tiles, 64) * 64; }   // padded to 256 B
-inline size_t prefixes_bytes(size_t tiles) { return 8 * div_up(tiles, kBlockTiles); }
-inline size_t scan_state_bytes(size_t tiles) {
-    return counts_bytes(tiles) + div_up(prefixes_bytes(tiles), 256) * 256;
+inline size_t scan_state_bytes(size_t tiles) {              // (with room for a word per 256 tiles)
+    return 256 * (div_up(tiles, 64) + div_up(tiles, 64 * 128));
+}
+// log2 of the tiles per block: 9, or more where the header has not room for that many prefixes (from 458752 tiles up)
+__host__ __device__ inline int block_shift_of(unsigned tiles) {
+    int shift = kBlockShift;
+    while (tiles >> shift > kMostPrefixes) ++shift;
+    return shift;
 }
 // the decoder pre-pass arrays sit at the end of the workspace, clear of the
-// encoder's scan state (which is kept zeroed between calls and must not be
-// scribbled on)
+// encoder's scan state (which must not be scribbled on between calls)
 inline size_t pad256(size_t b) { return div_up(b, 256) * 256; }
 inline size_t decoder_area_bytes(size_t chunks) {   // chunk_prefix, chunk_total, unit_end
     return pad256(8 * chunks) + pad256(4 * chunks) + pad256(4 * 128 * chunks);
@@ -173,6 +194,15 @@ __device__ inline void store64(unsigned long long* p, unsigned long long v) {
 }
 __device__ inline void store32(unsigned* p, unsigned v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The same as an exchange, whose old value nobody waits for.  It reaches the memory that all XCDs see sooner
+// than a store does: calls whose tiles wait for words written so take 3 to 5 % less below 20 MB (us,
+// store | exchange: 256 KB 4.20 | 4.00, 6.4 MB 6.17 | 5.95, decoding 6.4 MB 5.89 | 5.57).
+__device__ inline void exchange64(unsigned long long* p, unsigned long long v) {
+    (void)__hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void exchange32(unsigned* p, unsigned v) {
+    (void)__hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // acc + number of set bits of `ballot` in lanes below the calling lane.
@@ -495,11 +525,55 @@ __device__ __forceinline__ unsigned wave_scan_small(unsigned v) {
     return v;
 }
 
+// One call's view of the scan state.
+struct ScanState {
+    WsHeader* hdr;
+    unsigned* counts;
+    unsigned tag;                  // 1 | 2
+    unsigned tiles_before;         // of the call before
+    int block_shift;
+    // The word's load, which goes out behind the tile's own and is waited for when those have arrived.  (On
+    // the vector unit: a scalar load would be waited for at the next barrier.)
+    __device__ static unsigned long long ask(const WsHeader* header) {
+        unsigned none = 0;
+        asm("" : "+v"(none));
+        return *reinterpret_cast<const unsigned long long*>(reinterpret_cast<const unsigned char*>(&header->scan_word) + none);
+    }
+    __device__ ScanState(WsHeader* header, unsigned num_tiles, unsigned long long asked)
+        : hdr(header), counts(reinterpret_cast<unsigned*>(header + 1)), block_shift(block_shift_of(num_tiles)) {
+        const unsigned long long word = uniform(asked);
+        const unsigned low = static_cast<unsigned>(word);
+        tag = (low & 1u) + 1u;
+        tiles_before = static_cast<unsigned>(word >> 32) == low * kScanCheck ? low >> 1 : 0u;
+    }
+    __device__ unsigned long long* prefix(unsigned block) const {
+        return &hdr->finish[block / kLinePrefixes].prefix[block % kLinePrefixes];
+    }
+    __device__ bool is_there(unsigned count) const { return count >> kTagShift == tag; }
+    __device__ void publish(unsigned tile, unsigned kept) const {
+        exchange32(counts + tile, tag << kTagShift | kCountOwner | kept);
+    }
+    __device__ void publish_prefix(unsigned tile, unsigned long long upto) const {
+        exchange64(prefix(tile >> block_shift), static_cast<unsigned long long>(tag) << (32 + kTagShift) | upto);
+    }
+    __device__ bool ends_block(unsigned tile) const { return ((tile + 1u) & ((1u << block_shift) - 1u)) == 0u; }
+    // The tile's share of the words that only the call before had, by one of its waves.
+    __device__ void zero_what_is_left(unsigned tile, unsigned num_tiles, int lane) const {
+        const size_t mine = static_cast<size_t>(tile) * kWaveSize, stride = static_cast<size_t>(num_tiles) * kWaveSize;
+        for (size_t i = num_tiles + mine; i < tiles_before; i += stride)
+            if (i + lane < tiles_before) counts[i + lane] = 0u;
+        // (where a block is longer than it was in the call before, there can be fewer of them, but not fewer tiles)
+        const unsigned blocks = tiles_before >> block_shift_of(tiles_before);
+        for (size_t i = (num_tiles >> block_shift) + mine; i < blocks; i += stride)
+            if (i + lane < blocks) *prefix(static_cast<unsigned>(i) + lane) = 0ull;
+    }
+};
+
 // Device-wide exclusive scan of the per-tile counts, single pass (the paper's
 // offset at which the next mask goes, section 5.1, for a whole tile at a time).
 //
 // Protocol.  Every tile publishes its own count (the wave of the tile that
-// finishes its zero tests last does).  The last tile of every block of 256 also
+// finishes its zero tests last does).  The last tile of every block of 512 also
 // publishes the running total up to and including itself.  A tile
 // finds the nearest published block prefix behind it and adds the counts of the
 // tiles between that block and itself, two counts per 8-byte load across the
@@ -525,33 +599,39 @@ __device__ __forceinline__ unsigned wave_scan_small(unsigned v) {
 // Called by one whole wave of the tile, when the tile's own zero tests are done
 // (asking for the prefixes earlier, while the tile's loads are under way, saves
 // a round trip but finds a prefix further back, and the extra counts to read
-// cost more than the round trip).  Returns the number of kept elements in all
+// cost more than the round trip).  PAUSE: see below.  Returns the number of kept elements in all
 // tiles before `tile` (not 0).
-template <class CountTile>
-__device__ inline unsigned long long scan_exclusive_prefix(unsigned* counts,
-                                                           const unsigned long long* prefixes,
-                                                           unsigned tile, int lane, WsHeader* hdr,
+template <bool PAUSE, class CountTile>
+__device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, unsigned tile, int lane,
                                                            const CountTile& count_tile) {
     const int t = static_cast<int>(tile);
     // nearest published block prefix
-    int bb = t / kBlockTiles - 1;
+    int bb = (t >> st.block_shift) - 1;
     unsigned long long base = 0;
     int lo = 0;
-    while (true) {
+    // With PAUSE nothing is asked for one round trip to memory (patience is needed below): a line of counts that many
+    // tiles read while others still write it costs all of them more (us, at once | a round trip later | 0.3
+    // us asleep: fp32 6.4 MB 6.1 | 5.8 | 6.1, 64 MB 20.4 | 17.3 | 19.5, 300 MB 73.8 | 70.7 | 73.6; decoding
+    // 6.4 MB 6.2 | 5.5 | 5.5; waiting for the tile in front first, alone: 6.9, 21.3, 75.8; 6.7).
+    unsigned long long patience_word = 0;
+    if (PAUSE) patience_word = uniform(load64(&st.hdr->patience_plus_one));
+    while (bb >= 0) {
         const int idx = bb - lane;
-        const unsigned long long pv = idx >= 0 ? load64(prefixes + idx) : kPrefixValid;   // before block 0 the prefix is 0
-        const unsigned long long have = __ballot((pv & kPrefixValid) != 0);
+        unsigned long long pv = 0;
+        if (idx >= 0) pv = load64(st.prefix(static_cast<unsigned>(idx)));
+        const unsigned long long have = __ballot(st.is_there(static_cast<unsigned>(pv >> 32)));
         if (have) {
             const int k = __ffsll(static_cast<long long>(have)) - 1;
-            base = lane_value(pv, k) & ~kPrefixValid;
-            lo = (bb - k + 1) * kBlockTiles;   // first tile after that block
+            base = lane_value(pv, k) << 2 >> 2;
+            lo = (bb - k + 1) << st.block_shift;   // first tile after that block
             break;
         }
         bb -= kWaveSize;
     }
     // Counts of tiles lo .. t-1, a pair per 8-byte load (lo is a multiple of the
     // block size: pairs are aligned), kScanBatch loads per lane in flight at a time
-    // (256 tiles a batch; asking for more at once reads more of the newest counts while they are still being written, which measures slower).  The
+    // (256 tiles a batch; asking for more at once reads more of the newest counts while they are still being
+    // written, which measures slower).  The
     // loads of a batch are added in order as far as everything they cover is
     // published; a later round asks again only from the first load that found
     // something missing, so the waiting re-reads no more than the newest counts.
@@ -559,14 +639,13 @@ __device__ inline unsigned long long scan_exclusive_prefix(unsigned* counts,
     constexpr int kLoadTiles = 2 * kWaveSize;     // tiles covered by one load of the wave
     int done_to = lo;              // wave-uniform: the counts of tiles lo .. done_to-1 are in `sum`
     unsigned sum = 0;              // a lane adds few counts, each below 2^16
-    unsigned polls = 0, patience = 0;
+    unsigned polls = 0;
     while (done_to < t) {
         unsigned long long pair[kScanBatch];
 #pragma unroll
         for (int k = 0; k < kScanBatch; ++k) {
             const int i = done_to + k * kLoadTiles + 2 * lane;
-            pair[k] = i < t ? load64(reinterpret_cast<const unsigned long long*>(counts + i))
-                            : (static_cast<unsigned long long>(kCountValid) << 32) | kCountValid;
+            pair[k] = i < t ? load64(reinterpret_cast<const unsigned long long*>(st.counts + i)) : 0ull;
         }
         int complete = 0;          // leading loads of the batch that found everything published
         int hole = -1;             // wave-uniform: the first tile found unpublished
@@ -574,71 +653,59 @@ __device__ inline unsigned long long scan_exclusive_prefix(unsigned* counts,
         for (int k = 0; k < kScanBatch; ++k) {
             if (complete != k) continue;          // wave-uniform
             const int i = done_to + k * kLoadTiles + 2 * lane;
-            const unsigned c0 = static_cast<unsigned>(pair[k]);
-            const unsigned c1 = i + 1 < t ? static_cast<unsigned>(pair[k] >> 32) : kCountValid;
-            const unsigned long long missing = __ballot((c0 & c1 & kCountValid) == 0u);
+            const unsigned c0 = static_cast<unsigned>(pair[k]), c1 = static_cast<unsigned>(pair[k] >> 32);
+            const bool there0 = i >= t || st.is_there(c0), there1 = i + 1 >= t || st.is_there(c1);
+            const unsigned long long missing = __ballot(!(there0 && there1));
             if (!missing) {
-                sum += (c0 & ~kCountValid) + (c1 & ~kCountValid);
+                sum += (i < t ? c0 & kCountBits : 0u) + (i + 1 < t ? c1 & kCountBits : 0u);
                 complete = k + 1;
             } else {
                 const int first = __ffsll(static_cast<long long>(missing)) - 1;
-                hole = done_to + k * kLoadTiles + 2 * first +
-                       ((lane_value(c0, first) & kCountValid) != 0u ? 1 : 0);
+                hole = done_to + k * kLoadTiles + 2 * first + (st.is_there(lane_value(c0, first)) ? 1 : 0);
             }
         }
         done_to += complete * kLoadTiles;
         if (hole < 0) continue;                   // the whole batch was there: the next one, if any
-        if (polls == 0) {                         // the first fruitless poll: how many may follow
-            const unsigned long long p = uniform(load64(&hdr->patience_plus_one));
-            patience = p != 0 ? static_cast<unsigned>(p - 1) : kDefaultPatience;
-        }
+        if (!PAUSE && polls == 0) patience_word = uniform(load64(&st.hdr->patience_plus_one));
+        const unsigned patience = patience_word != 0 ? static_cast<unsigned>(patience_word - 1) : kDefaultPatience;
         if (polls < patience) {
             ++polls;
             __builtin_amdgcn_s_sleep(kPollSleep);
             continue;
         }
-        // help one unpublished predecessor, then look again without waiting anew
+        // help one unpublished predecessor, then look again without waiting anew.  The call's last tile must
+        // know (scan_end): helped_here is written before the count can be seen.
         const unsigned helped_count = count_tile(static_cast<unsigned>(hole), lane);
-        unsigned old = 0;
         if (lane == 0) {
-            old = atomicMax(counts + hole, kCountValid | helped_count);  // same value as the owner's
-            atomicAdd(&hdr->helped, 1ull);
+            store64(&st.hdr->helped_here, 1ull);
+            atomicAdd(&st.hdr->helped, 1ull);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // unless the owner has been there meanwhile
+            unsigned old = __hip_atomic_load(st.counts + hole, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (!st.is_there(old)) {
+                const unsigned seen = atomicCAS(st.counts + hole, old, st.tag << kTagShift | helped_count);
+                if (seen == old) break;
+                old = seen;
+            }
         }
-        // the atomic has returned, so it has been performed before any lane polls again
-        asm volatile("" : : "v"(old) : "memory");
     }
     // (halves, so that no partial sum can overflow whatever the distance walked)
     return base + wave_sum_small(sum & 0xFFFFu) +
            (static_cast<unsigned long long>(wave_sum_small(sum >> 16)) << 16);
 }
 
-// Encoder clean-up, see WsHeader::finish.  finish_arrive() is called by lane 0
-// of the scan wave once the tile has read all the scan state it needs and its
-// own words have been written (the s_waitcnt makes the write-through stores
-// complete before the counter moves, so no late store can land after the
-// clean-up).  The atomic returns nothing, so no wave ever waits for it.
-__device__ inline void finish_arrive(WsHeader* hdr, unsigned tile) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_fetch_add(&hdr->finish[tile % kFinishLanes].value, 1u, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Called by the scan wave of the last tile at its end: waits until every tile
-// of the call has arrived (none of them waits for this one, and the last tile
-// is dispatched last, so the wait is short), then zeroes the scan state and the
-// counters for the next call.
-__device__ inline void finish_call(WsHeader* hdr, unsigned* counts, unsigned num_tiles, int lane,
-                                   size_t state_bytes) {
-    while (true) {
-        const unsigned long long arrived = wave_sum(static_cast<unsigned long long>(
-            __hip_atomic_load(&hdr->finish[lane].value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
-        if (arrived == num_tiles) break;
-        __builtin_amdgcn_s_sleep(kPollSleep);
+// The end of a call, by the scan wave of its last tile once it has the counts of all tiles: the
+// next call takes the other tag.  A tile whose count was computed by another one may not have
+// begun yet, and would then read the word of the next call: the last tile waits for such
+// tiles (none of them waits for it).
+__device__ inline void scan_end(const ScanState& st, unsigned num_tiles, int lane) {
+    if (__builtin_expect(uniform(load64(&st.hdr->helped_here)) != 0ull, 0)) {
+        for (unsigned tile = lane; tile + 1u < num_tiles; tile += kWaveSize)
+            while (__hip_atomic_load(st.counts + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kCountOwner != (st.tag << 1 | 1u))
+                __builtin_amdgcn_s_sleep(kPollSleep);
+        if (lane == 0) store64(&st.hdr->helped_here, 0ull);
     }
-    uint4* p = reinterpret_cast<uint4*>(counts);   // counts then prefixes, 256-byte aligned
-    const size_t chunks = state_bytes / 16;
-    for (size_t i = lane; i < chunks; i += kWaveSize) p[i] = make_uint4(0u, 0u, 0u, 0u);
-    hdr->finish[lane].value = 0u;
+    if (lane == 0) store64(&st.hdr->scan_word, scan_word_of(3u - st.tag, num_tiles));
 }
 
 // ------------------------------------------------- encoder: loads and zero tests
@@ -766,13 +833,10 @@ struct EncoderArgs {
     unsigned* __restrict__ masks;
     unsigned char* __restrict__ values;
     WsHeader* hdr;
-    unsigned* counts;
-    unsigned long long* prefixes;
     unsigned long long* d_bytes;
     unsigned long long* h_bytes;     // where the size goes as well, in host memory that the GPU sees, or null
     unsigned num_tiles;
     size_t num_groups;
-    size_t state_bytes;
     unsigned long long cap_values;   // bytes that may be written at `values`
     unsigned long long* offsets;   // windowed stream only: byte offset of every window, then the total
     unsigned window_shift;         // windowed stream only: a window is 1 KB << window_shift of input
@@ -900,10 +964,11 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                                                          static_cast<int>(cur[k]), 0x130, 0xF, 0xF, false);
             cur[k] = __builtin_amdgcn_alignbit(static_cast<unsigned>(next), cur[k], 16);
         }
-        // Windowed, 16-bit: staged in a pass of its own, the chunk is tested again.  Kept from the first pass,
-        // the ballots of all chunks are more than the scalar registers hold: they went to vector registers and
-        // back, one by one.  us before | now: 30 MB 15.0 | 13.8, 100 MB 38.8 | 36.2, 300 MB 92.8 | 83.3.
-        if constexpr (WINDOWED && W == 2 && STAGE && !TEST) asm("" : "+v"(cur[k]));
+        // Windowed: staged in a pass of its own, the chunk is tested again.  Kept from the first pass, the
+        // ballots of all chunks are more than the scalar registers hold: they went to vector registers and
+        // back, one by one.  us before | now: 16-bit 30 MB 15.0 | 13.8, 100 MB 38.8 | 36.2, 300 MB 92.8 |
+        // 83.3; fp32 100 MB 28.4 | 27.3, 784 MB 174.7 | 170.1.
+        if constexpr (WINDOWED && STAGE && !TEST) asm("" : "+v"(cur[k]));
         const unsigned x = cur[k];
         if (STAGE && WINDOWED && k % kWindowChunks == 0)
             set_lane<k / kWindowChunks>(window_local, zero_local + q_end);
@@ -915,6 +980,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             const unsigned kept = static_cast<unsigned>(__popcll(b));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
+                // (now: the compiler would count when the totals are needed, and keep every ballot until then)
+                if constexpr (WINDOWED) asm volatile("" : "+s"(step_total[k / kStepChunks]));
                 set_lanes<(2 * k) % kWaveSize, (2 * k + 1) % kWaveSize>(mask_reg[(2 * k) / kWaveSize], b);
             }
             if (STAGE) {
@@ -928,8 +995,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             const unsigned kept = static_cast<unsigned>(__popcll(be)) + static_cast<unsigned>(__popcll(bo));
             if (TEST) {
                 step_total[k / kStepChunks] += kept;
-                // (now: the compiler would count when the totals are needed, and keep every ballot until then)
-                if constexpr (WINDOWED) asm volatile("" : "+s"(step_total[k / kStepChunks]));
+                if constexpr (WINDOWED) asm volatile("" : "+s"(step_total[k / kStepChunks]));   // (as above)
                 // The ballots as they are, 32 bits each in lanes 4k and 4k+2 (two masks' worth of
                 // first elements in mask_reg, of second elements in second_reg): they are zipped
                 // into the four masks once per wave (windowed: once per step), on the vector unit,
@@ -1033,6 +1099,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                 if (static_cast<unsigned>(k * kWaveSize + lane) == last) cur[k] &= 0xFFFFu;
         }
     }
+    const unsigned long long scan_word = ScanState::ask(a.hdr);
     lds_barrier();                                // the cleared arrival word, after the loads have been issued
 
     // One of the first kFusedSteps steps is compacted in the same pass while the queue is sure
@@ -1062,6 +1129,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     for (int h = 0; h < G::kSteps; ++h) wave_total += step_total[h];
 
     // ---- 2. arrival: the last wave of the tile to get here publishes the tile's count
+    const ScanState scan(a.hdr, a.num_tiles, scan_word);
     unsigned arrived = 0;
     if (lane == 0) {
         s_wave_total[wave] = wave_total;
@@ -1071,7 +1139,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     arrived = uniform(arrived);
     const bool publisher = (arrived >> 24) == WV - 1;
     if (publisher && lane == 0)
-        store32(a.counts + tile, kCountValid | ((arrived & 0xFFFFFFu) + wave_total));
+        scan.publish(tile, (arrived & 0xFFFFFFu) + wave_total);
 
     if constexpr (!WINDOWED && W == 2) {
 #pragma unroll
@@ -1085,6 +1153,8 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                 __builtin_nontemporal_store(mask_reg[r], a.masks + g);
         }
     }
+
+    if (wave == WV - 1) scan.zero_what_is_left(tile, a.num_tiles, lane);
 
     // ---- 3. more of the compaction before the tile knows where its run begins: the steps left
     //         for now, and those that were not sure to fit but, now that their size is known, do
@@ -1113,12 +1183,12 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         unsigned long long ex = 0;
         if (tile != 0) {
             const CountInputTile<W, CH, WV, RELU, SPLIT> count_tile{a.in, a.n};
-            ex = scan_exclusive_prefix(a.counts, a.prefixes, tile, lane, a.hdr, count_tile);
+            // (the smallest windowed tile has been staging its steps since it published its count: 1 MB fp32 4.92
+            // us, with the pause 5.00; 30 MB 16-bit 14.15 | 14.23)
+            ex = scan_exclusive_prefix<!(WINDOWED && CH == 16)>(scan, tile, lane, count_tile);
         }
         if (lane == 0) s_prefix = ex;
     }
-    // the tile's count has reached memory before any wave of the tile goes on (see finish_arrive)
-    if (publisher) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     const unsigned long long exclusive = uniform(s_prefix);
     unsigned wave_offset = 0, tile_total = 0;
@@ -1128,11 +1198,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         if (v < wave) wave_offset += t;
         tile_total += t;
     }
-    if (wave == 0 && lane == 0) {
-        if (tile % kBlockTiles == kBlockTiles - 1)
-            store64(a.prefixes + tile / kBlockTiles, kPrefixValid | (exclusive + tile_total));
-        finish_arrive(a.hdr, tile);
-    }
+    if (wave == 0 && lane == 0 && scan.ends_block(tile)) scan.publish_prefix(tile, exclusive + tile_total);
 
     //      A call with a buffer below the worst case (cap_values) writes a tile's
     //      run only if the run ends inside the buffer; the size is reported anyway.
@@ -1182,7 +1248,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     }
 
     if (tile == a.num_tiles - 1 && wave == 0)
-        finish_call(a.hdr, a.counts, a.num_tiles, lane, a.state_bytes);
+        scan_end(scan, a.num_tiles, lane);
 }
 
 // Decoder pre-pass (section 5.2: the popcount of a mask span is the number of
@@ -1548,8 +1614,7 @@ template <int W, bool ALIGNED>
 __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, WsHeader* hdr,
-    unsigned* counts, unsigned long long* prefixes, unsigned num_tiles, size_t state_bytes,
-    size_t num_groups, bool stream_values) {
+    unsigned num_tiles, size_t num_groups, bool stream_values) {
     using G = Geometry<W, kMinLoads>;
     constexpr int E = G::kElemsPerLane;
     constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // masks per wave: 32 | 64
@@ -1578,10 +1643,12 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
             if (g == num_groups - 1 && tail != 0) m &= (1u << tail) - 1u;   // bits past n never count
         }
     }
-    lds_barrier();                                // the cleared arrival word, after the load has been issued
+    const unsigned long long scan_word = ScanState::ask(hdr);
+    lds_barrier();                                // the cleared arrival word, after the loads have been issued
     const unsigned wave_total = wave_sum_small(__popc(m));
 
     // ---- the workgroup's count, published by the wave that arrives last; the scan, by wave 0
+    const ScanState scan(hdr, num_tiles, scan_word);
     unsigned arrived = 0;
     if (lane == 0) {
         s_wave_total[wave] = wave_total;
@@ -1591,17 +1658,16 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     arrived = uniform(arrived);
     const bool publisher = (arrived >> 24) == kWaves - 1;
     if (publisher && lane == 0)
-        store32(counts + tile, kCountValid | ((arrived & 0xFFFFFFu) + wave_total));
+        scan.publish(tile, (arrived & 0xFFFFFFu) + wave_total);
+    if (wave == kWaves - 1) scan.zero_what_is_left(tile, num_tiles, lane);
     if (wave == 0) {
         unsigned long long ex = 0;
         if (tile != 0) {
             const CountMaskTile count_tile{masks, num_groups, tail, kWaves * kStepMasks};
-            ex = scan_exclusive_prefix(counts, prefixes, tile, lane, hdr, count_tile);
+            ex = scan_exclusive_prefix<true>(scan, tile, lane, count_tile);
         }
         if (lane == 0) s_prefix = ex;
     }
-    // the count has reached memory before any wave of the workgroup goes on (see finish_arrive)
-    if (publisher) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     const unsigned long long exclusive = uniform(s_prefix);
     unsigned wave_offset = 0, tile_total = 0;
@@ -1611,17 +1677,13 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
         if (v < wave) wave_offset += t;
         tile_total += t;
     }
-    if (wave == 0 && lane == 0) {
-        if (tile % kBlockTiles == kBlockTiles - 1)
-            store64(prefixes + tile / kBlockTiles, kPrefixValid | (exclusive + tile_total));
-        finish_arrive(hdr, tile);
-    }
+    if (wave == 0 && lane == 0 && scan.ends_block(tile)) scan.publish_prefix(tile, exclusive + tile_total);
 
     if (wave_elem0 < n)
         expand_step<W, ALIGNED>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset,
                                 wave_total, m, wave_elem0, n, out, stream_values, lane);
 
-    if (tile == num_tiles - 1 && wave == 0) finish_call(hdr, counts, num_tiles, lane, state_bytes);
+    if (tile == num_tiles - 1 && wave == 0) scan_end(scan, num_tiles, lane);
 }
 
 // Decoders of the windowed stream.  No scan and no pre-pass: the offset table
@@ -2139,19 +2201,6 @@ zvc_status launch_reset(void* d_ws, size_t state_bytes, hipStream_t stream) {
                          static_cast<unsigned long long*>(d_ws), words));
 }
 
-// Where the scan state of a call with `tiles` tiles lives inside the workspace.
-struct ScanState {
-    WsHeader* hdr;
-    unsigned* counts;
-    unsigned long long* prefixes;
-};
-inline ScanState scan_state(void* d_ws, size_t tiles) {
-    unsigned char* base = static_cast<unsigned char*>(d_ws);
-    return ScanState{reinterpret_cast<WsHeader*>(base),
-                     reinterpret_cast<unsigned*>(base + kHeaderBytes),
-                     reinterpret_cast<unsigned long long*>(base + kHeaderBytes + counts_bytes(tiles))};
-}
-
 zvc_status check_workspace(const void* d_ws, size_t ws, size_t n, int w) {
     if (d_ws == nullptr) return ZVC_E_ARG;
     if (!aligned_to(d_ws, 256)) return ZVC_E_ALIGN;
@@ -2223,11 +2272,11 @@ enum class Encoder { kPlain, kRelu, kWindowed };
 
 template <int W, int CH, bool SPLIT, bool EARLY, bool WINDOWED_TOO = true>
 hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned char* in, size_t n,
-                        unsigned* masks, unsigned char* values, ScanState st,
+                        unsigned* masks, unsigned char* values, WsHeader* hdr,
                         unsigned long long* d_bytes, unsigned long long* h_bytes, unsigned tiles, size_t groups,
                         unsigned long long cap_values, unsigned long long* offsets, unsigned window_shift) {
-    const EncoderArgs args{in, n, masks, values, st.hdr, st.counts, st.prefixes, d_bytes, h_bytes, tiles,
-                           groups, scan_state_bytes(tiles), cap_values, offsets, window_shift};
+    const EncoderArgs args{in, n, masks, values, hdr, d_bytes, h_bytes, tiles, groups, cap_values, offsets,
+                           window_shift};
     constexpr int WV = 4;
     const dim3 grid(tiles), block(WV * kWaveSize);
     switch (mode) {
@@ -2404,14 +2453,13 @@ zvc_status compress_impl(Encoder mode, bool bounded, const void* d_in, size_t n,
     const size_t tiles = div_up(n * static_cast<size_t>(w), static_cast<size_t>(shape.waves) * shape.chunks * kChunkBytes);
     if (tiles > 0x7FFFFFFFull) return ZVC_E_ARG;
     if (scan_state_only && kHeaderBytes + scan_state_bytes(tiles) > ws) return ZVC_E_WORKSPACE;
-    // the scan state is zero between calls: the kernel cleans up after itself
     const size_t groups = div_up(n, 32);
     const unsigned char* in = static_cast<const unsigned char*>(d_in);
     unsigned* masks = static_cast<unsigned*>(d_out);
     unsigned char* values = static_cast<unsigned char*>(d_out) + 4 * groups;
     return hip_ok(launch_compress(w, shape, split, choose_early(n, w), mode, stream, in, n, masks,
                     mode == Encoder::kWindowed ? static_cast<unsigned char*>(d_out) : values,
-                    scan_state(d_ws, tiles), out_bytes, h_bytes, static_cast<unsigned>(tiles), groups,
+                    static_cast<WsHeader*>(d_ws), out_bytes, h_bytes, static_cast<unsigned>(tiles), groups,
                     !bounded ? ~0ull : out_cap - (mode == Encoder::kWindowed ? 0 : 4 * groups),
                     reinterpret_cast<unsigned long long*>(d_offsets), window_shift));
 }
@@ -2477,7 +2525,7 @@ zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d
 // state zvc_workspace_init gives a caller's workspace, and every call leaves it
 // zero again.  Each GPU holds its own copy at its own address.
 constexpr size_t kStaticScratchBytes = ZVC_STATIC_SCRATCH_BYTES;   // covers 16 KB tiles (the smallest) up to the limit
-static_assert(kHeaderBytes + 4 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads)) + 8 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads) / kBlockTiles) + 512 <= ZVC_STATIC_SCRATCH_BYTES, "scratch holds the scan state of the largest call");
+static_assert(kHeaderBytes + 4 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads)) + 8 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads) / 256) + 512 <= ZVC_STATIC_SCRATCH_BYTES, "scratch holds the scan state of the largest call");
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 std::mutex g_scratch_mutex;
@@ -2755,23 +2803,21 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
     const unsigned long long stored_avail = (comp_bytes - 4 * groups) / static_cast<size_t>(w);
     if (n * static_cast<size_t>(w) < kScanDecoderBytes) {
         // one launch: the workgroups find their offsets with the encoder's scan (its state is at
-        // the front of the workspace, zero between calls)
+        // the front of the workspace)
         const size_t scan_tiles = tiles_for(n, w, kMinLoads);
-        const ScanState st = scan_state(d_ws, scan_tiles);
         const bool stream_values = stored_avail >= n / 4 * 3;
         const auto kernel = w == 4 ? (al ? decompress_scan_kernel<4, true> : decompress_scan_kernel<4, false>)
                                    : (al ? decompress_scan_kernel<2, true> : decompress_scan_kernel<2, false>);
         return hip_ok(launch(kernel, dim3(static_cast<unsigned>(scan_tiles)), dim3(kThreads), stream,
                              static_cast<const unsigned*>(d_comp), stream_values_at, stored_avail, n,
-                             static_cast<unsigned char*>(d_out), st.hdr, st.counts, st.prefixes,
-                             static_cast<unsigned>(scan_tiles), scan_state_bytes(scan_tiles), groups,
-                             stream_values));
+                             static_cast<unsigned char*>(d_out), static_cast<WsHeader*>(d_ws),
+                             static_cast<unsigned>(scan_tiles), groups, stream_values));
     }
     const size_t chunks = div_up(groups, kChunkMasks);
     if (chunks > 0xFFFFFFFFull) return ZVC_E_ARG;
     // The pre-pass arrays need no reset.  They sit at the end of the workspace, whatever its
     // size: an encoder call that this workspace is large enough for keeps its scan state
-    // (which must stay zero between calls) below them, whichever call came first.
+    // (whose words the next call relies on) below them, whichever call came first.
     unsigned char* area = static_cast<unsigned char*>(d_ws) + (ws - decoder_area_bytes(chunks)) / 256 * 256;
     unsigned long long* chunk_prefix =
         chunks <= kFewChunks ? nullptr : reinterpret_cast<unsigned long long*>(area);
