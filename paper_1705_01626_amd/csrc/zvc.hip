@@ -63,10 +63,10 @@ struct Geometry {
     static constexpr int kElemsPerLane = 16 / W;                 // per 16-byte store: 4 | 8
     static constexpr int kLanesPerGroup = 32 / kElemsPerLane;    // lanes covering one mask: 8 | 4
     static constexpr int kGroupsPerLoad = kWaveSize / kLanesPerGroup;  // masks per KB of output: 8 | 16
-    // per-wave LDS staging buffer: kStageLoads wave-loads plus alignment slack
+    // per-wave LDS staging buffer: kStageLoads wave-loads, 16 bytes so that the slice can mirror the
+    // run's alignment, and up to 31 elements that a shifted piece stages without writing them
     static constexpr int kStageSteps = LOADS / kStageLoads;
-    // (16 bytes so the slice can mirror the destination's alignment)
-    static constexpr int kWaveStageBytes = kStageLoads * kWaveSize * 16 + 16;
+    static constexpr int kWaveStageBytes = kStageLoads * kWaveSize * 16 + 16 + 32 * W;
     // decompress_kernel: zeros, the waves' slices, a sum per wave
     static constexpr unsigned kDecodeLdsBytes = 16 + kWaves * kWaveStageBytes + 4 * kWaves;
     static_assert(LOADS % kStageLoads == 0, "tile is staged in whole steps");
@@ -1409,28 +1409,20 @@ __global__ __launch_bounds__(kThreads) void mask_prefix_kernel(
     if (tid == 0) hdr->finish_top.value = 0u;
 }
 
-// 4 KB of output by one wave: every lane rebuilds 16 bytes per store (expand_lane).
-// Lane i holds mask i of the 32 (64) and the offset in `lds` of its first stored
-// element; of the output only elements 0 .. left - 1 are the tensor's (`left` is the
-// same in all lanes).  `lds` begins with 16 bytes that belong to nothing else.
-template <int W, bool ALIGNED>
-__device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, unsigned mask_at, unsigned left,
-                                             unsigned char* __restrict__ to, int lane) {
-    using G = Geometry<W, kMinLoads>;
-    constexpr int E = G::kElemsPerLane;
-    constexpr int LPG = G::kLanesPerGroup;
-    // (every wave writes the zeros itself: LDS operations of one wave execute in order)
-    if (lane == 0) *reinterpret_cast<uint4*>(lds) = make_uint4(0u, 0u, 0u, 0u);
-    wave_lds_sync();
-    const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E, lower = (1u << bit0) - 1u;
+// How an output is written.  kAligned: 16 bytes a lane from a 16-byte boundary on.  kLoose: the same from
+// any element.  kShifted: pieces begin with a line of the output, see PieceShift.
+enum class Output { kAligned, kLoose, kShifted };
+
+// 4 KB of output by one wave: 16 bytes per lane and store, which `piece(jj)` rebuilds for the jj-th
+// store.  Of the output only elements 0 .. left - 1 are the tensor's (`left` is the same in all lanes).
+template <int W, bool ALIGNED, class Piece>
+__device__ __forceinline__ void store_piece(const Piece& piece, unsigned left, unsigned char* __restrict__ to, int lane) {
+    constexpr int E = Geometry<W, kMinLoads>::kElemsPerLane;
     const bool whole = left >= kStageLoads * kWaveSize * E;             // uniform
     uint4 v[kStageLoads];
 #pragma unroll
     for (int jj = 0; jj < kStageLoads; ++jj) {
-        const int from = 4 * (jj * G::kGroupsPerLoad + lane / LPG);     // the lane's mask
-        const unsigned gm = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask)));
-        const unsigned at = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask_at)));
-        v[jj] = expand_lane<W>(lds, at + W * static_cast<unsigned>(__popc(gm & lower)), gm >> bit0);
+        v[jj] = piece(jj);
         if (__builtin_expect(whole, 1)) {
             if (ALIGNED) store16_stream(to + (jj * kWaveSize + lane) * 16, v[jj]);
             else store16_loose<W>(to + (jj * kWaveSize + lane) * 16, v[jj]);
@@ -1459,6 +1451,84 @@ __device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, 
     }
 }
 
+// A piece that begins with a mask's first bit: lane i holds mask i of the 32 (64) and the offset in `lds`
+// of its first stored element.  `lds` begins with 16 bytes that belong to nothing else.
+template <int W, bool ALIGNED>
+__device__ __forceinline__ void expand_piece(unsigned char* lds, unsigned mask, unsigned mask_at, unsigned left,
+                                             unsigned char* __restrict__ to, int lane) {
+    using G = Geometry<W, kMinLoads>;
+    constexpr int LPG = G::kLanesPerGroup;
+    // (every wave writes the zeros itself: LDS operations of one wave execute in order)
+    if (lane == 0) *reinterpret_cast<uint4*>(lds) = make_uint4(0u, 0u, 0u, 0u);
+    wave_lds_sync();
+    const unsigned bit0 = static_cast<unsigned>(lane % LPG) * G::kElemsPerLane, lower = (1u << bit0) - 1u;
+    const auto piece = [&](int jj) __attribute__((always_inline)) -> uint4 {
+        const int from = 4 * (jj * G::kGroupsPerLoad + lane / LPG);     // the lane's mask
+        const unsigned gm = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask)));
+        const unsigned at = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask_at)));
+        return expand_lane<W>(lds, at + W * static_cast<unsigned>(__popc(gm & lower)), gm >> bit0);
+    };
+    store_piece<W, ALIGNED>(piece, left, to, lane);
+}
+
+// The same for a piece that begins with bit `bits` of lane 0's mask.  Lane i holds mask i of the piece and,
+// in `next`, the one behind; the stored elements of all masks follow each other in `lds`.  `to` is the
+// beginning of a line.
+template <int W>
+__device__ __forceinline__ void expand_shifted_piece(unsigned char* lds, unsigned mask, unsigned mask_at, unsigned next,
+                                                     unsigned bits, unsigned left, unsigned char* __restrict__ to, int lane) {
+    using G = Geometry<W, kMinLoads>;
+    constexpr int E = G::kElemsPerLane;
+    constexpr int LPG = G::kLanesPerGroup;
+    if (lane == 0) *reinterpret_cast<uint4*>(lds) = make_uint4(0u, 0u, 0u, 0u);
+    wave_lds_sync();
+    // the lane's elements begin with bit `bit0` of its mask and the next, taken as one word of 64 bits
+    const unsigned bit0 = static_cast<unsigned>(lane % LPG) * E + bits;              // below 64 - E
+    const unsigned long long lower = (1ull << bit0) - 1ull;
+    const unsigned lower_mask = static_cast<unsigned>(lower), lower_next = static_cast<unsigned>(lower >> 32);
+    const auto piece = [&](int jj) __attribute__((always_inline)) -> uint4 {
+        const int from = 4 * (jj * G::kGroupsPerLoad + lane / LPG);
+        const unsigned gm = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask)));
+        const unsigned gn = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(next)));
+        const unsigned at = static_cast<unsigned>(__builtin_amdgcn_ds_bpermute(from, static_cast<int>(mask_at)));
+        const unsigned before = static_cast<unsigned>(__popc(gm & lower_mask)) + static_cast<unsigned>(__popc(gn & lower_next));
+        const unsigned long long both = static_cast<unsigned long long>(gn) << 32 | gm;
+        return expand_lane<W>(lds, at + W * before, static_cast<unsigned>(both >> bit0));
+    };
+    store_piece<W, true>(piece, left, to, lane);
+}
+
+// `total` stored elements from element `first` of the value area on into LDS, by one wave, with aligned
+// 16-byte loads; what lies past values_avail elements reads as zero.  `lds` + `slice` is 16-byte aligned;
+// the run begins `shift` bytes behind it.  In two parts, so that the caller has something to do meanwhile.
+template <int W>
+struct StagedRun {
+    unsigned shift, valid, wanted;         // bytes
+    __device__ __forceinline__ StagedRun(unsigned char* at, const unsigned char* __restrict__ values,
+                                         unsigned long long values_avail, unsigned long long first, unsigned total,
+                                         bool stream_values, int lane) {
+        const unsigned char* src = values + first * W;
+        shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
+        unsigned long long readable = values_avail > first ? values_avail - first : 0ull;
+        if (readable > total) readable = total;
+        wanted = total * W;
+        valid = static_cast<unsigned>(readable) * W;
+        const unsigned end = valid != 0u ? shift + valid : 0u;
+        if (stream_values) wave_stage<true>(at, src - shift, end, lane);
+        else wave_stage<false>(at, src - shift, end, lane);
+    }
+    __device__ __forceinline__ void wait(unsigned char* at, int lane) const {
+        stage_wait();
+        if (__builtin_expect(valid < wanted, 0)) {           // the stream is cut short
+            wave_lds_sync();
+            for (unsigned i = shift + valid + W * lane; i < shift + wanted; i += W * kWaveSize) {
+                if (W == 4) *reinterpret_cast<unsigned*>(at + i) = 0u;
+                else *reinterpret_cast<unsigned short*>(at + i) = 0;
+            }
+        }
+    }
+};
+
 // One step of the decoder, by one wave: 4 KB of output from `m` (lane i holds
 // the step's mask i, bits past n cleared) and the step's `step_total` stored
 // elements, which begin at element `first` of the value area.  Stages them in
@@ -1473,33 +1543,105 @@ __device__ __forceinline__ void expand_step(unsigned char* lds, unsigned slice, 
     using G = Geometry<W, kMinLoads>;
     constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // 32 | 64 masks per step
     constexpr unsigned kStepElems = kStageLoads * kWaveSize * G::kElemsPerLane;
-    const unsigned char* src = values + first * W;
-    const unsigned shift = static_cast<unsigned>(reinterpret_cast<uintptr_t>(src) & 15u);
-    unsigned long long readable = values_avail > first ? values_avail - first : 0ull;
-    if (readable > step_total) readable = step_total;
-    const unsigned valid = static_cast<unsigned>(readable) * W;
-    const unsigned end = valid != 0u ? shift + valid : 0u;
-    if (stream_values) wave_stage<true>(lds + slice, src - shift, end, lane);
-    else wave_stage<false>(lds + slice, src - shift, end, lane);
+    const StagedRun<W> run(lds + slice, values, values_avail, first, step_total, stream_values, lane);
     // stored elements of the step before each of its masks, while the loads are under way
     const unsigned cnt = static_cast<unsigned>(__popc(m));
-    const unsigned mask_at = slice + shift + W * (wave_scan_small<kStepMasks>(cnt) - cnt);
-    stage_wait();
-    if (__builtin_expect(valid < step_total * W, 0)) {           // the stream is cut short
-        wave_lds_sync();
-        for (unsigned i = shift + valid + W * lane; i < shift + step_total * W; i += W * kWaveSize) {
-            if (W == 4) *reinterpret_cast<unsigned*>(lds + slice + i) = 0u;
-            else *reinterpret_cast<unsigned short*>(lds + slice + i) = 0;
-        }
-    }
+    const unsigned mask_at = slice + run.shift + W * (wave_scan_small<kStepMasks>(cnt) - cnt);
+    run.wait(lds + slice, lane);
     const unsigned left = n - wave_elem0 < kStepElems ? static_cast<unsigned>(n - wave_elem0) : kStepElems;
     expand_piece<W, ALIGNED>(lds, m, mask_at, left, out + wave_elem0 * W, lane);
+}
+
+// Outputs that do not begin with a 128-byte line.  A wave that writes from a group's beginning on then
+// shares the lines at both ends of each of its stores with other stores, and where the output is not
+// 16-byte aligned every store is split as well.  So a wave's piece begins SHIFT elements later, SHIFT the
+// elements up to the first line: its masks then begin with bit SHIFT mod 32 and end in the mask behind,
+// and the first wave writes the SHIFT elements before the first piece.  us, stores that follow the
+// output's alignment | shifted, at an odd element: fp16 52 MB 19.3 | 17.6 (aligned: 16.6); fp32 100 MB 32.9 | 25.9,
+// 300 MB 80.8 | 74.9 (71.4), 784 MB 238 | 206, of density 0.05 201 | 136.  planar_output() says which are shifted.
+constexpr unsigned kLineBytes = 128;
+template <int W>
+struct PieceShift {
+    using G = Geometry<W, kMinLoads>;
+    static constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;       // 32 | 64
+    unsigned elements, groups, bits;                 // bits: of the first mask that belong to the piece before
+    __device__ explicit PieceShift(const unsigned char* out) {
+        elements = static_cast<unsigned>(-reinterpret_cast<uintptr_t>(out) % kLineBytes) / W;
+        groups = elements / 32u;                     // 0 | 0 or 1
+        bits = elements % 32u;
+    }
+};
+// Lane i's masks for a shifted piece that begins with mask g0 before the shift: mask g0 + i, the mask that
+// the piece has there, and the one behind that.  `masks_of(g)`: mask g, 0 past the tensor's end.
+template <int W, class MasksOf>
+struct ShiftedMasks {
+    unsigned own, mask, next;
+    __device__ __forceinline__ ShiftedMasks(const PieceShift<W>& shift, size_t g0, int lane, const MasksOf& masks_of) {
+        own = masks_of(g0 + lane);
+        next = masks_of(g0 + 1 + lane);
+        mask = own;
+        if (W == 2 && shift.groups != 0) {           // uniform
+            mask = next;
+            next = masks_of(g0 + 2 + lane);
+        }
+    }
+};
+
+// expand_step for a shifted piece: `first` is the stored element that the piece's first mask begins
+// with (its bits before the piece included).
+template <int W>
+__device__ __forceinline__ void expand_shifted_step(unsigned char* lds, unsigned slice,
+                                                    const unsigned char* __restrict__ values,
+                                                    unsigned long long values_avail, unsigned long long first,
+                                                    unsigned mask, unsigned next, const PieceShift<W>& shift,
+                                                    size_t elem0, size_t n, unsigned char* __restrict__ out,
+                                                    bool stream_values, int lane) {
+    using G = Geometry<W, kMinLoads>;
+    constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;
+    constexpr unsigned kStepElems = kStageLoads * kWaveSize * G::kElemsPerLane;
+    const unsigned cnt = lane < kStepMasks ? static_cast<unsigned>(__popc(mask)) : 0u;
+    const unsigned upto = wave_scan_small<kStepMasks>(cnt);
+    const unsigned total = lane_value(upto, kStepMasks - 1) +
+                           static_cast<unsigned>(__popc(lane_value(next, kStepMasks - 1) & ((1u << shift.bits) - 1u)));
+    const StagedRun<W> run(lds + slice, values, values_avail, first, total, stream_values, lane);
+    const unsigned left = n - elem0 < kStepElems ? static_cast<unsigned>(n - elem0) : kStepElems;
+    run.wait(lds + slice, lane);
+    expand_shifted_piece<W>(lds, mask, slice + run.shift + W * (upto - cnt), next, shift.bits, left, out + elem0 * W, lane);
+}
+
+// The elements before the first piece, by the first wave: a lane each.
+template <int W>
+__device__ inline void expand_head(const unsigned char* __restrict__ values, unsigned long long values_avail, unsigned mask0,
+                                   unsigned mask1, unsigned count, unsigned char* __restrict__ out, int lane) {
+    if (static_cast<unsigned>(lane) >= count) return;
+    const unsigned mask = lane < 32 ? mask0 : mask1, bit = static_cast<unsigned>(lane) % 32u;
+    const unsigned at = (lane < 32 ? 0u : static_cast<unsigned>(__popc(mask0))) +
+                        static_cast<unsigned>(__popc(mask & ((1u << bit) - 1u)));
+    const bool stored = (mask >> bit & 1u) != 0u && at < values_avail;
+    if (W == 4) reinterpret_cast<unsigned*>(out)[lane] = stored ? reinterpret_cast<const unsigned*>(values)[at] : 0u;
+    else reinterpret_cast<unsigned short*>(out)[lane] = stored ? reinterpret_cast<const unsigned short*>(values)[at] : 0;
+}
+
+// A wave's part of a shifted output: its piece and, for the first wave, what lies before it.  `first` is the
+// first stored element of the part before the shift, whose masks are `own`.
+template <int W>
+__device__ __forceinline__ void expand_shifted(unsigned char* lds, unsigned slice, const unsigned char* __restrict__ values,
+                                               unsigned long long values_avail, unsigned long long first, unsigned own,
+                                               unsigned mask, unsigned next, const PieceShift<W>& shift, size_t elem0, size_t n,
+                                               unsigned char* __restrict__ out, bool stream_values, int lane) {
+    if (elem0 == 0 && shift.elements != 0)
+        expand_head<W>(values, values_avail, lane_value(own, 0), lane_value(own, 1),
+                       shift.elements < n ? shift.elements : static_cast<unsigned>(n), out, lane);
+    if (elem0 + shift.elements >= n) return;
+    if (W == 2 && shift.groups != 0) first += static_cast<unsigned>(__popc(lane_value(own, 0)));
+    expand_shifted_step<W>(lds, slice, values, values_avail, first, mask, next, shift, elem0 + shift.elements, n, out,
+                           stream_values, lane);
 }
 
 // Section 5.2 decoder.  Every wave works on its own: it expands one step, 4 KB
 // of output, and knows from the pre-pass where the step's stored elements begin
 // and end (expand_step does the rest).
-template <int W, int LOADS, bool ALIGNED>
+template <int W, int LOADS, Output OUTPUT>
 __global__ __launch_bounds__(kThreads) void decompress_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out,
@@ -1548,16 +1690,28 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     }
     // ---- the step's masks and where it begins and ends within its chunk, on their way meanwhile
     static_assert(kSteps == 1, "a wave expands one step");
-    unsigned m = 0, step_begin = 0, step_end = 0;
+    unsigned m = 0, next = 0, own = 0, step_begin = 0, step_end = 0;
+    const PieceShift<W> shift(out);
     if (wave_elem0 < n) {
-        const unsigned here = num_groups - wave_group0 < kStepMasks ? static_cast<unsigned>(num_groups - wave_group0) : kStepMasks;
-        if (static_cast<unsigned>(lane) < here) {
-            m = masks[wave_group0 + lane];
-            if (tail != 0 && wave_group0 + lane == num_groups - 1) m &= (1u << tail) - 1u;   // bits past n never count
+        const auto mask_of = [&](size_t g) -> unsigned {
+            unsigned v = 0;
+            if (g < num_groups) {
+                v = masks[g];
+                if (tail != 0 && g == num_groups - 1) v &= (1u << tail) - 1u;   // bits past n never count
+            }
+            return v;
+        };
+        if constexpr (OUTPUT != Output::kShifted) {
+            if (lane < kStepMasks) m = mask_of(wave_group0 + lane);
+        } else {
+            const ShiftedMasks<W, decltype(mask_of)> got(shift, wave_group0, lane, mask_of);
+            m = got.mask;
+            next = got.next;
+            own = got.own;
         }
         const size_t u = wave_group0 / kUnitMasks;
         step_begin = u % kChunkUnits != 0 ? unit_end[u - 1] : 0u;
-        step_end = unit_end[u + kStepUnits - 1];
+        if (OUTPUT != Output::kShifted) step_end = unit_end[u + kStepUnits - 1];
     }
 
     // ---- stored elements before the wave's chunk: the sum (below 2^27), or from the pre-pass
@@ -1576,8 +1730,13 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     if (wave_elem0 >= n) return;                  // nothing of the tensor in this wave's part
     if (chunk_prefix != nullptr) before_chunk = chunk_prefix[chunk];
 
-    expand_step<W, ALIGNED>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, before_chunk + step_begin,
-                            step_end - step_begin, m, wave_elem0, n, out, stream_values, lane);
+    if constexpr (OUTPUT != Output::kShifted) {
+        expand_step<W, OUTPUT == Output::kAligned>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, before_chunk + step_begin,
+                       step_end - step_begin, m, wave_elem0, n, out, stream_values, lane);
+    } else {
+        expand_shifted<W>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, before_chunk + step_begin, own, m,
+                          next, shift, wave_elem0, n, out, stream_values, lane);
+    }
 }
 
 // The same decoder in one launch, for small tensors: no pre-pass.  A workgroup
@@ -1610,7 +1769,7 @@ struct CountMaskTile {
     }
 };
 
-template <int W, bool ALIGNED>
+template <int W, Output OUTPUT>
 __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, WsHeader* hdr,
@@ -1635,17 +1794,27 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     const unsigned tail = static_cast<unsigned>(n % 32);
 
     // ---- the wave's masks (lane i holds mask i) and their set bits
-    unsigned m = 0;
-    {
-        const size_t g = wave_group0 + lane;
-        if (lane < kStepMasks && g < num_groups) {
-            m = masks[g];
-            if (g == num_groups - 1 && tail != 0) m &= (1u << tail) - 1u;   // bits past n never count
+    unsigned own = 0, m = 0, next = 0;
+    const PieceShift<W> shift(out);
+    const auto mask_of = [&](size_t g) -> unsigned {
+        unsigned v = 0;
+        if (g < num_groups) {
+            v = masks[g];
+            if (tail != 0 && g == num_groups - 1) v &= (1u << tail) - 1u;   // bits past n never count
         }
+        return v;
+    };
+    if constexpr (OUTPUT != Output::kShifted) {
+        if (lane < kStepMasks) own = mask_of(wave_group0 + lane);
+    } else {
+        const ShiftedMasks<W, decltype(mask_of)> got(shift, wave_group0, lane, mask_of);
+        own = got.own;
+        m = got.mask;
+        next = got.next;
     }
     const unsigned long long scan_word = ScanState::ask(hdr);
     lds_barrier();                                // the cleared arrival word, after the loads have been issued
-    const unsigned wave_total = wave_sum_small(__popc(m));
+    const unsigned wave_total = wave_sum_small(lane < kStepMasks ? static_cast<unsigned>(__popc(own)) : 0u);
 
     // ---- the workgroup's count, published by the wave that arrives last; the scan, by wave 0
     const ScanState scan(hdr, num_tiles, scan_word);
@@ -1679,9 +1848,14 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     }
     if (wave == 0 && lane == 0 && scan.ends_block(tile)) scan.publish_prefix(tile, exclusive + tile_total);
 
-    if (wave_elem0 < n)
-        expand_step<W, ALIGNED>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset,
-                                wave_total, m, wave_elem0, n, out, stream_values, lane);
+    if (wave_elem0 < n) {
+        if constexpr (OUTPUT != Output::kShifted)
+            expand_step<W, OUTPUT == Output::kAligned>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset,
+                           wave_total, own, wave_elem0, n, out, stream_values, lane);
+        else
+            expand_shifted<W>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset, own,
+                              m, next, shift, wave_elem0, n, out, stream_values, lane);
+    }
 
     if (tile == num_tiles - 1 && wave == 0) scan_end(scan, num_tiles, lane);
 }
@@ -2300,7 +2474,7 @@ constexpr size_t kScanDecoderBytes = size_t{16} << 20;
 // Tensors below this size never decode in the interleaved order (no gain there).
 inline bool interleaves(size_t n, int w) { return n * static_cast<size_t>(w) >= (size_t{64} << 20); }
 
-template <int W, int LOADS, bool ALIGNED>
+template <int W, int LOADS, Output OUTPUT>
 hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* masks,
                           const unsigned char* values, unsigned long long avail, size_t n,
                           unsigned char* out, const unsigned* unit_end,
@@ -2330,7 +2504,7 @@ hipError_t launch_decompress_as(dim3 grid, hipStream_t stream, const unsigned* m
     // there are few waves, loses with any (14.9 | 15.0 | 15.9 | 15.5).
     const bool seven = interleaves(n, W) && avail > n / (n * W >= (size_t{600} << 20) ? 6 : 4);
     const unsigned lds_pad = seven ? seven_per_cu(Geometry<W, LOADS>::kDecodeLdsBytes) : 0;
-    return launch_padded(decompress_kernel<W, LOADS, ALIGNED>, lds_pad, grid, dim3(kThreads), stream,
+    return launch_padded(decompress_kernel<W, LOADS, OUTPUT>, lds_pad, grid, dim3(kThreads), stream,
                          masks, values, avail, n, out, unit_end, chunk_prefix, chunk_total, groups, stream_values,
                          interleave);
 }
@@ -2410,15 +2584,27 @@ hipError_t launch_compress(int w, TileShape shape, bool split, bool early, Args.
 }
 
 // The decoder has one tile size (its waves are independent; one staging step per
-// wave measures best at every size) and a path for outputs that are not
-// 16-byte aligned.
+// wave measures best at every size).
 template <typename... Args>
-hipError_t launch_decompress(int w, bool aligned, Args... args) {
-    if (!aligned)
-        return w == 4 ? launch_decompress_as<4, kMinLoads, false>(args...)
-                      : launch_decompress_as<2, kMinLoads, false>(args...);
-    return w == 4 ? launch_decompress_as<4, kMinLoads, true>(args...)
-                  : launch_decompress_as<2, kMinLoads, true>(args...);
+hipError_t launch_decompress(int w, Output output, Args... args) {
+    if (output == Output::kShifted)
+        return w == 4 ? launch_decompress_as<4, kMinLoads, Output::kShifted>(args...)
+                      : launch_decompress_as<2, kMinLoads, Output::kShifted>(args...);
+    return w == 4 ? launch_decompress_as<4, kMinLoads, Output::kAligned>(args...)
+                  : launch_decompress_as<2, kMinLoads, Output::kAligned>(args...);
+}
+
+// How a planar decoder writes its output (us, as the output lies | shifted, density 0.3 where not stated).
+// Two launches: a store that begins in the middle of a line costs 5 to 30 %, but in 64-byte steps only
+// the largest fp32 outputs gain, 300 MB 74.0 | 73.1, 784 MB at 0.5 209.7 | 203.9, while 20 MB take 9.7 | 9.9, bf16
+// 400 MB 100.4 | 102.8.  16-byte steps: fp32 20 MB at 0.5 10.5 | 9.7, 300 MB 80.7 | 73.0; bf16 20 MB 10.8 | 10.1.
+// One launch: from 16-byte steps on as they lie (13 MB fp32 7.23 | 7.34, bf16 7.5 | 7.8), and below 8 MB in any case,
+// where the shifted pieces' longer chain counts more (odd elements, fp32 0.25 MB 4.2 | 4.4, 4 MB 5.4 | 5.6, 9 MB
+// 7.0 | 6.8, 13 MB 8.3 | 7.5; bf16 0.25 MB 4.4 | 4.7, 4 MB 5.7 | 5.9, 9 MB 7.5 | 7.3, 13 MB 8.8 | 7.8).
+inline Output planar_output(const void* out, size_t bytes, int w, bool one_launch) {
+    const size_t step = one_launch ? 16 : w == 4 && bytes >= (size_t{256} << 20) ? 128 : 64;
+    return aligned_to(out, step) ? Output::kAligned
+         : one_launch && bytes < (size_t{8} << 20) ? Output::kLoose : Output::kShifted;
 }
 
 // `bounded`: out_cap may be anything from the size of the mask area up; the
@@ -2794,20 +2980,23 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
     if (ranges_overlap(d_comp, comp_bytes, d_out, n * static_cast<size_t>(w))) return ZVC_E_ARG;
     if (zvc_status st = check_workspace(d_ws, ws, n, w)) return st;
     if (n == 0) return ZVC_OK;
-    const bool al = aligned_to(d_out, 16);
+    const bool small = n * static_cast<size_t>(w) < kScanDecoderBytes;
+    const Output output = planar_output(d_out, n * static_cast<size_t>(w), w, small);
     // a multiple of 8 workgroups: the interleaved order deals the parts out in rounds of 8
     const size_t tiles = div_up(tiles_for(n, w, kMinLoads), 8) * 8;
     if (tiles > 0x7FFFFFFFull) return ZVC_E_ARG;
     const size_t groups = div_up(n, 32);
     const unsigned char* stream_values_at = static_cast<const unsigned char*>(d_comp) + 4 * groups;
     const unsigned long long stored_avail = (comp_bytes - 4 * groups) / static_cast<size_t>(w);
-    if (n * static_cast<size_t>(w) < kScanDecoderBytes) {
+    if (small) {
         // one launch: the workgroups find their offsets with the encoder's scan (its state is at
         // the front of the workspace)
         const size_t scan_tiles = tiles_for(n, w, kMinLoads);
         const bool stream_values = stored_avail >= n / 4 * 3;
-        const auto kernel = w == 4 ? (al ? decompress_scan_kernel<4, true> : decompress_scan_kernel<4, false>)
-                                   : (al ? decompress_scan_kernel<2, true> : decompress_scan_kernel<2, false>);
+        const auto kernel =
+            output == Output::kAligned ? (w == 4 ? decompress_scan_kernel<4, Output::kAligned> : decompress_scan_kernel<2, Output::kAligned>)
+            : output == Output::kLoose ? (w == 4 ? decompress_scan_kernel<4, Output::kLoose> : decompress_scan_kernel<2, Output::kLoose>)
+                                       : (w == 4 ? decompress_scan_kernel<4, Output::kShifted> : decompress_scan_kernel<2, Output::kShifted>);
         return hip_ok(launch(kernel, dim3(static_cast<unsigned>(scan_tiles)), dim3(kThreads), stream,
                              static_cast<const unsigned*>(d_comp), stream_values_at, stored_avail, n,
                              static_cast<unsigned char*>(d_out), static_cast<WsHeader*>(d_ws),
@@ -2830,7 +3019,7 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
         return ZVC_E_HIP;
     const unsigned char* values = static_cast<const unsigned char*>(d_comp) + 4 * groups;
     const unsigned long long avail = (comp_bytes - 4 * groups) / static_cast<size_t>(w);
-    return hip_ok(launch_decompress(w, al, dim3(static_cast<unsigned>(tiles)), stream, masks, values, avail, n,
+    return hip_ok(launch_decompress(w, output, dim3(static_cast<unsigned>(tiles)), stream, masks, values, avail, n,
                                     static_cast<unsigned char*>(d_out), unit_end, chunk_prefix, chunk_total,
                                     groups));
 }
