@@ -599,9 +599,10 @@ struct ScanState {
 // Called by one whole wave of the tile, when the tile's own zero tests are done
 // (asking for the prefixes earlier, while the tile's loads are under way, saves
 // a round trip but finds a prefix further back, and the extra counts to read
-// cost more than the round trip).  PAUSE: see below.  Returns the number of kept elements in all
+// cost more than the round trip).  PAUSE: see there.  Returns the number of kept elements in all
 // tiles before `tile` (not 0).
-template <bool PAUSE, class CountTile>
+constexpr int kNoPause = -1, kDecoderPause = 14;
+template <int PAUSE, class CountTile>
 __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, unsigned tile, int lane,
                                                            const CountTile& count_tile) {
     const int t = static_cast<int>(tile);
@@ -609,12 +610,16 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
     int bb = (t >> st.block_shift) - 1;
     unsigned long long base = 0;
     int lo = 0;
-    // With PAUSE nothing is asked for one round trip to memory (patience is needed below): a line of counts that many
-    // tiles read while others still write it costs all of them more (us, at once | a round trip later | 0.3
-    // us asleep: fp32 6.4 MB 6.1 | 5.8 | 6.1, 64 MB 20.4 | 17.3 | 19.5, 300 MB 73.8 | 70.7 | 73.6; decoding
-    // 6.4 MB 6.2 | 5.5 | 5.5; waiting for the tile in front first, alone: 6.9, 21.3, 75.8; 6.7).
+    // Nothing is asked for one round trip to memory (patience is needed below) and PAUSE sleeps of 64 clocks, or
+    // at once with kNoPause: a line of counts that many tiles read while others still write it costs all
+    // of them more.  us, encoding, at once | a round trip later | 0.3 us asleep: fp32 6.4 MB 6.1 | 5.8 | 6.1, 64 MB
+    // 20.4 | 17.3 | 19.5, 300 MB 73.8 | 70.7 | 73.6 (waiting for the tile in front first, alone: 6.9, 21.3, 75.8); with 8
+    // sleeps more 6.4 MB 5.8 | 5.8, 12 MB 7.1 | 7.2.  Decoding, whose workgroups have their counts all at the same time, a round trip |
+    // and 8 | 12 | 16 | 24 sleeps: fp32 6.4 MB 5.7 | 4.85 | 4.9 | 4.9 | 5.1, 16 MB 7.0 | 6.55 | 6.05 | 6.1 | 6.3, 24 MB 9.3 |
+    // 8.2 | 7.9 | 7.7 | 7.9; bf16 6 MB 5.9 | 5.1 | 5.0 | 5.05 | 5.3.
     unsigned long long patience_word = 0;
-    if (PAUSE) patience_word = uniform(load64(&st.hdr->patience_plus_one));
+    if (PAUSE != kNoPause) patience_word = uniform(load64(&st.hdr->patience_plus_one));
+    if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
     while (bb >= 0) {
         const int idx = bb - lane;
         unsigned long long pv = 0;
@@ -666,7 +671,7 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
         }
         done_to += complete * kLoadTiles;
         if (hole < 0) continue;                   // the whole batch was there: the next one, if any
-        if (!PAUSE && polls == 0) patience_word = uniform(load64(&st.hdr->patience_plus_one));
+        if (PAUSE == kNoPause && polls == 0) patience_word = uniform(load64(&st.hdr->patience_plus_one));
         const unsigned patience = patience_word != 0 ? static_cast<unsigned>(patience_word - 1) : kDefaultPatience;
         if (polls < patience) {
             ++polls;
@@ -1185,7 +1190,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
             const CountInputTile<W, CH, WV, RELU, SPLIT> count_tile{a.in, a.n};
             // (the smallest windowed tile has been staging its steps since it published its count: 1 MB fp32 4.92
             // us, with the pause 5.00; 30 MB 16-bit 14.15 | 14.23)
-            ex = scan_exclusive_prefix<!(WINDOWED && CH == 16)>(scan, tile, lane, count_tile);
+            ex = scan_exclusive_prefix<WINDOWED && CH == 16 ? kNoPause : 0>(scan, tile, lane, count_tile);
         }
         if (lane == 0) s_prefix = ex;
     }
@@ -1638,6 +1643,18 @@ __device__ __forceinline__ void expand_shifted(unsigned char* lds, unsigned slic
                            stream_values, lane);
 }
 
+// Mask g of the tensor: none past its end, and bits past n never count (tail = n % 32).
+__device__ __forceinline__ auto masks_within(const unsigned* __restrict__ masks, size_t num_groups, unsigned tail) {
+    return [=](size_t g) __attribute__((always_inline)) -> unsigned {
+        unsigned v = 0;
+        if (g < num_groups) {
+            v = masks[g];
+            if (tail != 0 && g == num_groups - 1) v &= (1u << tail) - 1u;
+        }
+        return v;
+    };
+}
+
 // Section 5.2 decoder.  Every wave works on its own: it expands one step, 4 KB
 // of output, and knows from the pre-pass where the step's stored elements begin
 // and end (expand_step does the rest).
@@ -1693,14 +1710,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
     unsigned m = 0, next = 0, own = 0, step_begin = 0, step_end = 0;
     const PieceShift<W> shift(out);
     if (wave_elem0 < n) {
-        const auto mask_of = [&](size_t g) -> unsigned {
-            unsigned v = 0;
-            if (g < num_groups) {
-                v = masks[g];
-                if (tail != 0 && g == num_groups - 1) v &= (1u << tail) - 1u;   // bits past n never count
-            }
-            return v;
-        };
+        const auto mask_of = masks_within(masks, num_groups, tail);
         if constexpr (OUTPUT != Output::kShifted) {
             if (lane < kStepMasks) m = mask_of(wave_group0 + lane);
         } else {
@@ -1740,10 +1750,10 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
 }
 
 // The same decoder in one launch, for small tensors: no pre-pass.  A workgroup
-// expands 16 KB of output, in stream order.  Where its stored elements begin is
+// expands 16 or 32 KB of output, in stream order.  Where its stored elements begin is
 // the number of set bits in all masks before its own, which it gets the way the
-// encoder's tiles get their offsets: it publishes the popcount of its own 128
-// (256) masks and runs the device-wide scan over the workgroups before it
+// encoder's tiles get their offsets: it publishes the popcount of its own
+// masks and runs the device-wide scan over the workgroups before it
 // (scan_exclusive_prefix; same scan state in the workspace, same clean-up by the
 // last workgroup, same self-help if a predecessor has not been dispatched).  A
 // workgroup knows its count after one small load, so the scan's chain is short;
@@ -1769,8 +1779,8 @@ struct CountMaskTile {
     }
 };
 
-template <int W, Output OUTPUT>
-__global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
+template <int W, Output OUTPUT, int WV>
+__global__ __launch_bounds__(WV * kWaveSize) void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, WsHeader* hdr,
     unsigned num_tiles, size_t num_groups, bool stream_values) {
@@ -1779,8 +1789,8 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // masks per wave: 32 | 64
     static_assert(G::kStageSteps == 1, "a wave expands one step");
 
-    __shared__ __align__(16) unsigned char s_stage[16 + kWaves * G::kWaveStageBytes];   // (16: see expand_piece)
-    __shared__ unsigned s_wave_total[kWaves];
+    __shared__ __align__(16) unsigned char s_stage[16 + WV * G::kWaveStageBytes];   // (16: see expand_piece)
+    __shared__ unsigned s_wave_total[WV];
     __shared__ unsigned s_arrive;                 // waves arrived << 24 | set bits so far
     __shared__ unsigned long long s_prefix;
 
@@ -1789,21 +1799,14 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     const int wave = static_cast<int>(uniform(static_cast<unsigned>(tid / kWaveSize)));
     const unsigned tile = blockIdx.x;
     if (tid == 0) s_arrive = 0u;
-    const size_t wave_elem0 = (static_cast<size_t>(tile) * kWaves + wave) * (static_cast<size_t>(kMinLoads) * kWaveSize * E);
+    const size_t wave_elem0 = (static_cast<size_t>(tile) * WV + wave) * (static_cast<size_t>(kMinLoads) * kWaveSize * E);
     const size_t wave_group0 = wave_elem0 / 32;
     const unsigned tail = static_cast<unsigned>(n % 32);
 
     // ---- the wave's masks (lane i holds mask i) and their set bits
     unsigned own = 0, m = 0, next = 0;
     const PieceShift<W> shift(out);
-    const auto mask_of = [&](size_t g) -> unsigned {
-        unsigned v = 0;
-        if (g < num_groups) {
-            v = masks[g];
-            if (tail != 0 && g == num_groups - 1) v &= (1u << tail) - 1u;   // bits past n never count
-        }
-        return v;
-    };
+    const auto mask_of = masks_within(masks, num_groups, tail);
     if constexpr (OUTPUT != Output::kShifted) {
         if (lane < kStepMasks) own = mask_of(wave_group0 + lane);
     } else {
@@ -1825,15 +1828,15 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
                                          __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     arrived = uniform(arrived);
-    const bool publisher = (arrived >> 24) == kWaves - 1;
+    const bool publisher = (arrived >> 24) == WV - 1;
     if (publisher && lane == 0)
         scan.publish(tile, (arrived & 0xFFFFFFu) + wave_total);
-    if (wave == kWaves - 1) scan.zero_what_is_left(tile, num_tiles, lane);
+    if (wave == WV - 1) scan.zero_what_is_left(tile, num_tiles, lane);
     if (wave == 0) {
         unsigned long long ex = 0;
         if (tile != 0) {
-            const CountMaskTile count_tile{masks, num_groups, tail, kWaves * kStepMasks};
-            ex = scan_exclusive_prefix<true>(scan, tile, lane, count_tile);
+            const CountMaskTile count_tile{masks, num_groups, tail, WV * kStepMasks};
+            ex = scan_exclusive_prefix<kDecoderPause>(scan, tile, lane, count_tile);
         }
         if (lane == 0) s_prefix = ex;
     }
@@ -1841,7 +1844,7 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     const unsigned long long exclusive = uniform(s_prefix);
     unsigned wave_offset = 0, tile_total = 0;
 #pragma unroll
-    for (int v = 0; v < kWaves; ++v) {
+    for (int v = 0; v < WV; ++v) {
         const unsigned t = uniform(s_wave_total[v]);
         if (v < wave) wave_offset += t;
         tile_total += t;
@@ -1858,6 +1861,70 @@ __global__ __launch_bounds__(kThreads) void decompress_scan_kernel(
     }
 
     if (tile == num_tiles - 1 && wave == 0) scan_end(scan, num_tiles, lane);
+}
+
+// And without any scan, for the smallest tensors: a workgroup counts the bits of all masks before its own
+// itself, 16 bytes a thread and eight of them on their way at a time.  That is one round trip to memory where the scan takes
+// three (count, wait, look), and it is work that grows with the square of the tensor.  Workgroups begin
+// at different places, so that they do not all ask the same channel of the L2 at a time (a cold 4 MB
+// stream 6.3 -> 5.9 us).  us, scan | here with 4 | 8 waves: fp32 0.25 MB 4.2 | 3.25 | 3.6, 1 MB 4.3 | 3.5 | 3.7, 2 MB 4.5 | 4.1 |
+// 4.0, 3 MB 4.55 | 4.7 | 4.5, 4 MB 4.65 | 5.2 | 4.65 (from memory 5.1 | 5.9 | 5.4); bf16 0.25 MB 4.4 | 3.45 | 3.8, 1 MB 4.45 | 4.1 |
+// 4.1, 2 MB 4.6 | 5.3 | 4.7.
+template <int W, Output OUTPUT, int WV>
+__global__ __launch_bounds__(WV * kWaveSize) void decompress_direct_kernel(
+    const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
+    unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, size_t num_groups, bool stream_values) {
+    static_assert(OUTPUT != Output::kShifted, "small outputs are written as they lie");
+    using G = Geometry<W, kMinLoads>;
+    constexpr int E = G::kElemsPerLane;
+    constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // masks per wave: 32 | 64
+    constexpr unsigned kTogether = 8, kWorkers = WV * kWaveSize;
+
+    __shared__ __align__(16) unsigned char s_stage[16 + WV * G::kWaveStageBytes];   // (16: see expand_piece)
+    __shared__ unsigned s_before[WV], s_wave_total[WV];
+
+    const unsigned tid = threadIdx.x;
+    const int lane = static_cast<int>(tid & (kWaveSize - 1));
+    const int wave = static_cast<int>(uniform(tid / kWaveSize));
+    const unsigned tile = blockIdx.x;
+    const size_t wave_elem0 = (static_cast<size_t>(tile) * WV + wave) * (static_cast<size_t>(kMinLoads) * kWaveSize * E);
+
+    // ---- the masks of the workgroups before, four at a time, from some place on and around
+    const unsigned before = tile * (WV * kStepMasks / 4), from = __umulhi(tile * 2654435761u, before);
+    unsigned count = 0;
+    for (unsigned at = tid; at < before; at += kTogether * kWorkers) {
+        vec4u v[kTogether];
+#pragma unroll
+        for (unsigned k = 0; k < kTogether; ++k) {
+            unsigned i = at + k * kWorkers;
+            v[k] = vec4u{0u, 0u, 0u, 0u};
+            if (i < before) {
+                i += from;
+                if (i >= before) i -= before;
+                v[k] = *reinterpret_cast<const vec4u_at4*>(masks + 4 * i);
+            }
+        }
+#pragma unroll
+        for (unsigned k = 0; k < kTogether; ++k)
+            count += static_cast<unsigned>(__popc(v[k].x) + __popc(v[k].y) + __popc(v[k].z) + __popc(v[k].w));
+    }
+    const auto mask_of = masks_within(masks, num_groups, static_cast<unsigned>(n % 32));
+    const unsigned m = lane < kStepMasks ? mask_of(wave_elem0 / 32 + lane) : 0u;
+    const unsigned counted = wave_sum_small(count), wave_total = wave_sum_small(static_cast<unsigned>(__popc(m)));
+    if (lane == 0) {
+        s_before[wave] = counted;
+        s_wave_total[wave] = wave_total;
+    }
+    lds_barrier();
+    unsigned first = 0;
+#pragma unroll
+    for (int v = 0; v < WV; ++v) {
+        first += uniform(s_before[v]);
+        if (v < wave) first += uniform(s_wave_total[v]);
+    }
+    if (wave_elem0 < n)
+        expand_step<W, OUTPUT == Output::kAligned>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, first,
+                                                   wave_total, m, wave_elem0, n, out, stream_values, lane);
 }
 
 // Decoders of the windowed stream.  No scan and no pre-pass: the offset table
@@ -2467,9 +2534,26 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
     return hipErrorInvalidValue;
 }
 
-// Tensors below this size decode in one launch (decompress_scan_kernel): measured 1-2.5 us
-// faster than pre-pass + expand up to 19 MB, slower from 26 MB up.
-constexpr size_t kScanDecoderBytes = size_t{16} << 20;
+// How a tensor is decoded: every workgroup counts the masks before its own (kDirect); one launch with the
+// device-wide scan, in workgroups of 4 or 8 waves (kScan4, kScan8); two launches.  kDirect up to 80 KB of masks, with 4 waves
+// up to 48 KB: see decompress_direct_kernel.  Beyond, us with kScan4 | kScan8 | two launches.  Up to 32 MB the chip holds all
+// waves at once, and fewer workgroups look for fewer counts; above, the larger workgroups' second turn is the longer one.  From 64 MB
+// up the pre-pass wins, whose expand kernel touches no shared state.
+//   density 0.3, fp32    3 MB 4.6 | 4.6 | 5.8   4 MB 4.65 | 4.7 | 6.0   5 MB 5.2 | 4.8 | 6.1   6.1 MB 5.2 | 4.9 | 6.7   8.5 MB 5.9 | 5.7 |
+//                        6.4   16 MB 7.0 | 6.1 | 7.9   24 MB 8.55 | 7.8 | 9.7   32 MB 10.3 | 10.0 | 11.6   40 MB 12.5 | 13.4 | 13.5
+//                        50 MB 14.7 | 15.9 | 15.0   64 MB 17.8 | 18.3 | 18.2   100 MB 25.6 | 26.8 | 25.1
+//                16-bit  4 MB 4.8 | 4.9 | 6.2   6 MB 5.4 | 5.0 | 6.4   12 MB 6.2 | 5.9 | 7.1   19 MB 7.7 | 7.3 | 8.9   30 MB 10.2 | 9.8 |
+//                        11.7   40 MB 12.7 | 14.5 | 13.9   51 MB 14.9 | 16.1 | 15.0   64 MB 17.9 | 19.5 | 18.6   100 MB 25.8 | 28.5 | 25.9
+//   density 0.9, fp32    24 MB 12.1 | 11.9 | 13.0   50 MB 21.6 | 22.0 | 22.4; 16-bit 64 MB 26.5 | 27.5 | 27.5
+//   at an odd element, 0.3: fp32 32 MB 10.8 | 10.6 | 12.1; 16-bit 52 MB 16.5 | 18.0 | 17.2
+// (Two waves: 4 MB 5.2 for 5.4 with a shorter pause, but they need twice the scan state.)
+enum class Decoder { kDirect4, kDirect8, kScan4, kScan8, kTwoLaunches };
+inline Decoder choose_decoder(size_t n, int w) {
+    const size_t bytes = n * static_cast<size_t>(w), masks = 4 * div_up(n, 32);
+    if (masks <= (size_t{80} << 10)) return masks <= (size_t{48} << 10) ? Decoder::kDirect4 : Decoder::kDirect8;
+    if (bytes >= (size_t{64} << 20)) return Decoder::kTwoLaunches;
+    return bytes >= (size_t{9} << 19) && bytes <= (size_t{32} << 20) ? Decoder::kScan8 : Decoder::kScan4;
+}
 
 // Tensors below this size never decode in the interleaved order (no gain there).
 inline bool interleaves(size_t n, int w) { return n * static_cast<size_t>(w) >= (size_t{64} << 20); }
@@ -2605,6 +2689,27 @@ inline Output planar_output(const void* out, size_t bytes, int w, bool one_launc
     const size_t step = one_launch ? 16 : w == 4 && bytes >= (size_t{256} << 20) ? 128 : 64;
     return aligned_to(out, step) ? Output::kAligned
          : one_launch && bytes < (size_t{8} << 20) ? Output::kLoose : Output::kShifted;
+}
+
+// The one-launch decoders for (w, output, eight waves or four).  The smallest tensors' outputs are written as they lie.
+template <int W>
+auto direct_decoder_as(Output output, bool eight) {
+    return output == Output::kAligned ? (eight ? decompress_direct_kernel<W, Output::kAligned, 8> : decompress_direct_kernel<W, Output::kAligned, 4>)
+                                      : (eight ? decompress_direct_kernel<W, Output::kLoose, 8> : decompress_direct_kernel<W, Output::kLoose, 4>);
+}
+inline auto direct_decoder(int w, Output output, bool eight) {
+    return w == 4 ? direct_decoder_as<4>(output, eight) : direct_decoder_as<2>(output, eight);
+}
+template <int W>
+auto scan_decoder_as(Output output, bool eight) {
+    switch (output) {
+        case Output::kLoose: return eight ? decompress_scan_kernel<W, Output::kLoose, 8> : decompress_scan_kernel<W, Output::kLoose, 4>;
+        case Output::kShifted: return eight ? decompress_scan_kernel<W, Output::kShifted, 8> : decompress_scan_kernel<W, Output::kShifted, 4>;
+        default: return eight ? decompress_scan_kernel<W, Output::kAligned, 8> : decompress_scan_kernel<W, Output::kAligned, 4>;
+    }
+}
+inline auto scan_decoder(int w, Output output, bool eight) {
+    return w == 4 ? scan_decoder_as<4>(output, eight) : scan_decoder_as<2>(output, eight);
 }
 
 // `bounded`: out_cap may be anything from the size of the mask area up; the
@@ -2980,27 +3085,28 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
     if (ranges_overlap(d_comp, comp_bytes, d_out, n * static_cast<size_t>(w))) return ZVC_E_ARG;
     if (zvc_status st = check_workspace(d_ws, ws, n, w)) return st;
     if (n == 0) return ZVC_OK;
-    const bool small = n * static_cast<size_t>(w) < kScanDecoderBytes;
-    const Output output = planar_output(d_out, n * static_cast<size_t>(w), w, small);
     // a multiple of 8 workgroups: the interleaved order deals the parts out in rounds of 8
     const size_t tiles = div_up(tiles_for(n, w, kMinLoads), 8) * 8;
     if (tiles > 0x7FFFFFFFull) return ZVC_E_ARG;
     const size_t groups = div_up(n, 32);
     const unsigned char* stream_values_at = static_cast<const unsigned char*>(d_comp) + 4 * groups;
     const unsigned long long stored_avail = (comp_bytes - 4 * groups) / static_cast<size_t>(w);
-    if (small) {
-        // one launch: the workgroups find their offsets with the encoder's scan (its state is at
-        // the front of the workspace)
-        const size_t scan_tiles = tiles_for(n, w, kMinLoads);
+    const Decoder decoder = choose_decoder(n, w);
+    const Output output = planar_output(d_out, n * static_cast<size_t>(w), w, decoder != Decoder::kTwoLaunches);
+    if (decoder != Decoder::kTwoLaunches) {
+        const bool eight = decoder == Decoder::kScan8 || decoder == Decoder::kDirect8;
+        const unsigned waves = eight ? 8u : 4u, one_tiles = static_cast<unsigned>(
+            div_up(n * static_cast<size_t>(w), size_t{kStageLoads * kSlotBytes} * waves));
+        const dim3 grid(one_tiles), block(waves * kWaveSize);
+        const unsigned* masks = static_cast<const unsigned*>(d_comp);
+        unsigned char* out = static_cast<unsigned char*>(d_out);
         const bool stream_values = stored_avail >= n / 4 * 3;
-        const auto kernel =
-            output == Output::kAligned ? (w == 4 ? decompress_scan_kernel<4, Output::kAligned> : decompress_scan_kernel<2, Output::kAligned>)
-            : output == Output::kLoose ? (w == 4 ? decompress_scan_kernel<4, Output::kLoose> : decompress_scan_kernel<2, Output::kLoose>)
-                                       : (w == 4 ? decompress_scan_kernel<4, Output::kShifted> : decompress_scan_kernel<2, Output::kShifted>);
-        return hip_ok(launch(kernel, dim3(static_cast<unsigned>(scan_tiles)), dim3(kThreads), stream,
-                             static_cast<const unsigned*>(d_comp), stream_values_at, stored_avail, n,
-                             static_cast<unsigned char*>(d_out), static_cast<WsHeader*>(d_ws),
-                             static_cast<unsigned>(scan_tiles), groups, stream_values));
+        if (decoder == Decoder::kDirect4 || decoder == Decoder::kDirect8)
+            return hip_ok(launch(direct_decoder(w, output, eight), grid, block, stream, masks, stream_values_at, stored_avail,
+                                 n, out, groups, stream_values));
+        // the workgroups find their offsets with the encoder's scan (its state is at the front of the workspace)
+        return hip_ok(launch(scan_decoder(w, output, eight), grid, block, stream, masks, stream_values_at, stored_avail, n,
+                             out, static_cast<WsHeader*>(d_ws), one_tiles, groups, stream_values));
     }
     const size_t chunks = div_up(groups, kChunkMasks);
     if (chunks > 0xFFFFFFFFull) return ZVC_E_ARG;
