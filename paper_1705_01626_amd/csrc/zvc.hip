@@ -2537,8 +2537,8 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 // How a tensor is decoded: every workgroup counts the masks before its own (kDirect); one launch with the
 // device-wide scan, in workgroups of 4 or 8 waves (kScan4, kScan8); two launches.  kDirect up to 80 KB of masks, with 4 waves
 // up to 48 KB: see decompress_direct_kernel.  Beyond, us with kScan4 | kScan8 | two launches.  Up to 32 MB the chip holds all
-// waves at once, and fewer workgroups look for fewer counts; above, the larger workgroups' second turn is the longer one.  From 64 MB
-// up the pre-pass wins, whose expand kernel touches no shared state.
+// waves at once, and fewer workgroups look for fewer counts; above, the larger workgroups' second turn is the longer one.  From about 60 MB
+// up the pre-pass is as fast or wins: its expand kernel touches no shared state, and may write in any order.
 //   density 0.3, fp32    3 MB 4.6 | 4.6 | 5.8   4 MB 4.65 | 4.7 | 6.0   5 MB 5.2 | 4.8 | 6.1   6.1 MB 5.2 | 4.9 | 6.7   8.5 MB 5.9 | 5.7 |
 //                        6.4   16 MB 7.0 | 6.1 | 7.9   24 MB 8.55 | 7.8 | 9.7   32 MB 10.3 | 10.0 | 11.6   40 MB 12.5 | 13.4 | 13.5
 //                        50 MB 14.7 | 15.9 | 15.0   64 MB 17.8 | 18.3 | 18.2   100 MB 25.6 | 26.8 | 25.1
@@ -2551,7 +2551,7 @@ enum class Decoder { kDirect4, kDirect8, kScan4, kScan8, kTwoLaunches };
 inline Decoder choose_decoder(size_t n, int w) {
     const size_t bytes = n * static_cast<size_t>(w), masks = 4 * div_up(n, 32);
     if (masks <= (size_t{80} << 10)) return masks <= (size_t{48} << 10) ? Decoder::kDirect4 : Decoder::kDirect8;
-    if (bytes >= (size_t{64} << 20)) return Decoder::kTwoLaunches;
+    if (bytes >= (size_t{56} << 20)) return Decoder::kTwoLaunches;
     return bytes >= (size_t{9} << 19) && bytes <= (size_t{32} << 20) ? Decoder::kScan8 : Decoder::kScan4;
 }
 
