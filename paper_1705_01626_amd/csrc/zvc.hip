@@ -1733,8 +1733,8 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
 // the number of set bits in all masks before its own, which it gets the way the
 // encoder's tiles get their offsets: it publishes the popcount of its own
 // masks and runs the device-wide scan over the workgroups before it
-// (scan_exclusive_prefix; same scan state in the workspace, same clean-up by the
-// last workgroup, same self-help if a predecessor has not been dispatched).  A
+// (scan_exclusive_prefix; same scan state in the workspace, same tags, same
+// self-help if a predecessor has not been dispatched).  A
 // workgroup knows its count after one small load, so the scan's chain is short;
 // below a few tens of megabytes one launch beats the pre-pass's extra kernel,
 // above that the pre-pass wins because its expand kernel touches no shared state.

@@ -44,3 +44,13 @@ def test_calls_of_many_sizes_on_one_workspace(oracle, w, patience):
             zvc.zvc_window_compress(x, out, offsets, size, ws)
             assert int(size.item()) == stream.size and np.array_equal(out[:stream.size].cpu().numpy(), stream)
             assert np.array_equal(offsets.cpu().numpy().astype(np.uint64), table)
+
+
+@pytest.mark.parametrize("w", [4, 2])
+def test_calls_that_name_a_part_of_the_workspace(oracle, w):
+    """A call may be told of no more of the workspace than it needs: the words of larger calls lie past that part."""
+    large, small = 300 * 16384 // w - 5, 7 * 16384 // w + 3
+    ws = zvc.new_workspace(large, w, DEV)
+    part = ws[:zvc.zvc_workspace_bytes(small, w)]
+    for k, n in enumerate((large, small, large, small, small, large, large)):
+        assert_parity(random_tensor(n, w, 0.4, seed=n + k), oracle, "call %d" % k, part if n == small else ws)
