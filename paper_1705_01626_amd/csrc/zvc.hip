@@ -516,10 +516,14 @@ struct ScanState {
     __device__ static unsigned long long ask(const WsHeader* header) {
         unsigned none = 0;
         asm("" : "+v"(none));
-        return *reinterpret_cast<const unsigned long long*>(reinterpret_cast<const unsigned char*>(&header->scan_word) + none);
+        return load64(reinterpret_cast<const unsigned long long*>(reinterpret_cast<const unsigned char*>(&header->scan_word) + none));
     }
+    // Every wave builds its ScanState before it counts itself in at the tile's arrival word: the last tile turns the
+    // word over once it has every tile's count, and a tile's count is out once its waves have arrived.  The load
+    // has returned when the asm statement is reached, and no later access to memory is moved before it.
     __device__ ScanState(WsHeader* header, unsigned num_tiles, unsigned long long asked)
         : hdr(header), counts(reinterpret_cast<unsigned*>(header + 1)), block_shift(block_shift_of(num_tiles)) {
+        asm volatile("" : "+v"(asked) : : "memory");
         const unsigned long long word = uniform(asked);
         const unsigned low = static_cast<unsigned>(word);
         tag = (low & 1u) + 1u;

@@ -56,3 +56,18 @@ def test_input_that_is_read_once_is_read_with_the_streaming_hint(assembly):
         if "Lb1E" in name:                            # (at least 16-byte aligned)
             loads = re.findall(r"^\s*(global_load_dwordx4 .*?)(?:\s*//.*)?$", body, flags=re.M)
             assert len(loads) >= 8 and all(" nt" in x for x in loads), name
+
+
+def test_the_scan_word_is_there_before_a_wave_counts_itself_in(assembly):
+    """The last tile of a call overwrites the word once it has every tile's count, and a tile's count is out
+    once its waves have counted themselves in (the only LDS atomic with a result).  So a wave reads the word
+    with an atomic load that the other XCDs' caches do not serve, and has it before that."""
+    kernels = {**functions(assembly, "compress_kernel"), **functions(assembly, "decompress_scan_kernel")}
+    assert len(kernels) > 20
+    for name, body in kernels.items():
+        lines = [line.split("//")[0].strip() for line in body.splitlines()]
+        loads = [i for i, line in enumerate(lines) if re.match(r"global_load_dwordx2 .* offset:8\b", line)]
+        arrivals = [i for i, line in enumerate(lines) if line.startswith("ds_add_rtn_u32 ")]
+        assert len(loads) == 1 and len(arrivals) == 1, name
+        assert lines[loads[0]].endswith(" sc1"), name
+        assert any(re.match(r"s_waitcnt .*vmcnt\(0\)", line) for line in lines[loads[0]:arrivals[0]]), name
