@@ -131,9 +131,10 @@ zvc_status zvc_workspace_self_help_count(const void* d_ws, uint64_t* h_count);
  * in bytes, at least zvc_workspace_bytes(0, 4).  Every call leaves the
  * workspace ready for the next one, so no other reset is ever needed; only
  * after a call failed with ZVC_E_HIP (or its kernels were aborted) must the
- * workspace be initialised again.  A call may name fewer of its bytes than were
- * initialised; it may then still clear words that a larger call before it left
- * in the others, so these serve nothing else before a new initialisation. */
+ * workspace be initialised again.  A call may be told of fewer bytes (ws) than were
+ * initialised, if they are enough for it; it touches only those.  Bytes behind
+ * them that serve something else meanwhile have to be initialised again, all
+ * together, before a call is told of them. */
 zvc_status zvc_workspace_init(void* d_ws, size_t ws, hipStream_t stream);
 
 /* Count-only pass: *d_bytes = 4*ceil(n/32) + w*nnz, the size zvc_compress would

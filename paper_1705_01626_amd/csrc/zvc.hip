@@ -110,17 +110,18 @@ struct EncoderGeometry {
         CH == 64 ? 8704 : (CH * kChunkBytes / 2 > kStepMaxBytes ? CH * kChunkBytes / 2 : kStepMaxBytes) + 256;
     static_assert(kQueueBytes >= 128 + kStepMaxBytes, "a step always fits behind a carried-over partial line");
     static_assert(CH % kStepChunks == 0, "a wave's chunks are staged in whole steps");
-    static_assert(kTileElems < (1 << 24), "tile totals fit the arrival word");
+    static_assert(kTileElems <= 0x4000, "tile totals fit the arrival word and the scan's");
 };
 
 // Workspace header.  Lives at the start of the caller's workspace.
 struct WsHeader {
     unsigned long long patience_plus_one;   // 0: default; else polls before a waiting tile helps itself, plus one
-    unsigned long long scan_word;  // the next call's tag and the last one's number of tiles, see scan_word_of
+    unsigned long long scan_word;  // the scan's calls so far, see ScanCalls
     unsigned long long size_word;  // compressed size for zvc_offload's read-back
     unsigned long long helped;     // predecessor counts computed by a waiting tile since the workspace's init
     unsigned long long helped_here;   // not 0: a waiting tile of the present call has computed a predecessor's count
-    unsigned long long pad[27];
+    unsigned long long wide_calls;    // so far, see ScanCalls
+    unsigned long long pad[26];
     // The scan's running prefixes, and arrival counters, zero between calls.  Decoder's pre-pass: the
     // workgroup that completes a counter bumps finish_top, the one that completes finish_top is
     // the last.  Count-only pass: the same, with `sum` collecting the counts.
@@ -135,33 +136,61 @@ struct WsHeader {
 };
 static_assert(sizeof(WsHeader) == kHeaderBytes, "header size");
 
-// Scan state:
-//   counts   : a 32-bit word per tile, behind the header; the call's tag in the two highest bits, a bit
-//              that the tile itself wrote it, and the tile's own count of kept elements;
-//   prefixes : a 64-bit word per block of tiles, in the header's lines; the call's tag in the two
-//              highest bits, rest = kept elements in all tiles up to and including the block's last.
-// A word counts if it has the call's tag.  Calls on a workspace take the tags 1 and 2 in turn: every tile
-// writes its words once, which replaces what the call before left there, and the words of tiles that only
-// the call before had are zeroed.  hdr->scan_word has the next call's tag; the last tile turns it over
-// at the call's end: it has every tile's count by then, and a tile publishes its count after it has
-// read the word, so nobody reads it later.  (If counts were computed by waiting tiles, the last
-// tile first sees to it that their owners have started, see scan_end.)  So no tile waits for its
-// stores or counts itself finished, and the call does not end with a clean-up.  us with words that the
-// last tile zeroed once all had counted themselves finished | now, the other changes of the scan
-// included: fp32 256 KB 4.50 | 3.98, 6.4 MB 6.83 | 5.82, 24 MB 9.66 | 9.14, 100 MB 27.6 | 26.4, 300 MB
+// Scan state.
+//   counts   : a word per tile, behind the header: the call's number, a bit that the tile itself wrote it, and the
+//              tile's own count of kept elements (15 bits).  32 bits with the number's lowest 15, or (a
+//              wide call) 64 with all that matter;
+//   prefixes : a 64-bit word per block of tiles, in the header's lines: a tag of two bits, 1 and 2 in turn
+//              from call to call, and the kept elements in all tiles up to and including the block's last.
+// A count holds if it has the call's number, so nothing that earlier calls left there has to be cleared,
+// neither by them nor by a later one, which may be a tiny one or have been told of fewer bytes than they.  15 bits tell apart
+// the calls of two terms of 2^14 calls; what lies behind the tiles of a term's last call may be older than that in the term
+// after.  A call that has more tiles than that one, and than every such call since, is a wide one.  Its
+// counts have the number of wide calls so far, of which there cannot be 2^45.  Neither kind passes for the other, nor what the
+// decoder's pre-pass leaves in the same bytes for either: the two highest bits of each 32 are 1x in a count of 32 bits,
+// 0x and 01 in the lower and upper half of one of 64, 00 in the pre-pass's arrays.
+// A call's prefixes replace what the one before left, and the few that only that one had are zeroed.
+// The last tile counts the call in the header: it has every tile's count by then, and a tile's count is out
+// after its waves have read the word there, so nobody reads it later.  (If counts were
+// computed by waiting tiles, the last tile first sees to it that their owners have started, see
+// scan_end.)  So no tile waits for its stores or counts itself finished, and the call does not end with
+// a clean-up.  us with words that the last tile zeroed once all had counted themselves finished | now, the other
+// changes of the scan included: fp32 256 KB 4.50 | 3.98, 6.4 MB 6.83 | 5.82, 24 MB 9.66 | 9.14, 100 MB 27.6 | 26.4, 300 MB
 // 72.9 | 70.6; bf16 4 MB 6.35 | 5.53, 200 MB 55.6 | 53.0; decoding fp32 6.4 MB 6.35 | 5.8.
-constexpr unsigned kCountOwner = 1u << 29, kCountBits = kCountOwner - 1u;
-constexpr int kTagShift = 30;                 // in the upper 32 bits of a prefix
+constexpr int kCallShift = 16;                // of a count's word; of a wide one the number's lowest bits
+constexpr int kCallBits = 15, kTermBits = kCallBits - 1;
+constexpr unsigned kCountOwner = 1u << 15, kCountBits = kCountOwner - 1u;
+constexpr int kTagShift = 62;                 // of a prefix
 constexpr unsigned kLinePrefixes = 14, kMostPrefixes = kLinePrefixes * kFinishLanes;
 
-// scan_word: the next call's tag less one (bit 0), the number of tiles that the last call had, and in the
-// upper 32 bits a check, so that a workspace that was never initialised is at worst scanned wrongly and
-// nothing outside it written.
-constexpr unsigned kScanCheck = 0x9E3779B1u;
-__host__ __device__ inline unsigned long long scan_word_of(unsigned tag, unsigned tiles) {
-    const unsigned low = tiles << 1 | (tag - 1u);
-    return static_cast<unsigned long long>(low * kScanCheck) << 32 | low;
+__host__ __device__ inline unsigned narrow_mark(unsigned call) { return 1u << 31 | call << kCallShift; }
+__host__ __device__ inline unsigned long long wide_mark(unsigned long long number) {
+    return 1ull << 62 | (number >> kCallBits & ((1ull << 30) - 1ull)) << 32 | (number & ((1ull << kCallBits) - 1ull)) << kCallShift;
 }
+
+// hdr->scan_word; zero in a new workspace.
+struct ScanCalls {
+    unsigned call;                 // the next one's number, its lowest 15 bits
+    unsigned prefixes;             // that the last call left
+    unsigned limit;                // a call with more tiles is a wide one; 0: none is
+    __host__ __device__ explicit ScanCalls(unsigned long long word)
+        : call(static_cast<unsigned>(word) & ((1u << kCallBits) - 1u)), prefixes(static_cast<unsigned>(word) >> kCallBits),
+          limit(static_cast<unsigned>(word >> 32)) {
+        // (a workspace that was never initialised is at worst scanned wrongly, and nothing outside it written)
+        if (prefixes > kMostPrefixes) prefixes = kMostPrefixes;
+    }
+    __host__ __device__ unsigned long long word() const {
+        return static_cast<unsigned long long>(limit) << 32 | prefixes << kCallBits | call;
+    }
+    __host__ __device__ bool wide(unsigned tiles) const { return limit != 0u && tiles > limit; }
+    __host__ __device__ ScanCalls next(unsigned tiles, unsigned prefixes_left) const {
+        ScanCalls after = *this;
+        after.call = (call + 1u) % (1u << kCallBits);
+        after.prefixes = prefixes_left;
+        if (after.call % (1u << kTermBits) == 0u || wide(tiles)) after.limit = tiles;
+        return after;
+    }
+};
 
 __host__ __device__ inline size_t div_up(size_t a, size_t b) { return a / b + (a % b != 0); }
 
@@ -169,24 +198,29 @@ inline size_t tiles_for(size_t n, int w, int loads) {
     const size_t tile_elems = static_cast<size_t>(kThreads * 16 * loads / w);
     return div_up(n, tile_elems);
 }
-inline size_t scan_state_bytes(size_t tiles) {              // (with room for a word per 256 tiles)
-    return 256 * (div_up(tiles, 64) + div_up(tiles, 64 * 128));
-}
+inline size_t scan_state_bytes(size_t tiles) { return 8 * tiles; }     // (a wide call's)
 // log2 of the tiles per block: 9, or more where the header has not room for that many prefixes (from 458752 tiles up)
 __host__ __device__ inline int block_shift_of(unsigned tiles) {
     int shift = kBlockShift;
     while (tiles >> shift > kMostPrefixes) ++shift;
     return shift;
 }
-// the decoder pre-pass arrays sit at the end of the workspace, clear of the
-// encoder's scan state (which must not be scribbled on between calls)
+// The decoder's pre-pass arrays sit at the end of the workspace; where it is no larger than it has to be, in bytes
+// that the scan state of other calls takes as well.
 inline size_t pad256(size_t b) { return div_up(b, 256) * 256; }
 inline size_t decoder_area_bytes(size_t chunks) {   // chunk_prefix, chunk_total, unit_end
     return pad256(8 * chunks) + pad256(4 * chunks) + pad256(4 * 128 * chunks);
 }
 
+// A prefix of the pre-pass: 30 bits in each half, so that neither passes for a tile's count.
+__host__ __device__ inline unsigned long long in_halves(unsigned long long v) { return v >> 30 << 32 | (v & 0x3FFFFFFFull); }
+__host__ __device__ inline unsigned long long from_halves(unsigned long long v) { return v >> 32 << 30 | (v & 0x3FFFFFFFull); }
+
 // ------------------------------------------------------------ device helpers
 __device__ inline unsigned long long load64(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned load32(const unsigned* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline void store64(unsigned long long* p, unsigned long long v) {
@@ -507,48 +541,84 @@ __device__ __forceinline__ unsigned wave_scan_small(unsigned v) {
 // One call's view of the scan state.
 struct ScanState {
     WsHeader* hdr;
-    unsigned* counts;
-    unsigned tag;                  // 1 | 2
-    unsigned tiles_before;         // of the call before
+    ScanCalls calls;               // before this one
+    unsigned wide;                 // 0 | 1
+    unsigned mark0, mark1;         // what the call's counts have beside count and owner, in the words with even and odd index:
+                                   // two tiles', or one's lower and upper half
     int block_shift;
     // The word's load, which goes out behind the tile's own and is waited for when those have arrived.  (On
-    // the vector unit: a scalar load would be waited for at the next barrier.)
+    // the vector unit: a scalar load would be waited for at the next barrier.  One of 8 bytes: every wave of the
+    // call asks for it, and a second one costs the decoder 0.5 to 1.7 us from 20 MB up.)
     __device__ static unsigned long long ask(const WsHeader* header) {
         unsigned none = 0;
         asm("" : "+v"(none));
         return load64(reinterpret_cast<const unsigned long long*>(reinterpret_cast<const unsigned char*>(&header->scan_word) + none));
     }
-    // Every wave builds its ScanState before it counts itself in at the tile's arrival word: the last tile turns the
-    // word over once it has every tile's count, and a tile's count is out once its waves have arrived.  The load
+    // Every wave builds its ScanState before it counts itself in at the tile's arrival word: the last tile writes the
+    // next word once it has every tile's count, and a tile's count is out once its waves have arrived.  The load
     // has returned when the asm statement is reached, and no later access to memory is moved before it.
     __device__ ScanState(WsHeader* header, unsigned num_tiles, unsigned long long asked)
-        : hdr(header), counts(reinterpret_cast<unsigned*>(header + 1)), block_shift(block_shift_of(num_tiles)) {
-        asm volatile("" : "+v"(asked) : : "memory");
-        const unsigned long long word = uniform(asked);
-        const unsigned low = static_cast<unsigned>(word);
-        tag = (low & 1u) + 1u;
-        tiles_before = static_cast<unsigned>(word >> 32) == low * kScanCheck ? low >> 1 : 0u;
+        : hdr(header), calls(settled(asked)), wide(calls.wide(num_tiles) ? 1u : 0u), mark0(narrow_mark(calls.call)),
+          mark1(mark0), block_shift(block_shift_of(num_tiles)) {
+        if (__builtin_expect(wide != 0u, 0)) {
+            const unsigned long long mark = wide_mark(settled(load64(&header->wide_calls)));
+            mark0 = static_cast<unsigned>(mark);
+            mark1 = static_cast<unsigned>(mark >> 32);
+        }
     }
-    __device__ unsigned long long* prefix(unsigned block) const {
+    __device__ static unsigned long long settled(unsigned long long word) {
+        asm volatile("" : "+v"(word) : : "memory");
+        return uniform(word);
+    }
+    __host__ __device__ unsigned* counts() const { return reinterpret_cast<unsigned*>(hdr + 1); }
+    __host__ __device__ unsigned long long* wide_counts() const { return reinterpret_cast<unsigned long long*>(hdr + 1); }
+    __host__ __device__ unsigned long long mark() const { return static_cast<unsigned long long>(mark1) << 32 | mark0; }
+    // Whether the words with even and odd index are counts of this call.
+    __host__ __device__ bool is_there0(unsigned word) const { return (word ^ mark0) >> kCallShift == 0u; }
+    __host__ __device__ bool is_there1(unsigned word) const { return (word ^ mark1) >> (wide ? 0 : kCallShift) == 0u; }
+    // Whether the tile has written its count itself.
+    __device__ bool has_started(unsigned tile) const {
+        return wide ? (load64(wide_counts() + tile) ^ (mark() | kCountOwner)) <= kCountBits
+                    : (load32(counts() + tile) ^ (mark0 | kCountOwner)) <= kCountBits;
+    }
+    __device__ void publish(unsigned tile, unsigned kept) const {
+        if (__builtin_expect(wide != 0u, 0)) exchange64(wide_counts() + tile, mark() | kCountOwner | kept);
+        else exchange32(counts() + tile, mark0 | kCountOwner | kept);
+    }
+    // A count that another tile has computed, unless its owner has been there meanwhile.
+    __device__ void publish_for(unsigned tile, unsigned kept) const {
+        if (wide) {
+            unsigned long long* const p = wide_counts() + tile;
+            unsigned long long old = load64(p);
+            while ((old ^ mark()) >> kCallShift != 0ull) {
+                const unsigned long long seen = atomicCAS(p, old, mark() | kept);
+                if (seen == old) break;
+                old = seen;
+            }
+        } else {
+            unsigned* const p = counts() + tile;
+            unsigned old = load32(p);
+            while (!is_there0(old)) {
+                const unsigned seen = atomicCAS(p, old, mark0 | kept);
+                if (seen == old) break;
+                old = seen;
+            }
+        }
+    }
+    __host__ __device__ unsigned long long* prefix(unsigned block) const {
         return &hdr->finish[block / kLinePrefixes].prefix[block % kLinePrefixes];
     }
-    __device__ bool is_there(unsigned count) const { return count >> kTagShift == tag; }
-    __device__ void publish(unsigned tile, unsigned kept) const {
-        exchange32(counts + tile, tag << kTagShift | kCountOwner | kept);
-    }
+    __host__ __device__ unsigned long long tag() const { return 1ull + (calls.call & 1u); }
     __device__ void publish_prefix(unsigned tile, unsigned long long upto) const {
-        exchange64(prefix(tile >> block_shift), static_cast<unsigned long long>(tag) << (32 + kTagShift) | upto);
+        exchange64(prefix(tile >> block_shift), tag() << kTagShift | upto);
     }
-    __device__ bool ends_block(unsigned tile) const { return ((tile + 1u) & ((1u << block_shift) - 1u)) == 0u; }
-    // The tile's share of the words that only the call before had, by one of its waves.
-    __device__ void zero_what_is_left(unsigned tile, unsigned num_tiles, int lane) const {
-        const size_t mine = static_cast<size_t>(tile) * kWaveSize, stride = static_cast<size_t>(num_tiles) * kWaveSize;
-        for (size_t i = num_tiles + mine; i < tiles_before; i += stride)
-            if (i + lane < tiles_before) counts[i + lane] = 0u;
-        // (where a block is longer than it was in the call before, there can be fewer of them, but not fewer tiles)
-        const unsigned blocks = tiles_before >> block_shift_of(tiles_before);
-        for (size_t i = (num_tiles >> block_shift) + mine; i < blocks; i += stride)
-            if (i + lane < blocks) *prefix(static_cast<unsigned>(i) + lane) = 0ull;
+    __host__ __device__ bool ends_block(unsigned tile) const { return ((tile + 1u) & ((1u << block_shift) - 1u)) == 0u; }
+    // The tile's share of the prefixes that only the call before had, by one of its waves.
+    __host__ __device__ void zero_prefixes_left(unsigned tile, unsigned num_tiles, int lane) const {
+        const unsigned now = num_tiles >> block_shift;
+        if (__builtin_expect(calls.prefixes <= now || tile >= kMostPrefixes, 1)) return;
+        for (unsigned i = now + tile * kWaveSize + lane; i < calls.prefixes; i += min(num_tiles, kMostPrefixes) * kWaveSize)
+            *prefix(i) = 0ull;
     }
 };
 
@@ -607,7 +677,7 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
         const int idx = bb - lane;
         unsigned long long pv = 0;
         if (idx >= 0) pv = load64(st.prefix(static_cast<unsigned>(idx)));
-        const unsigned long long have = __ballot(st.is_there(static_cast<unsigned>(pv >> 32)));
+        const unsigned long long have = __ballot(pv >> kTagShift == st.tag());
         if (have) {
             const int k = __ffsll(static_cast<long long>(have)) - 1;
             base = lane_value(pv, k) << 2 >> 2;
@@ -616,43 +686,47 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
         }
         bb -= kWaveSize;
     }
-    // Counts of tiles lo .. t-1, a pair per 8-byte load (lo is a multiple of the
+    // Counts of tiles lo .. t-1, a pair (a wide one) per 8-byte load (lo is a multiple of the
     // block size: pairs are aligned), kScanBatch loads per lane in flight at a time
     // (256 tiles a batch; asking for more at once reads more of the newest counts while they are still being
-    // written, which measures slower).  The
+    // written, which measures slower.  So do 64-bit words in every call: a batch is 16 lines then and not 8.  fp32 6.4 MB
+    // 5.33 | 5.62 us, 16-bit 30 MB 12.6 | 13.5, decoding 40 MB 12.5 | 13.6).  The
     // loads of a batch are added in order as far as everything they cover is
     // published; a later round asks again only from the first load that found
     // something missing, so the waiting re-reads no more than the newest counts.
     constexpr int kScanBatch = 2;
-    constexpr int kLoadTiles = 2 * kWaveSize;     // tiles covered by one load of the wave
+    const int per = st.wide ? 1 : 2;              // tiles per 8 bytes
+    const unsigned count_bits1 = st.wide ? 0u : kCountBits;
     int done_to = lo;              // wave-uniform: the counts of tiles lo .. done_to-1 are in `sum`
     unsigned sum = 0;              // a lane adds few counts, each below 2^16
     unsigned polls = 0;
     while (done_to < t) {
         unsigned long long pair[kScanBatch];
+        const unsigned long long* const from =
+            reinterpret_cast<const unsigned long long*>(st.counts() + (st.wide ? 2 * static_cast<size_t>(done_to) : done_to));
 #pragma unroll
         for (int k = 0; k < kScanBatch; ++k) {
-            const int i = done_to + k * kLoadTiles + 2 * lane;
-            pair[k] = i < t ? load64(reinterpret_cast<const unsigned long long*>(st.counts + i)) : 0ull;
+            const int i = done_to + per * (k * kWaveSize + lane);
+            pair[k] = i < t ? load64(from + k * kWaveSize + lane) : 0ull;
         }
         int complete = 0;          // leading loads of the batch that found everything published
         int hole = -1;             // wave-uniform: the first tile found unpublished
 #pragma unroll
         for (int k = 0; k < kScanBatch; ++k) {
             if (complete != k) continue;          // wave-uniform
-            const int i = done_to + k * kLoadTiles + 2 * lane;
+            const int i = done_to + per * (k * kWaveSize + lane), i1 = i + per - 1;
             const unsigned c0 = static_cast<unsigned>(pair[k]), c1 = static_cast<unsigned>(pair[k] >> 32);
-            const bool there0 = i >= t || st.is_there(c0), there1 = i + 1 >= t || st.is_there(c1);
+            const bool there0 = i >= t || st.is_there0(c0), there1 = i1 >= t || st.is_there1(c1);
             const unsigned long long missing = __ballot(!(there0 && there1));
             if (!missing) {
-                sum += (i < t ? c0 & kCountBits : 0u) + (i + 1 < t ? c1 & kCountBits : 0u);
+                sum += (i < t ? c0 & kCountBits : 0u) + (i1 < t ? c1 & count_bits1 : 0u);
                 complete = k + 1;
             } else {
                 const int first = __ffsll(static_cast<long long>(missing)) - 1;
-                hole = done_to + k * kLoadTiles + 2 * first + (st.is_there(lane_value(c0, first)) ? 1 : 0);
+                hole = done_to + per * (k * kWaveSize + first) + (st.is_there0(lane_value(c0, first)) ? per - 1 : 0);
             }
         }
-        done_to += complete * kLoadTiles;
+        done_to += complete * per * kWaveSize;
         if (hole < 0) continue;                   // the whole batch was there: the next one, if any
         if (PAUSE == kNoPause && polls == 0) patience_word = uniform(load64(&st.hdr->patience_plus_one));
         const unsigned patience = patience_word != 0 ? static_cast<unsigned>(patience_word - 1) : kDefaultPatience;
@@ -668,13 +742,7 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
             store64(&st.hdr->helped_here, 1ull);
             atomicAdd(&st.hdr->helped, 1ull);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            // unless the owner has been there meanwhile
-            unsigned old = __hip_atomic_load(st.counts + hole, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while (!st.is_there(old)) {
-                const unsigned seen = atomicCAS(st.counts + hole, old, st.tag << kTagShift | helped_count);
-                if (seen == old) break;
-                old = seen;
-            }
+            st.publish_for(static_cast<unsigned>(hole), helped_count);
         }
     }
     // (halves, so that no partial sum can overflow whatever the distance walked)
@@ -683,17 +751,18 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
 }
 
 // The end of a call, by the scan wave of its last tile once it has the counts of all tiles: the
-// next call takes the other tag.  A tile whose count was computed by another one may not have
+// next call takes the next number.  A tile whose count was computed by another one may not have
 // begun yet, and would then read the word of the next call: the last tile waits for such
 // tiles (none of them waits for it).
 __device__ inline void scan_end(const ScanState& st, unsigned num_tiles, int lane) {
     if (__builtin_expect(uniform(load64(&st.hdr->helped_here)) != 0ull, 0)) {
         for (unsigned tile = lane; tile + 1u < num_tiles; tile += kWaveSize)
-            while (__hip_atomic_load(st.counts + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kCountOwner != (st.tag << 1 | 1u))
-                __builtin_amdgcn_s_sleep(kPollSleep);
+            while (!st.has_started(tile)) __builtin_amdgcn_s_sleep(kPollSleep);
         if (lane == 0) store64(&st.hdr->helped_here, 0ull);
     }
-    if (lane == 0) store64(&st.hdr->scan_word, scan_word_of(3u - st.tag, num_tiles));
+    if (lane != 0) return;
+    store64(&st.hdr->scan_word, st.calls.next(num_tiles, num_tiles >> st.block_shift).word());
+    if (__builtin_expect(st.wide != 0u, 0)) atomicAdd(&st.hdr->wide_calls, 1ull);
 }
 
 // ------------------------------------------------- encoder: loads and zero tests
@@ -1142,7 +1211,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
         }
     }
 
-    if (wave == WV - 1) scan.zero_what_is_left(tile, a.num_tiles, lane);
+    if (wave == WV - 1) scan.zero_prefixes_left(tile, a.num_tiles, lane);
 
     // ---- 3. more of the compaction before the tile knows where its run begins: the steps left
     //         for now, and those that were not sure to fit but, now that their size is known, do
@@ -1238,6 +1307,24 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     if (tile == a.num_tiles - 1 && wave == 0)
         scan_end(scan, a.num_tiles, lane);
 }
+
+// With more than 80 scalar registers a SIMD holds seven waves, not eight, and the scan's state would make them 82 to 92.  us with
+// them | with 80: windowed 16-bit 30 MB 15.05 | 14.7, 100 MB 37.6 | 36.8, 300 MB 89.5 | 87.2, fp32 64 MB 19.0 | 18.3; 16-bit 100 MB
+// 32.0 | 32.6, 300 MB 82.4 | 81.6; decoding 16-bit 40 MB 13.3 | 13.0.  Not where a tile is staged early, which
+// takes up to 106 and would save and reload them (fp32 24 MB 9.1 | 9.4).
+#define ZVC_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
+#define ZVC_EIGHT_WAVES_ENCODER(W, CH, RELU, WINDOWED, SPLIT) \
+    template __global__ ZVC_EIGHT_WAVES void compress_kernel<W, CH, 4, RELU, WINDOWED, SPLIT, false>(EncoderArgs)
+#define ZVC_EIGHT_WAVES_ENCODERS(W, CH, SPLIT)                 \
+    ZVC_EIGHT_WAVES_ENCODER(W, CH, false, false, SPLIT);       \
+    ZVC_EIGHT_WAVES_ENCODER(W, CH, true, false, SPLIT);        \
+    ZVC_EIGHT_WAVES_ENCODER(W, CH, false, true, SPLIT)
+ZVC_EIGHT_WAVES_ENCODERS(2, 16, false);
+ZVC_EIGHT_WAVES_ENCODERS(2, 16, true);
+ZVC_EIGHT_WAVES_ENCODERS(2, 32, false);
+ZVC_EIGHT_WAVES_ENCODERS(2, 32, true);
+ZVC_EIGHT_WAVES_ENCODER(4, 16, false, true, false);
+ZVC_EIGHT_WAVES_ENCODER(4, 32, false, true, false);
 
 // Decoder pre-pass (section 5.2: the popcount of a mask span is the number of
 // stored words the span consumes).  Where a span's stored elements start
@@ -1387,7 +1474,7 @@ __global__ __launch_bounds__(kThreads) void mask_prefix_kernel(
         }
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
-            if (c0 + k < num_chunks) chunk_prefix[c0 + k] = before;
+            if (c0 + k < num_chunks) chunk_prefix[c0 + k] = in_halves(before);
             before += t[k];
         }
         carry += all;
@@ -1721,7 +1808,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
         before_chunk = uniform(sum);
     }
     if (wave_elem0 >= n) return;                  // nothing of the tensor in this wave's part
-    if (chunk_prefix != nullptr) before_chunk = chunk_prefix[chunk];
+    if (chunk_prefix != nullptr) before_chunk = from_halves(chunk_prefix[chunk]);
 
     if constexpr (OUTPUT != Output::kShifted) {
         expand_step<W, OUTPUT == Output::kAligned>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, before_chunk + step_begin,
@@ -1737,7 +1824,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(
 // the number of set bits in all masks before its own, which it gets the way the
 // encoder's tiles get their offsets: it publishes the popcount of its own
 // masks and runs the device-wide scan over the workgroups before it
-// (scan_exclusive_prefix; same scan state in the workspace, same tags, same
+// (scan_exclusive_prefix; same scan state in the workspace, same numbers, same
 // self-help if a predecessor has not been dispatched).  A
 // workgroup knows its count after one small load, so the scan's chain is short;
 // below a few tens of megabytes one launch beats the pre-pass's extra kernel,
@@ -1763,7 +1850,7 @@ struct CountMaskTile {
 };
 
 template <int W, Output OUTPUT, int WV>
-__global__ __launch_bounds__(WV * kWaveSize) void decompress_scan_kernel(
+__global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, WsHeader* hdr,
     unsigned num_tiles, size_t num_groups, bool stream_values) {
@@ -1814,7 +1901,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void decompress_scan_kernel(
     const bool publisher = (arrived >> 24) == WV - 1;
     if (publisher && lane == 0)
         scan.publish(tile, (arrived & 0xFFFFFFu) + wave_total);
-    if (wave == WV - 1) scan.zero_what_is_left(tile, num_tiles, lane);
+    if (wave == WV - 1) scan.zero_prefixes_left(tile, num_tiles, lane);
     if (wave == 0) {
         unsigned long long ex = 0;
         if (tile != 0) {
@@ -2471,11 +2558,15 @@ constexpr size_t kLargeTensorBytes = size_t{160} << 20;
 constexpr TileShape kMinShape{16, 4};             // 16 KB, the smallest tile (sizes the workspace)
 static_assert(kMinShape.chunks * kMinShape.waves * kChunkBytes == kMinLoads * 16 * kThreads, "smallest tile");
 
+// From where on the tile is 32 KB.
+constexpr size_t medium_bytes(int w, bool windowed) {
+    return w == 4 ? size_t{windowed ? 38u : 14u} << 20 : size_t{windowed ? 120u : 48u} << 20;
+}
+
 inline TileShape choose_shape(size_t n, int w, bool windowed) {
     const size_t bytes = n * static_cast<size_t>(w);
-    const size_t medium = w == 4 ? size_t{windowed ? 38u : 14u} << 20 : size_t{windowed ? 120u : 48u} << 20;
     return bytes >= kLargeTensorBytes && w == 4 && !windowed ? TileShape{64, 4}
-         : bytes >= medium ? TileShape{32, 4} : kMinShape;
+         : bytes >= medium_bytes(w, windowed) ? TileShape{32, 4} : kMinShape;
 }
 
 // The input is read with the streaming hint at every size.  A tensor that is read once, just written or
@@ -2808,10 +2899,10 @@ zvc_status offload_impl(Encoder mode, const void* d_in, size_t n, int w, void* d
 
 // Scratch of zvc_compress_static: header and scan state for tensors of up to
 // ZVC_STATIC_MAX_BYTES.  Zero when the code object is loaded, which is the
-// state zvc_workspace_init gives a caller's workspace, and every call leaves it
-// zero again.  Each GPU holds its own copy at its own address.
-constexpr size_t kStaticScratchBytes = ZVC_STATIC_SCRATCH_BYTES;   // covers 16 KB tiles (the smallest) up to the limit
-static_assert(kHeaderBytes + 4 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads)) + 8 * (ZVC_STATIC_MAX_BYTES / (kMinLoads * 16 * kThreads) / 256) + 512 <= ZVC_STATIC_SCRATCH_BYTES, "scratch holds the scan state of the largest call");
+// state zvc_workspace_init gives a caller's workspace.  Each GPU holds its own copy at its own address.
+constexpr size_t kStaticScratchBytes = ZVC_STATIC_SCRATCH_BYTES;
+static_assert(kHeaderBytes + 8 * (ZVC_STATIC_MAX_BYTES / (32 << 10)) <= kStaticScratchBytes &&
+              kHeaderBytes + 8 * (medium_bytes(2, true) / (16 << 10)) <= kStaticScratchBytes, "scratch holds the scan state of every call");
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 std::mutex g_scratch_mutex;
@@ -2859,8 +2950,10 @@ size_t zvc_max_compressed_bytes(size_t n, int w) {
 
 size_t zvc_workspace_bytes(size_t n, int w) {
     if (w != 2 && w != 4) return 0;
+    // 4 bytes per smallest tile (and more) and the decoder's arrays, 524 bytes per 131072 elements: together
+    // they hold the scan state, 8 bytes per tile
     const size_t tiles = tiles_for(n, w, kMinLoads);
-    return kHeaderBytes + scan_state_bytes(tiles) +
+    return kHeaderBytes + 256 * (div_up(tiles, 64) + div_up(tiles, 64 * 128)) +
            decoder_area_bytes(div_up(div_up(n, 32), kChunkMasks));
 }
 
@@ -3106,9 +3199,7 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
     }
     const size_t chunks = div_up(groups, kChunkMasks);
     if (chunks > 0xFFFFFFFFull) return ZVC_E_ARG;
-    // The pre-pass arrays need no reset.  They sit at the end of the workspace, whatever its
-    // size: an encoder call that this workspace is large enough for keeps its scan state
-    // (whose words the next call relies on) below them, whichever call came first.
+    // The pre-pass arrays need no reset, and what they leave behind is no count of a later call's (see there).
     unsigned char* area = static_cast<unsigned char*>(d_ws) + (ws - decoder_area_bytes(chunks)) / 256 * 256;
     unsigned long long* chunk_prefix =
         chunks <= kFewChunks ? nullptr : reinterpret_cast<unsigned long long*>(area);
