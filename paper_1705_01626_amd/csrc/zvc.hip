@@ -2621,7 +2621,9 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 // up to 48 KB: see decompress_direct_kernel.  Beyond, us with kScan4 | kScan8 | two launches.  Up to 32 MB the chip holds all
 // waves at once, and fewer workgroups look for fewer counts; above, the larger workgroups' second turn is the longer one.  Then the
 // pre-pass is as fast or wins: its expand kernel touches no shared state, and may write in any order.  From 44 MB up on streams from
-// memory, from 56 MB at an odd element, where a piece has more to do between its masks and its stores.
+// memory, from 56 MB at an odd element, where a piece has more to do between its masks and its stores (and from 76 MB with three
+// quarters of the elements stored: there two launches were slower, on streams in the caches, than stores that follow the output's
+// alignment, and one is not).
 //   density 0.3, fp32    3 MB 4.6 | 4.6 | 5.8   4 MB 4.65 | 4.7 | 6.0   5 MB 5.2 | 4.8 | 6.1   6.1 MB 5.2 | 4.9 | 6.7   8.5 MB 5.9 | 5.7 |
 //                        6.4   16 MB 7.0 | 6.1 | 7.9   24 MB 8.55 | 7.8 | 9.7   32 MB 10.3 | 10.0 | 11.6   40 MB 12.5 | 13.4 | 13.5
 //                        50 MB 14.7 | 15.9 | 15.0   64 MB 17.8 | 18.3 | 18.2   100 MB 25.6 | 26.8 | 25.1
@@ -2629,15 +2631,22 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 //                        11.7   40 MB 12.7 | 14.5 | 13.9   51 MB 14.9 | 16.1 | 15.0   64 MB 17.9 | 19.5 | 18.6   100 MB 25.8 | 28.5 | 25.9
 //   density 0.9, fp32    24 MB 12.1 | 11.9 | 13.0   50 MB 21.6 | 22.0 | 22.4; 16-bit 64 MB 26.5 | 27.5 | 27.5
 //   at an odd element, 0.3: fp32 32 MB 10.8 | 10.6 | 12.1; 16-bit 52 MB 16.5 | 18.0 | 17.2
+//   at an odd element, one launch (kScan4) | two: fp32 of 0.1 | 0.3 | 0.6 | 0.9, 36 MB 10.5 | 12.5  12.1 | 13.5  13.7 | 14.9  16.3 | 17.6
+//                        46 MB 13.4 | 13.4  14.6 | 14.6  16.0 | 16.7  20.2 | 21.3   55 MB 15.4 | 15.2  16.7 | 16.6  18.6 | 19.1  23.1 | 24.6
+//                        (from memory 15.7 | 15.3  16.6 | 16.6  22.4 | 22.3  23.4 | 24.8)   75 MB 19.2 | 18.6  21.3 | 20.5  23.4 | 24.3  30.1 |
+//                        31.4 (from memory 19.6 | 18.7  21.2 | 20.5  29.2 | 27.3  31.1 | 31.7); 16-bit 55 MB 16.2 | 16.2  17.2 | 17.2  18.9 |
+//                        19.4  23.9 | 25.5   75 MB 20.3 | 20.6  21.8 | 21.8  24.0 | 25.0  31.6 | 32.3 (from memory 20.4 | 20.7  21.8 |
+//                        21.8  30.0 | 28.4  31.8 | 32.3)
 //   from memory, one launch | two: fp32 of 0.1 | 0.3 | 0.6, 40 MB 11.7 | 12.2  12.4 | 12.9  17.2 | 17.6   46 MB 13.1 | 12.8  13.9 | 13.8
 //                        19.2 | 19.7   51 MB 13.9 | 13.7  14.8 | 14.8  20.0 | 20.3; 16-bit 40 MB 12.0 | 12.7  12.6 | 13.5  17.5 | 18.3   46 MB
 //                        13.4 | 13.4  14.1 | 14.2  19.4 | 20.2; with zeros in clusters 51 MB of 0.3 16.7 | 16.2
 // (Two waves: 4 MB 5.2 for 5.4 with a shorter pause, but they need twice the scan state.)
 enum class Decoder { kDirect4, kDirect8, kScan4, kScan8, kTwoLaunches };
-inline Decoder choose_decoder(size_t n, int w, const void* out) {
+inline Decoder choose_decoder(size_t n, int w, const void* out, unsigned long long stored) {
     const size_t bytes = n * static_cast<size_t>(w), masks = 4 * div_up(n, 32);
     if (masks <= (size_t{80} << 10)) return masks <= (size_t{48} << 10) ? Decoder::kDirect4 : Decoder::kDirect8;
-    if (bytes >= (size_t{aligned_to(out, 16) ? 44u : 56u} << 20)) return Decoder::kTwoLaunches;
+    const unsigned one_launch_mb = aligned_to(out, 16) ? 44u : stored >= n / 4 * 3 ? 76u : 56u;
+    if (bytes >= (size_t{one_launch_mb} << 20)) return Decoder::kTwoLaunches;
     return bytes >= (size_t{9} << 19) && bytes <= (size_t{32} << 20) ? Decoder::kScan8 : Decoder::kScan4;
 }
 
@@ -3180,7 +3189,7 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
     const size_t groups = div_up(n, 32);
     const unsigned char* stream_values_at = static_cast<const unsigned char*>(d_comp) + 4 * groups;
     const unsigned long long stored_avail = (comp_bytes - 4 * groups) / static_cast<size_t>(w);
-    const Decoder decoder = choose_decoder(n, w, d_out);
+    const Decoder decoder = choose_decoder(n, w, d_out, stored_avail);
     const Output output = planar_output(d_out, n * static_cast<size_t>(w), w, decoder != Decoder::kTwoLaunches);
     if (decoder != Decoder::kTwoLaunches) {
         const bool eight = decoder == Decoder::kScan8 || decoder == Decoder::kDirect8;

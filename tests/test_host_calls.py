@@ -196,3 +196,48 @@ def test_order_and_occupancy_of_decoding(fake, w, nbytes, density, interleaved, 
     assert len(launched) == 1 and len(lines) == 2
     values = launched[0][0]
     assert (values["choice"], values["lds"] > 0) == (interleaved, bool(seven))
+
+
+ROUTE = re.compile(r"(?:decompress_(direct|scan)_kernelILi(\d)ELN.*?OutputE(\d)ELi(\d)E|17decompress_kernelILi(\d)ELi\d+ELN.*?OutputE(\d)E)")
+OUTPUTS = ("aligned", "loose", "shifted")
+
+
+def routes(fake, calls):
+    """How the planar decoder takes each of the calls (elements, width, the output's first element, density):
+    direct4 | direct8 | scan4 | scan8 | two, and how it writes."""
+    code = "".join("n, w = %d, %d\ncall('zvc_decompress', %d, 4 * -(-n // 32) + w * int(n * %f), n, w, %d, %d, room(n, w), 0)\n"
+                   % (n, w, STAGE, density, OUT + first * w, WS) for n, w, first, density in calls)
+    found = []
+    for _, _, name in run(fake, code):
+        got = ROUTE.search(name)
+        if got is None:
+            assert "mask_prefix_kernel" in name          # the first of two
+            continue
+        one, w, output, waves, two_w, two_output = got.groups()
+        found.append((one + waves if one else "two", OUTPUTS[int(output or two_output)]))
+        assert int(w or two_w) == calls[len(found) - 1][1]
+    assert len(found) == len(calls)
+    return found
+
+
+@pytest.mark.parametrize("w", [4, 2])
+def test_decoder_by_size(fake, w):
+    """Both sides of every limit of the planar decoder (the measurements stand beside the rules)."""
+    masks = 8 * 1024                                     # elements per KB of masks
+    aligned = [(48 * masks, "direct4"), (48 * masks + 32, "direct8"), (80 * masks, "direct8"), (80 * masks + 32, "scan4"),
+               (9 * MB // 2 // w - 1, "scan4"), (9 * MB // 2 // w, "scan8"), (32 * MB // w, "scan8"), (32 * MB // w + 1, "scan4"),
+               (44 * MB // w - 1, "scan4"), (44 * MB // w, "two")]
+    for density in (0.05, 0.5, 0.9):
+        assert routes(fake, [(n, w, 0, density) for n, _ in aligned]) == [(route, "aligned") for _, route in aligned]
+    odd = [(n, route, "loose" if n * w < 8 * MB else "shifted") for n, route in aligned[:-1]] + [
+        (8 * MB // w - 1, "scan8", "loose"), (8 * MB // w, "scan8", "shifted"), (44 * MB // w, "scan4", "shifted"),
+        (56 * MB // w - 1, "scan4", "shifted")]
+    for density in (0.05, 0.5, 0.9):
+        limit = 76 if density == 0.9 else 56
+        more = [(limit * MB // w - 1, "scan4", "shifted"), (limit * MB // w, "two", "shifted")]
+        assert routes(fake, [(n, w, 1, density) for n, _, _ in odd + more]) == [(route, out) for _, route, out in odd + more]
+    # whole 16 bytes that are no line: as they lie in one launch, in two only whole 64 bytes (128 in the largest fp32 outputs)
+    for first, small, large in ((16 // w, "shifted", "shifted"), (64 // w, "aligned", "shifted" if w == 4 else "aligned"),
+                                (128 // w, "aligned", "aligned")):
+        assert routes(fake, [(43 * MB // w, w, first, 0.5), (60 * MB // w, w, first, 0.5), (256 * MB // w, w, first, 0.5)]) == [
+            ("scan4", "aligned"), ("two", small), ("two", large)]
