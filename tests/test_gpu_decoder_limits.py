@@ -16,7 +16,7 @@ KB, MB = 1 << 10, 1 << 20
 
 
 def limits(w):
-    return [m * 8 for m in (48 * KB, 80 * KB)] + [k // w for k in (9 * MB // 2, 8 * MB, 16 * MB, 32 * MB, 44 * MB, 56 * MB)]
+    return [m * 8 for m in (48 * KB, 80 * KB)] + [k // w for k in (9 * MB // 2, 8 * MB, 16 * MB, 32 * MB, 44 * MB, 56 * MB, 76 * MB)]
 
 
 @pytest.mark.parametrize("w", [4, 2])

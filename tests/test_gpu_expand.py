@@ -1,11 +1,12 @@
 """The decoder's staging and expansion at its edges: streams that end anywhere among a wave's
 16-byte chunks and 1 KB loads, value areas at every offset modulo 16 bytes, tensors that end at
-every element of a lane's 16 bytes.  Both decoders, against numpy: what is not there is zero."""
+every element of a lane's 16 bytes.  All decoders, against numpy: what is not there is zero."""
 import numpy as np
 import pytest
 import torch
 
 from paper_1705_01626_amd import zvc
+from tests.decoder_routes import elements
 from tests.gpu_util import raw_bytes, say
 from tests.test_gpu_parity import random_tensor
 from tests.test_gpu_unaligned import assert_guard, guarded
@@ -14,12 +15,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("two_launches", [False, True])
+@pytest.mark.parametrize("route", ["direct4", "scan8", "two"])
 @pytest.mark.parametrize("w", [4, 2])
 @pytest.mark.parametrize("density", [0.1, 0.6, 1.0])
-def test_streams_cut_short_at_every_edge(oracle, w, density, two_launches):
-    step = 4096 // w                                  # elements that a wave expands
-    n = (17 << 20) // w + 3 if two_launches else 5 * step + 3
+def test_streams_cut_short_at_every_edge(oracle, w, density, route):
+    n = elements(route, w)
     x = random_tensor(n, w, density, seed=n + w)
     host = raw_bytes(x).view({2: np.uint16, 4: np.uint32}[w])
     stream = np.ascontiguousarray(oracle.compress_stream(raw_bytes(x), w))

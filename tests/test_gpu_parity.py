@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_1705_01626_amd import workloads, zvc
+from tests.decoder_routes import ROUTES, elements
 from tests.gpu_util import assert_parity, raw_bytes, say
 
 pytestmark = pytest.mark.gpu
@@ -229,26 +230,33 @@ def test_scan_wait_that_helps_itself(oracle):
 
 
 def test_single_launch_decoder_scan_that_helps_itself(oracle):
-    """Tensors below 16 MB decode in one launch whose workgroups find their offsets with the
+    """All but the smallest and the largest tensors decode in one launch whose workgroups find their offsets with the
     device-wide scan.  With zero patience on the decoder's workspace (the stream comes from a call
     on another one) every wait computes the missing workgroup's popcount itself; the output must
-    not change, and the workspace must be clean for the next call."""
-    for w, n in ((4, 3999999), (2, 8000001), (4, 4194303), (4, 4194304), (2, 33)):   # up to the 16 MB limit and just past it
+    not change, and the workspace must be ready for the next call.  Workgroups of 4 and 8 waves, outputs that
+    begin in the middle of a line (from 8 MB), and both other decoders."""
+    sizes = [(4, 3999999, 0), (2, 8000001, 0), (4, 4194303, 0), (4, 4194304, 0), (2, 33, 0)]
+    sizes += [(w, elements(route, w, first), first) for w in (4, 2) for first in (0, 1) for route in ROUTES if route != "direct8"]
+    helped_in_scans = 0
+    for w, n, first in sizes:
         x = random_tensor(n, w, 0.37, seed=n)
         res = assert_parity(x, oracle, "decoder input")
         ws = zvc.new_workspace(n, w, DEV)
         zvc.zvc_workspace_set_lookback_patience(ws, 0)
-        out = torch.empty_like(x)
-        out.view(torch.uint8).fill_(0x5A)
-        say("zero-patience decode n=%d w=%d" % (n, w))
+        room = torch.empty(first + n, dtype=x.dtype, device=DEV)
+        room.view(torch.uint8).fill_(0x5A)
+        out = room[first:]
+        say("zero-patience decode n=%d w=%d first=%d" % (n, w, first))
         zvc.zvc_decompress(res["comp"], res["bytes"], out, ws)
         torch.cuda.synchronize()
-        assert torch.equal(out.view(torch.uint8), x.view(torch.uint8))
+        assert torch.equal(out, x)
         helped = zvc.zvc_workspace_self_help_count(ws)
         say("self-help events while decoding: %d" % helped)
-        if n * w < (16 << 20) and n > 100000:
-            assert helped > 0
+        scans = elements("direct8", w) < n < elements("two", w, first)
+        assert scans or helped == 0
+        helped_in_scans += helped
         assert_parity(x, oracle, "the same workspace afterwards", ws)
+    assert helped_in_scans > 0
 
 
 def test_self_help_is_rare_in_normal_runs(oracle):
@@ -277,17 +285,18 @@ def test_self_help_is_rare_in_normal_runs(oracle):
 def test_small_decode_then_large_encode_on_one_workspace(oracle):
     """The decoder's scratch arrays must not land where a later, larger encoder
     call on the same workspace keeps its scan state."""
-    big_n, small_n, w = 40 * (1 << 20) + 5, 300007, 4
-    ws = zvc.new_workspace(big_n, w, DEV)
-    small = random_tensor(small_n, w, 0.999, seed=5)      # dense: large decoder prefix words
-    res = assert_parity(small, oracle, "small tensor on a large workspace", ws)
-    big = random_tensor(big_n, w, 0.3, seed=6)
-    assert_parity(big, oracle, "large tensor after it", ws)
-    out = torch.empty_like(small)
-    zvc.zvc_decompress(res["comp"], res["bytes"], out, ws)
-    assert_parity(big, oracle, "large tensor again, after a small decode", ws)
-    torch.cuda.synchronize()
-    assert torch.equal(out, small)
+    big_n, w = 40 * (1 << 20) + 5, 4
+    for small_n in (300007, elements("scan4", w), elements("two", w)):
+        ws = zvc.new_workspace(big_n, w, DEV)
+        small = random_tensor(small_n, w, 0.999, seed=5)      # dense: large decoder prefix words
+        res = assert_parity(small, oracle, "small tensor on a large workspace", ws)
+        big = random_tensor(big_n, w, 0.3, seed=6)
+        assert_parity(big, oracle, "large tensor after it", ws)
+        out = torch.empty_like(small)
+        zvc.zvc_decompress(res["comp"], res["bytes"], out, ws)
+        assert_parity(big, oracle, "large tensor again, after a small decode", ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, small)
 
 
 def test_decoder_many_chunks_and_reuse(oracle):
@@ -295,11 +304,13 @@ def test_decoder_many_chunks_and_reuse(oracle):
     finish prefixes the chunk totals and resets its counter.  Sizes from one
     chunk to several hundred, the same workspace reused back to back."""
     w = 4
-    n_max = 4096 * 32 * 300 + 12345
+    chunk = 4096 * 32
+    n_max = chunk * 300 + 12345
     ws = zvc.new_workspace(n_max, w, DEV)
-    # (tensors below 16 MB decode in one launch, without the pre-pass: the sizes from 33 chunks up take it)
-    for n in (4096 * 32, 4096 * 32 + 1, 4096 * 32 * 2 - 1, n_max, 4096 * 32 * 7 + 31, 1000,
-              4096 * 32 * 33 - 1, 4096 * 32 * 40 + 5, 4096 * 32 * 32, 4096 * 32 * 32 - 1):
+    # (smaller tensors decode in one launch, without the pre-pass: the sizes from 91 chunks up take it)
+    assert chunk * 91 - 1 >= elements("two", w)
+    for n in (chunk, chunk + 1, chunk * 2 - 1, n_max, chunk * 7 + 31, 1000, chunk * 33 - 1, chunk * 40 + 5, chunk * 32, chunk * 32 - 1,
+              chunk * 91 - 1, chunk * 91, chunk * 91 + 1, chunk * 128, chunk * 256 + 33, chunk * 100 + 5):
         x = random_tensor(n, w, 0.41, seed=n)
         assert_parity(x, oracle, "pre-pass chunks n=%d" % n, ws=ws)
 
@@ -308,14 +319,16 @@ def test_decoder_survives_garbage_stream(oracle):
     """Random bytes as a compressed stream: masks then claim any number of stored elements, but
     reads are clamped to comp_bytes and a step never stages more than it has room for, so the
     kernels finish normally; the workspace stays usable."""
-    for w, n in ((4, 700001), (2, 1300003), (4, 6000011), (2, 9000001)):     # one launch | pre-pass + expand
+    sizes = [(4, 700001, 0), (2, 1300003, 0), (4, 6000011, 0), (2, 9000001, 0)]
+    sizes += [(w, elements(route, w, first, True) + 8, first) for w in (4, 2) for first in (0, 1) for route in ROUTES]
+    for w, n, first in sizes:
         g = torch.Generator(device="cpu").manual_seed(n)
         cap = zvc.zvc_max_compressed_bytes(n, w)
         junk = torch.randint(0, 256, (cap,), generator=g, dtype=torch.uint8).to(DEV)
         ws = zvc.new_workspace(n, w, DEV)
-        out = torch.empty(n, dtype=DTYPES[w], device=DEV)
+        out = torch.empty(first + n, dtype=DTYPES[w], device=DEV)[first:]
         for comp_bytes in (cap, 4 * ((n + 31) // 32), 4 * ((n + 31) // 32) + w * (n // 3)):
-            say("garbage stream w=%d comp_bytes=%d" % (w, comp_bytes))
+            say("garbage stream w=%d n=%d first=%d comp_bytes=%d" % (w, n, first, comp_bytes))
             zvc.zvc_decompress(junk, comp_bytes, out, ws)
             torch.cuda.synchronize()
         x = random_tensor(n, w, 0.4, seed=1)

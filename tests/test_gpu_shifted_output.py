@@ -1,6 +1,6 @@
-"""Outputs that begin anywhere in a 128-byte line: the decoder's pieces then begin at the first line, in the
-middle of a mask, and the first wave writes what lies before.  Every offset; sizes around the shift, a mask, a
-wave's piece, a workgroup, and (two launches) around a chunk of the pre-pass; streams that end early."""
+"""Outputs that begin anywhere in a 128-byte line: from 8 MB on the decoder's pieces then begin at the first line, in the
+middle of a mask, and the first wave writes what lies before; smaller ones are written as they lie.  Every offset; sizes around
+the shift, a mask, a wave's piece, a workgroup, and (two launches) around a chunk of the pre-pass; streams that end early."""
 import numpy as np
 import pytest
 import torch
@@ -15,10 +15,39 @@ DEV = "cuda"
 LINE, PIECE = 128, 4096
 
 
-def decode(x, oracle, offset, label, cut=0):
+MB = 1 << 20
+CHUNK = 131072                                   # elements of a chunk of the pre-pass
+
+
+def every_offset(w):
+    """(elements, first element, density) of outputs in whole lines, at every offset that is written so: one launch where
+    the output is not 16-byte aligned, two where it is not 64-byte aligned (128 in the largest outputs of 32 bits)."""
+    line, step = LINE // w, 16 // w
+    one, two = 8 * MB // w + 77, 45 * MB // w + 77
+    return ([(one, first, 0.5) for first in range(line) if first % step] +
+            [(two, first, 0.5) for first in range(0, line, step) if first * w % 64] +
+            [(257 * MB // w + 5, 64 // w, 0.1)] * (w == 4))
+
+
+def chunk_edges(w):
+    """Two launches, a shift of one element, of almost a line and on both sides of a mask."""
+    line, chunks = LINE // w, 57 * MB // w // CHUNK + 1
+    return [(chunks * CHUNK + more, first, (0.3, 0.7, 0.05)[k % 3])
+            for k, first in enumerate((1, line // 2 - 1, line // 2 + 1, line - 1, line - 16 // w))
+            for more in ((0, 1) if k % 2 else (-first, line - first))]
+
+
+def early_ends(w):
+    """(elements, first element, stored elements that are missing): as it lies, one launch with 4 waves and 8, two launches."""
+    return [(5000, 3, 1), (5000, 3, 700), (PIECE // w + 20, 1, 5), (40, 1, 12), (9 * MB // w, 5, 1000), (36 * MB // w + 9, 7, 3000),
+            (57 * MB // w + 3, 1, 1), (57 * MB // w + 3, 5, 5000), (57 * MB // w + 3, LINE // w - 3, 3 * MB // w)]
+
+
+def decode(x, oracle, offset, label, cut=0, stream=None):
     n, w = x.numel(), x.element_size()
     host = raw_bytes(x)
-    stream = oracle.compress_stream(host, w)
+    if stream is None:
+        stream = oracle.compress_stream(host, w)
     comp = torch.from_numpy(stream).to(DEV)
     base, out = guarded(n, x.dtype, offset)
     say("%s n=%d w=%d offset %d cut %d" % (label, n, w, offset, cut))
@@ -45,23 +74,30 @@ def test_every_offset(oracle, w):
 
 
 @pytest.mark.parametrize("w", [4, 2])
+def test_every_offset_in_whole_lines(oracle, w):
+    made = {}
+    for n, first, density in every_offset(w):
+        if n not in made:
+            x = random_tensor(n, w, density, seed=n)
+            made = {n: (x, oracle.compress_stream(raw_bytes(x), w))}
+        decode(made[n][0], oracle, first, "whole lines", stream=made[n][1])
+
+
+@pytest.mark.parametrize("w", [4, 2])
 def test_chunk_edges(oracle, w):
-    chunk, line = 131072, LINE // w
-    chunks = (40 << 20) // w // chunk
-    for k, offset in enumerate((1, 2, line // 2 - 1, line // 2, line // 2 + 1, line - 1)):
-        for n in (chunks * chunk, chunks * chunk + 1, chunks * chunk - offset, chunks * chunk + line - offset):
-            x = random_tensor(n, w, (0.3, 0.9, 0.05)[k % 3], seed=n + k)
-            decode(x, oracle, offset, "chunk edge")
+    for n, first, density in chunk_edges(w):
+        decode(random_tensor(n, w, density, seed=n + first), oracle, first, "chunk edge")
 
 
 @pytest.mark.parametrize("w", [4, 2])
 def test_many_chunks_and_both_orders(oracle, w):
     """More chunks than the workgroups add up themselves, and the interleaved order."""
-    for n, density, offset in ((1025 * 131072 + 5, 0.04, 3), ((70 << 20) // w + 1, 0.04, 5), ((70 << 20) // w + 1, 0.5, 7)):
+    for n, density, offset in ((1025 * CHUNK + 5, 0.04, 3), ((77 << 20) // w + 1, 0.04, 5), ((77 << 20) // w + 1, 0.5, 7),
+                               ((77 << 20) // w + 1, 0.9, LINE // w - 5)):
         decode(random_tensor(n, w, density, seed=n), oracle, offset, "large")
 
 
 @pytest.mark.parametrize("w", [4, 2])
 def test_streams_that_end_early(oracle, w):
-    for n, offset, cut in ((5000, 3, 1), (5000, 3, 700), (PIECE // w + 20, 1, 5), (40, 1, 12), (9 << 20, 5, 1000)):
+    for n, offset, cut in early_ends(w):
         decode(random_tensor(n, w, 0.6, seed=n), oracle, offset, "early end", cut)

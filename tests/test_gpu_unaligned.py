@@ -1,12 +1,13 @@
 """Outputs and inputs that begin at any element of a larger buffer: every offset
 modulo 16 bytes, sizes at the edges of a lane's 16 bytes, a wave's 4 KB and a
-workgroup's 16 KB, and one size that takes the two-launch decoder.  Bit exact
+workgroup's 16 KB, and one size that takes the scan, one that takes two launches.  Bit exact
 against the oracle; the bytes around the output keep their values."""
 import numpy as np
 import pytest
 import torch
 
 from paper_1705_01626_amd import zvc
+from tests.decoder_routes import elements
 from tests.gpu_util import raw_bytes, say
 from tests.test_gpu_parity import random_tensor
 
@@ -36,8 +37,7 @@ def sizes(w):
 
 @pytest.mark.parametrize("w,offset", [(4, k) for k in (1, 2, 3)] + [(2, k) for k in range(1, 8)])
 def test_decoders_at_every_output_offset(oracle, w, offset):
-    big = (17 << 20) // w + 5                       # above the single-launch decoder's limit
-    for n in sizes(w) + [big]:
+    for n in sizes(w) + [elements("scan8", w) + 2, elements("two", w, offset) + 2]:
         x = random_tensor(n, w, 0.45, seed=n + offset)
         host = raw_bytes(x)
         ws = zvc.new_workspace(n, w, DEV)

@@ -9,6 +9,8 @@ import sys
 import pytest
 
 from paper_1705_01626_amd import build as zvc_build
+from tests import test_gpu_shifted_output as shifted
+from tests.decoder_routes import ROUTES, elements
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COMPUTE, COPY = 0x1000, 0x2000
@@ -241,3 +243,25 @@ def test_decoder_by_size(fake, w):
                                 (128 // w, "aligned", "aligned")):
         assert routes(fake, [(43 * MB // w, w, first, 0.5), (60 * MB // w, w, first, 0.5), (256 * MB // w, w, first, 0.5)]) == [
             ("scan4", "aligned"), ("two", small), ("two", large)]
+
+
+@pytest.mark.parametrize("w", [4, 2])
+def test_sizes_of_the_decoder_tests(fake, w):
+    """The sizes that the GPU tests use for a kernel take that kernel."""
+    for first in (0, 1, 16 // w):
+        for density in (0.05, 0.6, 1.0):
+            calls = [(elements(route, w, first, density > 0.7), w, first, density) for route in ROUTES]
+            assert [route for route, _ in routes(fake, calls)] == [route.split()[0] for route in ROUTES]
+
+
+@pytest.mark.parametrize("w", [4, 2])
+def test_sizes_of_the_shifted_outputs_tests(fake, w):
+    offsets = shifted.every_offset(w)
+    got = routes(fake, [(n, w, first, density) for n, first, density in offsets])
+    assert [out for _, out in got] == ["shifted"] * len(offsets) and {route for route, _ in got} == {"scan8", "two"}
+    edges = shifted.chunk_edges(w)
+    assert routes(fake, [(n, w, first, density) for n, first, density in edges]) == [("two", "shifted")] * len(edges)
+    ends = shifted.early_ends(w)
+    assert {out for _, out in routes(fake, [(n, w, first, 0.6) for n, first, _ in ends[:4]])} == {"loose"}
+    assert routes(fake, [(n, w, first, 0.6) for n, first, _ in ends[4:]]) == [
+        ("scan8", "shifted"), ("scan4", "shifted")] + [("two", "shifted")] * 3
