@@ -104,7 +104,8 @@ zvc_status zvc_check_stream(const void* h_comp, uint64_t bytes, size_t n, int w)
  * wait always ends.  Default 2000 (about a millisecond); 0 makes every wait
  * help at once, which tests use to exercise that path.  The setting belongs to
  * the workspace (a word in its header, written on `stream`; zvc_workspace_init
- * restores the default) and applies to the encoder calls that use it. */
+ * restores the default) and applies to the calls that use it: the encoders, and
+ * zvc_decompress where it scans. */
 zvc_status zvc_workspace_set_lookback_patience(void* d_ws, unsigned polls, hipStream_t stream);
 
 /* Measurement aid, not part of the method: enqueues a plain streaming kernel

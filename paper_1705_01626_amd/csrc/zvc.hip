@@ -13,7 +13,7 @@
 //   * the offset of a tile's first kept element in the packed stream -- where
 //     the next mask goes, a serial chain in the paper's hardware -- is a
 //     device-wide exclusive scan of per-tile counts done in the same pass:
-//     every tile publishes its count, every 256th tile a running prefix, and a
+//     every tile publishes its count, every 512th tile a running prefix, and a
 //     tile adds the counts between the nearest published prefix and itself;
 //   * kept elements are staged by each wave in an LDS queue in packed order and
 //     leave as whole 128-byte lines; masks leave as one contiguous run per wave.
@@ -22,8 +22,8 @@
 // alone, so a small pre-pass over the masks computes it for every 32 masks; the
 // expand kernel's waves then work independently: each stages its packed run in
 // LDS with aligned 16-byte loads and rebuilds 16 bytes of output per lane from
-// "bit ? next stored element : zero".  Small tensors decode in one launch that
-// uses the encoder's scan instead of the pre-pass.
+// "bit ? next stored element : zero".  Below some tens of megabytes a tensor decodes in one launch that
+// uses the encoder's scan instead of the pre-pass, and the smallest without either.
 //
 // Three variants share these kernels: a fused ReLU + ZVC encoder
 // (pre-activations in, stream of ReLU(x) out), an encoder that writes into a
@@ -155,8 +155,9 @@ static_assert(sizeof(WsHeader) == kHeaderBytes, "header size");
 // computed by waiting tiles, the last tile first sees to it that their owners have started, see
 // scan_end.)  So no tile waits for its stores or counts itself finished, and the call does not end with
 // a clean-up.  us with words that the last tile zeroed once all had counted themselves finished | now, the other
-// changes of the scan included: fp32 256 KB 4.50 | 3.98, 6.4 MB 6.83 | 5.82, 24 MB 9.66 | 9.14, 100 MB 27.6 | 26.4, 300 MB
-// 72.9 | 70.6; bf16 4 MB 6.35 | 5.53, 200 MB 55.6 | 53.0; decoding fp32 6.4 MB 6.35 | 5.8.
+// changes of the scan included: fp32 256 KB 4.63 | 4.02, 6.4 MB 6.12 | 5.38, 24 MB 9.4 | 9.1, 100 MB 29.3 | 28.4, 300 MB
+// 77.0 | 75.2; bf16 4 MB 5.9 | 5.4, 200 MB 58.9 | 57.0, 600 MB 163.6 | 156.1.  (A call that zeroes what only the call
+// before it had: 16 KB after 800 MB 27 us instead of 6.2.)
 constexpr int kCallShift = 16;                // of a count's word; of a wide one the number's lowest bits
 constexpr int kCallBits = 15, kTermBits = kCallBits - 1;
 constexpr unsigned kCountOwner = 1u << 15, kCountBits = kCountOwner - 1u;
@@ -667,9 +668,9 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
     // at once with kNoPause: a line of counts that many tiles read while others still write it costs all
     // of them more.  us, encoding, at once | a round trip later | 0.3 us asleep: fp32 6.4 MB 6.1 | 5.8 | 6.1, 64 MB
     // 20.4 | 17.3 | 19.5, 300 MB 73.8 | 70.7 | 73.6 (waiting for the tile in front first, alone: 6.9, 21.3, 75.8); with 8
-    // sleeps more 6.4 MB 5.8 | 5.8, 12 MB 7.1 | 7.2.  Decoding, whose workgroups have their counts all at the same time, a round trip |
-    // and 8 | 12 | 16 | 24 sleeps: fp32 6.4 MB 5.7 | 4.85 | 4.9 | 4.9 | 5.1, 16 MB 7.0 | 6.55 | 6.05 | 6.1 | 6.3, 24 MB 9.3 |
-    // 8.2 | 7.9 | 7.7 | 7.9; bf16 6 MB 5.9 | 5.1 | 5.0 | 5.05 | 5.3.
+    // sleeps more 6.4 MB 5.8 | 5.8, 12 MB 7.1 | 7.2.  Decoding, whose workgroups have their counts all at the same time, a round trip
+    // and 10 | 12 | 14 | 16 | 18 sleeps: fp32 6.4 MB 5.17 | 5.05 | 5.03 | 5.03 | 5.10 (without 5.7), 12 MB 6.05 | 5.78 | 5.77 | 5.79 |
+    // 5.85, 40 MB 13.06 | 12.87 | 12.76 | 12.76 | 12.80; bf16 20 MB 8.25 | 8.15 | 8.07 | 8.06 | 8.09.
     unsigned long long patience_word = 0;
     if (PAUSE != kNoPause) patience_word = uniform(load64(&st.hdr->patience_plus_one));
     if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
@@ -1425,8 +1426,8 @@ __global__ __launch_bounds__(kThreads) void mask_prefix_kernel(
     if (tid == 0) {
         store32(chunk_total + chunk, s_wave_total[0] + s_wave_total[1]);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the total is out before the count moves
-        // counted like the encoder's tiles: atomics on one address cost about 11 ns
-        // each here, so the arrivals are spread over 64 counters with one on top
+        // atomics on one address cost about 11 ns each here, so the arrivals are
+        // spread over 64 counters with one on top
         const unsigned slot = chunk % kFinishLanes;
         const unsigned quota = num_chunks / kFinishLanes + (slot < num_chunks % kFinishLanes ? 1u : 0u);
         unsigned last = 0;
@@ -1706,7 +1707,7 @@ __device__ __forceinline__ void expand_shifted(unsigned char* lds, unsigned slic
                                                unsigned char* __restrict__ out, bool stream_values, int lane) {
     if (elem0 == 0 && shift.elements != 0)
         expand_head<W>(values, values_avail, lane_value(own, 0), lane_value(own, 1),
-                       shift.elements < n ? shift.elements : static_cast<unsigned>(n), out, lane);
+                       shift.elements, out, lane);      // (a shifted output is larger than that, see planar_output)
     if (elem0 + shift.elements >= n) return;
     if (W == 2 && shift.groups != 0) first += static_cast<unsigned>(__popc(lane_value(own, 0)));
     expand_shifted_step<W>(lds, slice, values, values_avail, first, mask, next, shift, elem0 + shift.elements, n, out,
@@ -1833,7 +1834,7 @@ struct CountMaskTile {
     const unsigned* masks;
     size_t num_groups;
     unsigned tail;                 // n % 32
-    int tile_masks;                // masks per workgroup: 128 | 256
+    int tile_masks;                // masks per workgroup: 128 to 512
     // set bits in the masks of workgroup q, wave-uniform
     __device__ unsigned operator()(unsigned q, int lane) const {
         unsigned count = 0;
@@ -2621,9 +2622,9 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 // up to 48 KB: see decompress_direct_kernel.  Beyond, us with kScan4 | kScan8 | two launches.  Up to 32 MB the chip holds all
 // waves at once, and fewer workgroups look for fewer counts; above, the larger workgroups' second turn is the longer one.  Then the
 // pre-pass is as fast or wins: its expand kernel touches no shared state, and may write in any order.  From 44 MB up on streams from
-// memory, from 56 MB at an odd element, where a piece has more to do between its masks and its stores (and from 76 MB with three
-// quarters of the elements stored: there two launches were slower, on streams in the caches, than stores that follow the output's
-// alignment, and one is not).
+// memory (dense ones: one launch is ahead up to 60 MB, and in the caches at 0.6 as well), from 56 MB at an odd element, where a
+// piece has more to do between its masks and its stores (and from 76 MB with three quarters of the elements stored: there two
+// launches were slower, on streams in the caches, than stores that follow the output's alignment, and one is not).
 //   density 0.3, fp32    3 MB 4.6 | 4.6 | 5.8   4 MB 4.65 | 4.7 | 6.0   5 MB 5.2 | 4.8 | 6.1   6.1 MB 5.2 | 4.9 | 6.7   8.5 MB 5.9 | 5.7 |
 //                        6.4   16 MB 7.0 | 6.1 | 7.9   24 MB 8.55 | 7.8 | 9.7   32 MB 10.3 | 10.0 | 11.6   40 MB 12.5 | 13.4 | 13.5
 //                        50 MB 14.7 | 15.9 | 15.0   64 MB 17.8 | 18.3 | 18.2   100 MB 25.6 | 26.8 | 25.1
@@ -2639,7 +2640,9 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 //                        21.8  30.0 | 28.4  31.8 | 32.3)
 //   from memory, one launch | two: fp32 of 0.1 | 0.3 | 0.6, 40 MB 11.7 | 12.2  12.4 | 12.9  17.2 | 17.6   46 MB 13.1 | 12.8  13.9 | 13.8
 //                        19.2 | 19.7   51 MB 13.9 | 13.7  14.8 | 14.8  20.0 | 20.3; 16-bit 40 MB 12.0 | 12.7  12.6 | 13.5  17.5 | 18.3   46 MB
-//                        13.4 | 13.4  14.1 | 14.2  19.4 | 20.2; with zeros in clusters 51 MB of 0.3 16.7 | 16.2
+//                        13.4 | 13.4  14.1 | 14.2  19.4 | 20.2; with zeros in clusters 51 MB of 0.3 16.7 | 16.2; fp32 of 0.9, 46 MB
+//                        20.3 | 21.6   60 MB 24.8 | 26.0; in the caches of 0.6 | 0.9, 46 MB 15.5 | 16.5  20.0 | 20.9   60 MB 18.9 | 20.3
+//                        24.7 | 25.7 (from memory of 0.6 23.3 | 22.7)
 // (Two waves: 4 MB 5.2 for 5.4 with a shorter pause, but they need twice the scan state.)
 enum class Decoder { kDirect4, kDirect8, kScan4, kScan8, kTwoLaunches };
 inline Decoder choose_decoder(size_t n, int w, const void* out, unsigned long long stored) {

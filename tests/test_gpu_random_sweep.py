@@ -16,7 +16,7 @@ DEV = "cuda"
 DTYPES = {4: torch.int32, 2: torch.int16}
 CASES = int(os.environ.get("ZVC_SWEEP_CASES", "60"))      # more cases for a longer run
 SEED = int(os.environ.get("ZVC_SWEEP_SEED", "20240607"))
-MAX_N = int(os.environ.get("ZVC_SWEEP_MAX_N", str(5 << 20)))   # (the 16 KB tile kernels, and 32 KB for fp32 from 16 MB)
+MAX_N = int(os.environ.get("ZVC_SWEEP_MAX_N", str(5 << 20)))   # (the 16 KB tile kernels, and 32 KB for fp32 from 14 MB)
 LARGE_N = {4: (9 << 20) + 1, 2: (24 << 20) + 1}                # the 32 KB tile kernels, but for the windowed 16-bit one
 
 
