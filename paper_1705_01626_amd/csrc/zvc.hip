@@ -1938,9 +1938,9 @@ __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_sca
 // itself, 16 bytes a thread and eight of them on their way at a time.  That is one round trip to memory where the scan takes
 // three (count, wait, look), and it is work that grows with the square of the tensor.  Workgroups begin
 // at different places, so that they do not all ask the same channel of the L2 at a time (a cold 4 MB
-// stream 6.3 -> 5.9 us).  us, scan | here with 4 | 8 waves: fp32 0.25 MB 4.2 | 3.25 | 3.6, 1 MB 4.3 | 3.5 | 3.7, 2 MB 4.5 | 4.1 |
-// 4.0, 3 MB 4.55 | 4.7 | 4.5, 4 MB 4.65 | 5.2 | 4.65 (from memory 5.1 | 5.9 | 5.4); bf16 0.25 MB 4.4 | 3.45 | 3.8, 1 MB 4.45 | 4.1 |
-// 4.1, 2 MB 4.6 | 5.3 | 4.7.
+// stream 6.3 -> 5.9 us).  us, scan | here with 4 | 8 waves: fp32 0.25 MB 4.4 | 3.4 | 3.5, 1 MB 4.4 | 3.6 | 3.65, 2 MB 4.5 | 4.0 |
+// 3.9, 3 MB 4.7 | 4.5 | 4.4, 4 MB 4.7 | 5.1 | 4.6 (from memory 5.1 | 5.9 | 5.4); 16-bit 0.25 MB 4.5 | 3.5 | 3.7, 1 MB 4.55 | 4.0 |
+// 4.0, 2 MB 4.7 | 5.1 | 4.6, 4 MB 4.9 | 7.3 | 5.9.
 template <int W, Output OUTPUT, int WV>
 __global__ __launch_bounds__(WV * kWaveSize) void decompress_direct_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
@@ -2625,13 +2625,13 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 // memory (dense ones: one launch is ahead up to 60 MB, and in the caches at 0.6 as well), from 56 MB at an odd element, where a
 // piece has more to do between its masks and its stores (and from 76 MB with three quarters of the elements stored: there two
 // launches were slower, on streams in the caches, than stores that follow the output's alignment, and one is not).
-//   density 0.3, fp32    3 MB 4.6 | 4.6 | 5.8   4 MB 4.65 | 4.7 | 6.0   5 MB 5.2 | 4.8 | 6.1   6.1 MB 5.2 | 4.9 | 6.7   8.5 MB 5.9 | 5.7 |
-//                        6.4   16 MB 7.0 | 6.1 | 7.9   24 MB 8.55 | 7.8 | 9.7   32 MB 10.3 | 10.0 | 11.6   40 MB 12.5 | 13.4 | 13.5
-//                        50 MB 14.7 | 15.9 | 15.0   64 MB 17.8 | 18.3 | 18.2   100 MB 25.6 | 26.8 | 25.1
-//                16-bit  4 MB 4.8 | 4.9 | 6.2   6 MB 5.4 | 5.0 | 6.4   12 MB 6.2 | 5.9 | 7.1   19 MB 7.7 | 7.3 | 8.9   30 MB 10.2 | 9.8 |
-//                        11.7   40 MB 12.7 | 14.5 | 13.9   51 MB 14.9 | 16.1 | 15.0   64 MB 17.9 | 19.5 | 18.6   100 MB 25.8 | 28.5 | 25.9
-//   density 0.9, fp32    24 MB 12.1 | 11.9 | 13.0   50 MB 21.6 | 22.0 | 22.4; 16-bit 64 MB 26.5 | 27.5 | 27.5
-//   at an odd element, 0.3: fp32 32 MB 10.8 | 10.6 | 12.1; 16-bit 52 MB 16.5 | 18.0 | 17.2
+//   density 0.3, fp32    3 MB 4.7 | 4.8 | 6.5   4 MB 4.7 | 4.8 | 6.5   5 MB 5.2 | 4.9 | 6.5   6.1 MB 5.1 | 5.0 | 7.0   8.5 MB 5.85 | 5.8 |
+//                        6.8   16 MB 6.8 | 6.15 | 7.9   24 MB 8.3 | 7.6 | 9.5   32 MB 10.1 | 10.1 | 11.4   40 MB 12.5 | 13.4 | 13.1
+//                        50 MB 14.7 | 15.9 | 14.7   64 MB 17.7 | 18.8 | 17.7   100 MB 25.4 | 27.0 | 24.8
+//                16-bit  4 MB 4.9 | 5.0 | 6.55   6 MB 5.3 | 5.1 | 6.7   12 MB 6.4 | 5.9 | 7.35   19 MB 7.6 | 7.5 | 8.7   30 MB 10.2 | 9.9 |
+//                        11.3   40 MB 12.6 | 14.9 | 13.4   51 MB 15.15 | 17.65 | 15.2   64 MB 18.0 | 20.2 | 18.3   100 MB 26.0 | 29.3 | 25.3
+//   density 0.9, fp32    24 MB 12.0 | 11.7 | 13.2   50 MB 21.3 | 23.8 | 22.5; 16-bit 64 MB 26.2 | 29.3 | 27.0
+//   at an odd element, 0.3: fp32 32 MB 10.7 | 10.8 | 11.9; 16-bit 52 MB 16.5 | 17.75 | 16.2
 //   at an odd element, one launch (kScan4) | two: fp32 of 0.1 | 0.3 | 0.6 | 0.9, 36 MB 10.5 | 12.5  12.1 | 13.5  13.7 | 14.9  16.3 | 17.6
 //                        46 MB 13.4 | 13.4  14.6 | 14.6  16.0 | 16.7  20.2 | 21.3   55 MB 15.4 | 15.2  16.7 | 16.6  18.6 | 19.1  23.1 | 24.6
 //                        (from memory 15.7 | 15.3  16.6 | 16.6  22.4 | 22.3  23.4 | 24.8)   75 MB 19.2 | 18.6  21.3 | 20.5  23.4 | 24.3  30.1 |
