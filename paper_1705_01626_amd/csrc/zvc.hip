@@ -149,8 +149,8 @@ static_assert(sizeof(WsHeader) == kHeaderBytes, "header size");
 // counts have the number of wide calls so far, of which there cannot be 2^45.  Neither kind passes for the other, nor what the
 // decoder's pre-pass leaves in the same bytes for either: the two highest bits of each 32 are 1x in a count of 32 bits,
 // 0x and 01 in the lower and upper half of one of 64, 00 in the pre-pass's arrays.
-// A call's prefixes replace what the one before left, and the few that only that one had are zeroed.
-// The last tile counts the call in the header: it has every tile's count by then, and a tile's count is out
+// A call's prefixes replace what the one before left.
+// The last tile zeroes the few that only that one had, and counts the call in the header: it has every tile's count by then, and a tile's count is out
 // after its waves have read the word there, so nobody reads it later.  (If counts were
 // computed by waiting tiles, the last tile first sees to it that their owners have started, see
 // scan_end.)  So no tile waits for its stores or counts itself finished, and the call does not end with
@@ -183,7 +183,7 @@ struct ScanCalls {
     __host__ __device__ unsigned long long word() const {
         return static_cast<unsigned long long>(limit) << 32 | prefixes << kCallBits | call;
     }
-    __host__ __device__ bool wide(unsigned tiles) const { return limit != 0u && tiles > limit; }
+    __host__ __device__ bool wide(unsigned tiles) const { return limit - 1u < tiles - 1u; }
     __host__ __device__ ScanCalls next(unsigned tiles, unsigned prefixes_left) const {
         ScanCalls after = *this;
         after.call = (call + 1u) % (1u << kCallBits);
@@ -539,6 +539,13 @@ __device__ __forceinline__ unsigned wave_scan_small(unsigned v) {
     return v;
 }
 
+// Adds to the tile's arrival word in LDS, by one lane, and returns what was there.
+__device__ __forceinline__ unsigned arrive(unsigned* word, unsigned v) {
+    unsigned none = 0;
+    asm("" : "+v"(none));          // (or the compiler makes code for a sum over many lanes)
+    return __hip_atomic_fetch_add(word + none, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // One call's view of the scan state.
 struct ScanState {
     WsHeader* hdr;
@@ -614,12 +621,9 @@ struct ScanState {
         exchange64(prefix(tile >> block_shift), tag() << kTagShift | upto);
     }
     __host__ __device__ bool ends_block(unsigned tile) const { return ((tile + 1u) & ((1u << block_shift) - 1u)) == 0u; }
-    // The tile's share of the prefixes that only the call before had, by one of its waves.
-    __host__ __device__ void zero_prefixes_left(unsigned tile, unsigned num_tiles, int lane) const {
-        const unsigned now = num_tiles >> block_shift;
-        if (__builtin_expect(calls.prefixes <= now || tile >= kMostPrefixes, 1)) return;
-        for (unsigned i = now + tile * kWaveSize + lane; i < calls.prefixes; i += min(num_tiles, kMostPrefixes) * kWaveSize)
-            *prefix(i) = 0ull;
+    // The prefixes that only the call before had, by one wave.
+    __host__ __device__ void zero_prefixes_left(unsigned num_tiles, int lane) const {
+        for (unsigned i = (num_tiles >> block_shift) + lane; i < calls.prefixes; i += kWaveSize) *prefix(i) = 0ull;
     }
 };
 
@@ -761,6 +765,7 @@ __device__ inline void scan_end(const ScanState& st, unsigned num_tiles, int lan
             while (!st.has_started(tile)) __builtin_amdgcn_s_sleep(kPollSleep);
         if (lane == 0) store64(&st.hdr->helped_here, 0ull);
     }
+    st.zero_prefixes_left(num_tiles, lane);
     if (lane != 0) return;
     store64(&st.hdr->scan_word, st.calls.next(num_tiles, num_tiles >> st.block_shift).word());
     if (__builtin_expect(st.wide != 0u, 0)) atomicAdd(&st.hdr->wide_calls, 1ull);
@@ -1191,8 +1196,7 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
     unsigned arrived = 0;
     if (lane == 0) {
         s_wave_total[wave] = wave_total;
-        arrived = __hip_atomic_fetch_add(&s_arrive, (1u << 24) | wave_total, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+        arrived = arrive(&s_arrive, (1u << 24) | wave_total);
     }
     arrived = uniform(arrived);
     const bool publisher = (arrived >> 24) == WV - 1;
@@ -1211,8 +1215,6 @@ __global__ __launch_bounds__(WV * kWaveSize) void compress_kernel(EncoderArgs a)
                 __builtin_nontemporal_store(mask_reg[r], a.masks + g);
         }
     }
-
-    if (wave == WV - 1) scan.zero_prefixes_left(tile, a.num_tiles, lane);
 
     // ---- 3. more of the compaction before the tile knows where its run begins: the steps left
     //         for now, and those that were not sure to fit but, now that their size is known, do
@@ -1850,11 +1852,15 @@ struct CountMaskTile {
     }
 };
 
-template <int W, Output OUTPUT, int WV>
+//
+// STREAM: the stored elements are read with the streaming hint.  A template's parameter, because the code of both ways
+// in one kernel (6.2 KB for 5.8) is fetched on every call: us, both | one, fp32 3 MB 4.59 | 4.39, 6.4 MB 4.95 | 4.71, 16-bit 3 MB
+// 4.74 | 4.60, at an odd element 51 MB 16.2 | 16.0.
+template <int W, Output OUTPUT, int WV, bool STREAM>
 __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
     unsigned long long values_avail, size_t n, unsigned char* __restrict__ out, WsHeader* hdr,
-    unsigned num_tiles, size_t num_groups, bool stream_values) {
+    unsigned num_tiles, size_t num_groups) {
     using G = Geometry<W, kMinLoads>;
     constexpr int E = G::kElemsPerLane;
     constexpr int kStepMasks = kStageLoads * G::kGroupsPerLoad;   // masks per wave: 32 | 64
@@ -1895,14 +1901,12 @@ __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_sca
     unsigned arrived = 0;
     if (lane == 0) {
         s_wave_total[wave] = wave_total;
-        arrived = __hip_atomic_fetch_add(&s_arrive, (1u << 24) | wave_total, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+        arrived = arrive(&s_arrive, (1u << 24) | wave_total);
     }
     arrived = uniform(arrived);
     const bool publisher = (arrived >> 24) == WV - 1;
     if (publisher && lane == 0)
         scan.publish(tile, (arrived & 0xFFFFFFu) + wave_total);
-    if (wave == WV - 1) scan.zero_prefixes_left(tile, num_tiles, lane);
     if (wave == 0) {
         unsigned long long ex = 0;
         if (tile != 0) {
@@ -1925,10 +1929,10 @@ __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_sca
     if (wave_elem0 < n) {
         if constexpr (OUTPUT != Output::kShifted)
             expand_step<W, OUTPUT == Output::kAligned>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset,
-                           wave_total, own, wave_elem0, n, out, stream_values, lane);
+                           wave_total, own, wave_elem0, n, out, STREAM, lane);
         else
             expand_shifted<W>(s_stage, 16u + wave * G::kWaveStageBytes, values, values_avail, exclusive + wave_offset, own,
-                              m, next, shift, wave_elem0, n, out, stream_values, lane);
+                              m, next, shift, wave_elem0, n, out, STREAM, lane);
     }
 
     if (tile == num_tiles - 1 && wave == 0) scan_end(scan, num_tiles, lane);
@@ -2789,7 +2793,7 @@ inline Output planar_output(const void* out, size_t bytes, int w, bool one_launc
          : one_launch && bytes < (size_t{8} << 20) ? Output::kLoose : Output::kShifted;
 }
 
-// The one-launch decoders for (w, output, eight waves or four).  The smallest tensors' outputs are written as they lie.
+// The one-launch decoders for (w, output, eight waves or four, with the streaming hint or not).  The smallest tensors' outputs are written as they lie.
 template <int W>
 auto direct_decoder_as(Output output, bool eight) {
     return output == Output::kAligned ? (eight ? decompress_direct_kernel<W, Output::kAligned, 8> : decompress_direct_kernel<W, Output::kAligned, 4>)
@@ -2798,16 +2802,17 @@ auto direct_decoder_as(Output output, bool eight) {
 inline auto direct_decoder(int w, Output output, bool eight) {
     return w == 4 ? direct_decoder_as<4>(output, eight) : direct_decoder_as<2>(output, eight);
 }
-template <int W>
+template <int W, bool STREAM>
 auto scan_decoder_as(Output output, bool eight) {
     switch (output) {
-        case Output::kLoose: return eight ? decompress_scan_kernel<W, Output::kLoose, 8> : decompress_scan_kernel<W, Output::kLoose, 4>;
-        case Output::kShifted: return eight ? decompress_scan_kernel<W, Output::kShifted, 8> : decompress_scan_kernel<W, Output::kShifted, 4>;
-        default: return eight ? decompress_scan_kernel<W, Output::kAligned, 8> : decompress_scan_kernel<W, Output::kAligned, 4>;
+        case Output::kLoose: return eight ? decompress_scan_kernel<W, Output::kLoose, 8, STREAM> : decompress_scan_kernel<W, Output::kLoose, 4, STREAM>;
+        case Output::kShifted: return eight ? decompress_scan_kernel<W, Output::kShifted, 8, STREAM> : decompress_scan_kernel<W, Output::kShifted, 4, STREAM>;
+        default: return eight ? decompress_scan_kernel<W, Output::kAligned, 8, STREAM> : decompress_scan_kernel<W, Output::kAligned, 4, STREAM>;
     }
 }
-inline auto scan_decoder(int w, Output output, bool eight) {
-    return w == 4 ? scan_decoder_as<4>(output, eight) : scan_decoder_as<2>(output, eight);
+inline auto scan_decoder(int w, Output output, bool eight, bool stream_values) {
+    if (stream_values) return w == 4 ? scan_decoder_as<4, true>(output, eight) : scan_decoder_as<2, true>(output, eight);
+    return w == 4 ? scan_decoder_as<4, false>(output, eight) : scan_decoder_as<2, false>(output, eight);
 }
 
 // `bounded`: out_cap may be anything from the size of the mask area up; the
@@ -3206,8 +3211,8 @@ zvc_status zvc_decompress(const void* d_comp, size_t comp_bytes, size_t n, int w
             return hip_ok(launch(direct_decoder(w, output, eight), grid, block, stream, masks, stream_values_at, stored_avail,
                                  n, out, groups, stream_values));
         // the workgroups find their offsets with the encoder's scan (its state is at the front of the workspace)
-        return hip_ok(launch(scan_decoder(w, output, eight), grid, block, stream, masks, stream_values_at, stored_avail, n,
-                             out, static_cast<WsHeader*>(d_ws), one_tiles, groups, stream_values));
+        return hip_ok(launch(scan_decoder(w, output, eight, stream_values), grid, block, stream, masks, stream_values_at, stored_avail, n,
+                             out, static_cast<WsHeader*>(d_ws), one_tiles, groups));
     }
     const size_t chunks = div_up(groups, kChunkMasks);
     if (chunks > 0xFFFFFFFFull) return ZVC_E_ARG;

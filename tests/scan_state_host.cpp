@@ -30,8 +30,8 @@ size_t host_header_bytes() { return kHeaderBytes; }
 // The most bytes of scan state that a call for n elements may use: 16 KB tiles, a wide call.
 size_t host_scan_bytes(size_t n, int w) { return scan_state_bytes(tiles_for(n, w, kMinLoads)); }
 
-// What a call of `tiles` tiles does to the prefixes in `header`: the zeroing of every tile, the
-// prefix of every tile that ends a block.  -1 if the zeroing touches one that the call published; else their number.
+// What a call of `tiles` tiles does to the prefixes in `header`: the prefix of every tile that ends a block, the
+// last tile's zeroing.  -1 if the zeroing touches one that the call published; else their number.
 int host_prefix_call(unsigned char* header, unsigned tiles) {
     Call call(reinterpret_cast<WsHeader*>(header), tiles);
     const ScanState& st = *call.st;
@@ -41,9 +41,7 @@ int host_prefix_call(unsigned char* header, unsigned tiles) {
         *st.prefix(tile >> st.block_shift) = st.tag() << kTagShift | tile;
         ++published;
     }
-    // (later tiles have none to zero)
-    for (unsigned tile = 0; tile < tiles && tile < 2 * kMostPrefixes / kWaveSize; ++tile)
-        for (int lane = 0; lane < kWaveSize; ++lane) st.zero_prefixes_left(tile, tiles, lane);
+    for (int lane = 0; lane < kWaveSize; ++lane) st.zero_prefixes_left(tiles, lane);
     for (unsigned b = 0; b < published; ++b)
         if (*st.prefix(b) >> kTagShift != st.tag()) return -1;
     call.end(tiles);

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_1705_01626_amd import zvc
+from tests.decoder_routes import elements
 from tests.gpu_util import raw_bytes, say
 from tests.test_gpu_parity import random_tensor
 from tests.test_gpu_unaligned import assert_guard, guarded
@@ -52,3 +53,20 @@ def test_small_streams_that_end_early(oracle, w):
         zvc.zvc_decompress(torch.from_numpy(stream).to(DEV), stream.size - cut * w, out, zvc.new_workspace(n, w, DEV))
         torch.cuda.synchronize()
         assert np.array_equal(raw_bytes(out), expect.view(np.uint8)), "n=%d" % n
+
+
+@pytest.mark.parametrize("first", [0, 1])
+@pytest.mark.parametrize("route", ["scan4", "scan8", "scan4 large"])
+@pytest.mark.parametrize("w", [4, 2])
+def test_dense_streams(oracle, w, route, first):
+    """The kernels that read the stored elements with the streaming hint: three quarters of them stored, and all."""
+    for size, density in ((elements(route, w), 0.77), (elements(route, w) + (2 * MB // w if route == "scan4" else 77), 1.0)):
+        x = random_tensor(size, w, density, seed=size)
+        host = raw_bytes(x)
+        stream = oracle.compress_stream(host, w)
+        base, out = guarded(size, x.dtype, first)
+        say("w=%d n=%d density %g" % (w, size, density))
+        zvc.zvc_decompress(torch.from_numpy(stream).to(DEV), stream.size, out, zvc.new_workspace(size, w, DEV))
+        torch.cuda.synchronize()
+        assert np.array_equal(raw_bytes(out), host), "n=%d" % size
+        assert_guard(base, size, first, "n=%d" % size)

@@ -200,7 +200,7 @@ def test_order_and_occupancy_of_decoding(fake, w, nbytes, density, interleaved, 
     assert (values["choice"], values["lds"] > 0) == (interleaved, bool(seven))
 
 
-ROUTE = re.compile(r"(?:decompress_(direct|scan)_kernelILi(\d)ELN.*?OutputE(\d)ELi(\d)E|17decompress_kernelILi(\d)ELi\d+ELN.*?OutputE(\d)E)")
+ROUTE = re.compile(r"(?:decompress_(direct|scan)_kernelILi(\d)ELN.*?OutputE(\d)ELi(\d)E(?:Lb(\d)E)?|17decompress_kernelILi(\d)ELi\d+ELN.*?OutputE(\d)E)")
 OUTPUTS = ("aligned", "loose", "shifted")
 
 
@@ -215,9 +215,11 @@ def routes(fake, calls):
         if got is None:
             assert "mask_prefix_kernel" in name          # the first of two
             continue
-        one, w, output, waves, two_w, two_output = got.groups()
+        one, w, output, waves, hint, two_w, two_output = got.groups()
         found.append((one + waves if one else "two", OUTPUTS[int(output or two_output)]))
         assert int(w or two_w) == calls[len(found) - 1][1]
+        if one == "scan":                                # dense streams are read with the streaming hint
+            assert hint == "%d" % (calls[len(found) - 1][3] >= 0.75)
     assert len(found) == len(calls)
     return found
 
