@@ -659,7 +659,7 @@ struct ScanState {
 // a round trip but finds a prefix further back, and the extra counts to read
 // cost more than the round trip).  PAUSE: see there.  Returns the number of kept elements in all
 // tiles before `tile` (not 0).
-constexpr int kNoPause = -1, kDecoderPause = 14;
+constexpr int kNoPause = -1, kDecoderPause = 16;
 template <int PAUSE, class CountTile>
 __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, unsigned tile, int lane,
                                                            const CountTile& count_tile) {
@@ -673,8 +673,9 @@ __device__ inline unsigned long long scan_exclusive_prefix(const ScanState& st, 
     // of them more.  us, encoding, at once | a round trip later | 0.3 us asleep: fp32 6.4 MB 6.1 | 5.8 | 6.1, 64 MB
     // 20.4 | 17.3 | 19.5, 300 MB 73.8 | 70.7 | 73.6 (waiting for the tile in front first, alone: 6.9, 21.3, 75.8); with 8
     // sleeps more 6.4 MB 5.8 | 5.8, 12 MB 7.1 | 7.2.  Decoding, whose workgroups have their counts all at the same time, a round trip
-    // and 10 | 12 | 14 | 16 | 18 sleeps: fp32 6.4 MB 5.17 | 5.05 | 5.03 | 5.03 | 5.10 (without 5.7), 12 MB 6.05 | 5.78 | 5.77 | 5.79 |
-    // 5.85, 40 MB 13.06 | 12.87 | 12.76 | 12.76 | 12.80; bf16 20 MB 8.25 | 8.15 | 8.07 | 8.06 | 8.09.
+    // and 14 | 16 | 18 | 20 sleeps: fp32 3 MB 4.42 | 4.47 | 4.52, 6.4 MB 4.78 | 4.83 | 4.89 | 4.94 (without any 5.6), 30 MB 9.48 | 9.30 | 9.23,
+    // at an odd element 20 MB 7.58 | 7.50 | 7.44; 6.4 MB from memory, where the counts are less together, the kernel alone 6.92 | 6.88 |
+    // 6.87 | 6.82.
     unsigned long long patience_word = 0;
     if (PAUSE != kNoPause) patience_word = uniform(load64(&st.hdr->patience_plus_one));
     if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
@@ -1854,8 +1855,8 @@ struct CountMaskTile {
 
 //
 // STREAM: the stored elements are read with the streaming hint.  A template's parameter, because the code of both ways
-// in one kernel (6.2 KB for 5.8) is fetched on every call: us, both | one, fp32 3 MB 4.59 | 4.39, 6.4 MB 4.95 | 4.71, 16-bit 3 MB
-// 4.74 | 4.60, at an odd element 51 MB 16.2 | 16.0.
+// in one kernel (6.2 KB for 5.8) is fetched on every call: us with the same pause, both | one, fp32 3 MB 4.59 | 4.39, 6.4 MB 4.95 |
+// 4.71, 16-bit 3 MB 4.74 | 4.60, at an odd element 51 MB 16.2 | 16.0.
 template <int W, Output OUTPUT, int WV, bool STREAM>
 __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_scan_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
@@ -1942,9 +1943,9 @@ __global__ __launch_bounds__(WV * kWaveSize) ZVC_EIGHT_WAVES void decompress_sca
 // itself, 16 bytes a thread and eight of them on their way at a time.  That is one round trip to memory where the scan takes
 // three (count, wait, look), and it is work that grows with the square of the tensor.  Workgroups begin
 // at different places, so that they do not all ask the same channel of the L2 at a time (a cold 4 MB
-// stream 6.3 -> 5.9 us).  us, scan | here with 4 | 8 waves: fp32 0.25 MB 4.4 | 3.4 | 3.5, 1 MB 4.4 | 3.6 | 3.65, 2 MB 4.5 | 4.0 |
-// 3.9, 3 MB 4.7 | 4.5 | 4.4, 4 MB 4.7 | 5.1 | 4.6 (from memory 5.1 | 5.9 | 5.4); 16-bit 0.25 MB 4.5 | 3.5 | 3.7, 1 MB 4.55 | 4.0 |
-// 4.0, 2 MB 4.7 | 5.1 | 4.6, 4 MB 4.9 | 7.3 | 5.9.
+// stream 6.3 -> 5.9 us).  us, scan | here with 4 | 8 waves: fp32 0.25 MB 4.1 | 3.4 | 3.5, 1 MB 4.2 | 3.6 | 3.65, 2 MB 4.3 | 3.9 |
+// 3.9, 2.5 MB 4.4 | 4.4 | 4.3, 3 MB 4.4 | 4.55 | 4.4, 4 MB 4.5 | 5.15 | 4.5 (from memory 5.1 | 5.9 | 5.4); 16-bit 0.25 MB 4.3 | 3.5 |
+// 3.7, 1 MB 4.4 | 4.0 | 4.0, 1.25 MB 4.4 | 4.4 | 4.3, 2 MB 4.4 | 5.1 | 4.6, 4 MB 4.65 | 7.35 | 5.9.
 template <int W, Output OUTPUT, int WV>
 __global__ __launch_bounds__(WV * kWaveSize) void decompress_direct_kernel(
     const unsigned* __restrict__ masks, const unsigned char* __restrict__ values,
@@ -2629,12 +2630,12 @@ hipError_t launch_compress_as(Encoder mode, hipStream_t stream, const unsigned c
 // memory (dense ones: one launch is ahead up to 60 MB, and in the caches at 0.6 as well), from 56 MB at an odd element, where a
 // piece has more to do between its masks and its stores (and from 76 MB with three quarters of the elements stored: there two
 // launches were slower, on streams in the caches, than stores that follow the output's alignment, and one is not).
-//   density 0.3, fp32    3 MB 4.7 | 4.8 | 6.5   4 MB 4.7 | 4.8 | 6.5   5 MB 5.2 | 4.9 | 6.5   6.1 MB 5.1 | 5.0 | 7.0   8.5 MB 5.85 | 5.8 |
-//                        6.8   16 MB 6.8 | 6.15 | 7.9   24 MB 8.3 | 7.6 | 9.5   32 MB 10.1 | 10.1 | 11.4   40 MB 12.5 | 13.4 | 13.1
-//                        50 MB 14.7 | 15.9 | 14.7   64 MB 17.7 | 18.8 | 17.7   100 MB 25.4 | 27.0 | 24.8
-//                16-bit  4 MB 4.9 | 5.0 | 6.55   6 MB 5.3 | 5.1 | 6.7   12 MB 6.4 | 5.9 | 7.35   19 MB 7.6 | 7.5 | 8.7   30 MB 10.2 | 9.9 |
-//                        11.3   40 MB 12.6 | 14.9 | 13.4   51 MB 15.15 | 17.65 | 15.2   64 MB 18.0 | 20.2 | 18.3   100 MB 26.0 | 29.3 | 25.3
-//   density 0.9, fp32    24 MB 12.0 | 11.7 | 13.2   50 MB 21.3 | 23.8 | 22.5; 16-bit 64 MB 26.2 | 29.3 | 27.0
+//   density 0.3, fp32    3 MB 4.4 | 4.5 | 6.5   4 MB 4.5 | 4.6 | 6.5   5 MB 5.1 | 4.7 | 6.5   6.1 MB 5.1 | 4.7 | 7.0   8.5 MB 5.8 | 5.6 |
+//                        6.8   16 MB 6.8 | 6.2 | 7.9   24 MB 8.3 | 7.8 | 9.4   32 MB 10.0 | 9.9 | 11.3   40 MB 12.2 | 13.5 | 12.9
+//                        50 MB 14.6 | 15.8 | 14.6   64 MB 17.4 | 18.7 | 17.5   100 MB 25.1 | 26.8 | 24.7
+//                16-bit  4 MB 4.7 | 4.9 | 6.55   6 MB 5.4 | 5.0 | 6.7   12 MB 6.3 | 6.0 | 7.35   19 MB 7.7 | 7.5 | 8.6   30 MB 10.0 | 9.8 |
+//                        11.0   40 MB 12.6 | 14.2 | 13.4   51 MB 15.2 | 16.9 | 15.0   64 MB 17.9 | 19.4 | 18.05   100 MB 26.1 | 28.0 | 25.2
+//   density 0.9, fp32    24 MB 11.8 | 11.5 | 12.9   50 MB 21.2 | 22.7 | 22.6; 16-bit 64 MB 26.3 | 28.75 | 27.1
 //   at an odd element, 0.3: fp32 32 MB 10.7 | 10.8 | 11.9; 16-bit 52 MB 16.5 | 17.75 | 16.2
 //   at an odd element, one launch (kScan4) | two: fp32 of 0.1 | 0.3 | 0.6 | 0.9, 36 MB 10.5 | 12.5  12.1 | 13.5  13.7 | 14.9  16.3 | 17.6
 //                        46 MB 13.4 | 13.4  14.6 | 14.6  16.0 | 16.7  20.2 | 21.3   55 MB 15.4 | 15.2  16.7 | 16.6  18.6 | 19.1  23.1 | 24.6
